@@ -16,7 +16,8 @@
 // block's lowest layer there is only phase P over all tiles, with the causal mask.
 //
 // Tiling: a workgroup of 4 waves takes 128 query rows of one head, 32 rows per wave; key/value
-// tiles of 64 tokens go through LDS.
+// tiles of 64 tokens go through LDS (KS = 2: eight waves, two key groups that take every second key tile of the same rows and
+// are merged at the end: prefill_key_groups).
 //   S^T[key][row] = K[key][:] . Q[row][:]     v_mfma_f32_32x32x16_bf16, A = K fragment, B = Q
 //   O^T[dim][row] = sum_key V[key][dim] P[key][row]               A = V^T fragment, B = P
 // Query row = MFMA column (lane % 32) in both, so softmax state, P and the output slice of a
@@ -38,6 +39,7 @@ namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 
@@ -62,6 +64,22 @@ struct prefill_params {
     int *len, *flag;
     int len_old, len_new;
 };
+
+// The key tiles that query rows i0 .. i_last walk, in order: nD tiles from tD0 (phase D), nP1 sink tiles from 0, band tiles from tB.
+struct tile_list { int tD0, nD, nP1, tB, count; };
+__host__ __device__ inline tile_list tiles_of_rows(int i0, int i_last, int S, int W, bool has_shared)
+{
+    tile_list t = {0, 0, 0, 0, 0};
+    if (has_shared) {
+        if (i_last - W >= S) { t.tD0 = S / kBN; t.nD = (i_last - W) / kBN - t.tD0 + 1; }
+        if (S > 0) t.nP1 = ((S < i_last + 1 ? S : i_last + 1) - 1) / kBN + 1;
+        const int band = i0 - W + 1 > 0 ? (i0 - W + 1) / kBN : 0;
+        t.tB = t.nP1 > band ? t.nP1 : band;
+    }
+    const int tEnd = i_last / kBN;
+    t.count = t.nD + t.nP1 + (tEnd >= t.tB ? tEnd - t.tB + 1 : 0);
+    return t;
+}
 
 __device__ inline bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
@@ -153,8 +171,8 @@ __device__ inline float dot2_ones(unsigned pk, float acc)
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk), ones, acc, false);
 }
 
-template <int D, bool TAB>
-__global__ __launch_bounds__(256, 2) void prefill_kernel(prefill_params p)
+template <int D, bool TAB, int KS>
+__global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
 {
     constexpr int CPR = D / 8, KST = D / 16, NDB = D / 32, NKB = kBN / 32, NPS = kBN / 16;
     constexpr int BM = 128;
@@ -168,8 +186,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(prefill_params p)
     typedef __attribute__((address_space(3))) s16x4 *ltr_ptr;
     constexpr int FRAG = 64 * 16;
     constexpr int KBUF = NQK * FRAG, VBUF = kBN * D * 2; // 16 KB each at D = 128
-    extern __shared__ __attribute__((aligned(16))) char lds[];   // [K slot 0][K slot 1][V slot 0][V slot 1]
-    char *const ldsK = lds, *const ldsV = lds + 2 * KBUF;
+    extern __shared__ __attribute__((aligned(16))) char lds[];   // per key group: [K slot 0][K slot 1][V slot 0][V slot 1]
 
     const int nqt = (p.n + BM - 1) / BM;
     const int wg = blockIdx.x;
@@ -182,7 +199,9 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(prefill_params p)
     const int qt = nqt - 1 - rest / p.rep;
     const int i0 = qt * BM;
     const int i_last = min(i0 + BM, p.n) - 1;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, wave = (tid >> 6) & 3, lane = tid & 63;
+    const int grp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8); // key group: waves 4 grp .. 4 grp + 3
+    char *const ldsK = lds + grp * (2 * KBUF + 2 * VBUF), *const ldsV = ldsK + 2 * KBUF;
     const int n32 = lane & 31, jj = lane >> 5;
     const int iw0 = i0 + wave * 32;
     const int iw_last = min(iw0 + 32, p.n) - 1;
@@ -191,16 +210,11 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(prefill_params p)
     const int S = p.S, W = p.W;
     const float c = p.scale_log2e;
 
-    int tD0 = 0, nD = 0, nP1 = 0, tB = 0;
-    if (has_shared) {
-        if (i_last - W >= S) { tD0 = S / kBN; nD = (i_last - W) / kBN - tD0 + 1; }
-        if (S > 0) nP1 = (min(S, i_last + 1) - 1) / kBN + 1;
-        tB = max(nP1, max(0, i0 - W + 1) / kBN);
-    }
-    const int tEnd = i_last / kBN;
-    const int nP2 = tEnd >= tB ? tEnd - tB + 1 : 0;
-    const int T = nD + nP1 + nP2;
-    auto tile_of = [&](int t, int &kt, bool &phaseD) {
+    const tile_list tl = tiles_of_rows(i0, i_last, S, W, has_shared);
+    const int tD0 = tl.tD0, nD = tl.nD, nP1 = tl.nP1, tB = tl.tB, Tall = tl.count;
+    const int T = (Tall + KS - 1) / KS; // tiles of a key group: group g walks tiles g, g + KS, ... of the list
+    auto tile_of = [&](int u, int &kt, bool &phaseD) {
+        const int t = KS == 1 ? u : min(u * KS + grp, Tall - 1); // (past the end: the last tile again; mask_tile leaves nothing of it)
         phaseD = t < nD;
         kt = phaseD ? tD0 + t : (t < nD + nP1 ? t - nD : tB + (t - nD - nP1));
     };
@@ -311,7 +325,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(prefill_params p)
         const int cnt = x < 0 ? 0 : x > 63 ? 32 : 4 * (x >> 3) + min((x & 7) + 1, 4);
         return (unsigned)((1ull << cnt) - 1);
     };
-    auto mask_tile = [&](int kt, bool phaseD, f32x16 (&sc)[NKB]) {
+    auto mask_tile = [&](int u, int kt, bool phaseD, f32x16 (&sc)[NKB]) { // u-th tile of the wave's key group
         const int j0 = kt * kBN, j1 = j0 + kBN - 1;
         bool full; // every (row, key) pair of the wave counts: no masking needed
         if (phaseD) full = j0 >= S && j1 <= iw0 - W;
@@ -320,10 +334,12 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(prefill_params p)
         // A wave whose rows all lie past the prompt stores nothing, so it masks nothing either: the 32 compares and selects
         // per tile it would spend hold up the three other waves at every barrier, and that in the workgroups with most keys
         // (lowest layer, n = 3001, 16 heads x 64: 111.5 -> 54.2 us; n = 777, 32 heads x 128: 40.3 -> 27.6 us).
+        if (KS > 1) full = full && u * KS + grp < Tall;
         if (full || iw0 > iw_last) return;
         const int base = j0 + 4 * jj;
         const unsigned distant = first_bits(irow - W - base) & ~first_bits(S - 1 - base);
-        const unsigned ok = phaseD ? distant : first_bits(irow - base) & ~(has_shared ? distant : 0u);
+        unsigned ok = phaseD ? distant : first_bits(irow - base) & ~(has_shared ? distant : 0u);
+        if (KS > 1 && u * KS + grp >= Tall) ok = 0u;
 #pragma unroll
         for (int b = 0; b < NKB * 16; ++b) {
             const int keep = __builtin_amdgcn_sbfe((int)ok, b, 1); // all ones / zeros
@@ -368,7 +384,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(prefill_params p)
     tile_of(2, kt_c, ph_c);
     unsigned long long k_next = 0, v_next = 0; // TAB: addresses of the tiles the next iteration requests
     if constexpr (TAB) {
-        if (wg == 0 && tid == 0) { // the update launch before this one left the length for here
+        if (wg == 0 && threadIdx.x == 0) { // the update launch before this one left the length for here
             if (*p.len == p.len_old) *p.len = p.len_new;
             else atomicOr(p.flag, 1);
         }
@@ -380,7 +396,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(prefill_params p)
         request_k(kt_a, ph_a, 0, 0);
         if (T > 1) request_k(kt_b, ph_b, 1, 0);
     }
-    load_q(nD > 0 ? p.qs : p.q);
+    load_q(ph_a ? p.qs : p.q);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     {
@@ -393,7 +409,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(prefill_params p)
             const int s = op / NKB, kb = op % NKB;
             sA[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kfrag(ldsK, op)), qf[s], sA[kb], 0, 0, 0);
         }
-        mask_tile(kt_a, ph_a, sA);
+        mask_tile(0, kt_a, ph_a, sA);
         float mx = -__builtin_inff();
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb)
@@ -439,7 +455,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(prefill_params p)
             }
             m_ref = mx_next;
         }
-        if (t + 1 == nD) load_q(p.q); // the next tile is the first of the own-key phase
+        if (ph_a && !ph_b) load_q(p.q); // the next tile is the first of the own-key phase
         const float mr = m_ref;
         float ps = 0.f;
         const char *kl = ldsK + (slot ^ 1) * KBUF;   // K(t+1)
@@ -458,7 +474,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(prefill_params p)
         static_for<NS>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
             if constexpr (!FIRST && i == NMIX) {
-                mask_tile(kt_b, ph_b, sn); // boundary tiles only; S(t+1) is complete here
+                mask_tile(t + 1, kt_b, ph_b, sn); // boundary tiles only; S(t+1) is complete here
                 __builtin_amdgcn_sched_barrier(0);
             }
             if constexpr (i + kPF < NS) fr[i + kPF] = frag(i + kPF);
@@ -523,7 +539,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(prefill_params p)
             __builtin_amdgcn_sched_barrier(0);
         });
         if (FIRST) { // no last quarter: the same housekeeping without MFMAs in between
-            mask_tile(kt_b, ph_b, sn);
+            mask_tile(t + 1, kt_b, ph_b, sn);
 #pragma unroll
             for (int x = 0; x < NKB * 16; ++x) mxv[x & 3] = fmaxf(mxv[x & 3], sn[x >> 4][x & 15]);
         }
@@ -555,6 +571,35 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(prefill_params p)
         else pv(pA);
     }
 
+    if constexpr (KS == 2) {
+        // Group 1 leaves its state in LDS (register by register: a lane's counterpart in group 0 holds the same rows and dims)
+        // and group 0 merges it: one reference maximum, accumulators and row sums added.
+        f32x4 *const box = (f32x4 *)lds + (size_t)(wave * (4 * NDB)) * 64 + lane;
+        float2 *const box_ml = (float2 *)(lds + 4 * 4 * NDB * 64 * sizeof(f32x4)) + wave * 64 + lane;
+        __syncthreads(); // every wave has read its last V tile
+        if (grp == 1) {
+#pragma unroll
+            for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+                    box[(4 * db + a) * 64] = f32x4{oacc[db][4 * a], oacc[db][4 * a + 1], oacc[db][4 * a + 2], oacc[db][4 * a + 3]};
+            *box_ml = make_float2(m_ref, l_run);
+        }
+        __syncthreads();
+        if (grp == 1) return;
+        const float2 ml = *box_ml;
+        const float M = fmaxf(m_ref, ml.x); // (a group without a valid key of the row has kNegBig, weight 0 and sum 0)
+        const float f0 = __builtin_amdgcn_exp2f(m_ref - M), f1 = __builtin_amdgcn_exp2f(ml.x - M);
+        l_run = l_run * f0 + ml.y * f1;
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                const f32x4 o = box[(4 * db + a) * 64];
+#pragma unroll
+                for (int x = 0; x < 4; ++x) oacc[db][4 * a + x] = oacc[db][4 * a + x] * f0 + o[x] * f1;
+            }
+    }
     const float l = pair_sum(l_run);
     if (irow < p.n && irow >= p.q0) {
         const float inv = 1.f / l;
@@ -571,13 +616,59 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(prefill_params p)
     }
 }
 
+int prefill_key_groups(int cus, int Hq, int n, int q0, int S, int W, bool has_shared)
+{
+    const int last = (n - 1) / 128, first = q0 / 128, tiles = last - first + 1; // query tiles, handed out from the last to the first
+    const int64_t nwg = (int64_t)tiles * Hq;
+    if (cus < 1 || nwg > 2 * cus) return 1;
+    auto cost = [&](int64_t wg) { // key tiles of workgroup wg in launch order
+        const int i0 = (last - (int)(wg / Hq)) * 128;
+        return tiles_of_rows(i0, (i0 + 128 < n ? i0 + 128 : n) - 1, S, W, has_shared).count;
+    };
+    const int longest = cost(0);
+    int pair = longest;
+    for (int64_t wg = 0; wg < cus && wg < nwg; ++wg) { // workgroup 2 cus - 1 - wg runs where wg did
+        const int64_t second = 2 * (int64_t)cus - 1 - wg;
+        const int sum = cost(wg) + (second < nwg ? cost(second) : 0);
+        pair = sum > pair ? sum : pair;
+    }
+    return longest >= 4 && (0.62 * pair + 3.0 < longest || nwg <= cus) ? 2 : 1;
+}
+
 } // namespace
+
+// dynamic LDS: per key group two K slots and two V slots of kBN tokens x D bf16 each (64 KB at D = 128); two groups also need
+// room for the merge at the end: 128 rows x D fp32 and a (maximum, sum) per lane, which the slots' own bytes hold at D = 128
+constexpr int lds_bytes(int D, int key_groups)
+{
+    const int slots = key_groups * 4 * kBN * D * 2, merge = 128 * D * 4 + 256 * 8;
+    return key_groups > 1 && merge > slots ? merge : slots;
+}
+
+// One or two key groups per workgroup.  With two, a workgroup's 128 query rows are walked by eight waves, each half of them
+// every second key tile: half the iterations on the launch's longest path, at an iteration that takes longer (eight waves
+// meet at its barrier; with all CUs full of equal work two groups reach 0.87 of the rate of two separate workgroups) plus the
+// merge.  It pays where the launch is short of workgroups or of equal ones, so costs in key tiles are compared:
+//   one group  : the longest query tile, as long as every workgroup is resident (two per CU)
+//   two groups : one workgroup per CU, the first round's query tiles and, on the CUs that are free first, the second's
+// Measured per launch, one -> two groups (32/8 heads x 128 unless said): n = 777 24.3 -> 22.3 us, 1024 29.1 -> 25.8, 1500 42.9 -> 37.1,
+// 2048 58.3 -> 53.8, 3001 93 -> 108 (more than two rounds), 2048 rows behind 6144 210 -> 225 (equal tiles); 16/4 heads x 64:
+// n = 1024 20.5 -> 17.4, 3001 51.6 -> 39.7, 4096 70.0 -> 59.2, 6000 110 -> 125; 512 rows behind 7680 (128 workgroups) 114 -> 86.
+int pick_key_groups(const pod_layout &ly, int n, int q0, bool has_shared, int *groups)
+{
+    int dev = -1, cus = 0;
+    POD_HIP_TRY(hipGetDevice(&dev));
+    POD_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    *groups = prefill_key_groups(cus, ly.Hq, n, q0, ly.S, ly.W, has_shared);
+    return POD_OK;
+}
 
 // tile_tab != NULL: keys and values are located through the per-tile address table (k, v, k_shared are not read)
 static int launch_prefill(const pod_layout &ly, int n, int q0, const void *q, const void *k, const void *v,
                           const void *q_shared, const void *k_shared, const unsigned long long *tile_tab, int ntiles,
                           int *len, int *flag, uint64_t lowest_mask, float scale, void *out, hipStream_t st)
 {
+    int rc = POD_OK;
     prefill_params p;
     p.n = n; p.q0 = q0; p.Hq = ly.Hq; p.Hkv = ly.Hkv; p.rep = ly.rep; p.S = ly.S; p.W = ly.W;
     p.q = (const pod_bf16 *)q; p.k = (const pod_bf16 *)k; p.v = (const pod_bf16 *)v;
@@ -591,9 +682,12 @@ static int launch_prefill(const pod_layout &ly, int n, int q0, const void *q, co
     if (tile_tab && ntiles < (n + kBN - 1) / kBN) return pod_fail(POD_ERR_INVALID_ARG, "tile table of %d entries for %d keys", ntiles, n);
     // query tiles of 128 positions, counted from the end: the kernel takes tile (n + 127) / 128 - 1 - blockIdx.x / Hq
     const dim3 grid((unsigned)((n + 127) / 128 - q0 / 128) * (unsigned)ly.Hq);
-    // dynamic LDS: two K slots and two V slots of kBN tokens x D bf16 each (64 KB at D = 128)
-    const auto lds_bytes = [](int D) { return 4 * kBN * D * 2; };
-    // raising the dynamic-LDS limit to 64 KB is needed once per device; any host thread may get here first
+    // raising the dynamic-LDS limit is needed once per device; any host thread may get here first
+    static const struct { const void *fn; int lds; } variants[2][2][2] = { // [head dim 64 / 128][table][key groups - 1]
+        {{{(const void *)prefill_kernel<64, false, 1>, lds_bytes(64, 1)}, {(const void *)prefill_kernel<64, false, 2>, lds_bytes(64, 2)}},
+         {{(const void *)prefill_kernel<64, true, 1>, lds_bytes(64, 1)}, {(const void *)prefill_kernel<64, true, 2>, lds_bytes(64, 2)}}},
+        {{{(const void *)prefill_kernel<128, false, 1>, lds_bytes(128, 1)}, {(const void *)prefill_kernel<128, false, 2>, lds_bytes(128, 2)}},
+         {{(const void *)prefill_kernel<128, true, 1>, lds_bytes(128, 1)}, {(const void *)prefill_kernel<128, true, 2>, lds_bytes(128, 2)}}}};
     {
         static std::mutex attr_mutex;
         static bool attr_done[64] = {};
@@ -602,20 +696,18 @@ static int launch_prefill(const pod_layout &ly, int n, int q0, const void *q, co
         if (dev < 0 || dev >= 64) return pod_fail(POD_ERR_INVALID_ARG, "device %d outside [0, 64)", dev);
         std::lock_guard<std::mutex> lock(attr_mutex);
         if (!attr_done[dev]) {
-            POD_HIP_TRY(hipFuncSetAttribute((const void *)prefill_kernel<128, false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(128)));
-            POD_HIP_TRY(hipFuncSetAttribute((const void *)prefill_kernel<64, false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(64)));
-            POD_HIP_TRY(hipFuncSetAttribute((const void *)prefill_kernel<128, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(128)));
-            POD_HIP_TRY(hipFuncSetAttribute((const void *)prefill_kernel<64, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(64)));
+            for (const auto &by_dim : variants)
+                for (const auto &by_table : by_dim)
+                    for (const auto &v : by_table) POD_HIP_TRY(hipFuncSetAttribute(v.fn, hipFuncAttributeMaxDynamicSharedMemorySize, v.lds));
             attr_done[dev] = true;
         }
     }
-    if (ly.D == 128) {
-        if (tile_tab) hipLaunchKernelGGL((prefill_kernel<128, true>), grid, dim3(256), lds_bytes(128), st, p);
-        else hipLaunchKernelGGL((prefill_kernel<128, false>), grid, dim3(256), lds_bytes(128), st, p);
-    } else {
-        if (tile_tab) hipLaunchKernelGGL((prefill_kernel<64, true>), grid, dim3(256), lds_bytes(64), st, p);
-        else hipLaunchKernelGGL((prefill_kernel<64, false>), grid, dim3(256), lds_bytes(64), st, p);
-    }
+    int ks = 1;
+    rc = pick_key_groups(ly, n, q0, q_shared != nullptr, &ks);
+    if (rc) return rc;
+    const auto &var = variants[ly.D == 128][tile_tab != nullptr][ks - 1];
+    void *args[] = {&p};
+    POD_HIP_TRY(hipLaunchKernel(var.fn, grid, dim3(256 * ks), args, var.lds, st));
     POD_HIP_TRY(hipGetLastError());
     return POD_OK;
 }

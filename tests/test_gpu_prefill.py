@@ -41,6 +41,19 @@ def test_small_prompts_every_tile_kind(d, Hq, Hkv, n):
         assert_close(out, ref_prefill(c, layer, n, np.arange(n)), f"n={n} layer {layer}")
 
 
+@pytest.mark.parametrize("d,Hq,Hkv", [(128, 64, 4), (64, 64, 8)])
+@pytest.mark.parametrize("n", [193, 255, 321, 1290])
+def test_one_and_two_key_groups_per_workgroup(d, Hq, Hkv, n):
+    """Few workgroups: two key groups walk even and odd tiles of a query tile (an odd number of tiles leaves one of them a
+    tile that counts nothing; 193 is the shortest prompt that takes this form).  1290 x 64 heads: more workgroups than two
+    per CU, one group."""
+    c = Case(2, 2, Hq, Hkv, d, 8, 40, 1, n, seed=230 + n, with_oracle_cache=False)
+    rows = np.unique(np.concatenate([np.arange(0, n, 37), np.arange(max(0, n - 70), n)]))
+    for layer in range(2):
+        out = run_prefill(c, layer, n)
+        assert_close(out[torch.from_numpy(rows).to(out.device)], ref_prefill(c, layer, n, rows), f"n={n} layer {layer}")
+
+
 def test_window_larger_than_tile_and_prompt_shorter_than_window():
     c = Case(2, 2, 8, 2, 128, 64, 512, 1, 1500, seed=41, with_oracle_cache=False)
     for n in (400, 1500):
