@@ -181,7 +181,9 @@ from oracle import pod_grouping as pg
 
 
 @pytest.mark.parametrize("L,H,R,n", [(3, 2, 4, 64), (5, 4, 6, 1000), (2, 1, 1, 4), (4, 3, 3, 4100), (19, 2, 2, 514), (32, 1, 2, 1024),
-                                     (8, 2, 1, 8), (9, 1, 4, 333)])
+                                     (8, 2, 1, 8), (9, 1, 4, 333),
+                                     # enough workgroups for blocks of four layers; 18 heads do not deal out over 8 XCDs
+                                     (32, 8, 3, 68), (19, 18, 2, 34)])
 def test_layer_similarity_matches_the_oracle(L, H, R, n):
     rng = np.random.default_rng(L * 1000 + n)
     att = rng.dirichlet(np.full(n, 0.3), size=(L, H, R)).astype(np.float32)
