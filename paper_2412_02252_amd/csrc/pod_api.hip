@@ -749,10 +749,11 @@ extern "C" int pod_prefill_attention(pod_cache *cache, int layer, int seq_slot, 
             return pod_fail(POD_ERR_STATE, "slot %d at layer %d is not empty", seq_slot, layer);
     }
     if (lowest) { q_shared = nullptr; k_shared = nullptr; }
-    rc = pod_launch_prefill(ly, layer, n, 0, q, k, v, q_shared, k_shared, pod_make_headmap(cache, layer).lowest_mask, scale, out,
+    const pod_fill_args fill = pod_make_fill_args(cache, layer, write_cache ? seq_slot : 0, n);
+    rc = pod_launch_prefill(ly, layer, n, 0, q, k, v, q_shared, k_shared, fill.hm.lowest_mask, scale, out, write_cache ? &fill : nullptr,
                             (hipStream_t)stream);
     if (rc) return rc;
-    if (write_cache) return pod_cache_fill(cache, layer, seq_slot, n, k, v, stream);
+    if (write_cache) cache->host_len[(size_t)layer * ly.B + seq_slot] = n;
     return POD_OK;
 }
 
@@ -860,7 +861,7 @@ extern "C" int pod_prefill_attention_chunk(pod_cache *cache, int layer, int seq_
     rc = pod_launch_gather(cache, layer, seq_slot, (int)p0, T, k, v, k_shared, k_all, v_all, ks_all, st);
     if (rc) return rc;
     rc = pod_launch_prefill(ly, layer, (int)n, (int)p0, q, k_all, v_all, q_shared, ks_all, pod_make_headmap(cache, layer).lowest_mask,
-                            scale, out, st);
+                            scale, out, nullptr, st);
     if (rc) return rc;
     if (write_cache) {
         const int32_t cnt = T;

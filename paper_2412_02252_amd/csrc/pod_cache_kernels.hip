@@ -371,32 +371,9 @@ __global__ void chunk_dirty_kernel(const char *base, chunk_view cv)
 }
 
 // Grid-stride over 16-byte pieces of the prompt's K/V [n][Hkv][D].
-__global__ void fill_kernel(char *base, pod_layout ly, pod_headmap hm, int layer, int b, int n,
-                            const uint4 *__restrict__ k, const uint4 *__restrict__ v)
+__global__ __launch_bounds__(kThreads) void fill_kernel(pod_fill_args a, const void *k, const void *v)
 {
-    const int cpr = ly.D / 8;
-    const int rec_lo = n - ly.W > ly.S ? n - ly.W : ly.S; // first position of the recent window
-    uint4 *proxK = (uint4 *)(base + ly.off_proxK);
-    uint4 *proxV = (uint4 *)(base + ly.off_proxV);
-    uint4 *distK = (uint4 *)(base + ly.off_distK);
-    uint4 *distV = (uint4 *)(base + ly.off_distV);
-    const size_t total = (size_t)n * ly.Hkv * cpr;
-    for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += (size_t)gridDim.x * blockDim.x) {
-        const int c = (int)(idx % cpr);
-        const int h = (int)((idx / cpr) % ly.Hkv);
-        const int p = (int)(idx / ((size_t)cpr * ly.Hkv));
-        if (p < ly.S || p >= rec_lo) {
-            const int slot = p < ly.S ? p : ly.S + (p - ly.S) % ly.W;
-            const size_t pr = (pod_prox_row0(ly, layer, b, h) + slot) * cpr + c;
-            proxK[pr] = k[idx];
-            proxV[pr] = v[idx];
-        } else {
-            const size_t t = (size_t)(p - ly.S);
-            distV[(pod_dist_row0(ly, layer, b, h) + t) * cpr + c] = v[idx];
-            if ((hm.lowest_mask >> h) & 1) distK[(pod_distk_row0(ly, hm, b, h) + t) * cpr + c] = k[idx];
-        }
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) lens_ptr(base, ly)[(size_t)layer * ly.B + b] = n;
+    pod_fill_rows<1>(a, k, v, (size_t)blockIdx.x * blockDim.x + threadIdx.x, (size_t)gridDim.x * blockDim.x);
 }
 
 // Gather the logical views [tokens][Hkv][D] in position order.
@@ -473,11 +450,18 @@ int pod_launch_append(const pod_cache *c, int layer, const void *k_new, const vo
     return POD_OK;
 }
 
+pod_fill_args pod_make_fill_args(const pod_cache *c, int layer, int seq_slot, int n)
+{
+    pod_fill_args a;
+    a.base = c->base; a.ly = c->ly; a.hm = pod_make_headmap(c, layer);
+    a.layer = layer; a.b = seq_slot; a.n = n;
+    return a;
+}
+
 int pod_launch_fill(const pod_cache *c, int layer, int seq_slot, int n, const void *k, const void *v, hipStream_t st)
 {
     const size_t items = (size_t)n * c->ly.Hkv * (c->ly.D / 8);
-    hipLaunchKernelGGL(fill_kernel, dim3(grid_for(items)), dim3(kThreads), 0, st, c->base, c->ly, pod_make_headmap(c, layer), layer, seq_slot, n,
-                       (const uint4 *)k, (const uint4 *)v);
+    hipLaunchKernelGGL(fill_kernel, dim3(grid_for(items)), dim3(kThreads), 0, st, pod_make_fill_args(c, layer, seq_slot, n), k, v);
     POD_HIP_TRY(hipGetLastError());
     return POD_OK;
 }

@@ -89,6 +89,65 @@ struct pod_cache {
     int trace_cap; // workgroups it holds (8 x 8 bytes each)
 };
 
+// Cache construction from a prompt's rows (fill_kernel, and the workgroups of a prefill launch that do the same).
+struct pod_fill_args {
+    char *base;
+    pod_layout ly;
+    pod_headmap hm;
+    int32_t layer, b, n;
+};
+typedef __attribute__((ext_vector_type(4))) unsigned pod_u32x4; // (arrays of HIP's uint4 struct would stay in scratch memory)
+constexpr int kFillUnroll = 4; // 16-byte pieces of K and of V a thread of a prefill launch has in flight
+
+// Pieces first, first + stride, ... of k and v ([n][Hkv][D], 16-byte pieces) to where the cache keeps them; whoever takes piece 0
+// also stores the length.  U pieces of K and of V are in flight per thread.
+template <int U>
+__device__ inline void pod_fill_rows(const pod_fill_args &a, const void *k, const void *v, size_t first, size_t stride)
+{
+    const pod_layout &ly = a.ly;
+    const int cshift = ly.D == 128 ? 4 : 3; // 16-byte pieces per row: 8 or 16
+    const int rec_lo = a.n - ly.W > ly.S ? a.n - ly.W : ly.S; // first position of the recent window
+    const pod_u32x4 *const kp = (const pod_u32x4 *)k, *const vp = (const pod_u32x4 *)v;
+    pod_u32x4 *const proxK = (pod_u32x4 *)(a.base + ly.off_proxK), *const proxV = (pod_u32x4 *)(a.base + ly.off_proxV);
+    pod_u32x4 *const distK = (pod_u32x4 *)(a.base + ly.off_distK), *const distV = (pod_u32x4 *)(a.base + ly.off_distV);
+    const size_t total = (size_t)a.n * ly.Hkv << cshift;
+    for (size_t i0 = first; i0 < total; i0 += U * stride) {
+        pod_u32x4 kr[U], vr[U];
+        int p[U], h[U];
+        bool prox[U], low[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const size_t i = i0 + u * stride;
+            const unsigned row = (unsigned)((i < total ? i : 0) >> cshift); // (2^32 rows of at least 128 bytes do not fit any device)
+            p[u] = (int)(row / (unsigned)ly.Hkv);
+            h[u] = (int)(row - (unsigned)p[u] * (unsigned)ly.Hkv);
+            prox[u] = p[u] < ly.S || p[u] >= rec_lo;
+            low[u] = (a.hm.lowest_mask >> h[u]) & 1;
+            if (i < total) {
+                vr[u] = vp[i];
+                if (prox[u] || low[u]) kr[u] = kp[i]; // (distant keys are kept by the lowest layer of a block only)
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const size_t i = i0 + u * stride;
+            if (i >= total) continue;
+            const size_t c = i & ((1u << cshift) - 1);
+            if (prox[u]) {
+                const int slot = p[u] < ly.S ? p[u] : ly.S + (p[u] - ly.S) % ly.W;
+                const size_t pr = ((pod_prox_row0(ly, a.layer, a.b, h[u]) + slot) << cshift) + c;
+                proxK[pr] = kr[u];
+                proxV[pr] = vr[u];
+            } else {
+                const size_t t = (size_t)(p[u] - ly.S);
+                distV[((pod_dist_row0(ly, a.layer, a.b, h[u]) + t) << cshift) + c] = vr[u];
+                if (low[u]) distK[((pod_distk_row0(ly, a.hm, a.b, h[u]) + t) << cshift) + c] = kr[u];
+            }
+        }
+    }
+    if (first == 0) ((int32_t *)(a.base + ly.off_lens))[(size_t)a.layer * ly.B + a.b] = a.n;
+}
+
 // error reporting (pod_api.hip)
 int pod_fail(int code, const char *fmt, ...);
 int pod_hip_fail(hipError_t e, const char *what);
@@ -100,6 +159,7 @@ int pod_hip_fail(hipError_t e, const char *what);
     } while (0)
 
 pod_headmap pod_make_headmap(const pod_cache *c, int layer);
+pod_fill_args pod_make_fill_args(const pod_cache *c, int layer, int seq_slot, int n);
 
 // launchers (each validates nothing: the API layer did)
 int pod_launch_clear_header(const pod_cache *c, hipStream_t st);
@@ -174,6 +234,7 @@ int pod_decode_static_scratch(void **ptr, size_t *bytes);
 int pod_probe_xcds(int *nxcd); // once per device: over how many XCDs one-dimensional launches spread round-robin
 // lowest_mask: bit h set = kv head h takes every logit from (q, k); clear = distant logits from (q_shared, k_shared)
 // k, v, k_shared: rows for positions 0 .. n-1; q, q_shared, out: rows for positions q0 .. n-1
+// fill (may be NULL; q0 = 0): the same launch also builds the cache from k and v, as pod_launch_fill does
 int pod_launch_prefill(const pod_layout &ly, int layer, int n, int q0, const void *q, const void *k, const void *v,
                        const void *q_shared, const void *k_shared, uint64_t lowest_mask, float scale, void *out,
-                       hipStream_t st);
+                       const pod_fill_args *fill, hipStream_t st);

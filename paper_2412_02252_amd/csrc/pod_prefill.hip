@@ -46,6 +46,7 @@ typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 constexpr int kBN = 64;
 constexpr float kNegBig = -1.0e30f;
 constexpr int kPF = 2;        // LDS fragment reads in flight ahead of the MFMA that uses them (1 is slower, 3 no faster)
+constexpr unsigned kResidentWorkgroups = 512; // two one-group workgroups per CU
 constexpr float kLazy = 8.0f; // how far (log2) a tile's maximum may exceed the reference before rescaling
 
 struct prefill_params {
@@ -63,6 +64,9 @@ struct prefill_params {
     // else *flag is raised (the update kernel made the same test and stored nothing)
     int *len, *flag;
     int len_old, len_new;
+    // workgroups fill_lo .. fill_lo + fill_n - 1 of the launch store the prompt's k and v in the cache (none: fill_n = 0)
+    int fill_lo, fill_n;
+    pod_fill_args fill;
 };
 
 // The key tiles that query rows i0 .. i_last walk, in order: nD tiles from tD0 (phase D), nP1 sink tiles from 0, band tiles from tB.
@@ -189,7 +193,14 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
     extern __shared__ __attribute__((aligned(16))) char lds[];   // per key group: [K slot 0][K slot 1][V slot 0][V slot 1]
 
     const int nqt = (p.n + BM - 1) / BM;
-    const int wg = blockIdx.x;
+    int wg = blockIdx.x;
+    if (!TAB && wg >= p.fill_lo) {
+        wg -= p.fill_n;
+        if (wg < p.fill_lo) { // cache construction: nothing here reads what it writes
+            pod_fill_rows<kFillUnroll>(p.fill, p.k, p.v, (size_t)(wg + p.fill_n - p.fill_lo) * blockDim.x + threadIdx.x, (size_t)p.fill_n * blockDim.x);
+            return;
+        }
+    }
     const int kvh = wg % p.Hkv;
     const int rest = wg / p.Hkv;
     const int head = kvh * p.rep + rest % p.rep;
@@ -666,7 +677,7 @@ int pick_key_groups(const pod_layout &ly, int n, int q0, bool has_shared, int *g
 // tile_tab != NULL: keys and values are located through the per-tile address table (k, v, k_shared are not read)
 static int launch_prefill(const pod_layout &ly, int n, int q0, const void *q, const void *k, const void *v,
                           const void *q_shared, const void *k_shared, const unsigned long long *tile_tab, int ntiles,
-                          int *len, int *flag, uint64_t lowest_mask, float scale, void *out, hipStream_t st)
+                          int *len, int *flag, uint64_t lowest_mask, float scale, void *out, const pod_fill_args *fill, hipStream_t st)
 {
     int rc = POD_OK;
     prefill_params p;
@@ -681,7 +692,7 @@ static int launch_prefill(const pod_layout &ly, int n, int q0, const void *q, co
     if (scale <= 0.f) return pod_fail(POD_ERR_INVALID_ARG, "scale must be positive");
     if (tile_tab && ntiles < (n + kBN - 1) / kBN) return pod_fail(POD_ERR_INVALID_ARG, "tile table of %d entries for %d keys", ntiles, n);
     // query tiles of 128 positions, counted from the end: the kernel takes tile (n + 127) / 128 - 1 - blockIdx.x / Hq
-    const dim3 grid((unsigned)((n + 127) / 128 - q0 / 128) * (unsigned)ly.Hq);
+    const unsigned attn = (unsigned)((n + 127) / 128 - q0 / 128) * (unsigned)ly.Hq;
     // raising the dynamic-LDS limit is needed once per device; any host thread may get here first
     static const struct { const void *fn; int lds; } variants[2][2][2] = { // [head dim 64 / 128][table][key groups - 1]
         {{{(const void *)prefill_kernel<64, false, 1>, lds_bytes(64, 1)}, {(const void *)prefill_kernel<64, false, 2>, lds_bytes(64, 2)}},
@@ -705,6 +716,22 @@ static int launch_prefill(const pod_layout &ly, int n, int q0, const void *q, co
     int ks = 1;
     rc = pick_key_groups(ly, n, q0, q_shared != nullptr, &ks);
     if (rc) return rc;
+    // The cache construction rides in the same launch.  Where every attention workgroup is resident at once its workgroups come
+    // last, for the slots that are free from the start or as soon as the short query tiles are done; in launches of several
+    // rounds a few come first and copy next to workgroups that are busy multiplying.  (A launch of its own: n = 777 5.0 us per
+    // layer, 16384 tokens 25 us, and the gap before it.)
+    p.fill_lo = 0x7fffffff; p.fill_n = 0;
+    if (fill) {
+        const bool resident = ks == 2 || attn <= kResidentWorkgroups;
+        const size_t pieces = (size_t)n * ly.Hkv * (ly.D / 8), per_wg = (size_t)256 * ks * (resident ? kFillUnroll : 1);
+        size_t wgs = (pieces + per_wg - 1) / per_wg;
+        const size_t most = resident ? 256 : 32;
+        if (wgs > most) wgs = most;
+        p.fill = *fill;
+        p.fill_n = (int)wgs;
+        p.fill_lo = resident ? (int)attn : 0;
+    }
+    const dim3 grid(attn + (unsigned)p.fill_n);
     const auto &var = variants[ly.D == 128][tile_tab != nullptr][ks - 1];
     void *args[] = {&p};
     POD_HIP_TRY(hipLaunchKernel(var.fn, grid, dim3(256 * ks), args, var.lds, st));
@@ -714,15 +741,15 @@ static int launch_prefill(const pod_layout &ly, int n, int q0, const void *q, co
 
 int pod_launch_prefill(const pod_layout &ly, int layer, int n, int q0, const void *q, const void *k, const void *v,
                        const void *q_shared, const void *k_shared, uint64_t lowest_mask, float scale, void *out,
-                       hipStream_t st)
+                       const pod_fill_args *fill, hipStream_t st)
 {
     (void)layer;
-    return launch_prefill(ly, n, q0, q, k, v, q_shared, k_shared, nullptr, 0, nullptr, nullptr, lowest_mask, scale, out, st);
+    return launch_prefill(ly, n, q0, q, k, v, q_shared, k_shared, nullptr, 0, nullptr, nullptr, lowest_mask, scale, out, fill, st);
 }
 
 int pod_launch_prefill_tiles(const pod_layout &ly, int n, int q0, const void *q, const void *q_shared,
                              const unsigned long long *tile_tab, int ntiles, int *len, int *flag, uint64_t lowest_mask, float scale,
                              void *out, hipStream_t st)
 {
-    return launch_prefill(ly, n, q0, q, nullptr, nullptr, q_shared, nullptr, tile_tab, ntiles, len, flag, lowest_mask, scale, out, st);
+    return launch_prefill(ly, n, q0, q, nullptr, nullptr, q_shared, nullptr, tile_tab, ntiles, len, flag, lowest_mask, scale, out, nullptr, st);
 }
