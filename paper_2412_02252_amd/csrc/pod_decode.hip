@@ -69,7 +69,7 @@ struct decode_hot { // exactly two 64-byte lines, read in one go at kernel entry
     int32_t chunk;       // tokens per workgroup: distant chunks in the low 16 bits, proximal chunks in the high 16 bits
     int32_t max_nd;      // distant chunk slots per (sequence, head)
     int32_t nc;          // all chunk slots per (sequence, head): max_nd + proximal slots
-    int32_t use_hlen;    // 1: hlen[] holds the host mirror's length of every slot < B
+    int32_t use_hlen;    // bit 0: hlen[] holds the host mirror's length of every slot < B; bit 1 (FUSE 2 only): the step has a workgroup of its own
     // line 1: queries, partial results, device-side lengths
     const pod_bf16 *q, *q_shared;
     float scale_log2e;
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
     const u32x4 *kdist = hot.kdist, *vdist = hot.vdist, *kprox = hot.kprox, *vprox = hot.vprox;
     const int cd = hot.cd, prows = hot.prows, hkv = hot.hkv, max_nd = hot.max_nd;
     const int chunk_p = (int)((unsigned)hot.chunk >> 16);
-    const bool use_hlen = hot.use_hlen != 0;
+    const bool use_hlen = (hot.use_hlen & 1) != 0;
     // The host mirror's length is always within the buffers; whether it agrees with context_lens
     // and the device-side lengths is checked where the partials are merged (the combine kernel or the last
     // workgroup), which zeroes the output and raises the flag if not.  Without the mirror (batches beyond
@@ -414,9 +414,11 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
     // partials.  FUSE 2: the workgroup of the LAST distant piece, which is the pair's shortest on average (the first
     // proximal piece, which hosted the step before, is its longest: its tile loop ended 1.35 us after the others' and
     // its pair waited for it); the first proximal piece where there is no distant token, also when the cache is empty
-    // and that workgroup has no piece of its own.
-    const bool hosts_step = STEP && c == (FUSE == 2 && nd_eff > 0 ? nd_eff - 1 : max_nd);
-    const int expected = nd_eff + (FUSE == 2 && np_eff == 0 ? 1 : np_eff);
+    // and that workgroup has no piece of its own.  Launches that leave CUs free have one more workgroup per pair, behind the
+    // pieces' (c == nc), that takes the step and walks nothing.
+    const bool own_host = FUSE == 2 && (hot.use_hlen & 2) != 0;
+    const bool hosts_step = STEP && c == (own_host ? hot.nc : FUSE == 2 && nd_eff > 0 ? nd_eff - 1 : max_nd);
+    const int expected = nd_eff + (own_host ? np_eff + 1 : FUSE == 2 && np_eff == 0 ? 1 : np_eff);
     if (hosts_step) step_workgroup<D, LOC, NW, MODE>(p, hot, b, h, n, head_arg);
     const bool distant = c < max_nd;
     const int region_len = distant ? n_dist : n_prox;
@@ -732,7 +734,8 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
     }
     __syncthreads();
     const int NC = hot.nc + (STEP ? 1 : 0); // (a step keeps one more slot per head: step_workgroup's)
-    for (int t = threadIdx.x; t < hot.rep * D; t += blockDim.x) {
+    const int values = own_host && hosts_step ? 0 : hot.rep * D; // (a workgroup that only took the step has stored its partial)
+    for (int t = threadIdx.x; t < values; t += blockDim.x) {
         const int head = t / D, dim = t % D;
         float M = sm_m[0][head];
 #pragma unroll
@@ -770,7 +773,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
         const int last = arrive_last<LOC>(p.tickets + (size_t)b * hkv + h, expected);
         const unsigned long long tr_t3 = p.trace ? wall_clock64() : 0;
         auto trace_out = [&]() {
-            const size_t wg = LOC ? (size_t)blockIdx.x : ((size_t)b * hkv + h) * hot.nc + c;
+            const size_t wg = LOC ? (size_t)blockIdx.x : ((size_t)b * hkv + h) * gridDim.x + c;
             if (p.trace && threadIdx.x == 0 && wg < (size_t)p.trace_cap) {
                 unsigned long long *t = p.trace + 8 * wg;
                 t[0] = ((unsigned long long)(b * hkv + h) << 32) | (unsigned)c | (last ? 0x80000000u : 0u);
@@ -1827,7 +1830,6 @@ int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *
     p.walk_rev = c->walk_turns ? ((layer - c->lowest[(size_t)layer * H]) & 1) : 0;
     // 0: separate combine kernel; 1: the last workgroup of a (sequence, kv head) pair merges; 2: 1 + the cache update
     p.step = step ? 1 : 0;
-    // XCD-local hand-off: only where the pairs spread evenly over the XCDs (else some XCDs would sit idle)
     const int npairs = B * ly.Hkv;
     p.nxcd = c->nxcd > 0 ? c->nxcd : 1;
     p.npairs = npairs;
@@ -1875,10 +1877,21 @@ int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *
     p.hot.part_acc = (float *)ws;
     p.hot.part_ml = (float *)((char *)ws + acc_bytes);
 
-    const size_t WGS = (size_t)p.hot.nc;   // workgroups per (sequence, kv head) pair
-    p.slots = (int32_t)WGS;
     const int fuse = step ? (merge_inside ? 2 : 3) : (merge_inside ? 1 : 0);
-    const bool loc = merge_inside && c->xcd_local && c->nxcd >= 1 && (npairs % c->nxcd == 0 || npairs >= 8 * c->nxcd);
+    // XCD-local hand-off: where the pairs spread evenly over the XCDs (else some would sit idle while others stream), or where
+    // they are so few and short that each XCD's pieces have a CU each: the launch is then its latency, and one L2 hands a
+    // partial over sooner than memory does (per step: 2 pairs x 64 at 2048 tokens 7.05 -> 6.61 us, 3 pairs x 128 with 8 query
+    // heads 10.4 -> 9.1, 1 pair x 128 with 16 13.8 -> 11.2; at the line, 31 pieces of 256 tokens x 128 on one XCD, 18.1 either way).
+    const long xcd_cus = c->nxcd >= 1 ? cus / c->nxcd : 0, xcd_pairs = c->nxcd >= 1 ? (npairs + c->nxcd - 1) / c->nxcd : 0;
+    const bool loc = merge_inside && c->xcd_local && c->nxcd >= 1 &&
+                     (npairs % c->nxcd == 0 || npairs >= 8 * c->nxcd || xcd_pairs * p.hot.nc <= xcd_cus);
+    // The step's own workgroup where every workgroup of the launch still gets a CU (of its XCD): the new token's chain of short
+    // dependent accesses then runs beside the pieces instead of in front of one (2 pairs x 64 at 2048 tokens 8.92 -> 7.05 us,
+    // 8 pairs x 128 at 2048 9.8 -> 8.3).  Full launches keep the host inside: one more workgroup there waits for a CU.
+    const bool own_host = fuse == 2 && (loc ? xcd_pairs * (p.hot.nc + 1) <= xcd_cus : (long)npairs * (p.hot.nc + 1) <= cus);
+    if (own_host) p.hot.use_hlen |= 2;
+    const size_t WGS = (size_t)p.hot.nc + (own_host ? 1 : 0);   // workgroups per (sequence, kv head) pair
+    p.slots = (int32_t)WGS;
     const size_t loc_wgs = (size_t)((npairs + p.nxcd - 1) / p.nxcd) * p.nxcd * WGS;
     if (loc && loc_wgs > 0x7fffffffu) return pod_fail(POD_ERR_CAPACITY, "launch too large");
     const dim3 grid = loc ? dim3((unsigned)loc_wgs) : dim3((unsigned)WGS, (unsigned)ly.Hkv, (unsigned)B);
