@@ -299,3 +299,35 @@ def test_steps_and_reuse_steps_on_seeded_random_shapes(shape):
         for b in range(len(lens)):
             c.assert_cache_equal(layer, b)
     c.gpu.pod_cache_check()
+
+
+@pytest.mark.parametrize("reuse", [False, True], ids=["plain", "score-reuse"])
+@pytest.mark.parametrize("n", [7807, 8063, 8319])
+def test_who_takes_the_step_where_one_xcds_cus_run_out(n, reuse):
+    """One (sequence, kv head) pair, pieces of 256 tokens (the reading layer's pieces are cut for the same one round): 31 pieces
+    and the step's own workgroup have a CU each on one XCD; with 32 the last distant piece takes the step; more pieces than that
+    leave the XCD."""
+    c = Case(2, 2, 2, 1, 64, 8, 120, 1, 8400, seed=530)
+    scores = c.gpu.new_score_buffer() if reuse else None
+    for layer in range(2):
+        c.fill(layer, 0, n)
+    for s in range(2):
+        for layer in range(2):
+            out = c.step_reuse(layer, [n + s], scores) if reuse else c.step(layer, [n + s])
+            assert_close(out, c.decode_ref(layer, [n + s + 1]), f"step {s} layer {layer}")
+    for layer in range(2):
+        c.assert_cache_equal(layer, 0)
+    c.gpu.pod_cache_check()
+
+
+def test_steps_from_empty_caches_with_more_pairs_than_free_cus():
+    """160 pairs of one or two pieces: no CU is left for a workgroup that only takes the step, also while the cache is empty
+    and that workgroup's piece with it."""
+    B, S, W = 10, 4, 12
+    c = Case(2, 2, 16, 16, 64, S, W, B, 40, seed=531)
+    for p in range(20):
+        for layer in range(2):
+            assert_close(c.step(layer, [p] * B), c.decode_ref(layer, [p + 1] * B), f"position {p} layer {layer}")
+    for layer in range(2):
+        c.assert_cache_equal(layer, B - 1)
+    c.gpu.pod_cache_check()
