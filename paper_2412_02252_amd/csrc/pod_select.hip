@@ -102,16 +102,24 @@ constexpr int kSelChunkBlocks = 8;
 constexpr int kSelChunkRows = 32 * kSelChunkBlocks;
 template <int D> constexpr int kSelRowBytes = D * 2 + 16;
 
+// A thread's pieces are all requested before the first is stored: one after the other they are a chain of as many round trips
+// (one wave-wide load per round trip of an L2).
 template <int D>
 __device__ inline void stage_query_rows(const select_params &p, int h, int row0, char *lds)
 {
     constexpr int cpr = D / 8; // 16-byte pieces per row
-    for (int idx = threadIdx.x; idx < kSelChunkRows * cpr; idx += kSelThreads) {
-        const int row = idx / cpr, c = idx % cpr;
-        sel_u32x4 val = {0, 0, 0, 0}; // rows past the end: zeros (their logits are never used)
-        if (row0 + row < p.R) val = *(const sel_u32x4 *)(query_row(p, h, row0 + row, D) + c * 8);
-        *(sel_u32x4 *)(lds + row * kSelRowBytes<D> + c * 16) = val;
+    constexpr int PER = kSelChunkRows * cpr / kSelThreads, RPS = kSelThreads / cpr; // pieces per thread; rows between two of them
+    static_assert(kSelChunkRows * cpr % kSelThreads == 0 && kSelThreads % cpr == 0, "");
+    const int c = threadIdx.x % cpr, first = threadIdx.x / cpr;
+    sel_u32x4 val[PER];
+#pragma unroll
+    for (int x = 0; x < PER; ++x) {
+        const int row = row0 + first + x * RPS;
+        val[x] = sel_u32x4{0, 0, 0, 0}; // rows past the end: zeros (their logits are never used)
+        if (row < p.R) val[x] = *(const sel_u32x4 *)(query_row(p, h, row, D) + c * 8);
     }
+#pragma unroll
+    for (int x = 0; x < PER; ++x) *(sel_u32x4 *)(lds + (first + x * RPS) * kSelRowBytes<D> + c * 16) = val[x];
 }
 
 template <int D>
@@ -137,6 +145,13 @@ __global__ __launch_bounds__(kSelThreads) void select_stat_kernel(select_params 
     const int nblk = (p.R - row0 + 31) / 32 < kSelChunkBlocks ? (p.R - row0 + 31) / 32 : kSelChunkBlocks; // row blocks in use
     __shared__ __align__(16) char ldsq[kSelChunkRows * kSelRowBytes<D>];
     __shared__ float2 red[kSelThreads / 64][kSelChunkRows];
+    sel_u32x4 kf[D / 16], kn[D / 16];
+    auto key_row = [&](int key0) {
+        const int key = key0 + (lane & 31) < p.n ? key0 + (lane & 31) : p.n - 1;
+        return key_address(p, h, key, D);
+    };
+    int key0 = key_lo + wave * 32;
+    if (key0 < key_hi) load_row_fragments<D>(key_row(key0), lane, kn); // (on their way while the query rows are staged)
     stage_query_rows<D>(p, h, row0, ldsq);
     __syncthreads();
     float m[kSelChunkBlocks], l[kSelChunkBlocks];
@@ -148,20 +163,11 @@ __global__ __launch_bounds__(kSelThreads) void select_stat_kernel(select_params 
         l[rb] = 0.f;
         qpos[rb] = p.n - p.obs + (r < p.R ? r : 0) / p.rep;
     }
-    sel_u32x4 kf[D / 16], kn[D / 16];
-    auto key_row = [&](int key0) {
-        const int key = key0 + (lane & 31) < p.n ? key0 + (lane & 31) : p.n - 1;
-        return key_address(p, h, key, D);
-    };
-    int key0 = key_lo + wave * 32;
-    if (key0 < key_hi) load_row_fragments<D>(key_row(key0), lane, kn);
     for (; key0 < key_hi; key0 += kSelKeysPerIter) {
 #pragma unroll
         for (int kk = 0; kk < D / 16; ++kk) kf[kk] = kn[kk];
         if (key0 + kSelKeysPerIter < key_hi) load_row_fragments<D>(key_row(key0 + kSelKeysPerIter), lane, kn); // next block's keys
-#pragma unroll
-        for (int rb = 0; rb < kSelChunkBlocks; ++rb) {
-            if (rb >= nblk) continue; // (the same in every thread)
+        auto logits = [&](int rb) {
             sel_u32x4 qf[D / 16];
             lds_row_fragments<D>(ldsq, rb, lane, qf);
             sel_f32x16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
@@ -169,29 +175,42 @@ __global__ __launch_bounds__(kSelThreads) void select_stat_kernel(select_params 
             for (int kk = 0; kk < D / 16; ++kk)
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(sel_bf16x8, kf[kk]),
                                                                __builtin_bit_cast(sel_bf16x8, qf[kk]), acc, 0, 0, 0);
-            // accumulator e of this lane: key key0 + 8 (e / 4) + 4 (lane / 32) + e % 4, query row lane % 32 of block rb
-            float s[16], tmax = -INFINITY;
-            if (key0 + 31 <= p.n - p.obs) { // every query of the window sees all 32 keys (whole wave)
+            return acc;
+        };
+        // accumulator e of this lane: key key0 + 8 (e / 4) + 4 (lane / 32) + e % 4, query row lane % 32 of block rb
+        // (the scale is positive: it commutes with the maximum, and inside the exponent it is half of a multiply-add)
+        auto add_tile = [&](int rb, const sel_f32x16 &acc) {
+            float tmax = acc[0];
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    s[e] = acc[e] * p.scale_log2;
-                    tmax = fmaxf(tmax, s[e]);
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int ke = key0 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-                    s[e] = ke <= qpos[rb] ? acc[e] * p.scale_log2 : -INFINITY; // qpos < n: keys past the end drop out too
-                    tmax = fmaxf(tmax, s[e]);
-                }
-            }
+            for (int e = 1; e < 16; ++e) tmax = fmaxf(tmax, acc[e]);
             if (tmax > -INFINITY) {
-                const float mn = fmaxf(m[rb], tmax);
-                float add = 0.f;
+                const float mn = fmaxf(m[rb], tmax * p.scale_log2);
+                float add[2] = {0.f, 0.f};
 #pragma unroll
-                for (int e = 0; e < 16; ++e) add += fast_exp2(s[e] - mn);
-                l[rb] = l[rb] * exp2f(m[rb] - mn) + add; // m = -inf: l is 0 and stays 0
+                for (int e = 0; e < 16; ++e) add[e & 1] += fast_exp2(__builtin_fmaf(acc[e], p.scale_log2, -mn));
+                l[rb] = l[rb] * fast_exp2(m[rb] - mn) + (add[0] + add[1]); // m = -inf: l is 0 and stays 0
                 m[rb] = mn;
+            }
+        };
+        if (nblk == kSelChunkBlocks && key0 + 31 <= p.n - p.obs) {
+            // all row blocks in use, and every query of the window sees all 32 keys: the next block's products run while the
+            // vector pipe works on this one's
+            sel_f32x16 next = logits(0);
+#pragma unroll
+            for (int rb = 0; rb < kSelChunkBlocks; ++rb) {
+                const sel_f32x16 acc = next;
+                if (rb + 1 < kSelChunkBlocks) next = logits(rb + 1);
+                add_tile(rb, acc);
+            }
+        } else {
+#pragma unroll
+            for (int rb = 0; rb < kSelChunkBlocks; ++rb) {
+                if (rb >= nblk) continue; // (the same in every thread)
+                sel_f32x16 acc = logits(rb);
+                const int seen = qpos[rb] - key0 - 4 * (lane >> 5); // qpos < n: keys past the end drop out too
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[e] = 8 * (e >> 2) + (e & 3) <= seen ? acc[e] : -INFINITY;
+                add_tile(rb, acc);
             }
         }
     }
@@ -238,7 +257,7 @@ __global__ __launch_bounds__(kSelThreads) void select_reduce_kernel(select_param
 // Second pass.  Workgroup = (kSelVoteKeys distant keys, kv head); a wave takes key blocks of 32 and, per key block,
 // every chunk's row blocks: S = Q K^T, a lane owns key lane % 32 and adds up the weights of 16 query rows per MFMA
 // tile.  A distant key is older than every query of the observation window (obs <= W): no causal test.
-constexpr int kSelVoteBlocks = 4;                                  // key blocks per wave
+constexpr int kSelVoteBlocks = 2;                                  // key blocks per wave (4 leave half of the wave slots empty: 20.0 us, 2: 17.3, 1: 19.1)
 constexpr int kSelVoteKeys = kSelVoteBlocks * kSelKeysPerIter;     // keys per workgroup
 
 template <int D>
@@ -254,7 +273,14 @@ __global__ __launch_bounds__(kSelThreads) void select_vote_kernel(select_params 
     float vote[kSelVoteBlocks];
 #pragma unroll
     for (int kb = 0; kb < kSelVoteBlocks; ++kb) vote[kb] = 0.f;
+    sel_u32x4 kn[D / 16];
+    auto request_keys = [&](int kb) { // (clamped past the end: what is loaded there is not used)
+        const int key0 = wg_key0 + (kb * (kSelThreads / 64) + wave) * 32;
+        const int key = key0 + (lane & 31) < dist_hi ? key0 + (lane & 31) : dist_hi - 1;
+        load_row_fragments<D>(key_address(p, h, key, D), lane, kn);
+    };
     for (int row0 = 0; row0 < p.R; row0 += kSelChunkRows) {
+        request_keys(0);
         if (row0) __syncthreads(); // everyone is done with the previous chunk
         stage_query_rows<D>(p, h, row0, ldsq);
         {
@@ -267,10 +293,11 @@ __global__ __launch_bounds__(kSelThreads) void select_vote_kernel(select_params 
         for (int kb = 0; kb < kSelVoteBlocks; ++kb) {
             const int key0 = wg_key0 + (kb * (kSelThreads / 64) + wave) * 32;
             if (key0 >= dist_hi) continue; // (whole wave; no barrier inside)
-            const int key = key0 + (lane & 31) < dist_hi ? key0 + (lane & 31) : dist_hi - 1;
             sel_u32x4 kf[D / 16];
-            load_row_fragments<D>(key_address(p, h, key, D), lane, kf);
-            for (int rb = 0; rb < nblk; ++rb) {
+#pragma unroll
+            for (int kk = 0; kk < D / 16; ++kk) kf[kk] = kn[kk];
+            if (kb + 1 < kSelVoteBlocks) request_keys(kb + 1);
+            auto logits = [&](int rb) {
                 sel_u32x4 qf[D / 16];
                 lds_row_fragments<D>(ldsq, rb, lane, qf);
                 sel_f32x16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
@@ -278,7 +305,10 @@ __global__ __launch_bounds__(kSelThreads) void select_vote_kernel(select_params 
                 for (int kk = 0; kk < D / 16; ++kk)
                     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(sel_bf16x8, qf[kk]),
                                                                    __builtin_bit_cast(sel_bf16x8, kf[kk]), acc, 0, 0, 0);
-                // accumulator e of this lane: query row rb * 32 + 8 (e / 4) + 4 (lane / 32) + e % 4 of the chunk, key lane % 32
+                return acc;
+            };
+            // accumulator e of this lane: query row rb * 32 + 8 (e / 4) + 4 (lane / 32) + e % 4 of the chunk, key lane % 32
+            auto add_tile = [&](int rb, const sel_f32x16 &acc) {
 #pragma unroll
                 for (int e4 = 0; e4 < 4; ++e4) {
                     typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -286,6 +316,17 @@ __global__ __launch_bounds__(kSelThreads) void select_vote_kernel(select_params 
 #pragma unroll
                     for (int j = 0; j < 4; ++j) vote[kb] += fast_exp2(acc[4 * e4 + j] * p.scale_log2 - bq[j]);
                 }
+            };
+            if (nblk == kSelChunkBlocks) { // (the next block's products beside this one's exponentials, as in the first pass)
+                sel_f32x16 next = logits(0);
+#pragma unroll
+                for (int rb = 0; rb < kSelChunkBlocks; ++rb) {
+                    const sel_f32x16 acc = next;
+                    if (rb + 1 < kSelChunkBlocks) next = logits(rb + 1);
+                    add_tile(rb, acc);
+                }
+            } else {
+                for (int rb = 0; rb < nblk; ++rb) add_tile(rb, logits(rb));
             }
         }
     }
