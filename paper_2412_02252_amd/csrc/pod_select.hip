@@ -346,12 +346,18 @@ __device__ inline unsigned ordered_bits(float x)
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// Selection, one workgroup per kv head, over the pooled votes: find the keep-th largest by four rounds of 8-bit
-// histograms over the ordered bit patterns, then write the indices of the selected tokens in ascending order
-// (everything above the threshold, and the first `need` of those equal to it).  A thread owns a run of
-// ceil(m / 1024) consecutive tokens and keeps the first kTopCache of them in registers, so the five passes read
+// Selection, one workgroup per kv head, over the pooled votes: find the keep-th largest ordered bit pattern by histograms of
+// kTopBins equal parts of the range that still holds it - first from the smallest to the largest pattern there is, then inside
+// the part that was hit, a bit pattern of 32 bits in three rounds at most, the votes of one prompt in two - and write the
+// indices of the selected tokens in ascending order (everything above the threshold, and the first `need` of those equal to
+// it).  What a round costs are its LDS atomics, and lanes that hit the same counter take turns: parts of the range that occurs
+// keep them apart, where digits of the pattern (sign and exponent first, which all votes share) had them queue: 14272 tokens,
+// four rounds of 8-bit digits 27.2 us, this 18.4.  A thread owns a run of
+// ceil(m / 1024) consecutive tokens and keeps the first kTopCache of them in registers, so the passes read
 // memory only for prompts of more than 1024 * kTopCache distant tokens; token order is thread order, so one scan
 // over the threads' counts gives every thread the place of its first selected token.
+constexpr int kTopBins = 4096;
+static_assert(kTopBins == 4 * kTopThreads, "a thread searches four counters");
 constexpr int kTopCache = 32;
 
 __device__ inline float pooled_vote(const float *__restrict__ v, int t, int m, int r, int width, int use_max)
@@ -389,75 +395,94 @@ __global__ __launch_bounds__(kTopThreads) void select_top_kernel(const float *__
     const int t0 = tid * span;
     unsigned ck[kTopCache]; // ordered bit patterns of the pooled votes of tokens t0 + j
 #pragma unroll
-    for (int j = 0; j < kTopCache; ++j) { // (loads of clamped addresses, all in flight; what is not this thread's is zeroed after)
+    for (int j = 0; j < kTopCache; ++j) { // (loads of clamped addresses, all in flight before the first is used)
         const int t = t0 + j < m ? t0 + j : m - 1;
-        ck[j] = ordered_bits(pl[t]);
+        ck[j] = 0u;
+        if (j < span) ck[j] = __builtin_bit_cast(unsigned, pl[t]); // (span is the same in every thread)
     }
 #pragma unroll
-    for (int j = 0; j < kTopCache; ++j)
-        if (!(j < span && t0 + j < m)) ck[j] = 0u;
-    __shared__ unsigned hist[256];
-    __shared__ unsigned s_prefix, s_need;
+    for (int j = 0; j < kTopCache; ++j) ck[j] = j < span && t0 + j < m ? ordered_bits(__builtin_bit_cast(float, ck[j])) : 0u;
+    __shared__ __align__(16) unsigned hist[kTopBins];
+    __shared__ unsigned s_lo, s_need;
     __shared__ unsigned wave_tot[2][kTopThreads / 64];
-    if (tid == 0) { s_prefix = 0; s_need = (unsigned)keep; }
-    __syncthreads();
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        if (tid < 256) hist[tid] = 0;
-        __syncthreads();
-        const unsigned prefix = s_prefix, need_in = s_need;
-        // The first round's digit is the sign and most of the exponent: pooled votes share a handful of values, and
-        // one LDS atomic per token would queue up on those few counters, so there a wave adds each distinct digit once.
-        auto count = [&](unsigned key, bool valid) {
-            const unsigned digit = (key >> shift) & 255u;
-            if (shift == 24) {
-                unsigned long long todo = __ballot(valid);
-                while (todo) {
-                    const int leader = __ffsll((long long)todo) - 1;
-                    const unsigned d = (unsigned)__builtin_amdgcn_readlane((int)digit, leader); // (leader is the same in every lane)
-                    const unsigned long long same = __ballot(valid && digit == d);
-                    if (lane == leader) atomicAdd(&hist[d], (unsigned)__popcll(same));
-                    todo &= ~same;
-                }
-            } else if (valid && (key >> (shift + 8)) == (prefix >> (shift + 8))) {
-                atomicAdd(&hist[digit], 1u);
-            }
-        };
+    // every token of this thread's run and its key, in order (those that are not in registers eight loads at a time)
+    auto each_key = [&](auto &&f) {
 #pragma unroll
         for (int j = 0; j < kTopCache; ++j)
-            if (j < span) count(ck[j], t0 + j < m); // (the same test in every thread)
-        for (int j = kTopCache; j < span; ++j) count(t0 + j < m ? ordered_bits(pl[t0 + j]) : 0u, t0 + j < m);
-        __syncthreads();
-        // thread d < 256: candidates with digit >= d (suffix sums by wave, then over the waves above); the digit whose
-        // bucket holds the need-th largest candidate is the one with fewer than `need` above it and at least `need` from it on
-        unsigned mine = 0, from_here = 0;
-        if (tid < 256) {
-            mine = hist[tid];
-            from_here = mine;
-            for (int o = 1; o < 64; o <<= 1) {
-                const unsigned up = __shfl_down(from_here, o);
-                if (lane + o < 64) from_here += up;
-            }
-            if (lane == 0) wave_tot[0][wave] = from_here;
+            if (j < span && t0 + j < m) f(t0 + j, ck[j]);
+        for (int j = kTopCache; j < span; j += 8) {
+            float v[8];
+#pragma unroll
+            for (int x = 0; x < 8; ++x) v[x] = pl[t0 + j + x < m ? t0 + j + x : m - 1];
+#pragma unroll
+            for (int x = 0; x < 8; ++x)
+                if (j + x < span && t0 + j + x < m) f(t0 + j + x, ordered_bits(v[x]));
         }
-        __syncthreads();
-        if (tid < 256) {
-            for (int w = wave + 1; w < 4; ++w) from_here += wave_tot[0][w];
-            const unsigned above = from_here - mine;
-            if (above < need_in && need_in <= from_here) {
-                s_prefix = prefix | ((unsigned)tid << shift);
-                s_need = need_in - above;
-            }
-        }
-        __syncthreads();
+    };
+    unsigned lo = ~0u, hi = 0u; // smallest and largest key
+    each_key([&](int, unsigned key) { lo = key < lo ? key : lo; hi = key > hi ? key : hi; });
+    for (int o = 32; o >= 1; o >>= 1) {
+        const unsigned a = __shfl_xor(lo, o), b = __shfl_xor(hi, o);
+        lo = a < lo ? a : lo;
+        hi = b > hi ? b : hi;
     }
-    const unsigned thr = s_prefix, need = s_need; // need >= 1 entries equal to the threshold are taken, earliest first
+    if (lane == 0) { wave_tot[0][wave] = lo; wave_tot[1][wave] = hi; }
+    __syncthreads();
+    lo = wave_tot[0][lane % (kTopThreads / 64)];
+    hi = wave_tot[1][lane % (kTopThreads / 64)];
+    for (int o = kTopThreads / 128; o >= 1; o >>= 1) {
+        const unsigned a = __shfl_xor(lo, o), b = __shfl_xor(hi, o);
+        lo = a < lo ? a : lo;
+        hi = b > hi ? b : hi;
+    }
+    unsigned need = (unsigned)keep; // the threshold is the need-th largest of the keys in [lo, hi]; the same in every thread, like lo and hi
+    for (;;) {
+        const unsigned range = hi - lo;
+        const int shift = range < kTopBins ? 0 : 32 - 12 - __builtin_clz(range); // range >> shift < kTopBins
+        __syncthreads(); // (wave_tot, hist and s_* are read before they are written again)
+#pragma unroll
+        for (int x = 0; x < kTopBins / kTopThreads; ++x) hist[x * kTopThreads + tid] = 0;
+        __syncthreads();
+        each_key([&](int, unsigned key) { if (key >= lo && key <= hi) atomicAdd(&hist[(key - lo) >> shift], 1u); });
+        __syncthreads();
+        // thread t takes counters 4 t .. 4 t + 3; keys from its first counter on: its own, those of the wave's higher lanes, of the higher waves
+        unsigned c[4], own = 0;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) { c[x] = hist[4 * tid + x]; own += c[x]; }
+        unsigned from_here = own;
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned up = __shfl_down(from_here, o);
+            if (lane + o < 64) from_here += up;
+        }
+        if (lane == 0) wave_tot[0][wave] = from_here;
+        __syncthreads();
+        {   // what the waves above hold: their totals in one read, added up in a butterfly
+            unsigned up = lane > wave && lane < kTopThreads / 64 ? wave_tot[0][lane] : 0u;
+            for (int o = kTopThreads / 128; o >= 1; o >>= 1) up += __shfl_xor(up, o);
+            from_here += __shfl(up, 0);
+        }
+        unsigned above = from_here - own;
+        if (above < need && need <= from_here) { // exactly one thread: the need-th largest lies in one of its counters
+#pragma unroll
+            for (int x = 3; x >= 0; --x) {
+                if (above < need && need <= above + c[x]) {
+                    s_lo = lo + ((unsigned)(4 * tid + x) << shift);
+                    s_need = need - above;
+                }
+                above += c[x];
+            }
+        }
+        __syncthreads();
+        const unsigned part = (1u << shift) - 1;
+        lo = s_lo;
+        hi = hi - lo < part ? hi : lo + part;
+        need = s_need;
+        if (shift == 0) break;
+    }
+    const unsigned thr = lo; // need >= 1 entries equal to the threshold are taken, earliest first
     // tokens above / at the threshold in this thread's run, then in all runs before it
     unsigned n_gt = 0, n_eq = 0;
-#pragma unroll
-    for (int j = 0; j < kTopCache; ++j)
-        if (j < span && t0 + j < m) { n_gt += ck[j] > thr; n_eq += ck[j] == thr; }
-    for (int j = kTopCache; j < span; ++j)
-        if (t0 + j < m) { const unsigned key = ordered_bits(pl[t0 + j]); n_gt += key > thr; n_eq += key == thr; }
+    each_key([&](int, unsigned key) { n_gt += key > thr; n_eq += key == thr; });
     unsigned inc_gt = n_gt, inc_eq = n_eq;
     for (int o = 1; o < 64; o <<= 1) {
         const unsigned a = __shfl_up(inc_gt, o), b = __shfl_up(inc_eq, o);
@@ -466,8 +491,13 @@ __global__ __launch_bounds__(kTopThreads) void select_top_kernel(const float *__
     if (lane == 63) { wave_tot[0][wave] = inc_gt; wave_tot[1][wave] = inc_eq; }
     __syncthreads();
     unsigned gt_before = inc_gt - n_gt, eq_before = inc_eq - n_eq;
-    for (int w = 0; w < wave; ++w) { gt_before += wave_tot[0][w]; eq_before += wave_tot[1][w]; }
-    auto place = [&](int t, unsigned key) {
+    {   // (the waves below, as above)
+        unsigned a = lane < wave ? wave_tot[0][lane] : 0u, b = lane < wave ? wave_tot[1][lane] : 0u;
+        for (int o = kTopThreads / 128; o >= 1; o >>= 1) { a += __shfl_xor(a, o); b += __shfl_xor(b, o); }
+        gt_before += __shfl(a, 0);
+        eq_before += __shfl(b, 0);
+    }
+    each_key([&](int t, unsigned key) {
         const bool gt = key > thr, eq = key == thr;
         if (gt || (eq && eq_before < need)) {
             const unsigned pos = gt_before + (eq_before < need ? eq_before : need);
@@ -475,12 +505,7 @@ __global__ __launch_bounds__(kTopThreads) void select_top_kernel(const float *__
         }
         gt_before += gt;
         eq_before += eq;
-    };
-#pragma unroll
-    for (int j = 0; j < kTopCache; ++j)
-        if (j < span && t0 + j < m) place(t0 + j, ck[j]);
-    for (int j = kTopCache; j < span; ++j)
-        if (t0 + j < m) place(t0 + j, ordered_bits(pl[t0 + j]));
+    });
 }
 
 struct compact_params {

@@ -109,6 +109,23 @@ def test_selection_is_identical_on_the_same_float32_votes(m, keep, width, kind):
     assert np.array_equal(sel.cpu().numpy()[0], want)
 
 
+@pytest.mark.parametrize("m,keep", [(3000, 1), (3000, 1234), (36000, 35999)])
+def test_selection_over_every_range_of_votes(m, keep):
+    """Ranges of bit patterns that take one, two and three rounds of counting, and one value for all."""
+    rng = np.random.default_rng(m + keep)
+    votes = np.stack([np.full(m, np.float32(0.25)),
+                      (np.float32(1.0) + rng.integers(0, 4000, m).astype(np.float32) * np.float32(2.0 ** -23)).astype(np.float32),
+                      (1.0 + rng.random(m)).astype(np.float32),
+                      (rng.choice([-1.0, 1.0], m) * 10.0 ** rng.uniform(-37, 37, m)).astype(np.float32),
+                      np.where(np.arange(m) == m // 2, np.float32(3e38), rng.random(m).astype(np.float32) * np.float32(1e-3))]).astype(np.float32)
+    Hkv, S, W = len(votes), 2, 6
+    n = m + S + W
+    cache = pod.PodCache(pod.make_config(1, 1, Hkv, Hkv, 64, S, W, 1, n), DEV, guard_bytes=4096)
+    sel = torch.full((1, Hkv, keep), -1, dtype=torch.int32, device=DEV)
+    cache.pod_select_top(0, n, torch.from_numpy(votes).to(DEV), 1, pod.POOL_MAX, keep, sel, cache.new_select_workspace(n, 1, keep))
+    assert np.array_equal(sel.cpu().numpy()[0], ps.select_top(ps.pool_votes(votes, 1, "max"), keep))
+
+
 def _prefill(c, n, seq, obs, lowest_sel_inputs):
     """Stores a prompt of n tokens at every layer (through the prefill call); keeps, per lowest layer, (q_obs, k)."""
     for layer in range(c.L):
