@@ -513,9 +513,10 @@ struct compact_params {
     pod_layout ly;
     pod_headmap hm;
     int layer, b, n, keep;
+    int rows;                         // keep + W, or keep where the ring of the shorter sequence starts at the same slot
     const int32_t *sel_all;           // [L][Hkv][keep]
     int32_t sel_layer[kMaxKvHeads];   // the lowest layer of kv head h's block: whose selection h follows here
-    uint4 *ws;                        // [2][Hkv][keep + W][D] bf16: rows on their way (keys, then values)
+    uint4 *ws;                        // [2][Hkv][rows][D] bf16: rows on their way (keys, then values)
 };
 
 // stage 0 copies the surviving rows into the workspace, stage 1 copies them back to where the shorter sequence
@@ -528,7 +529,7 @@ __global__ void compact_move_kernel(compact_params p)
     const int32_t *lens = (const int32_t *)(p.base + ly.off_lens);
     if (lens[(size_t)p.layer * ly.B + p.b] != p.n) return;
     const int h = blockIdx.y, is_v = blockIdx.z;
-    const int cpr = ly.D / 8, rows = p.keep + ly.W, n_dist = p.n - ly.S - ly.W;
+    const int cpr = ly.D / 8, rows = p.rows, n_dist = p.n - ly.S - ly.W;
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= rows * cpr) return;
     const int row = idx / cpr, c = idx % cpr;
@@ -637,7 +638,10 @@ int pod_launch_compact(const pod_cache *c, int layer, int b, int n, const int32_
     p.base = c->base; p.ly = ly; p.hm = pod_make_headmap(c, layer);
     p.layer = layer; p.b = b; p.n = n; p.keep = keep; p.sel_all = sel_all; p.ws = (uint4 *)ws;
     for (int h = 0; h < ly.Hkv; ++h) p.sel_layer[h] = c->lowest[(size_t)layer * ly.Hkv + h];
-    const int items = (keep + ly.W) * (ly.D / 8);
+    // Recent position i of the ring is at slot (n - S + i) mod W before and at (keep + i) mod W after: where W divides the number of
+    // dropped tokens it is there already.
+    p.rows = keep + ((n - ly.S - ly.W - keep) % ly.W != 0 ? ly.W : 0);
+    const int items = p.rows * (ly.D / 8);
     const dim3 g((items + 255) / 256, ly.Hkv, 2);
     hipLaunchKernelGGL(compact_move_kernel<0>, g, dim3(256), 0, st, p);
     hipLaunchKernelGGL(compact_move_kernel<1>, g, dim3(256), 0, st, p);

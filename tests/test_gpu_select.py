@@ -179,6 +179,7 @@ MAP4 = np.array([[0, 0, 0], [0, 0, 1], [0, 2, 2], [0, 2, 3]], dtype=np.int32)   
     ("turned ring", 2, 2, 4, 2, 64, 3, 16, 270, 8, 13, 7, "max", None),      # the ring turns by (n - S - keep) % W = 14
     ("head-wise", 4, 1, 6, 3, 128, 8, 32, 333, 32, 100, 3, "max", MAP4),
     ("keep all", 2, 2, 4, 4, 128, 2, 20, 150, 4, 128, 1, "avg", None),
+    ("ring stays", 2, 2, 4, 2, 64, 3, 16, 91, 8, 40, 3, "max", None),        # 32 dropped tokens: the ring starts at the same slot
 ])
 def test_select_compact_and_decode_on(name, L, G, Hq, Hkv, d, S, W, n, obs, keep, width, kind, table):
     steps = 2 * W + 3                                         # the ring wraps twice: every kept recent token is demoted
