@@ -33,6 +33,7 @@
 #include <stddef.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "pod_internal.h"
 
@@ -49,6 +50,7 @@ constexpr int kWaves = 4;          // waves per workgroup ...
 constexpr int fuse_waves(int fuse) { return fuse == 1 || fuse == 2 ? 8 : kWaves; }
 constexpr int kTile = 32;          // tokens per wave iteration
 constexpr float kNegBig = -1.0e30f; // stands in for -inf (keeps exp2 arguments finite)
+constexpr int kRawBuffer = 0x00020000, kBufferNT = 2; // buffer descriptor word 3 of an untyped buffer; non-temporal access
 constexpr int kMinChunk = 128;     // smallest chunk (tokens) a workgroup takes
 constexpr int kMaxHostLens = 256;  // batch sizes up to this pass the host mirror's lengths as kernel arguments
 constexpr int kUnit = kWaves * kTile; // tokens of one step of a four-wave workgroup: the unit the even split counts in
@@ -649,8 +651,29 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
         }
 #undef POD_CONSUME_SV
 #undef POD_LOAD_SV
-    } else
-    for (int it = 0; it < ntile_w; ++it, t0 += tstep) {
+    } else {
+    // The distant logits a block's lowest layer leaves for its upper layers.  A wave's tiles but its last are whole, and their
+    // stores have no branch around them: lanes without a head, and proximal pieces, store out of the buffer's range, which the
+    // hardware drops.  Behind a branch the compiler cannot count the stores among the wave's outstanding accesses, and waits at
+    // the top of every tile for the last one's stores as well as for its own loads: launches of 4 sequences of 16-24K tokens
+    // 76.9 -> 74.2 us, 16 of 4-32K 238.6 -> 235.5, 4 of 60K 189.9 -> 187.0 (D = 128; D = 64 37.9 -> 37.4).  What such a launch
+    // still takes longer than one that writes nothing (62, 190, 155 us) is the stores' way to HBM among the reads: with the same
+    // stores to lines that stay in the L2 it takes 67, 206, 171, and neither whole lines per store nor other cache policies
+    // change it.  Non-temporal: lines that do not settle in the L2 cost a little less, score-reuse steps 1-2 % faster.
+    [[maybe_unused]] const auto store_logits = [&](const float (&sc)[8], int t, int bytes) { // the tile of token t; bytes: of the tile, or 0
+        const uint64_t at = (uint64_t)(p.scores + ((size_t)b * hkv + h) * p.score_stride * hot.rep) + (uint64_t)(t >> 5) * (128 * hot.rep);
+        const uint64_t uniform = (uint64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)(at >> 32)) << 32 |
+                                 (unsigned)__builtin_amdgcn_readfirstlane((int)at);
+        const __amdgpu_buffer_rsrc_t rsrc =
+            __builtin_amdgcn_make_buffer_rsrc((void *)uniform, 0, __builtin_amdgcn_readfirstlane(bytes), kRawBuffer);
+        const unsigned off = m16 < hot.rep ? 32u * (unsigned)(j * hot.rep + m16) : 0x40000000u;
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{sc[0], sc[1], sc[2], sc[3]}), rsrc, off, 0, kBufferNT);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{sc[4], sc[5], sc[6], sc[7]}), rsrc, off + 16u, 0, kBufferNT);
+    };
+    // (two dropped ones ahead of the loop: its first turn then has as many accesses behind its loads as the others)
+    if constexpr (MODE == 1) store_logits({}, 0, 0);
+    auto tile = [&](auto inner_tag, int it) {
+        constexpr bool INNER = decltype(inner_tag)::value; // not the wave's last tile
         // ---- K tile through LDS into A-operand order
 #pragma unroll
         for (int i = 0; i < NLD; ++i) {
@@ -678,7 +701,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
         // ---- next tile's loads go out before the softmax / PV work of this one.  Not past the piece's end: nothing
         // would use them, and the wave would still wait for them before it may hand its partial over and end (as long
         // as any other load on a saturated memory system: 3 us per workgroup measured).
-        if (it + 1 < ntile_w) { POD_LOAD_TILE(t0 + tstep) }
+        if (INNER || it + 1 < ntile_w) { POD_LOAD_TILE(t0 + tstep) }
 
         // ---- online softmax for head m16 over this lane's 8 tokens (base-2 domain)
         float sc[8];
@@ -688,16 +711,16 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
             sc[i] = (tok0 < end && (!STEP || tok0 != excl)) ? s0[i] * hot.scale_log2e : kNegBig;
             sc[4 + i] = (tok1 < end && (!STEP || tok1 != excl)) ? s1[i] * hot.scale_log2e : kNegBig;
         }
-        if constexpr (MODE == 1) {
+        if constexpr (MODE == 1 && INNER) {
+            store_logits(sc, t0, distant ? 128 * hot.rep : 0);
+        } else if constexpr (MODE == 1) {
             if (distant && m16 < hot.rep) { // the lowest layer's distant logits, for the block's upper layers
                 typedef __attribute__((address_space(1))) f32x4 *gf4_w;
                 const size_t tile = (size_t)(t0 >> 5);
                 const gf4_w dst = (gf4_w)(p.scores + ((size_t)b * hkv + h) * p.score_stride * hot.rep) +
                                   (tile * 4 * hot.rep + (size_t)j * hot.rep + m16) * 2;
                 if (!STEP || t0 + kTile <= end) {
-                    // (tokens past the chunk carry the mask value.  Non-temporal stores: stores inside the read stream cost
-                    // far more than their bytes - a layer that writes logits takes 17-22 % longer for 3 % more bytes - and
-                    // lines that do not settle in the L2 cost a little less: score-reuse steps 1-2 % faster)
+                    // (tokens past the chunk carry the mask value)
                     __builtin_nontemporal_store(f32x4{sc[0], sc[1], sc[2], sc[3]}, &dst[0]);
                     __builtin_nontemporal_store(f32x4{sc[4], sc[5], sc[6], sc[7]}, &dst[1]);
                 } else {   // a step's last, partly filled tile: the element behind the last row is step_workgroup's to store
@@ -711,6 +734,13 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
             }
         }
         softmax_pv(sc, vcur);
+    };
+    if constexpr (MODE == 1) {
+        for (int it = 0; it + 1 < ntile_w; ++it, t0 += tstep) tile(std::true_type{}, it);
+        if (ntile_w > 0) tile(std::false_type{}, ntile_w - 1);
+    } else {
+        for (int it = 0; it < ntile_w; ++it, t0 += tstep) tile(std::false_type{}, it);
+    }
     }
 
 #undef POD_LOAD_TILE

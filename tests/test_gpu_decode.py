@@ -181,6 +181,38 @@ def test_score_reuse_ragged_batch_and_steps():
     c.gpu.pod_cache_check()
 
 
+@pytest.mark.parametrize("d,Hq,Hkv", [(128, 8, 2), (64, 3, 3), (128, 16, 1)])
+def test_score_rows_hold_the_distant_logits_and_nothing_else(d, Hq, Hkv, monkeypatch):
+    """Pieces of 512 tokens, so that a wave has several tiles; lanes without a query head (rep 1 and 4) and the long
+    proximal region (600 tokens) store nothing, nor does anything land behind a sequence's last tile."""
+    monkeypatch.setenv("POD_DECODE_CHUNK", "512")
+    S, W, lens = 8, 592, [2300, 632, 600, 0, 1767]
+    B, rep, mark = len(lens), Hq // Hkv, 12345.0
+    c = Case(2, 2, Hq, Hkv, d, S, W, B, 2400, seed=77)
+    for b, n in enumerate(lens):
+        if n:
+            c.fill(0, b, n)
+    scores = c.gpu.new_score_buffer()
+    stride = (c.gpu.cfg.max_context - S - W + 31) // 32 * 32
+    rows = scores.view(torch.float32)[-B * Hq * stride:]
+    rows.fill_(mark)
+    c.decode_reuse(0, lens, scores)
+    # [tile][4 lane groups][query heads][2 halves][4 tokens] -> [query heads][tokens]
+    got = rows.view(B, Hkv, stride // 32, 4, rep, 2, 4).permute(0, 1, 4, 2, 5, 3, 6).reshape(B, Hq, stride).double().cpu()
+    for b, n in enumerate(lens):
+        dist = max(0, n - S - W)
+        assert torch.all(got[b, :, (dist + 31) // 32 * 32:] == mark), b
+        if dist == 0:
+            continue
+        q = c.queries(0, b, 1, "cpu", pos0=n - 1)[0].double()
+        k = c.keys(0, b, n, "cpu")[S:S + dist].double().repeat_interleave(rep, 1)
+        terms = q[None] * k * (c.scale * math.log2(math.e))
+        # d products summed in fp32 in any order, one rounded multiplication by the rounded scale
+        bound = (d + 2) * 2.0 ** -23 * terms.abs().sum(-1).T
+        assert torch.all((got[b, :, :dist] - terms.sum(-1).T).abs() <= bound), b
+    c.gpu.pod_cache_check()
+
+
 def test_score_reuse_detects_stale_scores():
     c = Case(4, 2, 4, 2, 64, 8, 32, 1, 512, seed=42)
     n = 300
