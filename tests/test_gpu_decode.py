@@ -213,6 +213,21 @@ def test_score_rows_hold_the_distant_logits_and_nothing_else(d, Hq, Hkv, monkeyp
     c.gpu.pod_cache_check()
 
 
+@pytest.mark.parametrize("d,Hq,Hkv", [(128, 4, 1), (64, 4, 2)])
+@pytest.mark.parametrize("pieces", [2, 15, 16, 17, 31, 32, 33])
+def test_merge_of_few_and_many_partials(pieces, d, Hq, Hkv, monkeypatch):
+    """Pieces of 128 tokens, one of them proximal: the merge takes one wave per head up to 16 partials, two up to 32."""
+    monkeypatch.setenv("POD_DECODE_CHUNK", "128")
+    n = 128 * pieces - 5
+    c = Case(2, 2, Hq, Hkv, d, 8, 120, 1, 128 * pieces, seed=500 + pieces)
+    for layer in range(2):
+        c.fill(layer, 0, n)
+    scores = c.gpu.new_score_buffer()
+    for layer in range(2):
+        assert_close(c.decode_reuse(layer, [n], scores), c.decode_ref(layer, [n]), f"{pieces} pieces, layer {layer}")
+    c.gpu.pod_cache_check()
+
+
 def test_score_reuse_detects_stale_scores():
     c = Case(4, 2, 4, 2, 64, 8, 32, 1, 512, seed=42)
     n = 300
