@@ -803,7 +803,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
         const int last = arrive_last<LOC>(p.tickets + (size_t)b * hkv + h, expected);
         const unsigned long long tr_t3 = p.trace ? wall_clock64() : 0;
         auto trace_out = [&]() {
-            const size_t wg = LOC ? (size_t)blockIdx.x : ((size_t)b * hkv + h) * gridDim.x + c;
+            const size_t wg = LOC ? (size_t)blockIdx.x : ((size_t)b * hkv + h) * (hot.nc + (own_host ? 1 : 0)) + c;
             if (p.trace && threadIdx.x == 0 && wg < (size_t)p.trace_cap) {
                 unsigned long long *t = p.trace + 8 * wg;
                 t[0] = ((unsigned long long)(b * hkv + h) << 32) | (unsigned)c | (last ? 0x80000000u : 0u);
