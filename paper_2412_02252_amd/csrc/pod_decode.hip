@@ -33,7 +33,6 @@
 #include <stddef.h>
 
 #include <mutex>
-#include <type_traits>
 
 #include "pod_internal.h"
 
@@ -672,48 +671,46 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
     };
     // (two dropped ones ahead of the loop: its first turn then has as many accesses behind its loads as the others)
     if constexpr (MODE == 1) store_logits({}, 0, 0);
-    auto tile = [&](auto inner_tag, int it) {
-        constexpr bool INNER = decltype(inner_tag)::value; // not the wave's last tile
-        // ---- K tile through LDS into A-operand order
-#pragma unroll
-        for (int i = 0; i < NLD; ++i) {
-            const int r = RPI * i + kr;
-            ldsK[r * CPR + (kc ^ (r % CPR))] = kreg[i];
-        }
-        u32x4 vcur[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) vcur[e] = vreg[e];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-
-        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < KST; ++s) {
-            const int col = 4 * s + j;
-            const u32x4 a0 = ldsK[m16 * CPR + (col ^ (m16 % CPR))];
-            const u32x4 a1 = ldsK[(16 + m16) * CPR + (col ^ ((16 + m16) % CPR))];
-            s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a0), qf[s], s0, 0, 0, 0);
-            s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a1), qf[s], s1, 0, 0, 0);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-
-        // ---- next tile's loads go out before the softmax / PV work of this one.  Not past the piece's end: nothing
-        // would use them, and the wave would still wait for them before it may hand its partial over and end (as long
-        // as any other load on a saturated memory system: 3 us per workgroup measured).
-        if (INNER || it + 1 < ntile_w) { POD_LOAD_TILE(t0 + tstep) }
-
-        // ---- online softmax for head m16 over this lane's 8 tokens (base-2 domain)
-        float sc[8];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int tok0 = t0 + 4 * j + i, tok1 = tok0 + 16;
-            sc[i] = (tok0 < end && (!STEP || tok0 != excl)) ? s0[i] * hot.scale_log2e : kNegBig;
-            sc[4 + i] = (tok1 < end && (!STEP || tok1 != excl)) ? s1[i] * hot.scale_log2e : kNegBig;
-        }
-        if constexpr (MODE == 1 && INNER) {
+    // One tile: K through LDS into A-operand order, S^T, and head m16's logits sc[] of this lane's 8 tokens (base-2 domain).  The next
+    // tile's loads go out before the softmax / PV work of this one.  Not past the piece's end (MORE): nothing would use
+    // them, and the wave would still wait for them before it may hand its partial over and end (as long as any other
+    // load on a saturated memory system: 3 us per workgroup measured).  A macro, as the loads are: called as one lambda from
+    // both loops below, the plain loop was scheduled worse (32 decode attentions at head dim 128, us: 7 pairs, 9000 tokens 409
+    // instead of 400; 8 pairs, 4096 tokens 330 instead of 318).
+#define POD_TILE_LOGITS(MORE)                                                                                         \
+    _Pragma("unroll") for (int i = 0; i < NLD; ++i) {                                                                 \
+        const int r = RPI * i + kr;                                                                                   \
+        ldsK[r * CPR + (kc ^ (r % CPR))] = kreg[i];                                                                   \
+    }                                                                                                                 \
+    u32x4 vcur[8];                                                                                                    \
+    _Pragma("unroll") for (int e = 0; e < 8; ++e) vcur[e] = vreg[e];                                                  \
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");                                                            \
+    __builtin_amdgcn_wave_barrier();                                                                                  \
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};                                                       \
+    _Pragma("unroll") for (int s = 0; s < KST; ++s) {                                                                 \
+        const int col = 4 * s + j;                                                                                    \
+        const u32x4 a0 = ldsK[m16 * CPR + (col ^ (m16 % CPR))];                                                       \
+        const u32x4 a1 = ldsK[(16 + m16) * CPR + (col ^ ((16 + m16) % CPR))];                                         \
+        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a0), qf[s], s0, 0, 0, 0);                              \
+        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a1), qf[s], s1, 0, 0, 0);                              \
+    }                                                                                                                 \
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");                                                            \
+    __builtin_amdgcn_wave_barrier();                                                                                  \
+    if (MORE) { POD_LOAD_TILE(t0 + tstep) }                                                                           \
+    float sc[8];                                                                                                      \
+    _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                                                   \
+        const int tok0 = t0 + 4 * j + i, tok1 = tok0 + 16;                                                            \
+        sc[i] = (tok0 < end && (!STEP || tok0 != excl)) ? s0[i] * hot.scale_log2e : kNegBig;                          \
+        sc[4 + i] = (tok1 < end && (!STEP || tok1 != excl)) ? s1[i] * hot.scale_log2e : kNegBig;                      \
+    }
+    if constexpr (MODE == 1) {
+        for (int it = 0; it + 1 < ntile_w; ++it, t0 += tstep) {
+            POD_TILE_LOGITS(true)
             store_logits(sc, t0, distant ? 128 * hot.rep : 0);
-        } else if constexpr (MODE == 1) {
+            softmax_pv(sc, vcur);
+        }
+        if (ntile_w > 0) {
+            POD_TILE_LOGITS(false)
             if (distant && m16 < hot.rep) { // the lowest layer's distant logits, for the block's upper layers
                 typedef __attribute__((address_space(1))) f32x4 *gf4_w;
                 const size_t tile = (size_t)(t0 >> 5);
@@ -732,15 +729,15 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
                     }
                 }
             }
+            softmax_pv(sc, vcur);
         }
-        softmax_pv(sc, vcur);
-    };
-    if constexpr (MODE == 1) {
-        for (int it = 0; it + 1 < ntile_w; ++it, t0 += tstep) tile(std::true_type{}, it);
-        if (ntile_w > 0) tile(std::false_type{}, ntile_w - 1);
     } else {
-        for (int it = 0; it < ntile_w; ++it, t0 += tstep) tile(std::false_type{}, it);
+        for (int it = 0; it < ntile_w; ++it, t0 += tstep) {
+            POD_TILE_LOGITS(it + 1 < ntile_w)
+            softmax_pv(sc, vcur);
+        }
     }
+#undef POD_TILE_LOGITS
     }
 
 #undef POD_LOAD_TILE
