@@ -944,7 +944,12 @@ __device__ void merge_and_store_split(const decode_params &p, const decode_hot &
                     if (first + k * NGW * split < nv) {       // (wave-uniform; rows past the end were not loaded)
                         float f = lane_value(w, k * NGW);     // the weight of this lane group's k-th row
 #pragma unroll
-                        for (int gg = 1; gg < NGW; ++gg) f = g == gg ? lane_value(w, k * NGW + gg) : f;
+                        for (int gg = 1; gg < NGW; ++gg) {
+                            // (read before the choice: in a branch on the reader's lane the compiler may put in what it knows of w
+                            // in that lane - its weight is 0 in lanes beyond ROWS - although another lane's is asked for)
+                            const float fg = lane_value(w, k * NGW + gg);
+                            f = g == gg ? fg : f;
+                        }
 #pragma unroll
                         for (int e = 0; e < VEC; ++e) a[e] += f * ak[k][e];
                     }
