@@ -70,7 +70,7 @@ struct decode_hot { // exactly two 64-byte lines, read in one go at kernel entry
     int32_t chunk;       // tokens per workgroup: distant chunks in the low 16 bits, proximal chunks in the high 16 bits
     int32_t max_nd;      // distant chunk slots per (sequence, head)
     int32_t nc;          // all chunk slots per (sequence, head): max_nd + proximal slots
-    int32_t use_hlen;    // bit 0: hlen[] holds the host mirror's length of every slot < B; bit 1 (FUSE 2 only): the step has a workgroup of its own
+    int32_t use_hlen;    // bit 0: hlen[] holds the host mirror's length of every slot < B; bit 1: see HOST of decode_partial_kernel
     // line 1: queries, partial results, device-side lengths
     const pod_bf16 *q, *q_shared;
     float scale_log2e;
@@ -326,11 +326,12 @@ __device__ void step_workgroup(const decode_params &p, const decode_hot &hot, in
 // theirs: over the old rows.  FUSE 3: a step whose partials decode_combine_kernel merges
 // (launches of several rounds of workgroups: there a workgroup that waits for its arrival to be counted holds its
 // slot idle, which costs more than the second launch).
-template <int D, int MODE, int FUSE = 0, bool LOC = false, int NW = fuse_waves(FUSE)>
+template <int D, int MODE, int FUSE = 0, bool LOC = false, int HOST = 0, int NW = fuse_waves(FUSE)>
 __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_params p)
 {
     static_assert(FUSE == 0 || MODE == 0 || ((FUSE == 2 || FUSE == 3) && (MODE == 1 || MODE == 2)),
                   "the fused forms serve the plain mode and, as a decode step, score reuse");
+    static_assert(HOST == 0 || FUSE == 2, "only a step that merges inside the launch has a workgroup of its own");
     constexpr bool STEP = FUSE == 2 || FUSE == 3, MERGE = FUSE == 1 || FUSE == 2;
     static_assert(!LOC || MERGE, "the XCD-local launch shape serves the fused merge");
     constexpr int CPR = D / 8;        // 16-byte pieces per row
@@ -366,7 +367,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
     const u32x4 *kdist = hot.kdist, *vdist = hot.vdist, *kprox = hot.kprox, *vprox = hot.vprox;
     const int cd = hot.cd, prows = hot.prows, hkv = hot.hkv, max_nd = hot.max_nd;
     const int chunk_p = (int)((unsigned)hot.chunk >> 16);
-    const bool use_hlen = (hot.use_hlen & 1) != 0;
+    const bool use_hlen = HOST == 2 ? (hot.use_hlen & 1) != 0 : hot.use_hlen != 0;
     // The host mirror's length is always within the buffers; whether it agrees with context_lens
     // and the device-side lengths is checked where the partials are merged (the combine kernel or the last
     // workgroup), which zeroes the output and raises the flag if not.  Without the mirror (batches beyond
@@ -415,9 +416,9 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
     // partials.  FUSE 2: the workgroup of the LAST distant piece, which is the pair's shortest on average (the first
     // proximal piece, which hosted the step before, is its longest: its tile loop ended 1.35 us after the others' and
     // its pair waited for it); the first proximal piece where there is no distant token, also when the cache is empty
-    // and that workgroup has no piece of its own.  Launches that leave CUs free have one more workgroup per pair, behind the
-    // pieces' (c == nc), that takes the step and walks nothing.
-    const bool own_host = FUSE == 2 && (hot.use_hlen & 2) != 0;
+    // and that workgroup has no piece of its own.  HOST 1: one more workgroup per pair, behind the pieces' (c == nc), takes the
+    // step and walks nothing; HOST 2: the launch says whether there is one (bit 1 of use_hlen).
+    const bool own_host = HOST == 1 || (HOST == 2 && (hot.use_hlen & 2) != 0);
     const bool hosts_step = STEP && c == (own_host ? hot.nc : FUSE == 2 && nd_eff > 0 ? nd_eff - 1 : max_nd);
     const int expected = nd_eff + (own_host ? np_eff + 1 : FUSE == 2 && np_eff == 0 ? 1 : np_eff);
     if (hosts_step) step_workgroup<D, LOC, NW, MODE>(p, hot, b, h, n, head_arg);
@@ -1920,11 +1921,16 @@ int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *
     const long xcd_cus = c->nxcd >= 1 ? cus / c->nxcd : 0, xcd_pairs = c->nxcd >= 1 ? (npairs + c->nxcd - 1) / c->nxcd : 0;
     const bool loc = merge_inside && c->xcd_local && c->nxcd >= 1 &&
                      (npairs % c->nxcd == 0 || npairs >= 8 * c->nxcd || xcd_pairs * p.hot.nc <= xcd_cus);
-    // The step's own workgroup where every workgroup of the launch still gets a CU (of its XCD): the new token's chain of short
-    // dependent accesses then runs beside the pieces instead of in front of one (2 pairs x 64 at 2048 tokens 8.92 -> 7.05 us,
-    // 8 pairs x 128 at 2048 9.8 -> 8.3).  Full launches keep the host inside: one more workgroup there waits for a CU.
-    const bool own_host = fuse == 2 && (loc ? xcd_pairs * (p.hot.nc + 1) <= xcd_cus : (long)npairs * (p.hot.nc + 1) <= cus);
-    if (own_host) p.hot.use_hlen |= 2;
+    // The step's own workgroup: the new token's chain of short dependent accesses then runs beside the pieces instead of in front
+    // of one.  XCD-local launches have one where every workgroup of the XCD still gets a CU (2 pairs x 64 at 2048 tokens
+    // 8.92 -> 7.05 us, 8 pairs x 128 at 2048 9.8 -> 8.3), launches that hand over through memory where every workgroup of the
+    // chip does; full ones keep the host inside, where one more workgroup would wait for a CU.  32 steps of a layer through memory,
+    // us, without -> with: plain x 128, 2 pairs at 14000 tokens (114 workgroups) 410 -> 373, 7 pairs at 20000 (252) 579 -> 557,
+    // 1 pair with 16 heads at 60000 (236) 1577 -> 1580; score reuse x 64, 3 pairs at 14000 (168) 343 -> 334.  Score reuse x 128 stops at
+    // half of the CUs: 2 pairs at 14000 405 -> 392, but 2 pairs at 20000 (162) 455 -> 461 and 3 at 14000 (171) 372 -> 382.
+    const int host_room = reuse_step && ly.D == 128 ? cus / 2 : cus;
+    const bool own_host = fuse == 2 && (loc ? xcd_pairs * (p.hot.nc + 1) <= xcd_cus : (long)npairs * (p.hot.nc + 1) <= host_room);
+    if (own_host && !reuse_step) p.hot.use_hlen |= 2;
     const size_t WGS = (size_t)p.hot.nc + (own_host ? 1 : 0);   // workgroups per (sequence, kv head) pair
     p.slots = (int32_t)WGS;
     const size_t loc_wgs = (size_t)((npairs + p.nxcd - 1) / p.nxcd) * p.nxcd * WGS;
@@ -1940,22 +1946,29 @@ int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *
     const dim3 grid_d((unsigned)(p.hot.max_nd > 0 ? p.hot.max_nd : 1), (unsigned)ly.Hkv, (unsigned)B);
     // score reuse: the writing launch for the kv heads whose block starts at this layer, the reading launch(es) for
     // the others (workgroups of the other kind leave at once); a gated read is two launches, proximal chunks first
+    // (Plain steps with and without a workgroup of their own: one kernel that is told, since as a constant the walk through memory
+    // came out 10 % longer.  Score reuse: two kernels, since as a flag the reader's registers cost every launch of it 2-4 %.)
+#define POD_LAUNCH_HOST(DD, MM, HOST)                                                        \
+    if (loc) hipLaunchKernelGGL((decode_partial_kernel<DD, MM, 2, true, HOST>), grid, dim3(fuse_waves(2) * 64), 0, st, p); \
+    else hipLaunchKernelGGL((decode_partial_kernel<DD, MM, 2, false, HOST>), grid, dim3(fuse_waves(2) * 64), 0, st, p);
+#define POD_LAUNCH_STEP(DD, MM)                                                              \
+    {                                                                                        \
+        if (MM == 0 || own_host) { POD_LAUNCH_HOST(DD, MM, (MM == 0 ? 2 : 1)) }              \
+        else { POD_LAUNCH_HOST(DD, MM, (MM == 0 ? 2 : 0)) }                                  \
+    }
 #define POD_LAUNCH_ALL(DD)                                                                   \
     if (reuse_step) {                                                                        \
         if (lowest_any) {                                                                    \
-            if (fuse == 2 && loc) hipLaunchKernelGGL((decode_partial_kernel<DD, 1, 2, true>), grid, dim3(fuse_waves(2) * 64), 0, st, p); \
-            else if (fuse == 2) hipLaunchKernelGGL((decode_partial_kernel<DD, 1, 2>), grid, dim3(fuse_waves(2) * 64), 0, st, p);         \
+            if (fuse == 2) POD_LAUNCH_STEP(DD, 1)                                            \
             else hipLaunchKernelGGL((decode_partial_kernel<DD, 1, 3>), grid, dim3(kWaves * 64), 0, st, p);                               \
         }                                                                                    \
         if (!lowest_all) {                                                                   \
-            if (fuse == 2 && loc) hipLaunchKernelGGL((decode_partial_kernel<DD, 2, 2, true>), grid, dim3(fuse_waves(2) * 64), 0, st, p); \
-            else if (fuse == 2) hipLaunchKernelGGL((decode_partial_kernel<DD, 2, 2>), grid, dim3(fuse_waves(2) * 64), 0, st, p);         \
+            if (fuse == 2) POD_LAUNCH_STEP(DD, 2)                                            \
             else hipLaunchKernelGGL((decode_partial_kernel<DD, 2, 3>), grid, dim3(kWaves * 64), 0, st, p);                               \
         }                                                                                    \
     }                                                                                        \
-    else if (fuse == 2 && loc) hipLaunchKernelGGL((decode_partial_kernel<DD, 0, 2, true>), grid, dim3(fuse_waves(2) * 64), 0, st, p); \
+    else if (fuse == 2) POD_LAUNCH_STEP(DD, 0)                                               \
     else if (fuse == 1 && loc) hipLaunchKernelGGL((decode_partial_kernel<DD, 0, 1, true>), grid, dim3(fuse_waves(1) * 64), 0, st, p); \
-    else if (fuse == 2) hipLaunchKernelGGL((decode_partial_kernel<DD, 0, 2>), grid, dim3(fuse_waves(2) * 64), 0, st, p);    \
     else if (fuse == 3) hipLaunchKernelGGL((decode_partial_kernel<DD, 0, 3>), grid, dim3(kWaves * 64), 0, st, p);               \
     else if (fuse == 1) hipLaunchKernelGGL((decode_partial_kernel<DD, 0, 1>), grid, dim3(fuse_waves(1) * 64), 0, st, p);    \
     else if (p.mode == 0) POD_LAUNCH_PARTIAL(DD, 0, grid);                                   \
@@ -1978,6 +1991,8 @@ int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *
     }
     else if (ly.D == 128) { POD_LAUNCH_ALL(128) } else { POD_LAUNCH_ALL(64) }
 #undef POD_LAUNCH_ALL
+#undef POD_LAUNCH_STEP
+#undef POD_LAUNCH_HOST
 #undef POD_LAUNCH_PARTIAL
     if (prof) { POD_HIP_TRY(hipEventRecord(mc->prof_ev[2 * mc->prof_n + 1], st)); mc->prof_n += 1; }
     if (fuse == 0 || fuse == 3) {

@@ -320,6 +320,34 @@ def test_who_takes_the_step_where_one_xcds_cus_run_out(n, reuse):
     c.gpu.pod_cache_check()
 
 
+@pytest.mark.parametrize("reuse,d,room,pieces", [(False, 128, 1, 41), (False, 128, 1, 84), (False, 128, 1, 85), (True, 128, 2, 41),
+                                                 (True, 128, 2, 42), (True, 64, 1, 84), (True, 64, 1, 85)])
+def test_the_step_has_a_workgroup_of_its_own_only_where_that_pays(reuse, d, room, pieces):
+    """Three pairs whose partials go through memory (on 256 CUs).  The launch's trace says how many workgroups there are: one more
+    per pair than the plan has pieces where all of them find a CU - for score reuse at head dim 128, on half of the CUs."""
+    Hkv, S, W = 3, 8, 120
+    n = 256 * (pieces - 1) + S + W - 40                        # one proximal piece, the last distant one not full
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    plan = pod.pod_decode_plan(cus, 1, Hkv, S + W, n + 1)
+    c = Case(2, 2, Hkv, Hkv, d, S, W, 1, n + 8, seed=532)
+    scores = c.gpu.new_score_buffer() if reuse else None
+    for layer in range(2):
+        c.fill(layer, 0, n)
+    trace = torch.zeros(8 * 1024, dtype=torch.int64, device=c.dev)
+    for layer in range(2):
+        c.gpu.pod_profile_set_trace(trace if layer == 0 else None)
+        out = c.step_reuse(layer, [n], scores) if reuse else c.step(layer, [n])
+        assert_close(out, c.decode_ref(layer, [n + 1]), f"layer {layer}")
+    for layer in range(2):
+        c.assert_cache_equal(layer, 0)
+    c.gpu.pod_cache_check()
+    words = trace.view(-1, 8).cpu()
+    own = Hkv * (plan["pieces"] + 1) <= cus // room
+    assert int((words[:, 6] != 0).sum()) == Hkv * (plan["pieces"] + own)
+    if cus == 256:
+        assert plan["pieces"] == pieces and own == (pieces != 85 and (room, pieces) != (2, 42))
+
+
 def test_steps_from_empty_caches_with_more_pairs_than_free_cus():
     """160 pairs of one or two pieces: no CU is left for a workgroup that only takes the step, also while the cache is empty
     and that workgroup's piece with it."""
