@@ -5,18 +5,20 @@
 //
 // With m = (p + q) / 2 the divergence is a difference of entropies: of one pair of elements,
 //     (p log2(p / m) + q log2(q / m)) / 2 = e(p) + e(q) - m log2(m),   e(x) = x log2(x) / 2,
-// so a layer's logarithms are taken once per element and a pair of layers costs one sum, one logarithm and one multiply-add
-// per element.  The difference is taken over two elements at a time (their e's are added up first), so
+// so a layer's logarithms are taken once per element and a pair of layers costs one sum, one logarithm, one multiplication and
+// one addition per element.  The difference is taken over two elements at a time (their e's are added up first), so
 // that what is accumulated over the rows is the small difference and not the two large sums it is made of.
 //
 // A workgroup takes one head, one half of its rows and a block pair (A, B) of BL layers each (A <= B): every element of up to
 // 2 BL layers is loaded once, 16 bytes per lane and layer, ahead of its use, and all the BL x BL (or, on the diagonal,
 // BL (BL - 1) / 2) layer pairs are accumulated from registers.  The two halves leave their sums in the two places
 // the symmetric result has for a pair; similarity_finish_kernel adds them (a fixed order: same bits on every call).
-// Bound by vector issue: three plain instructions and a logarithm per pair and element, plus a quarter of that for the e's
-// (vector pipes 96 % busy by counter).  32 layers x 32 heads x 32 rows x 2048: 671 -> 239 us; the 671 took
+// Bound by vector issue: three and a half plain instructions and a logarithm per pair and element, plus a quarter of that for
+// the e's (vector pipes 96 % busy by counter).  32 layers x 32 heads x 32 rows x 2048: 669 -> 270 us; the 669 took
 // p (log p - log m) + q (log q - log m) per element, in one workgroup per head and pair of 8-layer blocks with nothing requested
-// ahead.  Blocks of 8 layers read a row half as often but leave two waves per SIMD: 277 us here, 77 instead of 33 at 8 layers.
+// ahead.  With the pair's logarithms multiplied into (e(p) + e(q)) directly it takes 251 us, but rows with the same bits then come
+// out a rounding error away from 1 (one sampled row of 64 entries: every fourth).  Blocks of 8 layers read a row half as often but
+// leave two waves per SIMD: 15 % slower here, 77 instead of 33 us at 8 layers.
 #include "pod_internal.h"
 
 namespace {
@@ -84,12 +86,15 @@ __global__ __launch_bounds__(kSimThreads) void similarity_kernel(sim_params p)
         }
         return e;
     };
+    // (the pair's own sum is formed in the order of halve's: of two rows with the same bits it is exactly the two layers' sums, the
+    // divergence exactly 0 and the similarity exactly 1, which a threshold of 1 asks for)
     auto pair_term = [](const f2 &ea, const f2 &eb, const sim_f4 &a, const sim_f4 &b) {
+#pragma clang fp contract(off)
         float t[2];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float m = a[k] + b[k];
-            t[k >> 1] = __builtin_fmaf(-m, __builtin_amdgcn_logf(m), k & 1 ? t[k >> 1] : ea[k >> 1] + eb[k >> 1]);
+        for (int k = 0; k < 4; k += 2) {
+            const float m0 = a[k] + b[k], m1 = a[k + 1] + b[k + 1];
+            t[k >> 1] = (ea[k >> 1] + eb[k >> 1]) - __builtin_fmaf(m1, __builtin_amdgcn_logf(m1), m0 * __builtin_amdgcn_logf(m0));
         }
         return t[0] + t[1];
     };

@@ -204,6 +204,21 @@ def test_layer_similarity_matches_the_oracle(L, H, R, n):
     assert (got >= -1e-6).all() and (got <= 1 + 1e-6).all()
 
 
+@pytest.mark.parametrize("L,H,n", [(2, 400, 4), (8, 64, 8), (32, 40, 60), (3, 100, 256)])
+def test_layers_with_the_same_rows_have_similarity_one_exactly(L, H, n):
+    """One sampled row per head, so that no average rounds a remainder away; blocks of two and of four layers.  A threshold of 1
+    groups such layers."""
+    rng = np.random.default_rng(L * 1000 + n)
+    att = rng.dirichlet(np.full(n, 0.3), size=(L, H, 1)).astype(np.float32)
+    att[L - 1] = att[0]
+    att[1, : H // 2] = att[0, : H // 2]
+    got = pod.pod_layer_similarity(torch.from_numpy(att).cuda()).cpu().numpy()
+    assert (got[:, 0, L - 1] == 1).all() and (got[:, L - 1, 0] == 1).all()
+    assert (got[: H // 2, 0, 1] == 1).all()
+    lowest = pod.pod_group_layers(got[: H // 2, [0, 1]][:, :, [0, 1]], H // 2, 1.0)
+    assert (np.asarray(lowest) == 0).all()
+
+
 def test_similarity_to_grouping_to_cache_table():
     """Layers 0-2 share one attention pattern, layers 3-4 another (plus noise), per head differently:
     the GPU similarity, the host grouping and a cache built from the table agree with the oracle chain."""
