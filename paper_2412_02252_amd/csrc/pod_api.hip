@@ -695,8 +695,8 @@ extern "C" int pod_layer_similarity(const float *att, int num_layers, int num_he
     if (!att || !sim) return pod_fail(POD_ERR_INVALID_ARG, "att and sim must not be NULL");
     if (num_layers < 1 || num_heads < 1 || rows < 1 || n < 1)
         return pod_fail(POD_ERR_INVALID_ARG, "num_layers, num_heads, rows and n must be >= 1");
-    if (num_heads > 65535 || (int64_t)num_layers * (num_layers - 1) / 2 > INT32_MAX)
-        return pod_fail(POD_ERR_INVALID_ARG, "too many heads or layer pairs for one launch");
+    if (num_heads > 65535 || num_layers > 65535)
+        return pod_fail(POD_ERR_INVALID_ARG, "%d heads and %d layers: at most 65535 of each", num_heads, num_layers);
     if (((uintptr_t)att % 16) || ((size_t)rows * n) % 4)
         return pod_fail(POD_ERR_INVALID_ARG, "att must be 16-byte aligned and rows * n a multiple of 4");
     return pod_launch_similarity(att, num_layers, num_heads, rows, n, sim, (hipStream_t)stream);

@@ -38,7 +38,9 @@ struct sim_params {
     size_t rows;      // R * n elements of one (layer, head), contiguous
     int R;            // rows per (layer, head)
     int heads_by_xcd; // 8: workgroup w takes a head that is w mod 8; 1: heads in order
+    int pair0;        // the launch's first block pair
 };
+constexpr unsigned kSimLaunch = (1u << 24) - 1; // workgroups of one launch: a grid dimension holds less than 2^32 threads
 
 template <int BL>
 __global__ __launch_bounds__(kSimThreads) void similarity_kernel(sim_params p)
@@ -50,7 +52,7 @@ __global__ __launch_bounds__(kSimThreads) void similarity_kernel(sim_params p)
     const int h = rest % hx * p.heads_by_xcd + x;
     rest /= hx;
     const int half = rest % kSimHalves;
-    rest /= kSimHalves;
+    rest = p.pair0 + rest / kSimHalves;
     const int noff = p.nblk * (p.nblk - 1) / 2;
     int A = rest - noff, B = A;
     if (rest < noff) {
@@ -165,25 +167,32 @@ __global__ __launch_bounds__(kSimThreads) void similarity_kernel(sim_params p)
     }
 }
 
-// one thread per (head, a <= b): JS = sum of the two halves, mean over the rows; 1 on the diagonal
+// one thread per (head, a, b), a <= b: JS = sum of the two halves, mean over the rows; 1 on the diagonal
 __global__ void similarity_finish_kernel(sim_params p)
 {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x, LL = (size_t)p.L * p.L;
-    if (i >= LL * p.H) return;
-    const int a = (int)(i % LL) / p.L, b = (int)(i % LL) % p.L;
+    const unsigned i = blockIdx.x * blockDim.x + threadIdx.x, L = (unsigned)p.L, LL = L * L; // (at most 65535 layers)
+    if (i >= LL) return;
+    const unsigned a = i / L, b = i - a * L;
     if (a > b) return;
-    float *const m = p.sim + i / LL * LL;
+    float *const m = p.sim + (size_t)blockIdx.y * LL;
     const float s = a == b ? 1.f : 1.f - (m[(size_t)a * p.L + b] + m[(size_t)b * p.L + a]) / (float)p.R;
     m[(size_t)a * p.L + b] = s;
     m[(size_t)b * p.L + a] = s;
 }
 
 template <int BL>
-void launch_pairs(sim_params p, hipStream_t st)
+int launch_pairs(sim_params p, hipStream_t st)
 {
     p.nblk = (p.L + BL - 1) / BL;
-    const unsigned pairs = (unsigned)(p.nblk * (p.nblk + 1) / 2);
-    hipLaunchKernelGGL(similarity_kernel<BL>, dim3(pairs * kSimHalves * (unsigned)p.H), dim3(kSimThreads), 0, st, p);
+    const int64_t pairs = (int64_t)p.nblk * (p.nblk + 1) / 2;
+    const unsigned per_pair = (unsigned)p.H * kSimHalves, most = kSimLaunch / per_pair;
+    for (int64_t lo = 0; lo < pairs; lo += most) {
+        p.pair0 = (int)lo;
+        const unsigned here = (unsigned)(pairs - lo < most ? pairs - lo : most);
+        hipLaunchKernelGGL(similarity_kernel<BL>, dim3(here * per_pair), dim3(kSimThreads), 0, st, p);
+        POD_HIP_TRY(hipGetLastError());
+    }
+    return POD_OK;
 }
 
 } // namespace
@@ -191,7 +200,7 @@ void launch_pairs(sim_params p, hipStream_t st)
 int pod_launch_similarity(const float *att, int L, int H, int R, int n, float *sim, hipStream_t st)
 {
     sim_params p;
-    p.att = att; p.sim = sim; p.L = L; p.H = H; p.nblk = 0;
+    p.att = att; p.sim = sim; p.L = L; p.H = H; p.nblk = 0; p.pair0 = 0;
     p.rows = (size_t)R * n;
     p.R = R;
     p.heads_by_xcd = H % 8 == 0 ? 8 : 1;
@@ -199,10 +208,10 @@ int pod_launch_similarity(const float *att, int L, int H, int R, int n, float *s
     // often, for few heads or layers, whose rows come out of the L2 (8 layers x 4 heads: 22 us in blocks of two, 24 in blocks of four).
     auto workgroups = [&](int bl) { const long nb = (L + bl - 1) / bl; return nb * (nb + 1) / 2 * kSimHalves * H; };
     if (L > 1) {
-        if (workgroups(4) >= 512) launch_pairs<4>(p, st);
-        else launch_pairs<2>(p, st);
+        const int rc = workgroups(4) >= 512 ? launch_pairs<4>(p, st) : launch_pairs<2>(p, st);
+        if (rc) return rc;
     }
-    hipLaunchKernelGGL(similarity_finish_kernel, dim3((unsigned)(((size_t)L * L * H + 255) / 256)), dim3(256), 0, st, p);
+    hipLaunchKernelGGL(similarity_finish_kernel, dim3((unsigned)(((size_t)L * L + 255) / 256), (unsigned)H), dim3(256), 0, st, p);
     POD_HIP_TRY(hipGetLastError());
     return POD_OK;
 }

@@ -219,6 +219,21 @@ def test_layers_with_the_same_rows_have_similarity_one_exactly(L, H, n):
     assert (np.asarray(lowest) == 0).all()
 
 
+def test_layer_similarity_of_more_workgroups_than_a_grid_dimension_holds():
+    """512 layers x 1024 heads: 8256 pairs of four-layer blocks, in two halves per head, are 2^32 threads and more.  Every value is
+    compared."""
+    L, H, n = 512, 1024, 4
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    att = torch.softmax(torch.randn((L, H, 1, n), generator=gen, device="cuda"), -1).contiguous()
+    got = pod.pod_layer_similarity(att)
+    for h in range(H):
+        x = att[:, h, 0].double()
+        e, m = torch.special.xlogy(x, x).sum(1), 0.5 * (x[:, None] + x[None])
+        ref = 1 - (0.5 * (e[:, None] + e[None]) - torch.special.xlogy(m, m).sum(2)) / np.log(2.0)
+        assert (got[h].double() - ref).abs().max() < 2e-6, h      # four terms below 1 in fp32
+
+
 def test_similarity_to_grouping_to_cache_table():
     """Layers 0-2 share one attention pattern, layers 3-4 another (plus noise), per head differently:
     the GPU similarity, the host grouping and a cache built from the table agree with the oracle chain."""

@@ -1,4 +1,6 @@
 """CPU: host logic for head-wise blocks in libpod (layer grouping, sizes, table validation) against the oracle."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -58,3 +60,11 @@ def test_invalid_tables_are_refused():
         pod.pod_cache_bytes(pod.make_config(4, 1, 6, 3, 64, 4, 8, 1, 64, block_lowest=bad))
     with pytest.raises(ValueError):
         pod.make_config(4, 1, 6, 3, 64, 4, 8, 1, 64, block_lowest=MAP4[:3])
+
+
+@pytest.mark.parametrize("layers,heads", [(65536, 1), (1, 65536), (65537, 1), (2, 70000)])
+def test_similarity_refuses_what_it_cannot_launch(layers, heads):
+    """(Refused from the sizes alone: nothing is read or launched.)"""
+    buf = (C.c_float * 16)()
+    at = (C.addressof(buf) + 15) // 16 * 16
+    assert pod.binding.load().pod_layer_similarity(at, layers, heads, 1, 4, at, None) == pod.binding.ERR_INVALID_ARG
