@@ -627,20 +627,37 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
     }
 }
 
+// One or two key groups per workgroup.  With two, a workgroup's 128 query rows are walked by eight waves, each half of them
+// every second key tile: half the iterations on the launch's longest path, at an iteration that takes longer (eight waves
+// meet at its barrier; with all CUs full of equal work two groups reach 0.87 of the rate of two separate workgroups) plus the
+// merge.  It pays where the launch is short of workgroups or of equal ones, so costs in key tiles are compared:
+//   one group  : the longest query tile, as long as every workgroup is resident (two per CU)
+//   two groups : one workgroup per CU, the first round's query tiles and, on the CUs that are free first, the second's
+// Measured per launch, one -> two groups (32/8 heads x 128 unless said): n = 777 24.3 -> 22.3 us, 1024 29.1 -> 25.8, 1500 42.9 -> 37.1,
+// 2048 58.3 -> 53.8, 3001 93 -> 108 (more than two rounds), 2048 rows behind 6144 210 -> 225 (equal tiles); 16/4 heads x 64:
+// n = 1024 20.5 -> 17.4, 3001 51.6 -> 39.7, 4096 70.0 -> 59.2, 6000 110 -> 125; 512 rows behind 7680 (128 workgroups) 114 -> 86.
 int prefill_key_groups(int cus, int Hq, int n, int q0, int S, int W, bool has_shared)
 {
-    const int last = (n - 1) / 128, first = q0 / 128, tiles = last - first + 1; // query tiles, handed out from the last to the first
-    const int64_t nwg = (int64_t)tiles * Hq;
-    if (cus < 1 || nwg > 2 * cus) return 1;
-    auto cost = [&](int64_t wg) { // key tiles of workgroup wg in launch order
-        const int i0 = (last - (int)(wg / Hq)) * 128;
+    const int last = (n - 1) / 128, tiles = last - q0 / 128 + 1; // query tiles, handed out from the last to the first
+    if (cus < 1 || (int64_t)tiles * Hq > 2 * cus) return 1;
+    const int nwg = tiles * Hq;
+    auto cost = [&](int tile) { // key tiles that the workgroups of a query tile (in launch order) walk
+        const int i0 = (last - tile) * 128;
         return tiles_of_rows(i0, (i0 + 128 < n ? i0 + 128 : n) - 1, S, W, has_shared).count;
     };
     const int longest = cost(0);
     int pair = longest;
-    for (int64_t wg = 0; wg < cus && wg < nwg; ++wg) { // workgroup 2 cus - 1 - wg runs where wg did
-        const int64_t second = 2 * (int64_t)cus - 1 - wg;
-        const int sum = cost(wg) + (second < nwg ? cost(second) : 0);
+    // Workgroup 2 cus - 1 - w runs where workgroup w < cus did.  A query tile's workgroups, lo .. hi, meet those of two query tiles at most.
+    for (int t = 0; t < tiles && t * Hq < cus; ++t) {
+        const int lo = t * Hq, hi = (lo + Hq < cus ? lo + Hq : cus) - 1;
+        const int near = 2 * cus - 1 - hi, far = 2 * cus - 1 - lo < nwg ? 2 * cus - 1 - lo : nwg - 1;
+        int second = 0;
+        if (near < nwg) {
+            second = cost(near / Hq);
+            const int other = cost(far / Hq);
+            second = other > second ? other : second;
+        }
+        const int sum = cost(t) + second;
         pair = sum > pair ? sum : pair;
     }
     return longest >= 4 && (0.62 * pair + 3.0 < longest || nwg <= cus) ? 2 : 1;
@@ -656,30 +673,11 @@ constexpr int lds_bytes(int D, int key_groups)
     return key_groups > 1 && merge > slots ? merge : slots;
 }
 
-// One or two key groups per workgroup.  With two, a workgroup's 128 query rows are walked by eight waves, each half of them
-// every second key tile: half the iterations on the launch's longest path, at an iteration that takes longer (eight waves
-// meet at its barrier; with all CUs full of equal work two groups reach 0.87 of the rate of two separate workgroups) plus the
-// merge.  It pays where the launch is short of workgroups or of equal ones, so costs in key tiles are compared:
-//   one group  : the longest query tile, as long as every workgroup is resident (two per CU)
-//   two groups : one workgroup per CU, the first round's query tiles and, on the CUs that are free first, the second's
-// Measured per launch, one -> two groups (32/8 heads x 128 unless said): n = 777 24.3 -> 22.3 us, 1024 29.1 -> 25.8, 1500 42.9 -> 37.1,
-// 2048 58.3 -> 53.8, 3001 93 -> 108 (more than two rounds), 2048 rows behind 6144 210 -> 225 (equal tiles); 16/4 heads x 64:
-// n = 1024 20.5 -> 17.4, 3001 51.6 -> 39.7, 4096 70.0 -> 59.2, 6000 110 -> 125; 512 rows behind 7680 (128 workgroups) 114 -> 86.
-int pick_key_groups(const pod_layout &ly, int n, int q0, bool has_shared, int *groups)
-{
-    int dev = -1, cus = 0;
-    POD_HIP_TRY(hipGetDevice(&dev));
-    POD_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    *groups = prefill_key_groups(cus, ly.Hq, n, q0, ly.S, ly.W, has_shared);
-    return POD_OK;
-}
-
 // tile_tab != NULL: keys and values are located through the per-tile address table (k, v, k_shared are not read)
 static int launch_prefill(const pod_layout &ly, int n, int q0, const void *q, const void *k, const void *v,
                           const void *q_shared, const void *k_shared, const unsigned long long *tile_tab, int ntiles,
                           int *len, int *flag, uint64_t lowest_mask, float scale, void *out, const pod_fill_args *fill, hipStream_t st)
 {
-    int rc = POD_OK;
     prefill_params p;
     p.n = n; p.q0 = q0; p.Hq = ly.Hq; p.Hkv = ly.Hkv; p.rep = ly.rep; p.S = ly.S; p.W = ly.W;
     p.q = (const pod_bf16 *)q; p.k = (const pod_bf16 *)k; p.v = (const pod_bf16 *)v;
@@ -699,11 +697,12 @@ static int launch_prefill(const pod_layout &ly, int n, int q0, const void *q, co
          {{(const void *)prefill_kernel<64, true, 1>, lds_bytes(64, 1)}, {(const void *)prefill_kernel<64, true, 2>, lds_bytes(64, 2)}}},
         {{{(const void *)prefill_kernel<128, false, 1>, lds_bytes(128, 1)}, {(const void *)prefill_kernel<128, false, 2>, lds_bytes(128, 2)}},
          {{(const void *)prefill_kernel<128, true, 1>, lds_bytes(128, 1)}, {(const void *)prefill_kernel<128, true, 2>, lds_bytes(128, 2)}}}};
+    int dev = -1, cus = 0;
+    POD_HIP_TRY(hipGetDevice(&dev));
+    POD_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     {
         static std::mutex attr_mutex;
         static bool attr_done[64] = {};
-        int dev = -1;
-        POD_HIP_TRY(hipGetDevice(&dev));
         if (dev < 0 || dev >= 64) return pod_fail(POD_ERR_INVALID_ARG, "device %d outside [0, 64)", dev);
         std::lock_guard<std::mutex> lock(attr_mutex);
         if (!attr_done[dev]) {
@@ -713,9 +712,7 @@ static int launch_prefill(const pod_layout &ly, int n, int q0, const void *q, co
             attr_done[dev] = true;
         }
     }
-    int ks = 1;
-    rc = pick_key_groups(ly, n, q0, q_shared != nullptr, &ks);
-    if (rc) return rc;
+    const int ks = prefill_key_groups(cus, ly.Hq, n, q0, ly.S, ly.W, q_shared != nullptr);
     // The cache construction rides in the same launch.  Where every attention workgroup is resident at once its workgroups come
     // last, for the slots that are free from the start or as soon as the short query tiles are done; in launches of several
     // rounds a few come first and copy next to workgroups that are busy multiplying.  (A launch of its own: n = 777 5.0 us per
