@@ -46,7 +46,6 @@ typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 constexpr int kBN = 64;
 constexpr float kNegBig = -1.0e30f;
 constexpr int kPF = 2;        // LDS fragment reads in flight ahead of the MFMA that uses them (1 is slower, 3 no faster)
-constexpr unsigned kResidentWorkgroups = 512; // two one-group workgroups per CU
 constexpr float kLazy = 8.0f; // how far (log2) a tile's maximum may exceed the reference before rescaling
 
 struct prefill_params {
@@ -719,10 +718,10 @@ static int launch_prefill(const pod_layout &ly, int n, int q0, const void *q, co
     // layer, 16384 tokens 25 us, and the gap before it.)
     p.fill_lo = 0x7fffffff; p.fill_n = 0;
     if (fill) {
-        const bool resident = ks == 2 || attn <= kResidentWorkgroups;
+        const bool resident = ks == 2 || attn <= 2u * (unsigned)cus; // (two one-group workgroups per CU)
         const size_t pieces = (size_t)n * ly.Hkv * (ly.D / 8), per_wg = (size_t)256 * ks * (resident ? kFillUnroll : 1);
         size_t wgs = (pieces + per_wg - 1) / per_wg;
-        const size_t most = resident ? 256 : 32;
+        const size_t most = resident ? cus : (cus + 7) / 8;
         if (wgs > most) wgs = most;
         p.fill = *fill;
         p.fill_n = (int)wgs;

@@ -204,11 +204,14 @@ int pod_launch_similarity(const float *att, int L, int H, int R, int n, float *s
     p.rows = (size_t)R * n;
     p.R = R;
     p.heads_by_xcd = H % 8 == 0 ? 8 : 1;
-    // Blocks of four layers where they leave two workgroups per CU (256 CUs), else of two: more workgroups, which read a row more
+    // Blocks of four layers where they leave two workgroups per CU, else of two: more workgroups, which read a row more
     // often, for few heads or layers, whose rows come out of the L2 (8 layers x 4 heads: 22 us in blocks of two, 24 in blocks of four).
+    int dev = 0, cus = 0;
+    POD_HIP_TRY(hipGetDevice(&dev));
+    POD_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     auto workgroups = [&](int bl) { const long nb = (L + bl - 1) / bl; return nb * (nb + 1) / 2 * kSimHalves * H; };
     if (L > 1) {
-        const int rc = workgroups(4) >= 512 ? launch_pairs<4>(p, st) : launch_pairs<2>(p, st);
+        const int rc = workgroups(4) >= 2 * cus ? launch_pairs<4>(p, st) : launch_pairs<2>(p, st);
         if (rc) return rc;
     }
     hipLaunchKernelGGL(similarity_finish_kernel, dim3((unsigned)(((size_t)L * L + 255) / 256), (unsigned)H), dim3(256), 0, st, p);
