@@ -664,13 +664,10 @@ int prefill_key_groups(int cus, int Hq, int n, int q0, int S, int W, bool has_sh
 
 } // namespace
 
-// dynamic LDS: per key group two K slots and two V slots of kBN tokens x D bf16 each (64 KB at D = 128); two groups also need
-// room for the merge at the end: 128 rows x D fp32 and a (maximum, sum) per lane, which the slots' own bytes hold at D = 128
-constexpr int lds_bytes(int D, int key_groups)
-{
-    const int slots = key_groups * 4 * kBN * D * 2, merge = 128 * D * 4 + 256 * 8;
-    return key_groups > 1 && merge > slots ? merge : slots;
-}
+// dynamic LDS: per key group two K slots and two V slots of kBN tokens x D bf16 each (64 KB at D = 128).  The merge of two groups
+// (128 rows x D fp32 and a (maximum, sum) per lane) takes the slots' place.
+static constexpr int lds_bytes(int D, int key_groups) { return key_groups * 4 * kBN * D * 2; }
+static_assert(128 * 64 * 4 + 256 * 8 <= lds_bytes(64, 2) && 128 * 128 * 4 + 256 * 8 <= lds_bytes(128, 2), "the slots hold the merge");
 
 // tile_tab != NULL: keys and values are located through the per-tile address table (k, v, k_shared are not read)
 static int launch_prefill(const pod_layout &ly, int n, int q0, const void *q, const void *k, const void *v,
