@@ -27,8 +27,8 @@ constexpr int kSimThreads = 256;
 constexpr int kSimHalves = 2;
 typedef __attribute__((ext_vector_type(4))) float sim_f4;
 
-// Added to every element: nothing to a probability above 1e-29, and a zero becomes this, whose x log2(x) is below 1e-34 (the
-// hardware logarithm takes subnormal numbers for 0 and never meets one).  NaNs stay NaNs.
+// Added to every element: nothing to a probability of 2^-95 (2.5e-29) or more, whose spacing it does not reach half of, and a zero
+// becomes this, whose x log2(x) is below 1e-34 (the hardware logarithm takes subnormal numbers for 0 and never meets one).  NaNs stay NaNs.
 constexpr float kSimFloor = 0x1p-120f;
 
 struct sim_params {
