@@ -416,7 +416,7 @@ def main():
                    "rotating_blocks": R, "launch": mode, "launch_info": cache.pod_cache_launch_info(), "bytes_per_step": step_bytes(segs[0][0]),
                    "segments": NSEG, "ms_per_step_segments": stats(seg_ms_per_step),
                    "frac_of_hbm_peak_whole_step": round(value / HBM_PEAK_GBS, 4)},
-        "roofline": {"bound": "hbm", "kernel": "decode_partial_kernel<128, 0, 2, true, 8> (streams K/V, updates the cache, merges the partials)",
+        "roofline": {"bound": "hbm", "kernel": "decode_partial_kernel<128, 0, 2, true, 2, 8> (streams K/V, updates the cache, merges the partials)",
                      "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": None,
                      "traffic_note": "counters need a rocprofv3 run: profiles/decode_step_kernel_cfg2_pmc.txt holds "

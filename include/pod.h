@@ -326,7 +326,7 @@ int pod_score_skip_offset(const pod_config *cfg, size_t *offset);
  * Inter-layer attention similarity for the offline grouping ("Attention Similarity Measurement"):
  * sim[h][a][b] = 1 - mean over the sampled rows of the Jensen-Shannon divergence (base-2
  * logarithms, so in [0, 1]) between the attention rows of layers a and b for head h; 1 on the
- * diagonal.  One GPU pass over the rows per layer pair.
+ * diagonal and for layers with the same rows.  At most 65535 layers and as many heads.
  *   att : dev float [num_layers][num_heads][rows][n], every row a probability vector (the last
  *         `q` tokens of `N` samples flattened into rows = N * q); 16-byte aligned, rows * n a
  *         multiple of 4

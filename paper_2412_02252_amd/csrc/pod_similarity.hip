@@ -14,9 +14,9 @@
 // BL (BL - 1) / 2) layer pairs are accumulated from registers.  The two halves leave their sums in the two places
 // the symmetric result has for a pair; similarity_finish_kernel adds them (a fixed order: same bits on every call).
 // Bound by vector issue: three and a half plain instructions and a logarithm per pair and element, plus a quarter of that for
-// the e's (vector pipes 96 % busy by counter).  32 layers x 32 heads x 32 rows x 2048: 669 -> 270 us; the 669 took
+// the e's (vector pipes 96 % busy by counter).  32 layers x 32 heads x 32 rows x 2048: 673 -> 251 us; the 673 took
 // p (log p - log m) + q (log q - log m) per element, in one workgroup per head and pair of 8-layer blocks with nothing requested
-// ahead.  With the pair's logarithms multiplied into (e(p) + e(q)) directly it takes 251 us, but rows with the same bits then come
+// ahead.  With the pair's logarithms multiplied into e(p) + e(q) directly it takes 6 % less, but rows with the same bits then come
 // out a rounding error away from 1 (one sampled row of 64 entries: every fourth).  Blocks of 8 layers read a row half as often but
 // leave two waves per SIMD: 15 % slower here, 77 instead of 33 us at 8 layers.
 #include "pod_internal.h"
