@@ -632,6 +632,8 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
 // merge.  It pays where the launch is short of workgroups or of equal ones, so costs in key tiles are compared:
 //   one group  : the longest query tile, as long as every workgroup is resident (two per CU)
 //   two groups : one workgroup per CU, the first round's query tiles and, on the CUs that are free first, the second's
+// (a tile of two groups counts 0.62: half of them per group, at an iteration 1.24 times as long; 3 tiles for the merge and the
+// longer start; both fitted to the times below)
 // Measured per launch, one -> two groups (32/8 heads x 128 unless said): n = 777 24.3 -> 22.3 us, 1024 29.1 -> 25.8, 1500 42.9 -> 37.1,
 // 2048 58.3 -> 53.8, 3001 93 -> 108 (more than two rounds), 2048 rows behind 6144 210 -> 225 (equal tiles); 16/4 heads x 64:
 // n = 1024 20.5 -> 17.4, 3001 51.6 -> 39.7, 4096 70.0 -> 59.2, 6000 110 -> 125; 512 rows behind 7680 (128 workgroups) 114 -> 86.
