@@ -174,6 +174,19 @@ __device__ inline float dot2_ones(unsigned pk, float acc)
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk), ones, acc, false);
 }
 
+// 16 bytes per lane from base + off (off per lane) straight into LDS: lane l's go to dst + 16 l (dst the same in every lane).
+// Written as the instruction itself and waited for by hand (vmcnt), because the compiler, which cannot tell the slots apart, puts a
+// wait for ALL outstanding loads into LDS in front of the next transposing LDS read: every tile then stood still for the whole
+// latency of the loads it had just requested.  A load into LDS has no destination register, and nothing else in these kernels uses
+// M0.  Both layers of a request, before -> after (kernels alone, us): 16384 tokens x 32/8 heads x 128 4350 -> 4130,
+// 3001 x 16/4 x 64 84.4 -> 80.0, 777 x 32/8 x 128 48.1 -> 46.9.
+typedef const __attribute__((address_space(1))) char *gbyte_ptr;
+__device__ __forceinline__ void load_lds16(gbyte_ptr base, unsigned off, const char *dst)
+{
+    const unsigned at = (unsigned)(uintptr_t)(const __attribute__((address_space(3))) char *)dst;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(at), "v"(off), "s"(base) : "memory");
+}
+
 template <int D, bool TAB, int KS>
 __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
 {
@@ -183,7 +196,6 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
     constexpr int NPV = NDB * NPS;   // MFMAs of one PV tile (equal to NQK)
     static_assert(NQK == NPV, "slot schedule assumes as many QK as PV MFMAs per tile");
     typedef const __attribute__((address_space(1))) u32x4 *gvec_ptr;
-    typedef const __attribute__((address_space(1))) char *gbyte_ptr;
     typedef __attribute__((address_space(3))) char *lbyte_ptr;
     typedef __attribute__((ext_vector_type(4))) short s16x4;
     typedef __attribute__((address_space(3))) s16x4 *ltr_ptr;
@@ -256,8 +268,6 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
         v_off[x] = (unsigned)(16 * wave + VRI * x + v_r) * rowb + v_col;
         k_off[x] = (unsigned)(16 * wave + VRI * x + v_r) * rowb + k_col(x);
     }
-    typedef const __attribute__((address_space(1))) void *gvoid_ptr;
-    typedef __attribute__((address_space(3))) void *lvoid_ptr;
     const char *const k_dst0 = ldsK + wave_s * (16 * D * 2);            // this wave's part of K slot 0
     const char *const v_dst0 = ldsV + wave_s * (16 * D * 2);            // this wave's part of V slot 0
     // TAB: the tile's address comes out of the table with a scalar load; the callers fetch it an iteration ahead
@@ -273,14 +283,14 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
             for (int x = 0; x < VPW; ++x) {
                 unsigned off = k_off[x];
                 asm volatile("" : "+v"(off)); // (else the compiler keeps 64-bit copies of all offsets live: 8 more registers)
-                __builtin_amdgcn_global_load_lds((gvoid_ptr)(base + off), (lvoid_ptr)(k_dst0 + slot * KBUF + x * (VRI * D * 2)), 16, 0, 0);
+                load_lds16(base, off, k_dst0 + slot * KBUF + x * (VRI * D * 2));
             }
         } else {
             asm volatile("" ::: "memory"); // (keeps this a real branch: merged, both paths would pay for the clamping)
 #pragma unroll
             for (int x = 0; x < VPW; ++x) {
                 const unsigned off = (unsigned)min(16 * wave + VRI * x + v_r, p.n - 1 - j0) * rowb + k_col(x);
-                __builtin_amdgcn_global_load_lds((gvoid_ptr)(base + off), (lvoid_ptr)(k_dst0 + slot * KBUF + x * (VRI * D * 2)), 16, 0, 0);
+                load_lds16(base, off, k_dst0 + slot * KBUF + x * (VRI * D * 2));
             }
         }
     };
@@ -294,14 +304,14 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
             for (int x = 0; x < VPW; ++x) {
                 unsigned off = v_off[x];
                 asm volatile("" : "+v"(off));
-                __builtin_amdgcn_global_load_lds((gvoid_ptr)(base + off), (lvoid_ptr)(v_dst0 + slot * VBUF + x * (VRI * D * 2)), 16, 0, 0);
+                load_lds16(base, off, v_dst0 + slot * VBUF + x * (VRI * D * 2));
             }
         } else {
             asm volatile("" ::: "memory");
 #pragma unroll
             for (int x = 0; x < VPW; ++x) {
                 const unsigned off = (unsigned)min(16 * wave + VRI * x + v_r, p.n - 1 - j0) * rowb + v_col;
-                __builtin_amdgcn_global_load_lds((gvoid_ptr)(base + off), (lvoid_ptr)(v_dst0 + slot * VBUF + x * (VRI * D * 2)), 16, 0, 0);
+                load_lds16(base, off, v_dst0 + slot * VBUF + x * (VRI * D * 2));
             }
         }
     };
@@ -324,6 +334,8 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
         const gvec_ptr qr = (gvec_ptr)(src + ((size_t)qrow * p.Hq + head) * D);
 #pragma unroll
         for (int s = 0; s < KST; ++s) qf[s] = as_bf16x8(qr[2 * s + jj]);
+#pragma unroll
+        for (int s = 0; s < KST; ++s) asm volatile("" : "+v"(qf[s])); // (awaited here, not in every iteration where the paths with and without the load meet)
     };
 
     // Boundary tiles: -infinity on the logits that are not this phase's to count.  A lane's 32 logits of a tile are keys
