@@ -125,7 +125,7 @@ __device__ inline float pair_sum(float x)
 // Measured on gfx950: a wave issues roughly one vector instruction per 5-6 cycles, a 32x32x16
 // MFMA keeps the matrix pipe busy for 32 cycles, and with two waves per SIMD the pipe only
 // stays busy if each wave brings at most ~3 ordinary vector instructions, one transcendental
-// and one or two LDS reads per MFMA.  So an iteration is a sequence of MFMA slots of that shape,
+// and one or two LDS reads per MFMA (a synthetic loop of that mix: 17-18 ns per MFMA, 14 without any of it).  So an iteration is a sequence of MFMA slots of that shape,
 // taken from three different tiles:
 //   iteration t:  S(t+1) = K(t+1) Q^T        (logits of the next tile)
 //                 O += V(t-1)^T P(t-1)       (output update of the previous tile)
@@ -137,7 +137,7 @@ __device__ inline float pair_sum(float x)
 // the next iteration, which moves the reference maximum if the tile exceeds it by more than 2^8
 // and rescales the accumulators (rare).  Masked logits are -infinity (exponential 0 whatever the
 // reference); every wave walks every tile of its workgroup.  The row sum adds the bf16-rounded
-// probabilities (v_dot2c_f32_bf16 with ones), i.e. exactly the weights the PV product uses.
+// probabilities (add_four), i.e. exactly the weights the PV product uses.
 //
 // Data movement uses no registers: K and V tiles go from global memory straight into LDS
 // (global_load_lds_dwordx4: each wave instruction fills 1 KB of consecutive LDS, lane l its 16
@@ -152,8 +152,8 @@ __device__ inline float pair_sum(float x)
 //           4 (token % 4).  The A operand of the PV product (V^T: one dim, 8 tokens per lane) comes
 //           out of two ds_read_b64_tr_b16 (the LDS transpose read: inside 16 lanes, lane L receives
 //           element L % 4 of the four 8-byte rows addressed by lanes L / 4 + {0, 4, 8, 12}).
-// K(t+2) and V(t) are requested at the top of iteration t into the slots freed by the barrier
-// before, and awaited (vmcnt) before the barrier that ends the iteration.
+// K(t+2) and V(t) are requested at the start of iteration t into the slots freed by the barrier
+// before, and awaited (vmcnt) before the barrier that ends the iteration; their addresses are computed at the end of iteration t-1.
 // static_for<N>(f): f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>), each call its own
 // instantiation with a compile-time index (no reliance on the loop unroller for big bodies)
 template <class F, int... I>
@@ -167,24 +167,28 @@ __device__ __forceinline__ void static_for(F &&f)
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-__device__ inline float dot2_ones(unsigned pk, float acc)
+// Every element of acc plus the lane's own four bf16 values: in v_mfma_f32_4x4x4_16b_bf16 a lane holds one column of its block's
+// B operand, four values of k, and with ones for A every row of that column of the result is their sum.
+// (v_dot2c_f32_bf16, which this took before, does not run beside the matrix pipe as the other vector instructions do: synthetic loops,
+// two waves per SIMD, 14 ns per 32x32x16 MFMA alone and with four v_fma_f32 beside it, 22 with two dot products; the whole mix of an
+// iteration 17.5 -> 17.1 ns per MFMA, against 18.4 with the pairs taken apart and added.  16384 tokens x 32/8 heads x 128 4132 -> 4000 us.)
+__device__ inline f32x4 add_four(u32x2 v, f32x4 acc)
 {
-    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk), ones, acc, false);
+    typedef __attribute__((ext_vector_type(4))) short s16x4;
+    const s16x4 ones = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
+    return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_bit_cast(s16x4, v), acc, 0, 0, 0);
 }
 
-// 16 bytes per lane from base + off (off per lane) straight into LDS: lane l's go to dst + 16 l (dst the same in every lane).
+// 16 bytes per lane from base + off (off per lane) straight into LDS: lane l's go to LDS address dst + 16 l (dst the same in every lane).
 // Written as the instruction itself and waited for by hand (vmcnt), because the compiler, which cannot tell the slots apart, puts a
 // wait for ALL outstanding loads into LDS in front of the next transposing LDS read: every tile then stood still for the whole
 // latency of the loads it had just requested.  A load into LDS has no destination register, and nothing else in these kernels uses
 // M0.  Both layers of a request, before -> after (kernels alone, us): 16384 tokens x 32/8 heads x 128 4350 -> 4130,
 // 3001 x 16/4 x 64 84.4 -> 80.0, 777 x 32/8 x 128 48.1 -> 46.9.
 typedef const __attribute__((address_space(1))) char *gbyte_ptr;
-__device__ __forceinline__ void load_lds16(gbyte_ptr base, unsigned off, const char *dst)
+__device__ __forceinline__ void load_lds16(gbyte_ptr base, unsigned off, unsigned dst)
 {
-    const unsigned at = (unsigned)(uintptr_t)(const __attribute__((address_space(3))) char *)dst;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(at), "v"(off), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(base) : "memory");
 }
 
 template <int D, bool TAB, int KS>
@@ -192,6 +196,10 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
 {
     constexpr int CPR = D / 8, KST = D / 16, NDB = D / 32, NKB = kBN / 32, NPS = kBN / 16;
     constexpr int BM = 128;
+    // Where a tile's requests are issued.  All at once at the top of an iteration, next to another workgroup that multiplies meanwhile; one
+    // in each of the first slots where the eight waves of a CU belong to one workgroup and would all stand still for them (777 tokens x 32/8
+    // heads x 128, both layers 44.6 -> 43.6 us; with one key group it is the other way round, 16384 tokens 4050 -> 4074).
+    constexpr bool SPREAD = KS == 2;
     constexpr int NQK = NKB * KST;   // MFMAs of one S tile = K fragments of a tile
     constexpr int NPV = NDB * NPS;   // MFMAs of one PV tile (equal to NQK)
     static_assert(NQK == NPV, "slot schedule assumes as many QK as PV MFMAs per tile");
@@ -221,7 +229,8 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
     const int qt = nqt - 1 - rest / p.rep;
     const int i0 = qt * BM;
     const int i_last = min(i0 + BM, p.n) - 1;
-    const int tid = threadIdx.x, wave = (tid >> 6) & 3, lane = tid & 63;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) & 3; // (a scalar: what depends on the wave alone stays out of the vector pipe)
     const int grp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8); // key group: waves 4 grp .. 4 grp + 3
     char *const ldsK = lds + grp * (2 * KBUF + 2 * VBUF), *const ldsV = ldsK + 2 * KBUF;
     const int n32 = lane & 31, jj = lane >> 5;
@@ -235,10 +244,10 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
     const tile_list tl = tiles_of_rows(i0, i_last, S, W, has_shared);
     const int tD0 = tl.tD0, nD = tl.nD, nP1 = tl.nP1, tB = tl.tB, Tall = tl.count;
     const int T = (Tall + KS - 1) / KS; // tiles of a key group: group g walks tiles g, g + KS, ... of the list
-    auto tile_of = [&](int u, int &kt, bool &phaseD) {
+    auto tile_of = [&](int u, int &kt, bool &phaseD) __attribute__((always_inline)) {
         const int t = KS == 1 ? u : min(u * KS + grp, Tall - 1); // (past the end: the last tile again; mask_tile leaves nothing of it)
         phaseD = t < nD;
-        kt = phaseD ? tD0 + t : (t < nD + nP1 ? t - nD : tB + (t - nD - nP1));
+        kt = t + (phaseD ? tD0 : (t < nD + nP1 ? -nD : tB - nD - nP1));
     };
 
     // ---- global -> LDS.  Wave w moves K fragments w*NQK/4 .. and the V rows w*16 .. w*16+15.
@@ -261,59 +270,53 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
         return head_col + (unsigned)(16 * ((lane % CPR) ^ rot));
     };
     const unsigned v_col = head_col + (unsigned)(16 * ((lane % CPR) ^ ((4 * (v_r & 3)) & VSWZ)));
-    const int wave_s = __builtin_amdgcn_readfirstlane(wave);            // scalar copy: LDS destinations stay scalar
     unsigned k_off[VPW], v_off[VPW];
 #pragma unroll
     for (int x = 0; x < VPW; ++x) {
         v_off[x] = (unsigned)(16 * wave + VRI * x + v_r) * rowb + v_col;
         k_off[x] = (unsigned)(16 * wave + VRI * x + v_r) * rowb + k_col(x);
     }
-    const char *const k_dst0 = ldsK + wave_s * (16 * D * 2);            // this wave's part of K slot 0
-    const char *const v_dst0 = ldsV + wave_s * (16 * D * 2);            // this wave's part of V slot 0
+    const unsigned k_dst0 = (unsigned)(uintptr_t)(lbyte_ptr)lds + grp * (2 * KBUF + 2 * VBUF) + wave * (16 * D * 2); // this wave's part of K slot 0
+    const unsigned v_dst0 = k_dst0 + 2 * KBUF;                                                                        // ... of V slot 0
     // TAB: the tile's address comes out of the table with a scalar load; the callers fetch it an iteration ahead
-    auto k_tile = [&](int kt, bool phaseD) { return tab_k[(phaseD ? 2 * tab_stream : 0) + kt]; };
-    auto v_tile = [&](int kt) { return tab_k[tab_stream + kt]; };
-    auto request_k = [&](int kt, bool phaseD, int slot, unsigned long long tile) {
-        const int j0 = kt * kBN;
-        gbyte_ptr base;
-        if constexpr (TAB) base = (gbyte_ptr)tile;
-        else base = (gbyte_ptr)(phaseD ? p.ks : p.k) + (size_t)j0 * rowb;
-        if (__builtin_expect(j0 + kBN <= p.n, 1)) {
-#pragma unroll
-            for (int x = 0; x < VPW; ++x) {
-                unsigned off = k_off[x];
-                asm volatile("" : "+v"(off)); // (else the compiler keeps 64-bit copies of all offsets live: 8 more registers)
-                load_lds16(base, off, k_dst0 + slot * KBUF + x * (VRI * D * 2));
-            }
-        } else {
-            asm volatile("" ::: "memory"); // (keeps this a real branch: merged, both paths would pay for the clamping)
-#pragma unroll
-            for (int x = 0; x < VPW; ++x) {
-                const unsigned off = (unsigned)min(16 * wave + VRI * x + v_r, p.n - 1 - j0) * rowb + k_col(x);
-                load_lds16(base, off, k_dst0 + slot * KBUF + x * (VRI * D * 2));
-            }
-        }
+    auto k_tile = [&](int kt, bool phaseD) __attribute__((always_inline)) { return tab_k[(phaseD ? 2 * tab_stream : 0) + kt]; };
+    auto v_tile = [&](int kt) __attribute__((always_inline)) { return tab_k[tab_stream + kt]; };
+    // a tile's requests: its scalar base first, then one request after the other
+    const unsigned tile_bytes = kBN * rowb;
+    auto k_base = [&](int kt, bool phaseD, unsigned long long tile) __attribute__((always_inline)) {
+        if constexpr (TAB) return (gbyte_ptr)tile;
+        else return (gbyte_ptr)(phaseD ? p.ks : p.k) + (unsigned long long)(unsigned)kt * tile_bytes;
     };
-    auto request_v = [&](int kt, int slot, unsigned long long tile) {
-        const int j0 = kt * kBN;
-        gbyte_ptr base;
-        if constexpr (TAB) base = (gbyte_ptr)tile;
-        else base = (gbyte_ptr)p.v + (size_t)j0 * rowb;
-        if (__builtin_expect(j0 + kBN <= p.n, 1)) {
+    auto v_base = [&](int kt, unsigned long long tile) __attribute__((always_inline)) {
+        if constexpr (TAB) return (gbyte_ptr)tile;
+        else return (gbyte_ptr)p.v + (unsigned long long)(unsigned)kt * tile_bytes;
+    };
+    // (the lambdas are forced inline: one that becomes a function takes its captures through scratch memory)
+    auto request_k = [&](gbyte_ptr base, int slot, int x) __attribute__((always_inline)) {
+        load_lds16(base, k_off[x], k_dst0 + slot * KBUF + x * (VRI * D * 2));
+    };
+    auto request_v = [&](gbyte_ptr base, int slot, int x) __attribute__((always_inline)) {
+        load_lds16(base, v_off[x], v_dst0 + slot * VBUF + x * (VRI * D * 2));
+    };
+    // the prompt's last, partly filled tile: lanes past the end fetch its last row
+    auto request_k_part = [&](gbyte_ptr base, int slot, int rows) __attribute__((always_inline)) {
+        asm volatile("" ::: "memory"); // (keeps this a real branch: merged, both paths would pay for the clamping)
 #pragma unroll
-            for (int x = 0; x < VPW; ++x) {
-                unsigned off = v_off[x];
-                asm volatile("" : "+v"(off));
-                load_lds16(base, off, v_dst0 + slot * VBUF + x * (VRI * D * 2));
-            }
-        } else {
-            asm volatile("" ::: "memory");
+        for (int x = 0; x < VPW; ++x)
+            load_lds16(base, (unsigned)min(16 * wave + VRI * x + v_r, rows - 1) * rowb + k_col(x), k_dst0 + slot * KBUF + x * (VRI * D * 2));
+    };
+    auto request_v_part = [&](gbyte_ptr base, int slot, int rows) __attribute__((always_inline)) {
+        asm volatile("" ::: "memory");
 #pragma unroll
-            for (int x = 0; x < VPW; ++x) {
-                const unsigned off = (unsigned)min(16 * wave + VRI * x + v_r, p.n - 1 - j0) * rowb + v_col;
-                load_lds16(base, off, v_dst0 + slot * VBUF + x * (VRI * D * 2));
-            }
-        }
+        for (int x = 0; x < VPW; ++x)
+            load_lds16(base, (unsigned)min(16 * wave + VRI * x + v_r, rows - 1) * rowb + v_col, v_dst0 + slot * VBUF + x * (VRI * D * 2));
+    };
+    auto request_tile_k = [&](int kt, bool phaseD, int slot, unsigned long long tile) __attribute__((always_inline)) {
+        const gbyte_ptr base = k_base(kt, phaseD, tile);
+        if (__builtin_expect(kt * kBN + kBN <= p.n, 1)) {
+#pragma unroll
+            for (int x = 0; x < VPW; ++x) request_k(base, slot, x);
+        } else request_k_part(base, slot, p.n - kt * kBN);
     };
     // read offsets: K fragment lane slot; V^T transpose-read source row/piece of this lane
     // K fragment (key block kb, k-step s): lane (row n32, jj) reads piece 2 s + jj of row 32 kb + n32, stored at
@@ -330,12 +333,12 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
 
     bf16x8 qf[KST];
     const int qrow = max(min(irow, p.n - 1), p.q0) - p.q0;
-    auto load_q = [&](const pod_bf16 *src) {
+    auto load_q = [&](const pod_bf16 *src) __attribute__((always_inline)) {
         const gvec_ptr qr = (gvec_ptr)(src + ((size_t)qrow * p.Hq + head) * D);
 #pragma unroll
         for (int s = 0; s < KST; ++s) qf[s] = as_bf16x8(qr[2 * s + jj]);
 #pragma unroll
-        for (int s = 0; s < KST; ++s) asm volatile("" : "+v"(qf[s])); // (awaited here, not in every iteration where the paths with and without the load meet)
+        for (int s = 0; s < KST; ++s) asm volatile("" : "+v"(qf[s])); // awaited here, not wherever the paths with and without the load meet
     };
 
     // Boundary tiles: -infinity on the logits that are not this phase's to count.  A lane's 32 logits of a tile are keys
@@ -343,11 +346,11 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
     // without an interval), so one bit mask per tile says it all: two vector instructions per logit (bit out of the mask,
     // select by it) instead of the five to seven that comparing every key's position took (upper layers' launches at n = 777,
     // 32 heads x 128, window 256: 39.3 -> 29.9 us; n = 2048: 75.1 -> 66.4).
-    auto first_bits = [&](int x) { // mask of the elements b with key offset 8 (b >> 2) + (b & 3) <= x
+    auto first_bits = [&](int x) __attribute__((always_inline)) { // mask of the elements b with key offset 8 (b >> 2) + (b & 3) <= x
         const int cnt = x < 0 ? 0 : x > 63 ? 32 : 4 * (x >> 3) + min((x & 7) + 1, 4);
         return (unsigned)((1ull << cnt) - 1);
     };
-    auto mask_tile = [&](int u, int kt, bool phaseD, f32x16 (&sc)[NKB]) { // u-th tile of the wave's key group
+    auto mask_tile = [&](int u, int kt, bool phaseD, f32x16 (&sc)[NKB]) __attribute__((always_inline)) { // u-th tile of the wave's key group
         const int j0 = kt * kBN, j1 = j0 + kBN - 1;
         bool full; // every (row, key) pair of the wave counts: no masking needed
         if (phaseD) full = j0 >= S && j1 <= iw0 - W;
@@ -378,11 +381,11 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
         for (int r = 0; r < 16; ++r) oacc[db][r] = 0.f;
     float m_ref = kNegBig, l_run = 0.f;
 
-    auto kfrag = [&](const char *kl, int op) { // QK MFMA number op: the two key blocks alternate
+    auto kfrag = [&](const char *kl, int op) __attribute__((always_inline)) { // QK MFMA number op: the two key blocks alternate
         const int s = op / NKB, kb = op % NKB;
         return *(const u32x4 *)(kl + kb * 32 * (D * 2) + (k_rd0 ^ (32 * s)));
     };
-    auto vfrag = [&](const char *vl, int m) {  // PV MFMA number m = ks * NDB + db
+    auto vfrag = [&](const char *vl, int m) __attribute__((always_inline)) {  // PV MFMA number m = ks * NDB + db
         const int ks = m / NDB, db = m % NDB;
         const lbyte_ptr a = (lbyte_ptr)(vl + ks * 16 * (D * 2)) + v_rd[db];
         const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ltr_ptr)a);
@@ -410,15 +413,16 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
             if (*p.len == p.len_old) *p.len = p.len_new;
             else atomicOr(p.flag, 1);
         }
-        request_k(kt_a, ph_a, 0, k_tile(kt_a, ph_a));
-        if (T > 1) request_k(kt_b, ph_b, 1, k_tile(kt_b, ph_b));
+        request_tile_k(kt_a, ph_a, 0, k_tile(kt_a, ph_a));
+        if (T > 1) request_tile_k(kt_b, ph_b, 1, k_tile(kt_b, ph_b));
         if (T > 2) k_next = k_tile(kt_c, ph_c);
         v_next = v_tile(kt_a);
     } else {
-        request_k(kt_a, ph_a, 0, 0);
-        if (T > 1) request_k(kt_b, ph_b, 1, 0);
+        request_tile_k(kt_a, ph_a, 0, 0);
+        if (T > 1) request_tile_k(kt_b, ph_b, 1, 0);
     }
     load_q(ph_a ? p.qs : p.q);
+    gbyte_ptr kb_next = k_base(kt_c, ph_c, k_next), vb_next = v_base(kt_a, v_next); // what the next iteration requests
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     {
@@ -445,16 +449,33 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
     auto iteration = [&](auto first_tag, auto slot_tag, int t, f32x16 (&sc)[NKB], f32x16 (&sn)[NKB], u32x4 (&pprev)[NPS], u32x4 (&pcur)[NPS]) {
         constexpr bool FIRST = decltype(first_tag)::value;
         constexpr int slot = decltype(slot_tag)::value; // = t % 2: every LDS address below is a compile-time offset
-        // K(t+2) replaces K(t) and V(t) replaces V(t-2), both last read before the previous barrier.
-        // (Spreading the requests over the slots instead of issuing them here measured 10 % slower.)
-        if (t + 2 < T) request_k(kt_c, ph_c, slot, k_next);
-        request_v(kt_a, slot, v_next);
-        if constexpr (TAB) {
-            int kt_d; bool ph_d;
-            tile_of(t + 3, kt_d, ph_d);
-            if (t + 3 < T) k_next = k_tile(kt_d, ph_d);
-            if (t + 1 < T) v_next = v_tile(kt_b);
+        const char *kl = ldsK + (slot ^ 1) * KBUF;   // K(t+1)
+        const char *vl = ldsV + (slot ^ 1) * VBUF;   // V(t-1)
+        // slot list: entry >= 0 is QK MFMA number entry, entry < 0 is PV MFMA number -1 - entry
+        constexpr int NS = FIRST ? NQK : NQK + NPV;
+        constexpr int NMIX = FIRST ? NQK : NQK + NQK / 2; // slots of the QK, QK, PV mix
+        auto slot_op = [](int i) constexpr { return FIRST ? i : (i < NMIX ? ((i % 3 == 2) ? -1 - i / 3 : i - i / 3) : -1 - (i - NQK)); };
+        auto frag = [&](int i) { const int op = slot_op(i); return op >= 0 ? kfrag(kl, op) : vfrag(vl, -1 - op); };
+        u32x4 fr[NS];
+        float tt[16][2], ee[16][2]; // staged softmax values (each lives for one slot)
+        float mxv[4] = {-__builtin_inff(), -__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < kPF && i < NS; ++i) fr[i] = frag(i);
+        __builtin_amdgcn_sched_barrier(0);
+        // K(t+2) replaces K(t) and V(t) replaces V(t-2), both last read before the previous barrier.  (The first fragments are requested
+        // ahead of these, so that their way through the LDS overlaps them.)
+        bool more_k = t + 2 < T, more_v = true;
+        if (more_k) {
+            if (__builtin_expect(kt_c * kBN + kBN > p.n, 0)) { request_k_part(kb_next, slot, p.n - kt_c * kBN); more_k = false; }
+            else if constexpr (!SPREAD)
+#pragma unroll
+                for (int x = 0; x < VPW; ++x) request_k(kb_next, slot, x);
         }
+        if (__builtin_expect(kt_a * kBN + kBN > p.n, 0)) { request_v_part(vb_next, slot, p.n - kt_a * kBN); more_v = false; }
+        else if constexpr (!SPREAD)
+#pragma unroll
+            for (int x = 0; x < VPW; ++x) request_v(vb_next, slot, x);
         if (mx_next > m_ref + kLazy) { // (rows with nothing valid so far have mx = -inf and never trigger)
             // The reference moves before tile t is exponentiated: everything computed with the old one is brought
             // to the new one.  That is the row sum, the output accumulators (tiles <= t-2), and P(t-1), whose
@@ -477,22 +498,10 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
             }
             m_ref = mx_next;
         }
-        if (ph_a && !ph_b) load_q(p.q); // the next tile is the first of the own-key phase
+        if (__builtin_expect(ph_a && !ph_b, 0)) load_q(p.q); // the next tile is the first of the own-key phase
         const float mr = m_ref;
-        float ps = 0.f;
-        const char *kl = ldsK + (slot ^ 1) * KBUF;   // K(t+1)
-        const char *vl = ldsV + (slot ^ 1) * VBUF;   // V(t-1)
-        // slot list: entry >= 0 is QK MFMA number entry, entry < 0 is PV MFMA number -1 - entry
-        constexpr int NS = FIRST ? NQK : NQK + NPV;
-        constexpr int NMIX = FIRST ? NQK : NQK + NQK / 2; // slots of the QK, QK, PV mix
-        auto slot_op = [](int i) constexpr { return FIRST ? i : (i < NMIX ? ((i % 3 == 2) ? -1 - i / 3 : i - i / 3) : -1 - (i - NQK)); };
-        auto frag = [&](int i) { const int op = slot_op(i); return op >= 0 ? kfrag(kl, op) : vfrag(vl, -1 - op); };
-        u32x4 fr[NS];
-        float tt[16][2], ee[16][2]; // staged softmax values (each lives for one slot)
-        float mxv[4] = {-__builtin_inff(), -__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
+        f32x4 lsum = {0.f, 0.f, 0.f, 0.f}; // this tile's row sum, four times
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < kPF && i < NS; ++i) fr[i] = frag(i);
         static_for<NS>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
             if constexpr (!FIRST && i == NMIX) {
@@ -500,6 +509,8 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
                 __builtin_amdgcn_sched_barrier(0);
             }
             if constexpr (i + kPF < NS) fr[i + kPF] = frag(i + kPF);
+            if constexpr (SPREAD && i < VPW) if (more_v) request_v(vb_next, slot, i);
+            if constexpr (SPREAD && i >= VPW && i < 2 * VPW) if (more_k) request_k(kb_next, slot, i - VPW);
             constexpr int op = slot_op(i);
             if constexpr (op >= 0) {
                 constexpr int s = op / NKB, kb = op % NKB;
@@ -526,11 +537,11 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
                         if constexpr (v >= 2) {
                             constexpr int q = v - 2;
                             unsigned pk = pack_bf16(ee[q][0], ee[q][1]);
-                            ps = dot2_ones(pk, ps);
                             // an empty asm statement is a use the compiler cannot move: without it, work whose
                             // consumer sits in a later basic block is sunk out of the slot it was placed in
-                            asm volatile("" : "+v"(pk), "+v"(ps));
+                            asm volatile("" : "+v"(pk));
                             pcur[q >> 2][q & 3] = pk;
+                            if constexpr (q & 1) lsum = add_four(u32x2{pcur[q >> 2][(q & 3) - 1], pk}, lsum);
                         }
                         if constexpr (v >= 1 && v <= 16) {
                             constexpr int q = v - 1;
@@ -566,9 +577,15 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
             for (int x = 0; x < NKB * 16; ++x) mxv[x & 3] = fmaxf(mxv[x & 3], sn[x >> 4][x & 15]);
         }
         mx_next = pair_max(fmaxf(fmaxf(mxv[0], mxv[1]), fmaxf(mxv[2], mxv[3]))) * c;
-        l_run += ps;
+        l_run += lsum[0];
         kt_a = kt_b; ph_a = ph_b; kt_b = kt_c; ph_b = ph_c;
         tile_of(t + 3, kt_c, ph_c);
+        if constexpr (TAB) {
+            if (t + 3 < T) k_next = k_tile(kt_c, ph_c);
+            if (t + 1 < T) v_next = v_tile(kt_a);
+        }
+        kb_next = k_base(kt_c, ph_c, k_next);
+        vb_next = v_base(kt_a, v_next);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // this wave's K(t+2), V(t) pieces are in LDS
         __syncthreads();
     };
