@@ -65,6 +65,8 @@ struct prefill_params {
     int len_old, len_new;
     // workgroups fill_lo .. fill_lo + fill_n - 1 of the launch store the prompt's k and v in the cache (none: fill_n = 0)
     int fill_lo, fill_n;
+    // launches of one round: from this workgroup on (counted per kv head) the query tiles come in the opposite order
+    int turn, per_kvh;
     pod_fill_args fill;
 };
 
@@ -221,11 +223,13 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
         }
     }
     const int kvh = wg % p.Hkv;
-    const int rest = wg / p.Hkv;
+    int rest = wg / p.Hkv;
+    if (rest >= p.turn) rest = p.turn + p.per_kvh - 1 - rest;
     const int head = kvh * p.rep + rest % p.rep;
-    // (Query tiles are handed out from the last, which has most keys, to the first.  Which tiles share a CU does not
-    // matter: a workgroup takes about as long per key tile alone on its CU as next to a second one, so a launch of
-    // one round takes as long as its longest tile either way; pairing long tiles with short ones measured no gain.)
+    // Query tiles are handed out from the last, which has most keys, to the first; where every workgroup has its place from the
+    // start, the second workgroup of a CU comes from the other end of the list: a workgroup alone on its CU takes about 1.2 us per key
+    // tile, two together 1.5 to 2 each, so the longest gets the shortest beside it (8192 tokens in chunks of 2048 x 32/8 heads
+    // x 128, 512 workgroups of 98 to 128 key tiles in the last chunk: 1234 -> 1211 us per request of two layers).
     const int qt = nqt - 1 - rest / p.rep;
     const int i0 = qt * BM;
     const int i_last = min(i0 + BM, p.n) - 1;
@@ -655,18 +659,23 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
     }
 }
 
+// A launch of one round hands the second half of its workgroups out in the opposite order (prefill_params::turn) where the first half
+// ends with a whole group of kv heads.
+bool turns_order(int cus, int Hkv) { return cus % Hkv == 0; }
+
 // One or two key groups per workgroup.  With two, a workgroup's 128 query rows are walked by eight waves, each half of them
 // every second key tile: half the iterations on the launch's longest path, at an iteration that takes longer (eight waves
-// meet at its barrier; with all CUs full of equal work two groups reach 0.87 of the rate of two separate workgroups) plus the
-// merge.  It pays where the launch is short of workgroups or of equal ones, so costs in key tiles are compared:
-//   one group  : the longest query tile, as long as every workgroup is resident (two per CU)
-//   two groups : one workgroup per CU, the first round's query tiles and, on the CUs that are free first, the second's
-// (a tile of two groups counts 0.62: half of them per group, at an iteration 1.24 times as long; 3 tiles for the merge and the
-// longer start; both fitted to the times below)
-// Measured per launch, one -> two groups (32/8 heads x 128 unless said): n = 777 24.3 -> 22.3 us, 1024 29.1 -> 25.8, 1500 42.9 -> 37.1,
-// 2048 58.3 -> 53.8, 3001 93 -> 108 (more than two rounds), 2048 rows behind 6144 210 -> 225 (equal tiles); 16/4 heads x 64:
-// n = 1024 20.5 -> 17.4, 3001 51.6 -> 39.7, 4096 70.0 -> 59.2, 6000 110 -> 125; 512 rows behind 7680 (128 workgroups) 114 -> 86.
-int prefill_key_groups(int cus, int Hq, int n, int q0, int S, int W, bool has_shared)
+// meet at its barrier) plus the merge.  It pays where the launch is short of workgroups or of equal ones.  Compared are, in key tiles
+// of a workgroup alone on its CU (1.2 us at 32/8 heads x 128):
+//   one group  : of the two workgroups of a CU the longer one's tiles plus 0.66 of the other's
+//   two groups : one workgroup per CU, 0.75 of its tiles + 2.2 for the merge and the longer start; where a second one follows on the
+//                CU, 0.84 of both's tiles + 9.3 (that start again; and a chip that is busy twice clocks lower)
+// fitted to these times per launch, one -> two groups, us (lowest layers, window 512): 32/8 x 128 n = 200 10.9 -> 12.5, 400 13.6 -> 14.4,
+// 777 20.3 -> 20.1, 1024 24.6 -> 23.1, 1500 34.9 -> 33.7, 1800 41.2 -> 42.8, 2048 46.8 -> 47.5, upper layer 52.0 -> 57.5; 16/1 x 128 2048
+// 40.3 -> 35.3, 3001 57.3 -> 48.4, 4096 83.3 -> 77.4; 16/4 x 64 777 14.8 -> 13.6, 3001 42.0 -> 34.5, 4096 57.5 -> 51.4; behind other keys, 32/8
+// x 128: 512 rows behind 7680 148 -> 122, 1024 behind 7168 154 -> 141, 2048 behind 2048 116 -> 124, 2048 behind 6144 233 -> 240.  More than two
+// workgroups per CU: one group (5000 tokens 206 -> 226).
+int prefill_key_groups(int cus, int Hq, int Hkv, int n, int q0, int S, int W, bool has_shared)
 {
     const int last = (n - 1) / 128, tiles = last - q0 / 128 + 1; // query tiles, handed out from the last to the first
     if (cus < 1 || (int64_t)tiles * Hq > 2 * cus) return 1;
@@ -675,22 +684,24 @@ int prefill_key_groups(int cus, int Hq, int n, int q0, int S, int W, bool has_sh
         const int i0 = (last - tile) * 128;
         return tiles_of_rows(i0, (i0 + 128 < n ? i0 + 128 : n) - 1, S, W, has_shared).count;
     };
-    const int longest = cost(0);
-    int pair = longest;
-    // Workgroup 2 cus - 1 - w runs where workgroup w < cus did.  A query tile's workgroups, lo .. hi, meet those of two query tiles at most.
+    const bool turned = turns_order(cus, Hkv);
+    double one = cost(0), two = 0.75 * one + 2.2;
     for (int t = 0; t < tiles && t * Hq < cus; ++t) {
-        const int lo = t * Hq, hi = (lo + Hq < cus ? lo + Hq : cus) - 1;
-        const int near = 2 * cus - 1 - hi, far = 2 * cus - 1 - lo < nwg ? 2 * cus - 1 - lo : nwg - 1;
-        int second = 0;
-        if (near < nwg) {
-            second = cost(near / Hq);
-            const int other = cost(far / Hq);
-            second = other > second ? other : second;
+        const int lo = t * Hq, hi = (lo + Hq < cus ? lo + Hq : cus) - 1, own = cost(t);
+        if (lo + cus < nwg) { // one group: the workgroups at places cus + w of the launch run beside w
+            const int w = hi < nwg - cus ? hi : nwg - cus - 1;
+            const double both = own + 0.66 * cost((turned ? nwg - 1 - w : lo + cus) / Hq);
+            one = both > one ? both : one;
         }
-        const int sum = cost(t) + second;
-        pair = sum > pair ? sum : pair;
+        // two groups: workgroup 2 cus - 1 - w runs where w did; a query tile's workgroups, lo .. hi, meet those of two query tiles at most
+        const int near = 2 * cus - 1 - hi, far = 2 * cus - 1 - lo < nwg ? 2 * cus - 1 - lo : nwg - 1;
+        if (near < nwg) {
+            const int a = cost(near / Hq), b = cost(far / Hq);
+            const double both = 0.84 * (own + (a > b ? a : b)) + 9.3;
+            two = both > two ? both : two;
+        }
     }
-    return longest >= 4 && (0.62 * pair + 3.0 < longest || nwg <= cus) ? 2 : 1;
+    return two < one ? 2 : 1;
 }
 
 } // namespace
@@ -739,7 +750,7 @@ static int launch_prefill(const pod_layout &ly, int n, int q0, const void *q, co
             attr_done[dev] = true;
         }
     }
-    const int ks = prefill_key_groups(cus, ly.Hq, n, q0, ly.S, ly.W, q_shared != nullptr);
+    const int ks = prefill_key_groups(cus, ly.Hq, ly.Hkv, n, q0, ly.S, ly.W, q_shared != nullptr);
     // The cache construction rides in the same launch.  Where every attention workgroup is resident at once its workgroups come
     // last, for the slots that are free from the start or as soon as the short query tiles are done; in launches of several
     // rounds a few come first and copy next to workgroups that are busy multiplying.  (A launch of its own: n = 777 5.0 us per
@@ -755,6 +766,8 @@ static int launch_prefill(const pod_layout &ly, int n, int q0, const void *q, co
         p.fill_n = (int)wgs;
         p.fill_lo = resident ? (int)attn : 0;
     }
+    p.per_kvh = (int)(attn / (unsigned)ly.Hkv);
+    p.turn = ks == 1 && (int64_t)attn <= 2 * cus && turns_order(cus, ly.Hkv) ? cus / ly.Hkv : p.per_kvh;
     const dim3 grid(attn + (unsigned)p.fill_n);
     const auto &var = variants[ly.D == 128][tile_tab != nullptr][ks - 1];
     void *args[] = {&p};

@@ -55,6 +55,28 @@ def test_one_and_two_key_groups_per_workgroup(d, Hq, Hkv, S, n):
         assert_close(out[torch.from_numpy(rows).to(out.device)], ref_prefill(c, layer, n, rows), f"n={n} layer {layer}")
 
 
+@pytest.mark.parametrize("d,Hq,Hkv", [(128, 8, 2), (64, 12, 4)])
+@pytest.mark.parametrize("S,W,n", [(8, 40, 384), (8, 40, 385), (8, 40, 512), (8, 40, 513), (8, 40, 576), (8, 40, 577), (8, 40, 650), (70, 500, 577)])
+def test_shortest_launches_with_two_key_groups(d, Hq, Hkv, S, W, n):
+    """Launches short of workgroups take two key groups from nine key tiles on: 513 tokens in a lowest layer, 385 in an upper one, which
+    visits boundary tiles twice.  Odd and even numbers of tiles, whole and part last tiles; 70 sink tokens, window 500: one tile of
+    distant keys, so the second group starts with the layer's own keys."""
+    c = Case(2, 2, Hq, Hkv, d, S, W, 1, n, seed=270 + n, with_oracle_cache=False)
+    for layer in range(2):
+        assert_close(run_prefill(c, layer, n), ref_prefill(c, layer, n, np.arange(n)), f"n={n} layer {layer}")
+
+
+@pytest.mark.parametrize("d,Hq,Hkv,n", [(128, 64, 4, 600), (64, 64, 8, 600), (64, 128, 8, 400), (128, 66, 6, 520), (128, 64, 64, 640)])
+def test_launches_of_one_round(d, Hq, Hkv, n):
+    """Between one and two workgroups per CU (256 on this card), one key group: the second half takes the query tiles from the other end,
+    where whole groups of kv heads fill the first half (all but 6 kv heads); 64 x 5 query tiles leave the last half part empty."""
+    c = Case(2, 2, Hq, Hkv, d, 8, 40, 1, n, seed=280 + n, with_oracle_cache=False)
+    rows = np.unique(np.concatenate([np.arange(0, n, 29), np.arange(127, n, 128), np.arange(128, n, 128), [n - 1]]))
+    for layer in range(2):
+        out = run_prefill(c, layer, n)
+        assert_close(out[torch.from_numpy(rows).to(out.device)], ref_prefill(c, layer, n, rows), f"n={n} layer {layer}")
+
+
 def test_window_larger_than_tile_and_prompt_shorter_than_window():
     c = Case(2, 2, 8, 2, 128, 64, 512, 1, 1500, seed=41, with_oracle_cache=False)
     for n in (400, 1500):
