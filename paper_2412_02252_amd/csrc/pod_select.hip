@@ -519,7 +519,76 @@ struct compact_params {
     uint4 *ws;                        // [2][Hkv][rows][D] bf16: rows on their way (keys, then values)
 };
 
-// stage 0 copies the surviving rows into the workspace, stage 1 copies them back to where the shorter sequence
+// Row t of the selection of head h at the layer of its block's lowest layer; not a token of the distant store: row 0, and the flag.
+__device__ inline size_t selected_row(const compact_params &p, int h, int row, int n_dist)
+{
+    const int t = p.sel_all[((size_t)p.sel_layer[h] * p.ly.Hkv + h) * p.keep + row];
+    if (t >= 0 && t < n_dist) return (size_t)t;
+    atomicOr((int32_t *)(p.base + p.ly.off_flag), 1);
+    return 0;
+}
+
+// Compaction in one launch and without the workspace.  A workgroup owns 64 bytes of every row of one (kv head, keys or values):
+// nobody else reads or writes them, so it takes all surviving rows into its registers, waits until every wave has done so, and
+// stores them where the shorter sequence keeps them - any selection, in any order - first the distant rows, then the recent window where
+// that turns.  256 rows in flight per step and PER steps: up to 2048 rows with 8, 4096 with 16; what is larger goes through
+// the workspace (below).  The last workgroup to have read the stored length changes it (the count is kept where a decode step
+// keeps its own, zero between launches), or raises the flag if it was not n.  Bound by latency: the length, the selection, the rows, the
+// stores, one after the other.  Heads come first in the grid: a row's pieces then share an L2 where the heads go round the XCDs evenly.
+// Whole requests of two layers, three launches per layer (5.1 + 4.4 + 1.3 us) -> one, 8 kv heads x 128: 16384 tokens -> 1984 selected 134.4 -> 130.2 us,
+// 16001 (the ring turns) 143.3 -> 140.6, 20001 -> 4096 162.5 -> 156.7, 5001 -> 300 98.0 -> 89.9.
+// A workgroup moves its rows at the rate of one CU, so few of them are slower than the three launches, which spread over the chip: whole
+// requests, three -> one, 64 workgroups (8 x 128, 4200 tokens -> 400 selected) 105.2 -> 96.5 us, 32 (4 x 128, 5000 -> 500) 91.1 -> 93.1, 16
+// (4 x 64, 9000 -> 1000) 84.6 -> 87.2, 8 (1 x 128, 12000 -> 3000) 115 -> 131.  Hence at least 64.
+constexpr unsigned kCompactWorkgroups = 64;
+constexpr int kCompactThreads = 1024, kCompactPieces = 4, kCompactRows = kCompactThreads / kCompactPieces;
+template <int PER>
+__global__ __launch_bounds__(kCompactThreads) void compact_kernel(compact_params p)
+{
+    const pod_layout &ly = p.ly;
+    const int h = blockIdx.x, is_v = blockIdx.z;
+    int32_t *const len = (int32_t *)(p.base + ly.off_lens) + (size_t)p.layer * ly.B + p.b;
+    const bool ok = *len == p.n;
+    if (ok) {
+        const int cpr = ly.D / 8, n_dist = p.n - ly.S - ly.W;
+        const int c = blockIdx.y * kCompactPieces + threadIdx.x % kCompactPieces, row0 = threadIdx.x / kCompactPieces;
+        const bool low = (p.hm.lowest_mask >> h) & 1;
+        auto move = [&](pod_u32x4 *rows, int count, auto &&from, auto &&to) { // row to(i) = row from(i), i < count, all at once
+            pod_u32x4 val[PER];
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const int i = row0 + u * kCompactRows;
+                if (i < count) val[u] = rows[from(i) * cpr + c];
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // (a store of another wave must not overtake these)
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const int i = row0 + u * kCompactRows;
+                if (i < count) rows[to(i) * cpr + c] = val[u];
+            }
+        };
+        if (is_v || low) // (the keys of distant tokens are kept by the lowest layer of a block only)
+            move(is_v ? (pod_u32x4 *)(p.base + ly.off_distV) + pod_dist_row0(ly, p.layer, p.b, h) * cpr
+                      : (pod_u32x4 *)(p.base + ly.off_distK) + pod_distk_row0(ly, p.hm, p.b, h) * cpr,
+                 p.keep, [&](int i) { return selected_row(p, h, i, n_dist); }, [](int i) { return (size_t)i; });
+        if (p.rows > p.keep) // (position n - W + i before, S + keep + i after)
+            move((pod_u32x4 *)(p.base + (is_v ? ly.off_proxV : ly.off_proxK)) + (pod_prox_row0(ly, p.layer, p.b, h) + ly.S) * cpr, ly.W,
+                 [&](int i) { return (size_t)((p.n - ly.S + i) % ly.W); }, [&](int i) { return (size_t)((p.keep + i) % ly.W); });
+    }
+    __syncthreads(); // every wave has used the length it read
+    if (threadIdx.x == 0) {
+        int32_t *const done = (int32_t *)(p.base + ly.off_stepdone) + p.b;
+        const int all = (int)(gridDim.x * gridDim.y * gridDim.z);
+        if (__hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == all - 1) {
+            __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (ok) *len = ly.S + p.keep + ly.W;
+            else atomicOr((int32_t *)(p.base + ly.off_flag), 1);
+        }
+    }
+}
+
+// More than 4096 rows of a kind: stage 0 copies the surviving rows into the workspace, stage 1 copies them back to where the shorter sequence
 // keeps them; both do nothing unless the stored length is n (compact_commit_kernel then raises the flag).
 // Rows 0 .. keep - 1: selected distant rows; rows keep .. keep + W - 1: the recent window, oldest first.
 template <int STAGE>
@@ -538,16 +607,7 @@ __global__ void compact_move_kernel(compact_params p)
     uint4 *cache_row;
     if (row < p.keep) {
         if (!is_v && !low) return; // this layer keeps no distant keys for head h
-        size_t r = row;
-        if (STAGE == 0) {
-            const int t = p.sel_all[((size_t)p.sel_layer[h] * ly.Hkv + h) * p.keep + row];
-            if (t < 0 || t >= n_dist) {
-                atomicOr((int32_t *)(p.base + ly.off_flag), 1); // not a selection: copy row 0, report
-                r = 0;
-            } else {
-                r = (size_t)t;
-            }
-        }
+        const size_t r = STAGE == 0 ? selected_row(p, h, row, n_dist) : (size_t)row;
         cache_row = is_v ? (uint4 *)(p.base + ly.off_distV) + (pod_dist_row0(ly, p.layer, p.b, h) + r) * cpr + c
                          : (uint4 *)(p.base + ly.off_distK) + (pod_distk_row0(ly, p.hm, p.b, h) + r) * cpr + c;
     } else {
@@ -642,6 +702,14 @@ int pod_launch_compact(const pod_cache *c, int layer, int b, int n, const int32_
     // dropped tokens it is there already, which is one prompt length in W: 2048 of 4096 kept rows, per layer, 7.9 + 6.4 us at 16001 tokens,
     // 5.0 + 4.0 at 16384, where it happens to.
     p.rows = keep + ((n - ly.S - ly.W - keep) % ly.W != 0 ? ly.W : 0);
+    const int most = p.rows > keep && ly.W > keep ? ly.W : keep; // rows of one kind that move
+    const dim3 g1(ly.Hkv, ly.D / 8 / kCompactPieces, 2);
+    if (most <= 16 * kCompactRows && g1.x * g1.y * g1.z >= kCompactWorkgroups) {
+        if (most <= 8 * kCompactRows) hipLaunchKernelGGL(compact_kernel<8>, g1, dim3(kCompactThreads), 0, st, p);
+        else hipLaunchKernelGGL(compact_kernel<16>, g1, dim3(kCompactThreads), 0, st, p);
+        POD_HIP_TRY(hipGetLastError());
+        return POD_OK;
+    }
     const int items = p.rows * (ly.D / 8);
     const dim3 g((items + 255) / 256, ly.Hkv, 2);
     hipLaunchKernelGGL(compact_move_kernel<0>, g, dim3(256), 0, st, p);

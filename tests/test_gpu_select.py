@@ -233,6 +233,43 @@ def test_select_compact_and_decode_on(name, L, G, Hq, Hkv, d, S, W, n, obs, keep
     c.gpu.pod_cache_check()
 
 
+@pytest.mark.parametrize("d,Hkv,S,W,n,keep", [(128, 8, 4, 40, 2600, 1), (128, 8, 4, 40, 2600, 255), (128, 8, 4, 40, 2600, 2048), (128, 8, 4, 40, 2600, 2049),
+                                              (64, 16, 4, 2048, 5001, 300), (64, 16, 0, 2049, 7000, 257), (128, 8, 4, 40, 4400, 4096), (128, 8, 4, 40, 4400, 4097),
+                                              (128, 8, 4, 4100, 8400, 100), (64, 8, 4, 100, 3000, 700)])
+@pytest.mark.parametrize("order", ["ascending", "any"])
+def test_compaction_moves_the_selected_rows(d, Hkv, S, W, n, keep, order):
+    """One launch with up to 2048 or 4096 rows in flight, the workspace beyond that, for a ring that turns and one that does not (n chosen),
+    and for launches too small for it (8 x 64); selections in ascending order and in any, with repetitions: bit for bit."""
+    dev = torch.device("cuda:0")
+    gen_ = torch.Generator(device=dev).manual_seed(n + keep)
+    cfg = pod.make_config(2, 2, Hkv, Hkv, d, S, W, 2, n + 1)
+    cache = pod.PodCache(cfg, dev, guard_bytes=4096)
+    k, v = (torch.randn((2, n, Hkv, d), generator=gen_, device=dev).to(torch.bfloat16) for _ in range(2))
+    n_dist = n - S - W
+    if order == "ascending":
+        sel = torch.stack([torch.stack([torch.randperm(n_dist, generator=gen_, device=dev)[:keep].sort().values for _ in range(Hkv)]) for _ in range(2)])
+    else:
+        sel = torch.randint(0, n_dist, (2, Hkv, keep), generator=gen_, device=dev)
+    sel = sel.to(torch.int32).contiguous()
+    ws = cache.new_select_workspace(n, 1, keep)
+    for layer in range(2):
+        cache.pod_cache_fill(layer, 1, k[layer], v[layer])
+    for layer in range(2):
+        cache.pod_cache_compact(layer, 1, sel, ws)
+    cache.pod_cache_check()
+    cache.pod_cache_sync_lengths()
+    idx = sel[0].long().t()[:, :, None].expand(-1, -1, d) + S     # (both layers follow the lowest one's selection)
+    for layer in range(2):
+        assert cache.pod_cache_seq_len(layer, 1) == S + keep + W
+        got = cache.pod_cache_export_logical(layer, 1)
+        assert torch.equal(got["distV"], torch.gather(v[layer], 0, idx))
+        if layer == 0:
+            assert torch.equal(got["distK"], torch.gather(k[layer], 0, idx))
+        assert torch.equal(got["recentK"], k[layer][n - W:]) and torch.equal(got["recentV"], v[layer][n - W:])
+        if S:
+            assert torch.equal(got["sinkK"], k[layer][:S]) and torch.equal(got["sinkV"], v[layer][:S])
+
+
 @pytest.mark.parametrize("d,S,W,n,chunk", [(128, 8, 48, 1000, 300), (64, 0, 32, 555, 555), (128, 5, 100, 106, 50)])
 def test_votes_from_the_cached_keys_are_the_same_bits(d, S, W, n, chunk):
     # the prompt goes in through the chunk call (sink slots, distant rows and a wrapped ring), then the votes are taken
