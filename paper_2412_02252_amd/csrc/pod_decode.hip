@@ -1131,12 +1131,20 @@ __device__ void step_workgroup(const decode_params &p, const decode_hot &hot, in
 // the cache update (step_workgroup); the others leave the ring slot it rewrites out, as in decode_partial_kernel.
 // The tile loops are decode_partial_kernel's: the plain one, and for MODE 2's distant rows the one that reads logits;
 // there a unit of distant rows is twice as many tokens (even_unit_distant), so that all units cost about the same.
+// V comes in 16 pieces of D / 16 dims per row, one per lane of a group of 16: 16 bytes at D = 128, 8 at D = 64.  (With 16-byte pieces at D = 64
+// too, as in decode_partial_kernel, two lanes load each of them and use half of it.  Whole requests, 32 chats of 0.3-4K tokens x 16/4 x 64
+// 1529 -> 1430 us, 48 of 0.5-5K 1336 -> 1270, 4 of 3-30K x 8/8 x 64 958 -> 906.  The short launches of decode_partial_kernel gain nothing: 2 pairs
+// at 2048 tokens 453 -> 464, 32 of 0.6-6K 469 -> 461.)
+template <int D> struct v_piece { typedef u32x4 type; };
+template <> struct v_piece<64> { typedef __attribute__((ext_vector_type(2))) unsigned type; };
 template <int D, bool STEP, int MODE>
 __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_params p)
 {
     static_assert(MODE == 0 || (MODE == 2 && STEP), "plain launches, and score-reuse decode steps of upper layers");
     constexpr int NW = kWaves;
-    constexpr int CPR = D / 8, RPI = 64 / CPR, NLD = kTile / RPI, KST = D / 32, XN = 16 / CPR, NPV = 8 / XN;
+    constexpr int CPR = D / 8, RPI = 64 / CPR, NLD = kTile / RPI, KST = D / 32, NPV = D / 16;
+    typedef typename v_piece<D>::type vpiece;
+    typedef const __attribute__((address_space(1))) vpiece *gv_ptr;
     constexpr int kUnitD = even_unit_distant(MODE);   // tokens per unit of distant rows
     typedef const __attribute__((address_space(1))) u32x4 *gvec_ptr;
     const decode_hot hot = load_hot_args();
@@ -1156,7 +1164,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_para
     const unsigned long long tr_t0 = p.trace ? wall_clock64() : 0;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int m16 = lane & 15, j = lane >> 4;
-    const int kr = lane / CPR, kc = lane % CPR, vc = lane % CPR, vx = (lane / CPR) % XN;
+    const int kr = lane / CPR, kc = lane % CPR;
     constexpr int RS = D + 4 * (D / 32) + 1;
     constexpr size_t kTileBytes = sizeof(u32x4) * NW * kTile * CPR, kMergeBytes = sizeof(float) * NW * 16 * RS;
     __shared__ __attribute__((aligned(16))) char lds_raw[kTileBytes > kMergeBytes ? kTileBytes : kMergeBytes];
@@ -1196,7 +1204,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_para
         float m_run = kNegBig, l_run = 0.f;
 
         // ---- online softmax for head m16 over this lane's 8 tokens (base-2 domain), then O^T += V^T P
-        auto softmax_pv = [&](float (&sc)[8], const u32x4 (&vcur)[8]) {
+        auto softmax_pv = [&](float (&sc)[8], const vpiece (&vcur)[8]) {
             float mx = sc[0];
 #pragma unroll
             for (int i = 1; i < 8; ++i) mx = fmaxf(mx, sc[i]);
@@ -1220,8 +1228,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_para
 #pragma unroll
             for (int x = 0; x < NPV; ++x) {
                 u32x4 tlo, thi;
-                const int wd = (XN == 1) ? (x >> 1) : x;
-                auto dw = [&](const u32x4 &u) -> unsigned { return u[wd]; };
+                const int wd = x >> 1; // dword of the piece holding dim x
+                auto dw = [&](const vpiece &u) -> unsigned { return u[wd]; };
                 tlo.x = __builtin_amdgcn_perm(dw(vcur[1]), dw(vcur[0]), 0x05040100u);
                 tlo.y = __builtin_amdgcn_perm(dw(vcur[3]), dw(vcur[2]), 0x05040100u);
                 tlo.z = __builtin_amdgcn_perm(dw(vcur[5]), dw(vcur[4]), 0x05040100u);
@@ -1230,13 +1238,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_para
                 thi.y = __builtin_amdgcn_perm(dw(vcur[3]), dw(vcur[2]), 0x07060302u);
                 thi.z = __builtin_amdgcn_perm(dw(vcur[5]), dw(vcur[4]), 0x07060302u);
                 thi.w = __builtin_amdgcn_perm(dw(vcur[7]), dw(vcur[6]), 0x07060302u);
-                u32x4 vt;
-                if (XN == 1) {
-                    vt = (x & 1) ? thi : tlo;
-                } else {
-                    vt.x = vx ? thi.x : tlo.x; vt.y = vx ? thi.y : tlo.y;
-                    vt.z = vx ? thi.z : tlo.z; vt.w = vx ? thi.w : tlo.w;
-                }
+                const u32x4 vt = (x & 1) ? thi : tlo;
                 acc[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vt), pf, acc[x], 0, 0, 0);
             }
         };
@@ -1254,9 +1256,10 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_para
             const int last = end - 1;
             const int excl = (STEP && !distant && n >= prows) ? p.sink + (n - p.sink) % p.window : -1;
             const gvec_ptr Kb = (gvec_ptr)(distant ? hot.kdist + kslot_row * hot.cd * CPR : hot.kprox + pair * prows * CPR);
-            const gvec_ptr Vb = (gvec_ptr)(distant ? hot.vdist + pair * hot.cd * CPR : hot.vprox + pair * prows * CPR);
+            const gv_ptr Vb = (gv_ptr)(distant ? hot.vdist + pair * hot.cd * CPR : hot.vprox + pair * prows * CPR);
             const pod_bf16 *qsrc = (distant && hot.q_shared && head_arg >= 0) ? hot.q_shared : hot.q;
-            u32x4 kreg[NLD], vreg[8];
+            u32x4 kreg[NLD];
+            vpiece vreg[8];
             int t0 = start + wave * kTile;
             // (from the last tile to the first where a lower layer of the block has just read these keys: see decode_partial_kernel)
             const int ntile_w = t0 < end ? (end - t0 + NW * kTile - 1) / (NW * kTile) : 0;
@@ -1271,7 +1274,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_para
     _Pragma("unroll") for (int e = 0; e < 8; ++e) {                               \
         const int tok = (e < 4) ? 4 * j + e : 16 + 4 * j + (e - 4);               \
         const int row = min((T0) + tok, last);                                    \
-        vreg[e] = __builtin_nontemporal_load(&Vb[(size_t)row * CPR + vc]);        \
+        vreg[e] = __builtin_nontemporal_load(&Vb[(size_t)row * 16 + m16]);        \
     }
             if (ntile_w > 0) { POD_LOAD_TILE(t0) }
             bf16x8 qf[KST];
@@ -1290,7 +1293,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_para
                     const int r = RPI * i + kr;
                     ldsK[r * CPR + (kc ^ (r % CPR))] = kreg[i];
                 }
-                u32x4 vcur[8];
+                vpiece vcur[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) vcur[e] = vreg[e];
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1323,13 +1326,13 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_para
         // the per-lane order of the S^T accumulators; only V is streamed, two tiles in flight per wave.
         auto walk_sv = [&](const int start, const int end) {
             const int last = end - 1;
-            const gvec_ptr Vb = (gvec_ptr)(hot.vdist + pair * hot.cd * CPR);
-            u32x4 vreg[8];
+            const gv_ptr Vb = (gv_ptr)(hot.vdist + pair * hot.cd * CPR);
+            vpiece vreg[8];
             int t0 = start + wave * kTile;
                 typedef const __attribute__((address_space(1))) f32x4 *gf4_r;
                 const gf4_r sbase = (gf4_r)(p.scores + pair * p.score_stride * hot.rep) + ((size_t)j * hot.rep + (m16 < hot.rep ? m16 : 0)) * 2;
                 f32x4 sregA[2], sregB[2];
-                u32x4 vregB[8];
+                vpiece vregB[8];
 #define POD_LOAD_SV(SR, VR, T0)                                                   \
                 {                                                                     \
                     const gf4_r sp = sbase + (size_t)(min((T0), last) >> 5) * 8 * hot.rep; \
@@ -1339,11 +1342,11 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_para
                 _Pragma("unroll") for (int e = 0; e < 8; ++e) {                       \
                     const int tok = (e < 4) ? 4 * j + e : 16 + 4 * j + (e - 4);       \
                     const int row = min((T0) + tok, last);                            \
-                    VR[e] = __builtin_nontemporal_load(&Vb[(size_t)row * CPR + vc]);  \
+                    VR[e] = __builtin_nontemporal_load(&Vb[(size_t)row * 16 + m16]);  \
                 }
 #define POD_CONSUME_SV(SR, VR, T0, TNEXT)                                         \
                 {                                                                     \
-                    u32x4 vcur[8];                                                    \
+                    vpiece vcur[8];                                                   \
                     float sc[8];                                                      \
                     _Pragma("unroll") for (int e = 0; e < 8; ++e) vcur[e] = VR[e];    \
                     _Pragma("unroll") for (int i = 0; i < 4; ++i) {                   \
@@ -1386,7 +1389,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_para
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int slot = 4 * j + i;
-                    const int dim = (XN == 1) ? 8 * slot + x : 8 * (slot % 8) + 2 * x + slot / 8;
+                    const int dim = D / 16 * slot + x;
                     sm_acc[((size_t)wave * hot.rep + m16) * RS + dim + 4 * (dim >> 5)] = acc[x][i];
                 }
             if (j == 0) { sm_m[wave][m16] = m_run; sm_l[wave][m16] = l_run; }
