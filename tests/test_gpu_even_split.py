@@ -143,6 +143,24 @@ def test_one_long_sequence_among_many_short_ones(monkeypatch):
     c.gpu.pod_cache_check()
 
 
+@pytest.mark.parametrize("d,Hq,Hkv,B,lo,step", [(64, 8, 8, 24, 300, 37), (128, 8, 4, 30, 130, 91), (64, 16, 8, 70, 5, 13), (128, 4, 4, 40, 1, 60)])
+def test_parts_of_whole_pairs_and_parts_that_cross(d, Hq, Hkv, B, lo, step, monkeypatch):
+    """More units than workgroups: parts padded to whole pairs where they fit, parts that cross from pair to pair where the
+    pairs outnumber the workgroups (70 x 8); sequences of a few tokens among them."""
+    monkeypatch.setenv("POD_DECODE_FUSED", "0")
+    lens = [lo + (step * i * i) % 900 for i in range(B)]
+    c = Case(2, 2, Hq, Hkv, d, 8, 64, B, 1210, seed=9350 + B)
+    fill_all(c, lens)
+    for s in range(2):
+        pos = [n + s for n in lens]
+        for layer in range(2):
+            assert_close(c.step(layer, pos), c.decode_ref(layer, [p + 1 for p in pos]), f"step {s} layer {layer}")
+    ctx = [n + 2 for n in lens]
+    for layer in range(2):
+        assert_close(c.decode(layer, ctx), c.decode_ref(layer, ctx), f"decode layer {layer}")
+    c.gpu.pod_cache_check()
+
+
 def test_wrong_context_length_is_flagged_in_the_even_split(monkeypatch):
     monkeypatch.setenv("POD_DECODE_FUSED", "0")
     lens = [900, 300, 77]
