@@ -1131,16 +1131,18 @@ __device__ void step_workgroup(const decode_params &p, const decode_hot &hot, in
 // the cache update (step_workgroup); the others leave the ring slot it rewrites out, as in decode_partial_kernel.
 // The tile loops are decode_partial_kernel's: the plain one, and for MODE 2's distant rows the one that reads logits;
 // there a unit of distant rows is twice as many tokens (even_unit_distant), so that all units cost about the same.
+// MERGE: the parts are padded to whole pairs, so every workgroup has one part, and the pair's last one merges, as in decode_partial_kernel.
 // V comes in 16 pieces of D / 16 dims per row, one per lane of a group of 16: 16 bytes at D = 128, 8 at D = 64.  (With 16-byte pieces at D = 64
 // too, as in decode_partial_kernel, two lanes load each of them and use half of it.  Whole requests, 32 chats of 0.3-4K tokens x 16/4 x 64
 // 1529 -> 1430 us, 48 of 0.5-5K 1336 -> 1270, 4 of 3-30K x 8/8 x 64 958 -> 906.  The short launches of decode_partial_kernel gain nothing: 2 pairs
 // at 2048 tokens 453 -> 464, 32 of 0.6-6K 469 -> 461.)
 template <int D> struct v_piece { typedef u32x4 type; };
 template <> struct v_piece<64> { typedef __attribute__((ext_vector_type(2))) unsigned type; };
-template <int D, bool STEP, int MODE>
+template <int D, bool STEP, int MODE, bool MERGE = false>
 __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_params p)
 {
     static_assert(MODE == 0 || (MODE == 2 && STEP), "plain launches, and score-reuse decode steps of upper layers");
+    static_assert(!MERGE || (MODE == 0 && D == 64), "the merge inside is for plain launches at head dimension 64");
     constexpr int NW = kWaves;
     constexpr int CPR = D / 8, RPI = 64 / CPR, NLD = kTile / RPI, KST = D / 32, NPV = D / 16;
     typedef typename v_piece<D>::type vpiece;
@@ -1150,6 +1152,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_para
     const decode_hot hot = load_hot_args();
     const int hkv = hot.hkv, prows = hot.prows;
     const int w = blockIdx.x;
+    [[maybe_unused]] int done_b = -1, done_h = 0, done_n = 0, done_parts = 0; // MERGE: the pair whose partial this workgroup has stored
     if (w >= p.bal_nwg) {
         if constexpr (STEP) {
             const int pr = w - p.bal_nwg;
@@ -1158,8 +1161,9 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_para
             const int n = load_hlen_arg(b), head_arg = load_head_arg(h);
             if ((MODE == 2 && head_arg < 0) || n < 0) return;
             step_workgroup<D, false, NW, MODE>(p, hot, b, h, n, head_arg);
+            done_b = b; done_h = h; done_n = n; done_parts = (load_cum_arg(b + 1) - load_cum_arg(b)) / p.bal_q;
         }
-        return;
+        if constexpr (!MERGE || !STEP) return; // (else on to the merge: there are no units for it to walk)
     }
     const unsigned long long tr_t0 = p.trace ? wall_clock64() : 0;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -1411,10 +1415,34 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_para
             }
             typedef __attribute__((address_space(1))) float *gfloat_ptr;
             const size_t slot = ((size_t)b * hot.hq + (size_t)h * hot.rep + head) * NC + (w - w_lo);
-            ((gfloat_ptr)hot.part_acc)[slot * D + dim] = A;
-            if (dim == 0) { ((gfloat_ptr)hot.part_ml)[slot * 2] = M; ((gfloat_ptr)hot.part_ml)[slot * 2 + 1] = Lsum; }
+            if constexpr (MERGE) { // read by another workgroup of this launch
+                store_part<false>(hot.part_acc + slot * D + dim, A);
+                if (dim == 0) { store_part<false>(hot.part_ml + slot * 2, M); store_part<false>(hot.part_ml + slot * 2 + 1, Lsum); }
+            } else {
+                ((gfloat_ptr)hot.part_acc)[slot * D + dim] = A;
+                if (dim == 0) { ((gfloat_ptr)hot.part_ml)[slot * 2] = M; ((gfloat_ptr)hot.part_ml)[slot * 2 + 1] = Lsum; }
+            }
+        }
+        if constexpr (MERGE) { // (padded to whole pairs: this was the workgroup's only part)
+            done_b = b; done_h = h; done_n = n; done_parts = U / p.bal_q;
+            break;
         }
         __syncthreads(); // the merge buffer is the next pair's K tiles
+    }
+    if constexpr (MERGE) {
+        // The last of the pair's parts (and a step's own workgroup) merges them.  What is checked is decode_partial_kernel's: the call's length
+        // against the stored ones and against the one that was walked.
+        if (done_b >= 0 && arrive_last<false>(p.tickets + (size_t)done_b * hkv + done_h, done_parts + (STEP ? 1 : 0))) {
+            bool valid = true, bad = false;
+            if constexpr (!STEP) {
+                const int v_ctx = hot.ctx[done_b], v_dev = hot.lens_layer[done_b], v_low = hot.lens_lowest[done_b];
+                if (v_ctx == 0) valid = false;
+                else if (v_ctx < 0 || v_ctx > p.maxctx || v_ctx > p.max_len || v_ctx != v_dev || (v_ctx > prows && v_low != v_ctx) || v_ctx != done_n) {
+                    valid = false; bad = true;
+                }
+            }
+            merge_and_store<D, false, NW>(p, hot, done_b, done_h, done_parts, 0, STEP, valid, bad);
+        }
     }
     if (p.trace && threadIdx.x == 0 && w < p.trace_cap) { // measurement aid: workgroup, XCD and CU, clock at start and end
         unsigned long long *t = p.trace + 8 * (size_t)w;
@@ -1821,7 +1849,7 @@ bool pod_plan_even(int slots, int B, int Hkv, int P, int unit_d, const int32_t *
 // rows in the padding.)  32 chats of 0.3-4K tokens x 4 kv heads x 64, 445 workgroups of 5 units, took 7.3 to 13.6 us per workgroup, median 10.3;
 // padded to 492 the request takes 1294 us instead of 1411.  12 of 1.5-15K x 4 x 128 1643 -> 1589; long launches, whose workgroups walk many
 // units, the same either way, and so score reuse (0.993-0.999), which keeps the plain split.
-static void pad_even_plan(int slots, int B, int Hkv, int32_t *unit_cum, pod_even_plan_t *pl)
+static bool pad_even_plan(int slots, int B, int Hkv, int32_t *unit_cum, pod_even_plan_t *pl)
 {
     const int q = pl->q;
     long wgs = 0;
@@ -1831,7 +1859,7 @@ static void pad_even_plan(int slots, int B, int Hkv, int32_t *unit_cum, pod_even
         wgs += (long)parts * Hkv;
         most = parts > most ? parts : most;
     }
-    if (wgs > slots || wgs * q > 0x3fffffff) return;
+    if (wgs > slots || wgs * q > 0x3fffffff) return false;
     int32_t units = 0, padded = 0;
     for (int b = 0; b < B; ++b) {
         const int32_t U = unit_cum[b + 1] - units;
@@ -1840,6 +1868,7 @@ static void pad_even_plan(int slots, int B, int Hkv, int32_t *unit_cum, pod_even
         unit_cum[b + 1] = padded;
     }
     pl->nwg = (int32_t)wgs; pl->total = (int32_t)(wgs * q); pl->most = most;
+    return true;
 }
 
 int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *q_shared, const int32_t *ctx, int B,
@@ -1920,12 +1949,19 @@ int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *
     // (score reuse: the decode step of a layer none of whose kv heads starts a block.  A layer that writes the logits
     // gains nothing from it: 16 sequences 218 us either way, 4 x 128K tokens 399 against 387 us.)
     const int even_mode = reuse_step ? 2 : 0;
+    bool even_merge = false;
     bool even = !merge_inside && p.hot.use_hlen && c->even_split && (p.mode == 0 || (reuse_step && !lowest_any));
     p.bal_unit_d = even_unit_distant(even_mode);
     if (even) {
         pod_even_plan_t ev;
         even = pod_plan_even(2 * cus, B, H, ly.P, p.bal_unit_d, p.hlen, p.unit_cum, &ev);
-        if (even && even_mode == 0) pad_even_plan(2 * cus, B, H, p.unit_cum, &ev);
+        // Where no workgroup crosses, each hands over once, at its end, and the last of a pair's merges: at head dimension 64 with few query
+        // heads per kv head, whose partials are small, that costs less than the second launch.  Requests, us, second launch -> inside: 32 chats
+        // x 16/4 x 64 1294 -> 1194, 4 of 3-30K x 8/8 x 64 898 -> 846, 20 of 0.5-5K 817 -> 781; but 24 of 0.2-2.5K x 32/8 x 128 1039 -> 1036, 12 of
+        // 1.5-15K x 32/4 x 128 1585 -> 1619.
+        even_merge = even && even_mode == 0 && pad_even_plan(2 * cus, B, H, p.unit_cum, &ev) && c->fused_merge && ly.D == 64 && ly.rep <= 4;
+        if (!step) // (an empty sequence has no workgroup that would write its rows)
+            for (int b = 0; b < B; ++b) even_merge = even_merge && p.hlen[b] > 0;
         // (a batch of one very long and many short sequences cuts the long one into more parts than fixed pieces
         // would: where the caller's scratch does not hold them the launch keeps to fixed pieces)
         if (even && (size_t)B * ly.Hq * ((size_t)ev.most + (step ? 1 : 0)) * (ly.D + 2) * sizeof(float) > ws_bytes) even = false;
@@ -2014,6 +2050,8 @@ int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *
         const dim3 egrid((unsigned)p.bal_nwg + (step ? (unsigned)npairs : 0u));
 #define POD_LAUNCH_EVEN(DD)                                                                                                   \
         if (even_mode == 2) hipLaunchKernelGGL((decode_even_kernel<DD, true, 2>), egrid, dim3(kWaves * 64), 0, st, p);    \
+        else if (even_merge && step) hipLaunchKernelGGL((decode_even_kernel<64, true, 0, true>), egrid, dim3(kWaves * 64), 0, st, p);  \
+        else if (even_merge) hipLaunchKernelGGL((decode_even_kernel<64, false, 0, true>), egrid, dim3(kWaves * 64), 0, st, p); \
         else if (step) hipLaunchKernelGGL((decode_even_kernel<DD, true, 0>), egrid, dim3(kWaves * 64), 0, st, p);              \
         else hipLaunchKernelGGL((decode_even_kernel<DD, false, 0>), egrid, dim3(kWaves * 64), 0, st, p);
         if (ly.D == 128) { POD_LAUNCH_EVEN(128) } else { POD_LAUNCH_EVEN(64) }
@@ -2025,7 +2063,7 @@ int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *
 #undef POD_LAUNCH_HOST
 #undef POD_LAUNCH_PARTIAL
     if (prof) { POD_HIP_TRY(hipEventRecord(mc->prof_ev[2 * mc->prof_n + 1], st)); mc->prof_n += 1; }
-    if (fuse == 0 || fuse == 3) {
+    if ((fuse == 0 || fuse == 3) && !(even && even_merge)) {
         // Few partials per head (the even split of a batch leaves a pair to a handful of workgroups): one wave per head and 64 dims
         // takes them in one pass.  With 256 threads most lane groups have nothing to load and the others load clamped rows:
         // 32 sequences of up to 4K tokens x 16 heads x 64, 8.6 -> 4.7 us; 16 of up to 32K x 32 x 128, 6.4 -> 4.8 us.

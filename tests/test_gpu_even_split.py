@@ -161,6 +161,58 @@ def test_parts_of_whole_pairs_and_parts_that_cross(d, Hq, Hkv, B, lo, step, monk
     c.gpu.pod_cache_check()
 
 
+@pytest.mark.parametrize("Hq,Hkv,B,lo,step", [(8, 8, 24, 300, 37), (16, 4, 44, 130, 91), (6, 2, 80, 3, 77)])
+def test_parts_of_whole_pairs_merged_inside(Hq, Hkv, B, lo, step):
+    """Head dimension 64 and few query heads per kv head: the last part of a pair merges.  Steps, then the same attention again; an empty
+    sequence (merged by the second launch); wrong lengths and positions, whose rows come out zero; a graph replayed three times."""
+    lens = [lo + (step * i * i) % 900 for i in range(B)]
+    c = Case(2, 2, Hq, Hkv, 64, 8, 64, B, 1210, seed=9360 + B)
+    fill_all(c, lens)
+    for s in range(2):
+        pos = [n + s for n in lens]
+        for layer in range(2):
+            assert_close(c.step(layer, pos), c.decode_ref(layer, [p + 1 for p in pos]), f"step {s} layer {layer}")
+    ctx = [n + 2 for n in lens]
+    refs = [c.decode_ref(layer, ctx) for layer in range(2)]
+    for _ in range(2):
+        for layer in range(2):
+            assert_close(c.decode(layer, ctx), refs[layer], f"decode layer {layer}")
+    c.gpu.pod_cache_check()
+    qs = [c.decode_queries(layer, ctx, c.dev) for layer in range(2)]
+    ctx_dev = torch.tensor(ctx, dtype=torch.int32, device=c.dev)
+    out = torch.empty((2,) + tuple(qs[0].shape), dtype=torch.bfloat16, device=c.dev)
+    for layer in range(2):
+        c.gpu.pod_decode_attention(layer, qs[layer], qs[0] if layer else None, ctx_dev, c.scale, out=out[layer])
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for layer in range(2):
+            c.gpu.pod_decode_attention(layer, qs[layer], qs[0] if layer else None, ctx_dev, c.scale, out=out[layer])
+    for _ in range(3):
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        for layer in range(2):
+            assert_close(out[layer], refs[layer], f"replay layer {layer}")
+    wrong = ctx_dev.clone()
+    wrong[1] -= 1
+    got = c.gpu.pod_decode_attention(0, qs[0], None, wrong, c.scale)
+    with pytest.raises(pod.PodError) as e:
+        c.gpu.pod_cache_check()
+    assert e.value.code == pod.binding.ERR_STATE
+    assert float(got[1].float().abs().max()) == 0.0
+    keep = [i for i in range(B) if i != 1]
+    assert_close(got[keep], refs[0][keep], "the other sequences")
+    k, v = torch.randn((2, B, Hkv, 64), device=c.dev).to(torch.bfloat16)
+    bad = ctx_dev.clone()
+    bad[2] += 1                                                              # sequence 2 holds one token less
+    got = c.gpu.pod_decode_step(0, k, v, qs[0], None, bad, c.scale)
+    with pytest.raises(pod.PodError) as e:
+        c.gpu.pod_cache_check()
+    assert e.value.code == pod.binding.ERR_STATE
+    assert float(got[2].float().abs().max()) == 0.0 and float(got[3].float().abs().max()) > 0.0
+
+
 def test_wrong_context_length_is_flagged_in_the_even_split(monkeypatch):
     monkeypatch.setenv("POD_DECODE_FUSED", "0")
     lens = [900, 300, 77]
