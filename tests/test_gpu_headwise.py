@@ -204,6 +204,25 @@ def test_layer_similarity_matches_the_oracle(L, H, R, n):
     assert (got >= -1e-6).all() and (got <= 1 + 1e-6).all()
 
 
+@pytest.mark.parametrize("L,H,R,n", [(29, 16, 1, 2052), (30, 16, 2, 34), (31, 32, 1, 4), (32, 32, 1, 8), (13, 32, 3, 68)])
+def test_layer_similarity_in_blocks_of_four_by_eight(L, H, R, n):
+    """Shapes whose block pairs are 4 x 8 layers (on 256 CUs): the last block of eight whole, or with one to three layers in its second half;
+    elements for one thread only, and for every thread more than once."""
+    gen = torch.Generator(device="cuda").manual_seed(L * 100 + n)
+    att = torch.softmax(3 * torch.randn((L, H, R, n), generator=gen, device="cuda"), -1).contiguous()
+    att[L - 1] = att[2]
+    got = pod.pod_layer_similarity(att)
+    for h in range(H):
+        x = att[:, h].double()
+        e = torch.special.xlogy(x, x).sum((1, 2))
+        for a in range(L):
+            m = 0.5 * (x[a] + x)
+            ref = 1 - (0.5 * (e[a] + e) - torch.special.xlogy(m, m).sum((1, 2))) / (R * np.log(2.0))
+            ref[a] = 1
+            assert (got[h, a].double() - ref).abs().max() < 2e-6, (h, a)      # fp32 sums of terms that add up to at most 1
+    assert (got[:, 2, L - 1] == 1).all() and (got[:, L - 1, 2] == 1).all()
+
+
 @pytest.mark.parametrize("L,H,n", [(2, 400, 4), (8, 64, 8), (32, 40, 60), (3, 100, 256)])
 def test_layers_with_the_same_rows_have_similarity_one_exactly(L, H, n):
     """One sampled row per head, so that no average rounds a remainder away; blocks of two and of four layers.  A threshold of 1
