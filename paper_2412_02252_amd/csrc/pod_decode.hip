@@ -196,6 +196,12 @@ __device__ inline unsigned pack_bf16(float lo, float hi)
     return __builtin_bit_cast(unsigned, t);
 }
 
+// 2^x as the bare instruction.  exp2f wraps it in four more that keep results below the smallest normal number; here it only
+// forms weights relative to a maximum, where 2^-126 of the whole is past what the sum can hold, and normal results are the same
+// bits.  Whole requests, exp2f -> this: 32 steps of 2 pairs x 64 at 2048 tokens 444 -> 430 us, 32 sequences of 0.1-2K tokens
+// 1197 -> 1187, 24K gated 202 -> 198.
+__device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
 // MODE 0: every logit is computed here.  MODE 1 (lowest layer of a block, score reuse): the same,
 // and the scaled logits of distant chunks are also written to p.scores.  MODE 2 (upper layer, score
 // reuse): distant chunks take their logits from p.scores instead of reading the block's distant
@@ -513,14 +519,14 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
             for (int v = sub; v < np; v += 16) {
                 const float m2 = ml[2 * v], l2 = ml[2 * v + 1];
                 const float M = fmaxf(m, m2);
-                l = __fadd_rn(__fmul_rn(l, __builtin_amdgcn_exp2f(m - M)), __fmul_rn(l2, __builtin_amdgcn_exp2f(m2 - M)));
+                l = __fadd_rn(__fmul_rn(l, fast_exp2(m - M)), __fmul_rn(l2, fast_exp2(m2 - M)));
                 m = M;
             }
 #pragma unroll
             for (int off = 8; off >= 1; off >>= 1) {
                 const float m2 = __shfl_xor(m, off), l2 = __shfl_xor(l, off);
                 const float M = fmaxf(m, m2);
-                l = __fadd_rn(__fmul_rn(l, __builtin_amdgcn_exp2f(m - M)), __fmul_rn(l2, __builtin_amdgcn_exp2f(m2 - M)));
+                l = __fadd_rn(__fmul_rn(l, fast_exp2(m - M)), __fmul_rn(l2, fast_exp2(m2 - M)));
                 m = M;
             }
             m = __shfl(m, lane & 48);                      // the group's first lane decides for all
@@ -562,10 +568,10 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
         mx = fmaxf(mx, __shfl_xor(mx, 16));
         mx = fmaxf(mx, __shfl_xor(mx, 32));
         const float m_new = fmaxf(m_run, mx);
-        const float alpha = exp2f(m_run - m_new);
+        const float alpha = fast_exp2(m_run - m_new);
         float ps = 0.f;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) { sc[i] = exp2f(sc[i] - m_new); ps += sc[i]; }
+        for (int i = 0; i < 8; ++i) { sc[i] = fast_exp2(sc[i] - m_new); ps += sc[i]; }
         ps += __shfl_xor(ps, 16);
         ps += __shfl_xor(ps, 32);
         l_run = l_run * alpha + ps;
@@ -771,7 +777,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
         float A = 0.f, Lsum = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            const float f = exp2f(sm_m[w][head] - M);
+            const float f = fast_exp2(sm_m[w][head] - M);
             A += f * sm_acc[((size_t)w * hot.rep + head) * RS + dim + 4 * (dim >> 5)];
             Lsum += f * sm_l[w][head];
         }
@@ -935,8 +941,8 @@ __device__ void merge_and_store_split(const decode_params &p, const decode_hot &
                     for (int e = 0; e < VEC; ++e) a[e] = g == 0 ? as[e] : 0.f;
                 }
                 const float m_new = fmaxf(m_run, wave_max(mk.x));
-                const float alpha = exp2f(m_run - m_new);
-                const float w = have ? exp2f(mk.x - m_new) : 0.f;
+                const float alpha = fast_exp2(m_run - m_new);
+                const float w = have ? fast_exp2(mk.x - m_new) : 0.f;
                 L = L * alpha + wave_sum(w * mk.y);
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) a[e] *= alpha;
@@ -973,7 +979,7 @@ __device__ void merge_and_store_split(const decode_params &p, const decode_hot &
             if (active && s == 0) {
                 const float m2 = sm_ml[wave + 1][0], L2 = sm_ml[wave + 1][1];
                 const float m_new = fmaxf(m_run, m2);
-                const float f1 = exp2f(m_run - m_new), f2 = exp2f(m2 - m_new);
+                const float f1 = fast_exp2(m_run - m_new), f2 = fast_exp2(m2 - m_new);
                 L = f1 * L + f2 * L2;
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) a[e] = f1 * a[e] + f2 * sm_a[wave + 1][VEC * x + e];
@@ -1076,7 +1082,7 @@ __device__ void step_workgroup(const decode_params &p, const decode_hot &hot, in
             }
         }
         const float m = fmaxf(sn, sd);
-        const float pn = exp2f(sn - m), pd = demote ? exp2f(sd - m) : 0.f;
+        const float pn = fast_exp2(sn - m), pd = demote ? fast_exp2(sd - m) : 0.f;
         const size_t ps = head * stride + hot.nc;
         if (lane < CPR) {
             float *dst = hot.part_acc + ps * D + 8 * lane;
@@ -1215,10 +1221,10 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_para
             mx = fmaxf(mx, __shfl_xor(mx, 16));
             mx = fmaxf(mx, __shfl_xor(mx, 32));
             const float m_new = fmaxf(m_run, mx);
-            const float alpha = exp2f(m_run - m_new);
+            const float alpha = fast_exp2(m_run - m_new);
             float ps = 0.f;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) { sc[i] = exp2f(sc[i] - m_new); ps += sc[i]; }
+            for (int i = 0; i < 8; ++i) { sc[i] = fast_exp2(sc[i] - m_new); ps += sc[i]; }
             ps += __shfl_xor(ps, 16);
             ps += __shfl_xor(ps, 32);
             l_run = l_run * alpha + ps;
@@ -1409,7 +1415,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_para
             float A = 0.f, Lsum = 0.f;
 #pragma unroll
             for (int v = 0; v < NW; ++v) {
-                const float f = exp2f(sm_m[v][head] - M);
+                const float f = fast_exp2(sm_m[v][head] - M);
                 A += f * sm_acc[((size_t)v * hot.rep + head) * RS + dim + 4 * (dim >> 5)];
                 Lsum += f * sm_l[v][head];
             }
@@ -1541,12 +1547,12 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(decode_
 #pragma unroll
         for (int k = 1; k < UN; ++k) mb = fmaxf(mb, mk[k]);
         const float m_new = fmaxf(m_run, mb);
-        const float alpha = exp2f(m_run - m_new);
+        const float alpha = fast_exp2(m_run - m_new);
         a *= alpha;
         l_run *= alpha;
 #pragma unroll
         for (int k = 0; k < UN; ++k) {
-            const float f = exp2f(mk[k] - m_new);
+            const float f = fast_exp2(mk[k] - m_new);
             a += f * ak[k];
             l_run += f * lk[k];
         }
@@ -1565,7 +1571,7 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(decode_
     float L = 0.f;
 #pragma unroll
     for (int k = 0; k < NG; ++k) {
-        const float f = exp2f(sm[k] - M);
+        const float f = fast_exp2(sm[k] - M);
         o += f * sa[k][x];
         L += f * sl[k];
     }
