@@ -371,9 +371,10 @@ __global__ void chunk_dirty_kernel(const char *base, chunk_view cv)
 }
 
 // Grid-stride over 16-byte pieces of the prompt's K/V [n][Hkv][D].
+template <bool NT>
 __global__ __launch_bounds__(kThreads) void fill_kernel(pod_fill_args a, const void *k, const void *v)
 {
-    pod_fill_rows<1>(a, k, v, (size_t)blockIdx.x * blockDim.x + threadIdx.x, (size_t)gridDim.x * blockDim.x);
+    pod_fill_rows<1, NT>(a, k, v, (size_t)blockIdx.x * blockDim.x + threadIdx.x, (size_t)gridDim.x * blockDim.x);
 }
 
 // Gather the logical views [tokens][Hkv][D] in position order.
@@ -412,6 +413,8 @@ __global__ void export_kernel(const char *base, pod_layout ly, pod_headmap hm, i
         }
     }
 }
+
+constexpr size_t kPastCachesFill = (size_t)16 << 20, kPastCachesCache = (size_t)128 << 20; // bytes of a prompt's K and V, of a cache
 
 int grid_for(size_t items)
 {
@@ -460,8 +463,16 @@ pod_fill_args pod_make_fill_args(const pod_cache *c, int layer, int seq_slot, in
 
 int pod_launch_fill(const pod_cache *c, int layer, int seq_slot, int n, const void *k, const void *v, hipStream_t st)
 {
-    const size_t items = (size_t)n * c->ly.Hkv * (c->ly.D / 8);
-    hipLaunchKernelGGL(fill_kernel, dim3(grid_for(items)), dim3(kThreads), 0, st, pod_make_fill_args(c, layer, seq_slot, n), k, v);
+    // Bound by HBM; one piece per thread (up to 2^28 pieces), so that the launch walks memory in order.  Stores go past the caches where the
+    // rows would not stay there until they are read: caches of half the 256 MB that the chip keeps (a fill reads as much as it writes), fills
+    // of 16 MB.  Requests, fills and 12-32 steps, us, plain -> past the caches: 16 sequences of 4-32K tokens x 8 x 128 6238 -> 6168, 12 of 1.5-15K x
+    // 4 x 128 1569 -> 1541, 4 of 128K 17016 -> 16800, one of 32K (206 MB) 1674 -> 1661; but one of 16K and its selection (103 MB) 142.5 -> 144.9,
+    // 8 of 0.5-3K (2-12 MB each) 625 -> 630.
+    const size_t items = (size_t)n * c->ly.Hkv * (c->ly.D / 8), wgs = (items + kThreads - 1) / kThreads;
+    const dim3 g((unsigned)(wgs < ((size_t)1 << 20) ? wgs : (size_t)1 << 20));
+    const pod_fill_args a = pod_make_fill_args(c, layer, seq_slot, n);
+    if (items * 32 >= kPastCachesFill && c->ly.total_bytes >= kPastCachesCache) hipLaunchKernelGGL(fill_kernel<true>, g, dim3(kThreads), 0, st, a, k, v);
+    else hipLaunchKernelGGL(fill_kernel<false>, g, dim3(kThreads), 0, st, a, k, v);
     POD_HIP_TRY(hipGetLastError());
     return POD_OK;
 }

@@ -100,8 +100,8 @@ typedef __attribute__((ext_vector_type(4))) unsigned pod_u32x4; // (arrays of HI
 constexpr int kFillUnroll = 4; // 16-byte pieces of K and of V a thread of a prefill launch has in flight
 
 // Pieces first, first + stride, ... of k and v ([n][Hkv][D], 16-byte pieces) to where the cache keeps them; whoever takes piece 0
-// also stores the length.  U pieces of K and of V are in flight per thread.
-template <int U>
+// also stores the length.  U pieces of K and of V are in flight per thread.  NT: the stores go past the caches.
+template <int U, bool NT = false>
 __device__ inline void pod_fill_rows(const pod_fill_args &a, const void *k, const void *v, size_t first, size_t stride)
 {
     const pod_layout &ly = a.ly;
@@ -111,6 +111,10 @@ __device__ inline void pod_fill_rows(const pod_fill_args &a, const void *k, cons
     pod_u32x4 *const proxK = (pod_u32x4 *)(a.base + ly.off_proxK), *const proxV = (pod_u32x4 *)(a.base + ly.off_proxV);
     pod_u32x4 *const distK = (pod_u32x4 *)(a.base + ly.off_distK), *const distV = (pod_u32x4 *)(a.base + ly.off_distV);
     const size_t total = (size_t)a.n * ly.Hkv << cshift;
+    auto store = [](pod_u32x4 *dst, pod_u32x4 val) {
+        if (NT) __builtin_nontemporal_store(val, dst);
+        else *dst = val;
+    };
     for (size_t i0 = first; i0 < total; i0 += U * stride) {
         pod_u32x4 kr[U], vr[U];
         int p[U], h[U];
@@ -136,12 +140,12 @@ __device__ inline void pod_fill_rows(const pod_fill_args &a, const void *k, cons
             if (prox[u]) {
                 const int slot = p[u] < ly.S ? p[u] : ly.S + (p[u] - ly.S) % ly.W;
                 const size_t pr = ((pod_prox_row0(ly, a.layer, a.b, h[u]) + slot) << cshift) + c;
-                proxK[pr] = kr[u];
-                proxV[pr] = vr[u];
+                store(proxK + pr, kr[u]);
+                store(proxV + pr, vr[u]);
             } else {
                 const size_t t = (size_t)(p[u] - ly.S);
-                distV[((pod_dist_row0(ly, a.layer, a.b, h[u]) + t) << cshift) + c] = vr[u];
-                if (low[u]) distK[((pod_distk_row0(ly, a.hm, a.b, h[u]) + t) << cshift) + c] = kr[u];
+                store(distV + (((pod_dist_row0(ly, a.layer, a.b, h[u]) + t) << cshift) + c), vr[u]);
+                if (low[u]) store(distK + (((pod_distk_row0(ly, a.hm, a.b, h[u]) + t) << cshift) + c), kr[u]);
             }
         }
     }

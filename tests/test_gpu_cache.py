@@ -94,6 +94,20 @@ def test_other_slots_and_layers_stay_untouched():
     assert exp["distK"].shape[0] == 28
 
 
+@pytest.mark.parametrize("heads,dim,n,batch", [(8, 128, 4095, 6), (8, 128, 4096, 6), (8, 128, 4096, 2), (7, 128, 4682, 6), (5, 64, 13108, 6)])
+def test_fills_on_both_sides_of_the_stores_past_the_caches(heads, dim, n, batch):
+    # 16 MB of keys and values (4096 tokens x 8 x 128) in a cache of 128 MB (six slots); the ragged ones end inside a workgroup; another
+    # slot must stay as it was
+    c = Case(2, 2, heads, heads, dim, 3, 37, batch, n + 100, seed=n)
+    for layer in range(2):
+        c.fill(layer, 1, 50)
+        c.fill(layer, 0, n)
+    for layer in range(2):
+        c.assert_cache_equal(layer, 0)
+        c.assert_cache_equal(layer, 1)
+    c.gpu.pod_cache_check()
+
+
 def test_error_paths():
     c = Case(2, 2, 4, 2, 64, 4, 8, 2, 16, seed=6)
     E = pod.binding
