@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
 """Benchmark of the PoD attention hot path on one MI355X.
 
-Workload (benchmark configs[1]): LLaMA3-8B-shaped decode, one layer block of G=2 layers,
+Workload: LLaMA3-8B-shaped decode, one layer block of G=2 layers,
 32 query / 8 KV heads, head_dim 128, batch 1, context 32768 (+1 per step), S=64, W=2048, bf16,
 RoPE-rotated keys (base 500000).  A *step* is one pass of the whole path for one new token:
 the block's lowest layer takes the token (cache update with window-to-distant demotion +

@@ -45,8 +45,8 @@ def test_small_prompts_every_tile_kind(d, Hq, Hkv, n):
 @pytest.mark.parametrize("S,n", [(8, 104), (8, 105), (8, 128), (8, 129), (70, 130), (8, 193), (8, 255), (8, 321), (8, 1290)])
 def test_one_and_two_key_groups_per_workgroup(d, Hq, Hkv, S, n):
     """Few workgroups: two key groups walk even and odd tiles of a query tile (an odd number of tiles leaves one of them a
-    tile that counts nothing).  The form starts at four tiles: at 193 tokens in a lowest layer, at 105 in an upper layer, which
-    visits boundary tiles in both phases (each group then walks two tiles).  70 sink tokens, 130 tokens: one tile of distant keys,
+    tile that counts nothing).  Four tiles, short of where the form starts: 193 tokens in a lowest layer, 105 in an upper layer,
+    which visits boundary tiles in both phases.  70 sink tokens, 130 tokens: one tile of distant keys,
     so one group starts with the layer's own keys.  1290 x 64 heads: more workgroups than two per CU, one group."""
     c = Case(2, 2, Hq, Hkv, d, S, 40, 1, n, seed=230 + n, with_oracle_cache=False)
     rows = np.unique(np.concatenate([np.arange(0, n, 37), np.arange(max(0, n - 70), n)]))
