@@ -24,6 +24,8 @@
 // has a fixed order: the votes are reproducible bit for bit.
 #include <math.h>
 
+#include <type_traits>
+
 #include "pod_internal.h"
 
 namespace {
@@ -531,55 +533,101 @@ __device__ inline size_t selected_row(const compact_params &p, int h, int row, i
 // Compaction in one launch and without the workspace.  A workgroup owns 64 bytes of every row of one (kv head, keys or values):
 // nobody else reads or writes them, so it takes all surviving rows into its registers, waits until every wave has done so, and
 // stores them where the shorter sequence keeps them - any selection, in any order - first the distant rows, then the recent window where
-// that turns.  256 rows in flight per step and PER steps: up to 2048 rows with 8, 4096 with 16; what is larger goes through
-// the workspace (below).  The last workgroup to have read the stored length changes it (the count is kept where a decode step
-// keeps its own, zero between launches), or raises the flag if it was not n.  Bound by latency: the length, the selection, the rows, the
-// stores, one after the other.  Heads come first in the grid: a row's pieces then share an L2 where the heads go round the XCDs evenly.
-// Whole requests of two layers, three launches per layer (5.1 + 4.4 + 1.3 us) -> one, 8 kv heads x 128: 16384 tokens -> 1984 selected 134.4 -> 130.2 us,
-// 16001 (the ring turns) 143.3 -> 140.6, 20001 -> 4096 162.5 -> 156.7, 5001 -> 300 98.0 -> 89.9.
-// A workgroup moves its rows at the rate of one CU, so few of them are slower than the three launches, which spread over the chip: whole
-// requests, three -> one, 64 workgroups (8 x 128, 4200 tokens -> 400 selected) 105.2 -> 96.5 us, 32 (4 x 128, 5000 -> 500) 91.1 -> 93.1, 16
-// (4 x 64, 9000 -> 1000) 84.6 -> 87.2, 8 (1 x 128, 12000 -> 3000) 115 -> 131.  Hence at least 64.
-constexpr unsigned kCompactWorkgroups = 64;
-constexpr int kCompactThreads = 1024, kCompactPieces = 4, kCompactRows = kCompactThreads / kCompactPieces;
-template <int PER>
+// that turns.  A thread has a piece of up to 16 rows in flight (by_rows: a power of two that covers the count, so that few rows are not
+// fetched many times over by lanes past the last), 4096 rows per workgroup; what is larger goes through the workspace (below).  The last
+// workgroup to have read the stored length changes it (the count is kept where a decode step keeps its own, zero between launches), or
+// raises the flag if it was not n.  Bound by latency, four accesses one after the other (the length, the selection, the rows, the
+// stores): every pass over a thread's rows is straight code, indices from clamped positions, bad entries turned into row 0 by a select.  A
+// condition around each row's access instead makes the compiler wait for every index and every row before the next is requested.  Two
+// workgroups whose pieces make up a 128-byte line run on one XCD (an L2 that holds a line for half of it reads and writes it for nothing).
+// Fill and compaction of two layers, us, three launches per layer -> one (in brackets: with a condition around each row, heads dealt out
+// in grid order), 8 kv heads x 128: 3000 tokens -> 300 selected 32.5 -> 27.6 (27.4), 16384 -> 1984 63.3 -> 59.3 (59.5), 16001 -> 1984, where a window of
+// 2048 turns, 71.1 -> 68.3 (70.8), 16001 -> 900 with a window of 4096 77.4 -> 72.0 (78.8); 9 x 128, that last one, 86 -> 76 (87).
+// A workgroup moves its rows at the rate of one CU: few workgroups are faster at few rows and slower at many, 32 of them (4 x 128) 300 rows 27.1 -> 24.9,
+// 1984 45.4 -> 43.5, 2048 and a window of 256 37.5 -> 38.3, of 4096 and 4096 63.6 -> 71.7; 16 (4 x 64) 300 rows 26.2 -> 23.9, 2048 + 256
+// 28.9 -> 31.1.  64 (8 x 128) are faster up to 6000 rows or so and level from there on (4096 alone, out of 16384, 84.4 -> 85.6; 4096 + 4096
+// 101 -> 96, but 80 and 72 workgroups, 10 and 9 x 128, 122 -> 128 and 112 -> 122); 104 (13 x 128), 4096 + 4096 156 -> 150.  Hence 64 up to 6144 rows
+// and 96 beyond.
+constexpr int kCompactWorkgroups = 64, kCompactManyRows = 6144, kCompactManyWorkgroups = 96;
+constexpr int kCompactThreads = 1024, kCompactPieces = 4, kCompactRows = kCompactThreads / kCompactPieces, kCompactMost = 16;
+template <int MOST, class F>
+__device__ __forceinline__ void by_rows(int count, F &&f) // f(rows a thread takes a piece of, at most)
+{
+    if (count <= 1 * kCompactRows) f(std::integral_constant<int, 1>{});
+    else if (count <= 2 * kCompactRows) f(std::integral_constant<int, 2>{});
+    else if (count <= 4 * kCompactRows) f(std::integral_constant<int, 4>{});
+    else if (MOST == 8 || count <= 8 * kCompactRows) f(std::integral_constant<int, 8>{});
+    else f(std::integral_constant<int, MOST>{});
+}
+
+// Row to(i) of rows = row src[i / kCompactRows], i < count, all at once.  (past the last row src is the last once more, which is not stored)
+template <int PER, class To>
+__device__ __forceinline__ void move_rows(pod_u32x4 *rows, int cpr, int c, const int (&src)[PER], int row0, int count, To &&to)
+{
+    pod_u32x4 val[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) val[u] = rows[(size_t)src[u] * cpr + c];
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // (a store of another wave must not overtake these)
+    __builtin_amdgcn_s_waitcnt(0x0f70);              // (vmcnt(0) again, for the compiler: else every store waits for the one before it)
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int i = row0 + u * kCompactRows;
+        if (i < count) rows[(size_t)to(i) * cpr + c] = val[u];
+    }
+}
+
+// (up to 2048 rows in a kernel of its own: two workgroups per CU instead of one, 40 kv heads x 128, 1024 rows, 126 -> 122 us)
+template <int MOST>
 __global__ __launch_bounds__(kCompactThreads) void compact_kernel(compact_params p)
 {
     const pod_layout &ly = p.ly;
-    const int h = blockIdx.x, is_v = blockIdx.z;
+    const int line = blockIdx.z * gridDim.x + blockIdx.x; // of the 2 Hkv D / 64 columns of 128 bytes: column, then keys or values, then kv head
+    if (line >= 2 * ly.Hkv * (ly.D / 64)) return;
+    const int col = line / (2 * ly.Hkv), pair = line - col * (2 * ly.Hkv), is_v = pair >= ly.Hkv, h = is_v ? pair - ly.Hkv : pair;
     int32_t *const len = (int32_t *)(p.base + ly.off_lens) + (size_t)p.layer * ly.B + p.b;
     const bool ok = *len == p.n;
     if (ok) {
         const int cpr = ly.D / 8, n_dist = p.n - ly.S - ly.W;
-        const int c = blockIdx.y * kCompactPieces + threadIdx.x % kCompactPieces, row0 = threadIdx.x / kCompactPieces;
+        const int c = (2 * col + blockIdx.y) * kCompactPieces + threadIdx.x % kCompactPieces, row0 = threadIdx.x / kCompactPieces;
         const bool low = (p.hm.lowest_mask >> h) & 1;
-        auto move = [&](pod_u32x4 *rows, int count, auto &&from, auto &&to) { // row to(i) = row from(i), i < count, all at once
-            pod_u32x4 val[PER];
+        if (is_v || low) { // (the keys of distant tokens are kept by the lowest layer of a block only)
+            const int32_t *const sel = p.sel_all + ((size_t)p.sel_layer[h] * ly.Hkv + h) * p.keep;
+            pod_u32x4 *const rows = is_v ? (pod_u32x4 *)(p.base + ly.off_distV) + pod_dist_row0(ly, p.layer, p.b, h) * cpr
+                                         : (pod_u32x4 *)(p.base + ly.off_distK) + pod_distk_row0(ly, p.hm, p.b, h) * cpr;
+            by_rows<MOST>(p.keep, [&](auto per) __attribute__((always_inline)) {
+                constexpr int PER = decltype(per)::value;
+                int src[PER];
+                bool bad = false;
 #pragma unroll
-            for (int u = 0; u < PER; ++u) {
-                const int i = row0 + u * kCompactRows;
-                if (i < count) val[u] = rows[from(i) * cpr + c];
-            }
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // (a store of another wave must not overtake these)
-            __syncthreads();
+                for (int u = 0; u < PER; ++u) src[u] = sel[min(row0 + u * kCompactRows, p.keep - 1)];
 #pragma unroll
-            for (int u = 0; u < PER; ++u) {
-                const int i = row0 + u * kCompactRows;
-                if (i < count) rows[to(i) * cpr + c] = val[u];
-            }
-        };
-        if (is_v || low) // (the keys of distant tokens are kept by the lowest layer of a block only)
-            move(is_v ? (pod_u32x4 *)(p.base + ly.off_distV) + pod_dist_row0(ly, p.layer, p.b, h) * cpr
-                      : (pod_u32x4 *)(p.base + ly.off_distK) + pod_distk_row0(ly, p.hm, p.b, h) * cpr,
-                 p.keep, [&](int i) { return selected_row(p, h, i, n_dist); }, [](int i) { return (size_t)i; });
-        if (p.rows > p.keep) // (position n - W + i before, S + keep + i after)
-            move((pod_u32x4 *)(p.base + (is_v ? ly.off_proxV : ly.off_proxK)) + (pod_prox_row0(ly, p.layer, p.b, h) + ly.S) * cpr, ly.W,
-                 [&](int i) { return (size_t)((p.n - ly.S + i) % ly.W); }, [&](int i) { return (size_t)((p.keep + i) % ly.W); });
+                for (int u = 0; u < PER; ++u) {
+                    const bool in = (unsigned)src[u] < (unsigned)n_dist;
+                    bad = bad || !in;
+                    src[u] = in ? src[u] : 0;
+                }
+                move_rows<PER>(rows, cpr, c, src, row0, p.keep, [](int i) { return i; });
+                if (bad) atomicOr((int32_t *)(p.base + ly.off_flag), 1);
+            });
+        }
+        if (p.rows > p.keep) { // (position n - W + i before, S + keep + i after)
+            const int W = ly.W, from = (p.n - ly.S) % W, to = p.keep % W;
+            auto ring = [W](int x) { return x >= W ? x - W : x; };
+            pod_u32x4 *const rows = (pod_u32x4 *)(p.base + (is_v ? ly.off_proxV : ly.off_proxK)) + (pod_prox_row0(ly, p.layer, p.b, h) + ly.S) * cpr;
+            by_rows<MOST>(W, [&](auto per) __attribute__((always_inline)) {
+                constexpr int PER = decltype(per)::value;
+                int src[PER];
+#pragma unroll
+                for (int u = 0; u < PER; ++u) src[u] = ring(from + min(row0 + u * kCompactRows, W - 1));
+                move_rows<PER>(rows, cpr, c, src, row0, W, [&](int i) { return ring(to + i); });
+            });
+        }
     }
     __syncthreads(); // every wave has used the length it read
     if (threadIdx.x == 0) {
         int32_t *const done = (int32_t *)(p.base + ly.off_stepdone) + p.b;
-        const int all = (int)(gridDim.x * gridDim.y * gridDim.z);
+        const int all = 2 * 2 * ly.Hkv * (ly.D / 64);
         if (__hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == all - 1) {
             __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (ok) *len = ly.S + p.keep + ly.W;
@@ -588,8 +636,8 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(compact_params
     }
 }
 
-// More than 4096 rows of a kind: stage 0 copies the surviving rows into the workspace, stage 1 copies them back to where the shorter sequence
-// keeps them; both do nothing unless the stored length is n (compact_commit_kernel then raises the flag).
+// More than 4096 rows of a kind, or too few workgroups for one launch: stage 0 copies the surviving rows into the workspace, stage 1 copies
+// them back to where the shorter sequence keeps them; both do nothing unless the stored length is n (compact_commit_kernel then raises the flag).
 // Rows 0 .. keep - 1: selected distant rows; rows keep .. keep + W - 1: the recent window, oldest first.
 template <int STAGE>
 __global__ void compact_move_kernel(compact_params p)
@@ -703,10 +751,11 @@ int pod_launch_compact(const pod_cache *c, int layer, int b, int n, const int32_
     // 5.0 + 4.0 at 16384, where it happens to.
     p.rows = keep + ((n - ly.S - ly.W - keep) % ly.W != 0 ? ly.W : 0);
     const int most = p.rows > keep && ly.W > keep ? ly.W : keep; // rows of one kind that move
-    const dim3 g1(ly.Hkv, ly.D / 8 / kCompactPieces, 2);
-    if (most <= 16 * kCompactRows && g1.x * g1.y * g1.z >= kCompactWorkgroups) {
+    const int xcds = c->nxcd > 0 ? c->nxcd : 1, lines = 2 * ly.Hkv * (ly.D / 64);
+    if (most <= kCompactMost * kCompactRows && 2 * lines >= (p.rows <= kCompactManyRows ? kCompactWorkgroups : kCompactManyWorkgroups)) {
+        const dim3 g1(xcds, 2, (lines + xcds - 1) / xcds);
         if (most <= 8 * kCompactRows) hipLaunchKernelGGL(compact_kernel<8>, g1, dim3(kCompactThreads), 0, st, p);
-        else hipLaunchKernelGGL(compact_kernel<16>, g1, dim3(kCompactThreads), 0, st, p);
+        else hipLaunchKernelGGL(compact_kernel<kCompactMost>, g1, dim3(kCompactThreads), 0, st, p);
         POD_HIP_TRY(hipGetLastError());
         return POD_OK;
     }

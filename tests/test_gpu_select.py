@@ -235,11 +235,14 @@ def test_select_compact_and_decode_on(name, L, G, Hq, Hkv, d, S, W, n, obs, keep
 
 @pytest.mark.parametrize("d,Hkv,S,W,n,keep", [(128, 8, 4, 40, 2600, 1), (128, 8, 4, 40, 2600, 255), (128, 8, 4, 40, 2600, 2048), (128, 8, 4, 40, 2600, 2049),
                                               (64, 16, 4, 2048, 5001, 300), (64, 16, 0, 2049, 7000, 257), (128, 8, 4, 40, 4400, 4096), (128, 8, 4, 40, 4400, 4097),
-                                              (128, 8, 4, 4100, 8400, 100), (64, 8, 4, 100, 3000, 700)])
+                                              (128, 8, 4, 4100, 8400, 100), (64, 8, 4, 100, 3000, 700),
+                                              (128, 9, 4, 256, 2600, 256), (128, 9, 4, 1025, 4000, 512), (64, 17, 4, 513, 3000, 513), (64, 17, 0, 1024, 5000, 1024),
+                                              (128, 12, 4, 4096, 12000, 2401), (128, 8, 4, 4096, 12000, 2401)])
 @pytest.mark.parametrize("order", ["ascending", "any"])
 def test_compaction_moves_the_selected_rows(d, Hkv, S, W, n, keep, order):
-    """One launch with up to 2048 or 4096 rows in flight, the workspace beyond that, for a ring that turns and one that does not (n chosen),
-    and for launches too small for it (8 x 64); selections in ascending order and in any, with repetitions: bit for bit."""
+    """One launch with 1, 2, 4, 8 or 16 rows per thread in flight (256 to 4096 rows), the workspace beyond that, for a ring that turns and one
+    that does not (n chosen), and for launches too small for it (8 x 64; more than 6144 rows on 8 x 128, 12 x 128 being enough); kv heads that go
+    round the XCDs unevenly; selections in ascending order and in any, with repetitions: bit for bit."""
     dev = torch.device("cuda:0")
     gen_ = torch.Generator(device=dev).manual_seed(n + keep)
     cfg = pod.make_config(2, 2, Hkv, Hkv, d, S, W, 2, n + 1)
