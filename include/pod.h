@@ -336,6 +336,12 @@ int pod_score_skip_offset(const pod_config *cfg, size_t *offset);
 int pod_layer_similarity(const float *att, int num_layers, int num_heads, int rows, int n, float *sim, void *stream);
 
 /*
+ * Host logic, no device needed: how pod_layer_similarity cuts the layer pairs of a head into workgroups on a device with
+ * num_cus compute units: each takes plan[0] layers against plan[1] others (2 x 2, 4 x 4 or 4 x 8; the results do not depend on it).
+ */
+int pod_similarity_plan(int num_cus, int num_layers, int num_heads, int rows, int n, int32_t plan[2]);
+
+/*
  * Offline grouping of layers into head-wise blocks ("Greedy Layer Grouping Algorithm"; host
  * arrays, no GPU work).  sim: float [num_q_heads][num_layers][num_layers], sim[h][a][b] the
  * attention similarity of layers a and b for query head h.  For each kv head, bottom-up: layer

@@ -21,7 +21,7 @@ EXPORTS = [
     "pod_cache_fill", "pod_decode_attention", "pod_prefill_attention", "pod_cache_export_logical",
     "pod_profile_enable", "pod_profile_disable", "pod_profile_read", "pod_profile_read_each", "pod_profile_stream_read", "pod_profile_set_trace", "pod_profile_mfma_feed",
     "pod_score_buffer_bytes", "pod_decode_attention_reuse", "pod_decode_attention_gated", "pod_score_skip_offset",
-    "pod_group_layers", "pod_layer_similarity",
+    "pod_group_layers", "pod_layer_similarity", "pod_similarity_plan",
     "pod_decode_attention_static", "pod_cache_region_counts", "pod_decode_step", "pod_cache_set_length_source", "pod_cache_launch_info",
     "pod_cache_sync_lengths", "pod_cache_append_many", "pod_prefill_chunk_workspace_bytes", "pod_prefill_chunk_in_place_bytes", "pod_prefill_attention_chunk", "pod_decode_even_plan",
     "pod_decode_plan", "pod_decode_step_reuse",
@@ -89,6 +89,7 @@ def load():
         "pod_score_skip_offset": [cfgp, szp],
         "pod_group_layers": [vp, C.c_int, C.c_int, C.c_int, C.c_float, vp],
         "pod_layer_similarity": [vp, C.c_int, C.c_int, C.c_int, C.c_int, vp, vp],
+        "pod_similarity_plan": [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int32)],
         "pod_decode_attention_reuse": [vp, C.c_int, vp, i32p, C.c_int, C.c_int, C.c_float, vp, C.c_size_t, vp,
                                        C.c_size_t, vp, vp],
         "pod_cache_append_many": [vp, C.c_int, vp, vp, i32p, i32p, C.c_int, C.c_int, vp],
@@ -167,6 +168,13 @@ def pod_layer_similarity(att: torch.Tensor) -> torch.Tensor:
     sim = torch.empty((H, L, L), dtype=torch.float32, device=att.device)
     _check(load().pod_layer_similarity(_ptr(att, torch.float32), L, H, R, n, _ptr(sim, torch.float32), _stream()))
     return sim
+
+
+def pod_similarity_plan(num_cus: int, num_layers: int, num_heads: int, rows: int, n: int) -> tuple:
+    """Layers per workgroup of pod_layer_similarity: (held, streamed)."""
+    plan = (C.c_int32 * 2)()
+    _check(load().pod_similarity_plan(num_cus, num_layers, num_heads, rows, n, plan))
+    return plan[0], plan[1]
 
 
 def pod_cache_bytes(cfg: PodConfig) -> int:

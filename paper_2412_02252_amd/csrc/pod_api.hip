@@ -702,6 +702,16 @@ extern "C" int pod_layer_similarity(const float *att, int num_layers, int num_he
     return pod_launch_similarity(att, num_layers, num_heads, rows, n, sim, (hipStream_t)stream);
 }
 
+extern "C" int pod_similarity_plan(int num_cus, int num_layers, int num_heads, int rows, int n, int32_t plan[2])
+{
+    if (!plan) return pod_fail(POD_ERR_INVALID_ARG, "plan is NULL");
+    if (num_cus < 1 || num_layers < 1 || num_heads < 1 || rows < 1 || n < 1 || num_heads > 65535 || num_layers > 65535)
+        return pod_fail(POD_ERR_INVALID_ARG, "num_cus, num_layers, num_heads, rows and n must be >= 1, at most 65535 layers and heads");
+    const pod_similarity_blocks blocks = pod_plan_similarity(num_cus, num_layers, num_heads, (size_t)rows * n);
+    plan[0] = blocks.a; plan[1] = blocks.b;
+    return POD_OK;
+}
+
 extern "C" int pod_group_layers(const float *sim, int num_layers, int num_q_heads, int num_kv_heads, float threshold,
                                 int32_t *lowest_out)
 {

@@ -214,21 +214,16 @@ int launch_pairs(sim_params p, hipStream_t st)
 
 } // namespace
 
-int pod_launch_similarity(const float *att, int L, int H, int R, int n, float *sim, hipStream_t st)
+// Blocks of 4 x 4 layers where they leave two workgroups per CU, else of 2 x 2: more workgroups, which read a row more
+// often, for few heads or layers, whose rows come out of the L2 (8 layers x 4 heads: 22 us in blocks of two, 24 in blocks of four).
+// 4 x 8 instead of 4 x 4 where that takes enough off the CU with most work, block pairs dealt out in order and costing their layer pairs
+// and 0.9 per layer whose e's they take, times the elements of a head's rows.  Half as many workgroups with twice the sums to add
+// up at their ends hide less latency, which is worth some 130 000 of these units: us, 4 x 4 -> 4 x 8 (estimate per element; units), 32 layers x 32
+// heads x 65536 elements 243 -> 222 (182 -> 167; 980 000), 24000 98.5 -> 92.0, 12000 56.1 -> 54.6 (180 000), 6000 36.2 -> 35.6 (90 000), 3072 25.5 -> 27.0, 768
+// 21.3 -> 23.7; 48 x 32 x 6000 65.1 -> 63.6 (190 000), 3072 42.1 -> 43.2 (100 000); 32 x 16 x 24000 60.6 -> 59.9 (170 000), 12000 37.0 -> 38.0 (86 000); 32 x 8 x 24000
+// 39.2 -> 41.0 (86 000); 24 x 32, whose 768 workgroups would give a quarter of the CUs two whole block pairs and more, x 65536 154 -> 162 (112 -> 115).
+pod_similarity_blocks pod_plan_similarity(int cus, int L, int H, size_t rows)
 {
-    sim_params p;
-    p.att = att; p.sim = sim; p.L = L; p.H = H; p.nblk = 0; p.pair0 = 0;
-    p.rows = (size_t)R * n;
-    p.R = R;
-    p.heads_by_xcd = H % 8 == 0 ? 8 : 1;
-    int dev = 0, cus = 0;
-    POD_HIP_TRY(hipGetDevice(&dev));
-    POD_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    // Blocks of 4 x 4 layers where they leave two workgroups per CU, else of 2 x 2: more workgroups, which read a row more
-    // often, for few heads or layers, whose rows come out of the L2 (8 layers x 4 heads: 22 us in blocks of two, 24 in blocks of four).
-    // 4 x 8 instead of 4 x 4 where the CU with most work gets less that way, block pairs dealt out in order and costing their layer pairs
-    // and 0.9 per layer whose e's they take (us, 4 x 4 -> 4 x 8, and this estimate: 32 x 32 heads 248 -> 217, 182 -> 167; 29 x 16 124 -> 111,
-    // 102 -> 95; 24 x 32, whose 768 workgroups would give a quarter of the CUs two whole block pairs and more, 63 -> 70, 112 -> 115).
     auto most_work = [&](int ba, int bb) {
         const int per = bb / ba;
         const int64_t nb = (L + bb - 1) / bb, each = (int64_t)kSimHalves * H, whole = per * (nb * (nb - 1) / 2);
@@ -248,11 +243,24 @@ int pod_launch_similarity(const float *att, int L, int H, int R, int n, float *s
         }
         return most;
     };
+    const int64_t nb = (L + 3) / 4;
+    if (nb * (nb + 1) / 2 * kSimHalves * H < 2 * cus) return {2, 2};
+    return {4, (most_work(4, 4) - most_work(4, 8)) * (double)rows > 130e3 ? 8 : 4};
+}
+
+int pod_launch_similarity(const float *att, int L, int H, int R, int n, float *sim, hipStream_t st)
+{
+    sim_params p;
+    p.att = att; p.sim = sim; p.L = L; p.H = H; p.nblk = 0; p.pair0 = 0;
+    p.rows = (size_t)R * n;
+    p.R = R;
+    p.heads_by_xcd = H % 8 == 0 ? 8 : 1;
+    int dev = 0, cus = 0;
+    POD_HIP_TRY(hipGetDevice(&dev));
+    POD_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     if (L > 1) {
-        const int64_t nb = (L + 3) / 4;
-        const int rc = nb * (nb + 1) / 2 * kSimHalves * H < 2 * cus ? launch_pairs<2, 2>(p, st)
-                       : most_work(4, 8) < most_work(4, 4)          ? launch_pairs<4, 8>(p, st)
-                                                                    : launch_pairs<4, 4>(p, st);
+        const pod_similarity_blocks blocks = pod_plan_similarity(cus, L, H, p.rows);
+        const int rc = blocks.a == 2 ? launch_pairs<2, 2>(p, st) : blocks.b == 8 ? launch_pairs<4, 8>(p, st) : launch_pairs<4, 4>(p, st);
         if (rc) return rc;
     }
     hipLaunchKernelGGL(similarity_finish_kernel, dim3((unsigned)(((size_t)L * L + 255) / 256), (unsigned)H), dim3(256), 0, st, p);

@@ -204,10 +204,13 @@ def test_layer_similarity_matches_the_oracle(L, H, R, n):
     assert (got >= -1e-6).all() and (got <= 1 + 1e-6).all()
 
 
-@pytest.mark.parametrize("L,H,R,n", [(29, 16, 1, 2052), (30, 16, 2, 34), (31, 32, 1, 4), (32, 32, 1, 8), (13, 32, 3, 68)])
-def test_layer_similarity_in_blocks_of_four_by_eight(L, H, R, n):
-    """Shapes whose block pairs are 4 x 8 layers (on 256 CUs): the last block of eight whole, or with one to three layers in its second half;
+@pytest.mark.parametrize("L,H,R,n,streamed", [(29, 16, 1, 2052, 4), (30, 16, 2, 34, 4), (31, 32, 1, 4, 4), (32, 32, 1, 8, 4), (13, 32, 3, 68, 4),
+                                              (29, 16, 1, 20004, 8), (30, 32, 1, 10004, 8), (31, 32, 3, 3404, 8), (32, 32, 2, 5000, 8), (45, 32, 1, 4444, 8)])
+def test_layer_similarity_in_blocks_of_four_by_four_and_by_eight(L, H, R, n, streamed):
+    """Block pairs of 4 x 4 and (on 256 CUs) 4 x 8 layers: the last block of eight whole, or with one to three layers in its second half;
     elements for one thread only, and for every thread more than once."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert cus != 256 or pod.pod_similarity_plan(cus, L, H, R, n) == (4, streamed)
     gen = torch.Generator(device="cuda").manual_seed(L * 100 + n)
     att = torch.softmax(3 * torch.randn((L, H, R, n), generator=gen, device="cuda"), -1).contiguous()
     att[L - 1] = att[2]

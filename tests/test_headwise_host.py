@@ -68,3 +68,14 @@ def test_similarity_refuses_what_it_cannot_launch(layers, heads):
     buf = (C.c_float * 16)()
     at = (C.addressof(buf) + 15) // 16 * 16
     assert pod.binding.load().pod_layer_similarity(at, layers, heads, 1, 4, at, None) == pod.binding.ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("layers,heads,elements,blocks", [
+    (32, 32, 65536, (4, 8)), (32, 32, 12000, (4, 8)), (32, 32, 3072, (4, 4)), (32, 16, 768, (4, 4)), (45, 8, 6000, (4, 4)), (40, 32, 1792, (4, 4)),
+    (24, 32, 65536, (4, 4)), (16, 24, 65536, (2, 2)), (2, 1, 4, (2, 2)), (65535, 65535, 1 << 20, (4, 8))])
+def test_similarity_blocks_follow_the_work(layers, heads, elements, blocks):
+    """Blocks of 4 x 8 layers only where there are enough elements per head for half as many workgroups to pay (256 CUs)."""
+    assert pod.pod_similarity_plan(256, layers, heads, 1, elements) == blocks
+    for bad in ((0, 2, 2, 1, 4), (256, 0, 2, 1, 4), (256, 2, 65536, 1, 4), (256, 2, 2, 0, 4), (256, 2, 2, 1, 0)):
+        with pytest.raises(pod.PodError):
+            pod.pod_similarity_plan(*bad)
