@@ -176,6 +176,13 @@ int pod_cache_fill(pod_cache *cache, int layer, int seq_slot, int n, const void 
                    void *stream);
 
 /*
+ * Host logic, no device needed: *past_caches = 1 if a pod_cache_fill of n tokens into seq_slot stores them past the chip's
+ * caches (long prompts into a cache that then holds more than stays there), 0 if not.  held: HOST int64 [max_batch],
+ * tokens each slot holds; held[seq_slot] is not read.
+ */
+int pod_fill_plan(const pod_config *cfg, const int64_t *held, int seq_slot, int n, int *past_caches);
+
+/*
  * Decode attention (Eq. 3 + Eq. 4 as one joint softmax), one query token per sequence,
  * over what the cache holds for `layer` after the token's own K/V was appended.
  *   q            : dev bf16 [B][Hq][d], this layer's query

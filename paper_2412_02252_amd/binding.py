@@ -21,7 +21,7 @@ EXPORTS = [
     "pod_cache_fill", "pod_decode_attention", "pod_prefill_attention", "pod_cache_export_logical",
     "pod_profile_enable", "pod_profile_disable", "pod_profile_read", "pod_profile_read_each", "pod_profile_stream_read", "pod_profile_set_trace", "pod_profile_mfma_feed",
     "pod_score_buffer_bytes", "pod_decode_attention_reuse", "pod_decode_attention_gated", "pod_score_skip_offset",
-    "pod_group_layers", "pod_layer_similarity", "pod_similarity_plan",
+    "pod_group_layers", "pod_layer_similarity", "pod_similarity_plan", "pod_fill_plan",
     "pod_decode_attention_static", "pod_cache_region_counts", "pod_decode_step", "pod_cache_set_length_source", "pod_cache_launch_info",
     "pod_cache_sync_lengths", "pod_cache_append_many", "pod_prefill_chunk_workspace_bytes", "pod_prefill_chunk_in_place_bytes", "pod_prefill_attention_chunk", "pod_decode_even_plan",
     "pod_decode_plan", "pod_decode_step_reuse",
@@ -89,6 +89,7 @@ def load():
         "pod_score_skip_offset": [cfgp, szp],
         "pod_group_layers": [vp, C.c_int, C.c_int, C.c_int, C.c_float, vp],
         "pod_layer_similarity": [vp, C.c_int, C.c_int, C.c_int, C.c_int, vp, vp],
+        "pod_fill_plan": [cfgp, C.POINTER(C.c_int64), C.c_int, C.c_int, C.POINTER(C.c_int)],
         "pod_similarity_plan": [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int32)],
         "pod_decode_attention_reuse": [vp, C.c_int, vp, i32p, C.c_int, C.c_int, C.c_float, vp, C.c_size_t, vp,
                                        C.c_size_t, vp, vp],
@@ -175,6 +176,14 @@ def pod_similarity_plan(num_cus: int, num_layers: int, num_heads: int, rows: int
     plan = (C.c_int32 * 2)()
     _check(load().pod_similarity_plan(num_cus, num_layers, num_heads, rows, n, plan))
     return plan[0], plan[1]
+
+
+def pod_fill_plan(cfg: PodConfig, held, seq_slot: int, n: int) -> bool:
+    """Whether a pod_cache_fill of n tokens stores them past the chip's caches; held: tokens each slot holds."""
+    assert len(held) == cfg.max_batch
+    out = C.c_int()
+    _check(load().pod_fill_plan(C.byref(cfg), (C.c_int64 * len(held))(*held), seq_slot, n, C.byref(out)))
+    return bool(out.value)
 
 
 def pod_cache_bytes(cfg: PodConfig) -> int:

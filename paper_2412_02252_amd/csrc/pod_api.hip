@@ -151,12 +151,22 @@ extern "C" int pod_cache_live_bytes(const pod_config *cfg, int64_t n, size_t *po
     int rc = make_layout(cfg, &ly);
     if (rc) return rc;
     if (n < 0) return pod_fail(POD_ERR_INVALID_ARG, "n must be >= 0");
-    const size_t row = (size_t)ly.D * 2; // one head
-    const size_t n_prox = (size_t)(n < ly.P ? n : ly.P);
-    const size_t n_dist = (size_t)(n > ly.P ? n - ly.P : 0);
-    // per kv head: K and V of the proximal tokens and V of the distant ones at every layer; distant K once per block
-    if (pod_bytes) *pod_bytes = row * ((size_t)ly.L * ly.Hkv * (2 * n_prox + n_dist) + (size_t)ly.nslots * n_dist);
-    if (dense_bytes) *dense_bytes = row * ly.Hkv * 2 * (size_t)ly.L * (size_t)n;
+    if (pod_bytes) *pod_bytes = pod_live_bytes(ly, n);
+    if (dense_bytes) *dense_bytes = (size_t)ly.D * 2 * ly.Hkv * 2 * (size_t)ly.L * (size_t)n;
+    return POD_OK;
+}
+
+extern "C" int pod_fill_plan(const pod_config *cfg, const int64_t *held, int seq_slot, int n, int *past_caches)
+{
+    pod_layout ly;
+    int rc = make_layout(cfg, &ly);
+    if (rc) return rc;
+    if (!held || !past_caches) return pod_fail(POD_ERR_INVALID_ARG, "held and past_caches must not be NULL");
+    if (seq_slot < 0 || seq_slot >= ly.B || n < 1 || n > ly.maxctx)
+        return pod_fail(POD_ERR_INVALID_ARG, "seq_slot %d outside [0, %d) or n = %d outside [1, %d]", seq_slot, ly.B, n, ly.maxctx);
+    for (int b = 0; b < ly.B; ++b)
+        if (held[b] < 0 && b != seq_slot) return pod_fail(POD_ERR_INVALID_ARG, "held[%d] is negative", b);
+    *past_caches = pod_fill_past_caches(ly, held, held, seq_slot, n) ? 1 : 0;
     return POD_OK;
 }
 

@@ -414,7 +414,7 @@ __global__ void export_kernel(const char *base, pod_layout ly, pod_headmap hm, i
     }
 }
 
-constexpr size_t kPastCachesFill = (size_t)16 << 20, kPastCachesCache = (size_t)128 << 20; // bytes of a prompt's K and V, of a cache
+constexpr size_t kPastCachesFill = (size_t)16 << 20, kPastCachesLive = (size_t)128 << 20; // bytes of a prompt's K and V, of all that is held
 
 int grid_for(size_t items)
 {
@@ -461,18 +461,42 @@ pod_fill_args pod_make_fill_args(const pod_cache *c, int layer, int seq_slot, in
     return a;
 }
 
+size_t pod_live_bytes(const pod_layout &ly, int64_t n)
+{
+    const size_t row = (size_t)ly.D * 2; // one head
+    const size_t n_prox = (size_t)(n < ly.P ? n : ly.P);
+    const size_t n_dist = (size_t)(n > ly.P ? n - ly.P : 0);
+    // per kv head: K and V of the proximal tokens and V of the distant ones at every layer; distant K once per block
+    return row * ((size_t)ly.L * ly.Hkv * (2 * n_prox + n_dist) + (size_t)ly.nslots * n_dist);
+}
+
+// Stores go past the caches where the rows would not stay there until they are read: where the cache, once all its layers hold what
+// this fill and the other slots bring (held, held2: the longer of the two per slot), has more than half of the 256 MB that the chip
+// keeps (a fill reads as much as it writes), and the fill itself has 16 MB.  What is held counts, not what the cache has room for.
+// Requests, fills and steps, us, plain -> past the caches: 16 sequences of 4-32K tokens x 8 x 128 and 16 steps 6238 -> 6168, 4 of 128K 17016 -> 16800;
+// 2 layers x 8 x 128 and one step (bytes held): 8 sequences of 4096 tokens (236 MB) 200.9 -> 182.5, 4 of 4096 (118 MB) 93.0 -> 92.8, one of 65536 (394 MB) 245 -> 239,
+// 32768 (206 MB) 126.4 -> 128.4 (and 32 steps 1674 -> 1661), 24000 (152 MB) 99.7 -> 98.8; but 20000 (127 MB) 84.4 -> 87.7, 16384 (105 MB) 75.9 -> 78.6, 2 of 8192
+// (108 MB) 81.4 -> 84.1, and in a cache of 16 slots (12000 tokens) 64.8 -> 66.3; 16 layers of 4096 (207 MB) 287 -> 269.
+bool pod_fill_past_caches(const pod_layout &ly, const int64_t *held, const int64_t *held2, int seq_slot, int n)
+{
+    if ((size_t)n * ly.Hkv * ly.D * 4 < kPastCachesFill) return false;
+    size_t live = pod_live_bytes(ly, n);
+    for (int b = 0; b < ly.B && live < kPastCachesLive; ++b)
+        if (b != seq_slot) live += pod_live_bytes(ly, held[b] > held2[b] ? held[b] : held2[b]);
+    return live >= kPastCachesLive;
+}
+
 int pod_launch_fill(const pod_cache *c, int layer, int seq_slot, int n, const void *k, const void *v, hipStream_t st)
 {
-    // Bound by HBM; one piece per thread (up to 2^28 pieces), so that the launch walks memory in order.  Stores go past the caches where the
-    // rows would not stay there until they are read: caches of half the 256 MB that the chip keeps (a fill reads as much as it writes), fills
-    // of 16 MB.  Requests, fills and 12-32 steps, us, plain -> past the caches: 16 sequences of 4-32K tokens x 8 x 128 6238 -> 6168, 12 of 1.5-15K x
-    // 4 x 128 1569 -> 1541, 4 of 128K 17016 -> 16800, one of 32K (206 MB) 1674 -> 1661; but one of 16K and its selection (103 MB) 142.5 -> 144.9,
-    // 8 of 0.5-3K (2-12 MB each) 625 -> 630.
+    // Bound by HBM; one piece per thread (up to 2^28 pieces), so that the launch walks memory in order.
     const size_t items = (size_t)n * c->ly.Hkv * (c->ly.D / 8), wgs = (items + kThreads - 1) / kThreads;
     const dim3 g((unsigned)(wgs < ((size_t)1 << 20) ? wgs : (size_t)1 << 20));
     const pod_fill_args a = pod_make_fill_args(c, layer, seq_slot, n);
-    if (items * 32 >= kPastCachesFill && c->ly.total_bytes >= kPastCachesCache) hipLaunchKernelGGL(fill_kernel<true>, g, dim3(kThreads), 0, st, a, k, v);
-    else hipLaunchKernelGGL(fill_kernel<false>, g, dim3(kThreads), 0, st, a, k, v);
+    // (a slot's other layers hold as much or are about to: this layer's lengths and the first one's)
+    if (pod_fill_past_caches(c->ly, c->host_len + (size_t)layer * c->ly.B, c->host_len, seq_slot, n))
+        hipLaunchKernelGGL(fill_kernel<true>, g, dim3(kThreads), 0, st, a, k, v);
+    else
+        hipLaunchKernelGGL(fill_kernel<false>, g, dim3(kThreads), 0, st, a, k, v);
     POD_HIP_TRY(hipGetLastError());
     return POD_OK;
 }

@@ -170,6 +170,8 @@ int pod_launch_clear_header(const pod_cache *c, hipStream_t st);
 int pod_launch_reset(const pod_cache *c, int seq_slot, hipStream_t st);
 int pod_launch_append(const pod_cache *c, int layer, const void *k_new, const void *v_new,
                       const int32_t *positions, int B, hipStream_t st);
+size_t pod_live_bytes(const pod_layout &ly, int64_t n); // what n tokens of one sequence take in all layers
+bool pod_fill_past_caches(const pod_layout &ly, const int64_t *held, const int64_t *held2, int seq_slot, int n); // (host logic)
 int pod_launch_fill(const pod_cache *c, int layer, int seq_slot, int n, const void *k, const void *v,
                     hipStream_t st);
 // sequences b_first .. b_first + B - 1; k_new, v_new: [B][T][Hkv][D] and counts: host array [B], both starting at

@@ -84,3 +84,21 @@ def test_selection_workspace_sizes_and_shape_checks():
     with pytest.raises(pod.PodError) as e:
         pod.pod_select_workspace_bytes(cfg, 40001, obs, keep)
     assert e.value.code == pod.binding.ERR_CAPACITY
+
+
+def test_fills_go_past_the_caches_by_what_is_held_not_by_what_fits():
+    """16384 tokens of 8 x 128 take 105 MB in two layers: with nothing else held they stay in a 256 MB cache next to their source's tail,
+    however many slots the cache has room for."""
+    def plan(n, held, layers=2, slots=16, slot=0):
+        return pod.pod_fill_plan(pod.make_config(layers, 2, 32, 8, 128, 64, 2048, slots, 65536), held + [0] * (slots - len(held)), slot, n)
+    assert not plan(16384, []) and not plan(16384, [], slots=1) and not plan(20000, [])
+    assert plan(24000, []) and plan(24000, [], slots=1) and plan(32768, [])
+    assert plan(16384, [0, 16384]) and not plan(16384, [0, 4096 // 2])      # another slot's rows count
+    assert plan(4096, [4096] * 8, slot=5) and not plan(4096, [4096] * 4, slot=3)
+    assert not plan(16384, [65536])                                         # the slot's own entry does not
+    assert not plan(4095, [0] + [65536] * 15)                               # fills under 16 MB never
+    assert plan(4096, [], layers=32)                                        # ... and all the layers that follow do
+    cfg = pod.make_config(2, 2, 32, 8, 128, 64, 2048, 2, 1000)
+    for held, slot, n in (([0, 0], 2, 10), ([0, 0], -1, 10), ([0, 0], 0, 0), ([0, 0], 0, 1001), ([0, -1], 0, 10)):
+        with pytest.raises(pod.PodError):
+            pod.pod_fill_plan(cfg, held, slot, n)

@@ -94,17 +94,20 @@ def test_other_slots_and_layers_stay_untouched():
     assert exp["distK"].shape[0] == 28
 
 
-@pytest.mark.parametrize("heads,dim,n,batch", [(8, 128, 4095, 6), (8, 128, 4096, 6), (8, 128, 4096, 2), (7, 128, 4682, 6), (5, 64, 13108, 6)])
-def test_fills_on_both_sides_of_the_stores_past_the_caches(heads, dim, n, batch):
-    # 16 MB of keys and values (4096 tokens x 8 x 128) in a cache of 128 MB (six slots); the ragged ones end inside a workgroup; another
-    # slot must stay as it was
+@pytest.mark.parametrize("heads,dim,n,batch,past", [(8, 128, 4095, 8, False), (8, 128, 4096, 8, True), (8, 128, 4096, 2, False), (7, 128, 4682, 8, True),
+                                                    (5, 64, 13108, 8, True)])
+def test_fills_on_both_sides_of_the_stores_past_the_caches(heads, dim, n, batch, past):
+    # 16 MB of keys and values (4096 tokens x 8 x 128) next to 128 MB that are held (six slots of that); the ragged ones end inside a
+    # workgroup; another slot must stay as it was
     c = Case(2, 2, heads, heads, dim, 3, 37, batch, n + 100, seed=n)
     for layer in range(2):
         c.fill(layer, 1, 50)
-        c.fill(layer, 0, n)
+        for slot in [b for b in range(batch) if b != 1]:
+            c.fill(layer, slot, n)
+    assert pod.pod_fill_plan(c.cfg, [n] * (batch - 1) + [0], batch - 1, n) == past
     for layer in range(2):
-        c.assert_cache_equal(layer, 0)
-        c.assert_cache_equal(layer, 1)
+        for slot in {0, 1, batch - 1}:
+            c.assert_cache_equal(layer, slot)
     c.gpu.pod_cache_check()
 
 
