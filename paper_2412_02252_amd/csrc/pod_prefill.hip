@@ -184,13 +184,13 @@ __device__ inline f32x4 add_four(u32x2 v, f32x4 acc)
 // 16 bytes per lane from base + off (off per lane) straight into LDS: lane l's go to LDS address dst + 16 l (dst the same in every lane).
 // Written as the instruction itself and waited for by hand (vmcnt), because the compiler, which cannot tell the slots apart, puts a
 // wait for ALL outstanding loads into LDS in front of the next transposing LDS read: every tile then stood still for the whole
-// latency of the loads it had just requested.  A load into LDS has no destination register, and nothing else in these kernels uses
-// M0.  Both layers of a request, before -> after (kernels alone, us): 16384 tokens x 32/8 heads x 128 4350 -> 4130,
+// latency of the loads it had just requested.  A load into LDS has no destination register; M0 is declared as changed, which costs nothing
+// since nothing else in these kernels uses it.  Both layers of a request, before -> after (kernels alone, us): 16384 tokens x 32/8 heads x 128 4350 -> 4130,
 // 3001 x 16/4 x 64 84.4 -> 80.0, 777 x 32/8 x 128 48.1 -> 46.9.
 typedef const __attribute__((address_space(1))) char *gbyte_ptr;
 __device__ __forceinline__ void load_lds16(gbyte_ptr base, unsigned off, unsigned dst)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(base) : "memory", "m0");
 }
 
 template <int D, bool TAB, int KS>
