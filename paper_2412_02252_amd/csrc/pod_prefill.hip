@@ -336,11 +336,14 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
     for (int db = 0; db < NDB; ++db) v_rd[db] = v_rd0 ^ (64 * db);
 
     bf16x8 qf[KST];
-    const int qrow = max(min(irow, p.n - 1), p.q0) - p.q0;
     auto load_q = [&](const pod_bf16 *src) __attribute__((always_inline)) {
-        const gvec_ptr qr = (gvec_ptr)(src + ((size_t)qrow * p.Hq + head) * D);
+        int row = irow, half = jj;
+        // (with two key groups the own query's address, kept from the start to the phase change, does not fit the registers: computed again.
+        // 777 tokens x 32/8 heads x 128, lowest / upper layer 19.4 / 24.7 -> 18.8 / 24.1 us)
+        if constexpr (KS == 2) asm volatile("" : "+v"(row), "+v"(half));
+        const gvec_ptr qr = (gvec_ptr)(src + ((size_t)(max(min(row, p.n - 1), p.q0) - p.q0) * p.Hq + head) * D);
 #pragma unroll
-        for (int s = 0; s < KST; ++s) qf[s] = as_bf16x8(qr[2 * s + jj]);
+        for (int s = 0; s < KST; ++s) qf[s] = as_bf16x8(qr[2 * s + half]);
 #pragma unroll
         for (int s = 0; s < KST; ++s) asm volatile("" : "+v"(qf[s])); // awaited here, not wherever the paths with and without the load meet
     };
