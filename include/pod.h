@@ -528,14 +528,15 @@ int pod_profile_mfma_feed(int variant, int iters, void *dev_out, size_t out_byte
  * to max_context_len tokens is cut into split-K pieces on a device with num_cus compute units, without tuning
  * overrides (proximal_rows = sink + window).  plan[0] waves per workgroup, plan[1] tokens per distant piece, plan[2]
  * tokens per proximal piece, plan[3] distant pieces per (sequence, kv head) pair, plan[4] all pieces per pair,
- * plan[5] 1 if the last workgroup of a pair merges the partials inside the launch, 0 if a second kernel does.
+ * plan[5] 1 if the last workgroup of a pair merges these pieces' partials inside the launch, 0 if a second kernel does
+ * (or the launch takes the even split below instead).
  * Pieces are whole tiles of 32 tokens and cover the regions; plan[4] never exceeds what pod_workspace_bytes provides for.
  * Returns POD_ERR_INVALID_ARG for non-positive arguments or a NULL plan.
  */
 int pod_decode_plan(int num_cus, int batch, int num_kv_heads, int proximal_rows, int max_context_len, int32_t plan[6]);
 
 /*
- * Host logic, no device needed: the even split a launch takes where pod_decode_plan's plan[5] is 0 and the host
+ * Host logic, no device needed: the even split of a launch where pod_decode_plan's plan[5] is 0 and the host
  * knows the lengths (batch <= 256, lengths not taken from the device): plain launches, and score-reuse decode steps
  * of layers none of whose kv heads starts a block (they read logits).  context_lens: HOST int32 [batch], tokens each sequence holds (<= 0:
  * none).  The rows of the batch stand in one line - sequence after sequence, inside a sequence kv head after kv head,
@@ -544,10 +545,22 @@ int pod_decode_plan(int num_cus, int batch, int num_kv_heads, int proximal_rows,
  * half the bytes), 128 proximal rows; a region's last unit may be short.  unit_cum: HOST out int32 [batch + 1],
  * units per kv head of the sequences before b.  plan[0] units per workgroup q (workgroup w walks units
  * [w q, (w + 1) q) of the line), plan[1] workgroups, plan[2] units in all, plan[3] the largest number of workgroups
- * that share one (sequence, kv head) pair = partial results per pair; all 0 if no sequence holds a token.
+ * that share one (sequence, kv head) pair = partial results per pair; all 0 if no sequence holds a token.  Score-reuse
+ * steps are launched so; plain launches too, unless padding fits (pod_decode_even_launch).
  */
 int pod_decode_even_plan(int num_cus, int batch, int num_kv_heads, int proximal_rows, int distant_unit_tokens,
                          const int32_t *context_lens, int32_t plan[4], int32_t *unit_cum);
+
+/*
+ * Host logic, no device needed: the split such a launch really takes.  The same, but with 128-token distant units every
+ * pair's units are padded to a multiple of plan[0] where all workgroups still fit one round (2 num_cus): then plan[4] is 1, unit_cum
+ * and plan[2] count the padding, no workgroup walks rows of two pairs, every pair that holds a token has
+ * (unit_cum[b + 1] - unit_cum[b]) / plan[0] workgroups, each with rows of its own, and at head dimension 64 with at most
+ * four query heads per kv head (and no empty sequence, or a decode step) the last of them merges the pair's partials inside
+ * the launch.  plan[4] is 0 where pod_decode_even_plan's split is taken as it is.
+ */
+int pod_decode_even_launch(int num_cus, int batch, int num_kv_heads, int proximal_rows, int distant_unit_tokens,
+                           const int32_t *context_lens, int32_t plan[5], int32_t *unit_cum);
 
 /*
  * Measurement aid: while dev_buf is set (NULL = off), every workgroup of a pod_decode_step / fused
@@ -556,7 +569,7 @@ int pod_decode_even_plan(int num_cus, int batch, int num_kv_heads, int proximal_
  * the XCD it ran on, and the device's 100 MHz clock at its start, at the end of its tile loop, when its partial was
  * stored, when its arrival was counted, and at its end.  Launches whose partials a second kernel merges record too:
  * words 0, 2, 3 and 6 as above (start, end of the tile loop, end), word 1 = XCD id | hardware id register << 8 (which
- * CU); an even-split launch (pod_decode_even_plan) records per walking workgroup its number, that word 1, and the
+ * CU); an even-split launch (pod_decode_even_launch) records per walking workgroup its number, that word 1, and the
  * clock at its start (words 2 and 3) and end (word 6).  bytes / 64 workgroups are recorded; later launches overwrite
  * earlier ones.  The caller owns dev_buf.
  */

@@ -126,7 +126,6 @@ struct decode_params {
     // workgroups that walk rows, bal_total units in all; unit_cum[b] = units of the sequences before b (per kv head)
     int32_t bal_q, bal_nwg, bal_total;
     int32_t walk_rev;            // 1: walk the tiles of the distant keys a lower layer of the block has just read from the last to the first
-    int32_t bal_unit_d;          // tokens per unit of distant rows (kUnit; twice that where an upper layer reads logits instead of keys)
     int32_t hlen[kMaxHostLens];
     int32_t unit_cum[kMaxHostLens + 1];
     // per kv head: (slot * max_batch of the distant-key store the head reads at this layer) | sign bit if this
@@ -1855,7 +1854,7 @@ bool pod_plan_even(int slots, int B, int Hkv, int P, int unit_d, const int32_t *
 // rows in the padding.)  32 chats of 0.3-4K tokens x 4 kv heads x 64, 445 workgroups of 5 units, took 7.3 to 13.6 us per workgroup, median 10.3;
 // padded to 492 the request takes 1294 us instead of 1411.  12 of 1.5-15K x 4 x 128 1643 -> 1589; long launches, whose workgroups walk many
 // units, the same either way, and so score reuse (0.993-0.999), which keeps the plain split.
-static bool pad_even_plan(int slots, int B, int Hkv, int32_t *unit_cum, pod_even_plan_t *pl)
+static bool pad_even_split(int slots, int B, int Hkv, int32_t *unit_cum, pod_even_plan_t *pl)
 {
     const int q = pl->q;
     long wgs = 0;
@@ -1874,6 +1873,15 @@ static bool pad_even_plan(int slots, int B, int Hkv, int32_t *unit_cum, pod_even
         unit_cum[b + 1] = padded;
     }
     pl->nwg = (int32_t)wgs; pl->total = (int32_t)(wgs * q); pl->most = most;
+    return true;
+}
+
+// The split a launch takes: padded where units of distant rows are the plain launches'.
+bool pod_plan_even_launch(int slots, int B, int Hkv, int P, int unit_d, const int32_t *lens, int32_t *unit_cum, pod_even_plan_t *pl, bool *padded)
+{
+    *padded = false;
+    if (!pod_plan_even(slots, B, Hkv, P, unit_d, lens, unit_cum, pl)) return false;
+    *padded = unit_d == kUnit && pad_even_split(slots, B, Hkv, unit_cum, pl);
     return true;
 }
 
@@ -1957,15 +1965,15 @@ int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *
     const int even_mode = reuse_step ? 2 : 0;
     bool even_merge = false;
     bool even = !merge_inside && p.hot.use_hlen && c->even_split && (p.mode == 0 || (reuse_step && !lowest_any));
-    p.bal_unit_d = even_unit_distant(even_mode);
     if (even) {
         pod_even_plan_t ev;
-        even = pod_plan_even(2 * cus, B, H, ly.P, p.bal_unit_d, p.hlen, p.unit_cum, &ev);
+        bool padded = false;
+        even = pod_plan_even_launch(2 * cus, B, H, ly.P, even_unit_distant(even_mode), p.hlen, p.unit_cum, &ev, &padded);
         // Where no workgroup crosses, each hands over once, at its end, and the last of a pair's merges: at head dimension 64 with few query
         // heads per kv head, whose partials are small, that costs less than the second launch.  Requests, us, second launch -> inside: 32 chats
         // x 16/4 x 64 1294 -> 1194, 4 of 3-30K x 8/8 x 64 898 -> 846, 20 of 0.5-5K 817 -> 781; but 24 of 0.2-2.5K x 32/8 x 128 1039 -> 1036, 12 of
         // 1.5-15K x 32/4 x 128 1585 -> 1619.
-        even_merge = even && even_mode == 0 && pad_even_plan(2 * cus, B, H, p.unit_cum, &ev) && c->fused_merge && ly.D == 64 && ly.rep <= 4;
+        even_merge = even && padded && c->fused_merge && ly.D == 64 && ly.rep <= 4;
         if (!step) // (an empty sequence has no workgroup that would write its rows)
             for (int b = 0; b < B; ++b) even_merge = even_merge && p.hlen[b] > 0;
         // (a batch of one very long and many short sequences cuts the long one into more parts than fixed pieces

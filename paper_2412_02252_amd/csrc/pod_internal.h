@@ -205,6 +205,8 @@ pod_decode_plan_t pod_plan_decode(int cus, int B, int Hkv, int P, int max_len, i
 // unit_d = tokens per unit of distant rows (128, or 256 for an upper layer that reads logits instead of keys)
 struct pod_even_plan_t { int32_t q, nwg, total, most; };
 bool pod_plan_even(int slots, int B, int Hkv, int P, int unit_d, const int32_t *lens, int32_t *unit_cum, pod_even_plan_t *pl);
+// ... as the launch takes it: with every pair's units padded to whole workgroups where that fits (*padded)
+bool pod_plan_even_launch(int slots, int B, int Hkv, int P, int unit_d, const int32_t *lens, int32_t *unit_cum, pod_even_plan_t *pl, bool *padded);
 int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *q_shared,
                       const int32_t *ctx, int B, int max_len, float scale, void *ws, size_t ws_bytes,
                       void *scores, float tau, void *out, hipStream_t st, const pod_step_args *step = nullptr);

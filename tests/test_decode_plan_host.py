@@ -105,7 +105,7 @@ def test_even_split_covers_every_unit_once_and_the_merge_counts_agree(seed):
             assert (b, h, u) not in seen
             seen[(b, h, u)] = w
     assert len(seen) == total
-    # what decode_combine_kernel derives from a pair's length alone: as many partials as workgroups touch the pair,
+    # what decode_combine_kernel derives from the units before and of a pair: as many partials as workgroups touch the pair,
     # in slots 0 .. count - 1, each written by exactly one workgroup
     most = 0
     for b in range(B):
@@ -126,3 +126,61 @@ def test_even_split_rejects_bad_arguments():
         pod.pod_decode_even_plan(256, 8, 2112, [100] * 257)
     with pytest.raises(pod.PodError):
         pod.pod_decode_even_plan(256, 8, 2112, [100], distant_unit_tokens=64)
+
+
+@pytest.mark.parametrize("seed", range(60))
+def test_the_split_that_is_launched_takes_every_unit_once(seed):
+    """Padded where every pair's whole workgroups fit one round: no workgroup has units of two pairs, none only padding, a pair's
+    arrivals are its workgroups, and no pair has more partials than without.  Else, and for 256-token units, the split as it is."""
+    rng = np.random.default_rng(7300 + seed)
+    cus = int(rng.choice([4, 64, 256, 304]))
+    Hkv = int(rng.choice([1, 2, 4, 8, 11]))
+    P = int(rng.choice([40, 136, 528, 4224]))
+    B = int(rng.integers(1, 50))
+    lens = [int(x) for x in rng.choice([0, 1, 127, 128, 129, P, P + 1, 700, 3000, 5000, 40000], size=B)]
+    ud = int(rng.choice([128, 128, 128, 256]))
+    plain, plan = pod.pod_decode_even_plan(cus, Hkv, P, lens, ud), pod.pod_decode_even_launch(cus, Hkv, P, lens, ud)
+    units = [(max(n - P, 0) + ud - 1) // ud + (min(n, P) + 127) // 128 for n in lens]
+    q = plain["units_per_workgroup"]
+    fits = sum(units) > 0 and ud == 128 and Hkv * sum(-(-u // q) for u in units) <= 2 * cus
+    assert plan["padded"] == fits
+    if not fits:
+        assert {k: v for k, v in plan.items() if k != "padded"} == plain
+        return
+    cum, nwg = plan["unit_cum"], plan["workgroups"]
+    parts_of = [-(-u // q) for u in units]
+    assert plan["units_per_workgroup"] == q and cum == [q * sum(parts_of[:b]) for b in range(B + 1)]
+    assert plan["units"] == cum[B] * Hkv == nwg * q and nwg <= 2 * cus
+    assert plan["partials_per_pair"] == max(parts_of) <= plain["partials_per_pair"]
+    parts = walk_even_split(plan, Hkv, P, lens)
+    assert sorted(w for w, *_ in parts) == list(range(nwg))                # one part each
+    arrivals, seen = {}, {}
+    for w, b, h, u0, cnt, slot in parts:
+        assert u0 % q == 0 and slot == u0 // q and cnt == q
+        assert u0 < units[b], "a part that is only padding"
+        for u in range(u0, min(u0 + cnt, units[b])):
+            assert (b, h, u) not in seen
+            seen[(b, h, u)] = w
+        arrivals[(b, h)] = arrivals.get((b, h), 0) + 1
+    assert len(seen) == Hkv * sum(units)
+    for b in range(B):
+        U = cum[b + 1] - cum[b]
+        for h in range(Hkv):
+            # what the merging kernel waits for, and what decode_combine_kernel counts
+            assert arrivals.get((b, h), 0) == U // q == parts_of[b]
+            g0 = cum[b] * Hkv + h * U
+            assert ((g0 + U - 1) // q - g0 // q + 1 if U else 0) == parts_of[b]
+
+
+def test_the_launched_split_of_the_benchmark_batches():
+    """28 chats: padded; pairs that outnumber the workgroups of a round: as it is; nothing held: nothing launched."""
+    chats = [300 + 122 * i for i in range(28)]
+    assert pod.pod_decode_even_launch(256, 4, 528, chats)["padded"]
+    assert not pod.pod_decode_even_launch(256, 8, 72, [100 + i for i in range(70)])["padded"]
+    assert pod.pod_decode_even_launch(256, 4, 528, [0, 0])["workgroups"] == 0
+
+
+def test_launched_split_rejects_bad_arguments():
+    for args in ((0, 8, 2112, [100]), (256, 8, 2112, [100] * 257), (256, 8, 0, [100]), (256, 8, 2112, [100], 64)):
+        with pytest.raises(pod.PodError):
+            pod.pod_decode_even_launch(*args)
