@@ -1449,7 +1449,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_para
             merge_and_store<D, false, NW>(p, hot, done_b, done_h, done_parts, 0, STEP, valid, bad);
         }
     }
-    if (p.trace && threadIdx.x == 0 && w < p.trace_cap) { // measurement aid: workgroup, XCD and CU, clock at start and end
+    if (p.trace && threadIdx.x == 0 && w < p.bal_nwg && w < p.trace_cap) { // measurement aid: walking workgroup, XCD and CU, clock at start and end
         unsigned long long *t = p.trace + 8 * (size_t)w;
         t[0] = (unsigned long long)w;
         t[1] = (unsigned long long)xcc_id() | ((unsigned long long)__builtin_amdgcn_s_getreg((32 - 1) << 11 | 4) << 8);

@@ -213,6 +213,27 @@ def test_parts_of_whole_pairs_merged_inside(Hq, Hkv, B, lo, step):
     assert float(got[2].float().abs().max()) == 0.0 and float(got[3].float().abs().max()) > 0.0
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_the_trace_holds_the_walking_workgroups_of_the_launched_split(d):
+    """Steps merged inside (d = 64) and by the second launch: one record per workgroup of pod_decode_even_launch's split, none for the
+    workgroups that only take the new token."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    lens = [130 + (91 * i * i) % 900 for i in range(44)]
+    c = Case(2, 2, 16, 4, d, 8, 64, len(lens), 1210, seed=9380 + d)
+    fill_all(c, lens)
+    split = pod.pod_decode_even_launch(cus, 4, 72, lens)
+    assert cus != 256 or split["padded"]
+    trace = torch.zeros(8 * 2048, dtype=torch.int64, device=c.dev)
+    c.gpu.pod_profile_set_trace(trace)
+    out = c.step(0, lens)
+    c.gpu.pod_profile_set_trace(None)
+    assert_close(out, c.decode_ref(0, [n + 1 for n in lens]), f"d={d}")
+    words = trace.view(-1, 8).cpu()
+    n = split["workgroups"]
+    assert (words[:n, 0] == torch.arange(n)).all() and (words[:n, 6] >= words[:n, 2]).all() and (words[:n, 2] > 0).all()
+    assert (words[n:] == 0).all()
+
+
 def test_wrong_context_length_is_flagged_in_the_even_split(monkeypatch):
     monkeypatch.setenv("POD_DECODE_FUSED", "0")
     lens = [900, 300, 77]
