@@ -163,8 +163,8 @@ def test_parts_of_whole_pairs_and_parts_that_cross(d, Hq, Hkv, B, lo, step, monk
 
 @pytest.mark.parametrize("Hq,Hkv,B,lo,step", [(8, 8, 24, 300, 37), (16, 4, 44, 130, 91), (6, 2, 80, 3, 77)])
 def test_parts_of_whole_pairs_merged_inside(Hq, Hkv, B, lo, step):
-    """Head dimension 64 and few query heads per kv head: the last part of a pair merges.  Steps, then the same attention again; an empty
-    sequence (merged by the second launch); wrong lengths and positions, whose rows come out zero; a graph replayed three times."""
+    """Head dimension 64 and few query heads per kv head: the last part of a pair merges.  Steps, then the same attention again;
+    wrong lengths and positions, whose rows come out zero; a graph replayed three times."""
     lens = [lo + (step * i * i) % 900 for i in range(B)]
     c = Case(2, 2, Hq, Hkv, 64, 8, 64, B, 1210, seed=9360 + B)
     fill_all(c, lens)
@@ -211,6 +211,36 @@ def test_parts_of_whole_pairs_merged_inside(Hq, Hkv, B, lo, step):
         c.gpu.pod_cache_check()
     assert e.value.code == pod.binding.ERR_STATE
     assert float(got[2].float().abs().max()) == 0.0 and float(got[3].float().abs().max()) > 0.0
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,B", [(16, 4, 64, 44), (8, 8, 64, 24), (8, 4, 128, 44)])
+def test_empty_sequences_in_the_padded_split(Hq, Hkv, d, B):
+    """First, in the middle and last in the batch: no part walks them.  Attention leaves the merge to the second launch, which writes their
+    zero rows; a step gives each its first token, which the merging kernel's own workgroup for the pair (d = 64) takes alone; then both
+    again with nothing empty."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    lens = [0 if b in (0, 7, 8, B - 1) else 130 + (91 * b * b) % 900 for b in range(B)]
+    empty, held = [b for b in range(B) if not lens[b]], [b for b in range(B) if lens[b]]
+    assert cus != 256 or (pod.pod_decode_even_launch(cus, Hkv, 72, lens)["padded"] and not pod.pod_decode_plan(cus, B, Hkv, 72, max(lens))["merge_inside"])
+    c = Case(2, 2, Hq, Hkv, d, 8, 64, B, 1210, seed=9370 + B)
+    one = Case(2, 2, Hq, Hkv, d, 8, 64, B, 1210, seed=9370 + B)              # (the oracle wants a token in each: its reference for the others)
+    fill_all(c, lens)
+    fill_all(one, [max(n, 1) for n in lens])
+    for _ in range(2):
+        for layer in range(2):
+            got = c.decode(layer, lens, max_context_len=max(lens))
+            assert float(got[empty].float().abs().max()) == 0.0
+            assert_close(got[held], one.decode_ref(layer, [max(n, 1) for n in lens])[held], f"empty sequences, layer {layer}")
+    for s in range(2):
+        pos = [n + s for n in lens]
+        for layer in range(2):
+            assert_close(c.step(layer, pos), c.decode_ref(layer, [p + 1 for p in pos]), f"step {s} layer {layer}")
+    ctx = [n + 2 for n in lens]
+    for layer in range(2):
+        assert_close(c.decode(layer, ctx), c.decode_ref(layer, ctx), f"decode layer {layer}")
+        for b in empty + held[:2]:
+            c.assert_cache_equal(layer, b)
+    c.gpu.pod_cache_check()
 
 
 @pytest.mark.parametrize("d", [64, 128])
