@@ -273,6 +273,104 @@ def test_compaction_moves_the_selected_rows(d, Hkv, S, W, n, keep, order):
             assert torch.equal(got["sinkK"], k[layer][:S]) and torch.equal(got["sinkV"], v[layer][:S])
 
 
+def _filled(L, G, Hkv, d, S, W, n, keep, seed, table=None):
+    gen_ = torch.Generator(device="cuda").manual_seed(seed)
+    cache = pod.PodCache(pod.make_config(L, G, Hkv, Hkv, d, S, W, 2, n + 8, block_lowest=table), torch.device("cuda:0"), guard_bytes=4096)
+    k, v = (torch.randn((L, n, Hkv, d), generator=gen_, device="cuda").to(torch.bfloat16) for _ in range(2))
+    sel = torch.randint(0, n - S - W, (L, Hkv, keep), generator=gen_, device="cuda").to(torch.int32).contiguous()
+    for layer in range(L):
+        cache.pod_cache_fill(layer, 1, k[layer], v[layer])
+    return cache, k, v, sel, cache.new_select_workspace(n, 1, keep)
+
+
+def _step_once(cache, L, Hkv, d, n):
+    """A decode step of slot 1 (slot 0 takes its first token): the stored lengths have to advance."""
+    gen_ = torch.Generator(device="cuda").manual_seed(n)
+    kn, vn, q = torch.randn((3, 2, Hkv, d), generator=gen_, device="cuda").to(torch.bfloat16)
+    pos = torch.tensor([0, n], dtype=torch.int32, device="cuda")
+    for layer in range(L):
+        cache.pod_decode_step(layer, kn, vn, q, q if layer else None, pos, d ** -0.5)
+    cache.pod_cache_check()
+    cache.pod_cache_sync_lengths()
+    assert [cache.pod_cache_seq_len(layer, b) for layer in range(L) for b in range(2)] == [1, n + 1] * L
+
+
+@pytest.mark.parametrize("Hkv,d,keep", [(8, 128, 10), (8, 128, 600), (17, 64, 300), (2, 64, 10)])
+def test_a_selection_entry_out_of_range_is_row_zero_and_reported(Hkv, d, keep):
+    """In one launch (64 workgroups and more) and in three: entries below 0, at the end of the distant store and far beyond it, in the keys'
+    and in the values' pass; the other rows are right, and the sequence goes on."""
+    L, S, W, n = 2, 4, 40, 1500
+    cache, k, v, sel, ws = _filled(L, 2, Hkv, d, S, W, n, keep, 31 + Hkv)
+    n_dist = n - S - W
+    for h, at, bad in ((0, 0, -1), (1, keep - 1, n_dist), (Hkv - 1, keep // 2, 2 ** 31 - 1)):
+        sel[0, h, at] = bad
+    for layer in range(L):
+        cache.pod_cache_compact(layer, 1, sel, ws)
+        with pytest.raises(pod.PodError) as e:
+            cache.pod_cache_check()
+        assert e.value.code == pod.binding.ERR_STATE
+    cache.pod_cache_check()                                   # (the failed check has cleared the flag)
+    cache.pod_cache_sync_lengths()
+    rows = torch.where((sel[0] >= 0) & (sel[0] < n_dist), sel[0], 0).long().t()[:, :, None].expand(-1, -1, d) + S
+    for layer in range(L):
+        assert cache.pod_cache_seq_len(layer, 1) == S + keep + W
+        got = cache.pod_cache_export_logical(layer, 1)
+        assert torch.equal(got["distV"], torch.gather(v[layer], 0, rows))
+        assert layer or torch.equal(got["distK"], torch.gather(k[layer], 0, rows))
+        assert torch.equal(got["recentK"], k[layer][n - W:]) and torch.equal(got["sinkV"], v[layer][:S])
+    _step_once(cache, L, Hkv, d, S + keep + W)
+
+
+@pytest.mark.parametrize("Hkv,d,keep", [(8, 128, 10), (16, 64, 600), (2, 64, 10)])
+def test_a_stored_length_that_differs_leaves_the_cache_as_it_is(Hkv, d, keep):
+    """The device holds another length than the host believes (a step of a captured graph replayed behind its back would leave it so):
+    the flag, nothing moved, nothing counted that is left over - the next compaction and steps advance the lengths."""
+    L, S, W, n = 2, 4, 40, 1500
+    cache, k, v, sel, ws = _filled(L, 2, Hkv, d, S, W, n, keep, 41 + Hkv)
+    lens = (cache.buf.view(torch.int32) == n).nonzero().flatten()     # the two stored lengths come first in the buffer
+    at = [int(x) for x in lens[:2]]
+    assert at[1] - at[0] == 2                                          # [layer][slot]
+    words = cache.buf.view(torch.int32)
+    words[at[0]] = n - 1
+    before = cache.buf.clone()
+    cache.pod_cache_compact(0, 1, sel, ws)
+    with pytest.raises(pod.PodError) as e:
+        cache.pod_cache_check()
+    assert e.value.code == pod.binding.ERR_STATE
+    assert torch.equal(cache.buf, before)                              # (the check clears the flag it found)
+    words[at[0]] = n
+    cache.pod_cache_sync_lengths()                                     # the host believes the device again
+    for layer in range(L):
+        assert cache.pod_cache_seq_len(layer, 1) == n
+        cache.pod_cache_compact(layer, 1, sel, ws)
+    cache.pod_cache_check()
+    rows = sel[0].long().t()[:, :, None].expand(-1, -1, d) + S
+    for layer in range(L):
+        assert torch.equal(cache.pod_cache_export_logical(layer, 1)["distV"], torch.gather(v[layer], 0, rows))
+    _step_once(cache, L, Hkv, d, S + keep + W)
+
+
+@pytest.mark.parametrize("Hkv,d", [(8, 128), (19, 64)])
+def test_compaction_of_head_wise_blocks_in_one_launch(Hkv, d):
+    """Every head follows the selection of its own block's lowest layer, and only that layer keeps the head's distant keys."""
+    L, S, W, n, keep = 4, 4, 40, 1501, 301                             # (the ring turns)
+    table = np.array([[0 if h % 3 == 0 else l - l % 2 if h % 3 == 1 else l for h in range(Hkv)] for l in range(L)], dtype=np.int32)
+    cache, k, v, sel, ws = _filled(L, 1, Hkv, d, S, W, n, keep, 51, table)
+    for layer in range(L):
+        cache.pod_cache_compact(layer, 1, sel, ws)
+    cache.pod_cache_check()
+    for layer in range(L):
+        got = cache.pod_cache_export_logical(layer, 1)
+        mine = torch.stack([sel[int(table[layer, h]), h] for h in range(Hkv)])
+        rows = mine.long().t()[:, :, None].expand(-1, -1, d) + S
+        assert torch.equal(got["distV"], torch.gather(v[layer], 0, rows)), layer
+        low = [h for h in range(Hkv) if table[layer, h] == layer]
+        if low:
+            assert torch.equal(got["distK"][:, low], torch.gather(k[layer], 0, rows)[:, low]), layer
+        assert torch.equal(got["recentK"], k[layer][n - W:]) and torch.equal(got["recentV"], v[layer][n - W:])
+        assert torch.equal(got["sinkK"], k[layer][:S])
+
+
 @pytest.mark.parametrize("d,S,W,n,chunk", [(128, 8, 48, 1000, 300), (64, 0, 32, 555, 555), (128, 5, 100, 106, 50)])
 def test_votes_from_the_cached_keys_are_the_same_bits(d, S, W, n, chunk):
     # the prompt goes in through the chunk call (sink slots, distant rows and a wrapped ring), then the votes are taken
