@@ -757,13 +757,22 @@ static int launch_prefill(const pod_layout &ly, int n, int q0, const void *q, co
     // The cache construction rides in the same launch.  Where every attention workgroup is resident at once its workgroups come
     // last, for the slots that are free from the start or as soon as the short query tiles are done; in launches of several
     // rounds a few come first and copy next to workgroups that are busy multiplying.  (A launch of its own: n = 777 5.0 us per
-    // layer, 16384 tokens 25 us, and the gap before it.)
+    // layer, 16384 tokens 25 us, and the gap before it.)  How few: one of them copies some 600 pieces per us beside such a neighbour, so that
+    // an eighth of the CUs is enough for long prompts and few kv heads, but with many kv heads the launch ends with their copying: one
+    // per 300 pieces and key tile that a CU walks, up to half of the CUs.  Both layers with cache, us, an eighth -> this (attention alone):
+    // 64/64 x 128 n = 1100 127 -> 80 (71), 1500 180 -> 123 (115), 3001 398 -> 369 (342), 40/40 x 128 2200 178 -> 155 (148), 32/32 x 128 2200 137 -> 117
+    // (116), 64/64 x 64 1500 90 -> 81 (74); 32/8 x 128 3001 191 with an eighth, 195 with three eighths.
     p.fill_lo = 0x7fffffff; p.fill_n = 0;
     if (fill) {
         const bool resident = ks == 2 || attn <= 2u * (unsigned)cus; // (two one-group workgroups per CU)
         const size_t pieces = (size_t)n * ly.Hkv * (ly.D / 8), per_wg = (size_t)256 * ks * (resident ? kFillUnroll : 1);
-        size_t wgs = (pieces + per_wg - 1) / per_wg;
-        const size_t most = resident ? cus : (cus + 7) / 8;
+        size_t wgs = (pieces + per_wg - 1) / per_wg, most = cus;
+        if (!resident) {
+            const size_t tiles = (size_t)(n + 127) / 128, walked = tiles * (tiles + 1) * ly.Hq / cus; // key tiles per CU
+            most = pieces / (300 * walked) / 8 * 8; // (as many on every XCD)
+            if (most > (size_t)cus / 2) most = cus / 2;
+            if (most < ((size_t)cus + 7) / 8) most = (cus + 7) / 8;
+        }
         if (wgs > most) wgs = most;
         p.fill = *fill;
         p.fill_n = (int)wgs;

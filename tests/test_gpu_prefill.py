@@ -104,6 +104,21 @@ def test_prefill_builds_the_same_cache_as_fill():
     c.gpu.pod_cache_check()
 
 
+@pytest.mark.parametrize("Hq,Hkv,d,n", [(64, 64, 128, 1025), (64, 64, 64, 1153), (64, 32, 64, 1100), (64, 4, 64, 1100), (32, 32, 128, 4097)])
+def test_launches_of_several_rounds_build_the_same_cache_as_fill(Hq, Hkv, d, n):
+    """Workgroups that copy in front of those that attend: as many as half of the CUs for many kv heads and few rounds (on 256 CUs), an
+    eighth for few kv heads, in between for long prompts; pieces left over in every case."""
+    c = Case(2, 2, Hq, Hkv, d, 8, 40, 2, n, seed=45)
+    for layer in range(2):
+        out = run_prefill(c, layer, n, write_cache=True, seq=1)
+        rows = np.array([0, 127, 128, n - 1])
+        assert_close(out[torch.from_numpy(rows).to(out.device)], ref_prefill(c, layer, n, rows, seq=1), f"n={n} layer {layer}")
+        c.cpu.fill(layer, 1, gen.bf16_bits(c.keys(layer, 1, n, "cpu")), gen.bf16_bits(c.values(layer, 1, n, "cpu")))
+        c.assert_cache_equal(layer, 1)
+    assert c.gpu.pod_cache_seq_len(0, 0) == 0
+    c.gpu.pod_cache_check()
+
+
 def test_prefill_then_decode_continues():
     c = Case(2, 2, 8, 2, 128, 8, 40, 1, 600, seed=44)
     n = 200
