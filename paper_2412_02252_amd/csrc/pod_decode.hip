@@ -1971,8 +1971,9 @@ int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *
         even = pod_plan_even_launch(2 * cus, B, H, ly.P, even_unit_distant(even_mode), p.hlen, p.unit_cum, &ev, &padded);
         // Where no workgroup crosses, each hands over once, at its end, and the last of a pair's merges: at head dimension 64 with few query
         // heads per kv head, whose partials are small, that costs less than the second launch.  Requests, us, second launch -> inside: 32 chats
-        // x 16/4 x 64 1294 -> 1194, 4 of 3-30K x 8/8 x 64 898 -> 846, 20 of 0.5-5K 817 -> 781; but 24 of 0.2-2.5K x 32/8 x 128 1039 -> 1036, 12 of
-        // 1.5-15K x 32/4 x 128 1585 -> 1619.
+        // x 16/4 x 64 1294 -> 1194, 4 of 3-30K x 8/8 x 64 898 -> 846, 20 of 0.5-5K 817 -> 781.  28 of 0.3-3.6K at 1, 2, 4, 8 and 16 query heads per kv
+        // head (4 x 64) 642 -> 613, 649 -> 623, 664 -> 624, 686 -> 676, 766 -> 795; 8 heads x 64 at 8 each, 4 of 3-30K (22 partials) 906 -> 911.  At head dimension
+        // 128 24 of 0.2-2.5K x 32/8 1039 -> 1036, 12 of 1.5-15K x 32/4 1585 -> 1619.
         even_merge = even && padded && c->fused_merge && ly.D == 64 && ly.rep <= 4;
         if (!step) // (an empty sequence has no workgroup that would write its rows)
             for (int b = 0; b < B; ++b) even_merge = even_merge && p.hlen[b] > 0;
