@@ -188,10 +188,13 @@ __device__ inline f32x4 add_four(u32x2 v, f32x4 acc)
 // since nothing else in these kernels uses it.  Both layers of a request, before -> after (kernels alone, us): 16384 tokens x 32/8 heads x 128 4350 -> 4130,
 // 3001 x 16/4 x 64 84.4 -> 80.0, 777 x 32/8 x 128 48.1 -> 46.9.
 typedef const __attribute__((address_space(1))) char *gbyte_ptr;
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm" // (M0 is reserved, i.e. never allocated, which is no reason not to name it here)
 __device__ __forceinline__ void load_lds16(gbyte_ptr base, unsigned off, unsigned dst)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(base) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 template <int D, bool TAB, int KS>
 __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(prefill_params p)
