@@ -241,14 +241,14 @@ __device__ inline bool gate_skips(float mp, float lp, float md, float ld, float 
 //  * LOC (the fast one): every workgroup of a (sequence, kv head) pair runs on ONE XCD - the launch is one-dimensional
 //    and workgroups go to the XCDs round-robin, so the pair is chosen from (workgroup index) mod (number of XCDs).
 //    Producer and consumer then meet in that XCD's L2: ordinary stores (the vector L1 writes through), an atomic
-//    counter executed in the L2, ordinary loads after the consumer has dropped its own L1.  A round trip is a few
+//    counter executed in the L2, loads that pass the consumer's own L1.  A round trip is a few
 //    hundred ns.  The placement is checked, not assumed: every arrival adds the id of the XCD it runs on (XCC_ID
 //    hardware register) and its square to the pair's counter word, and the merging workgroup accepts the partials
 //    only if all ids were equal (n * sum of squares == square of the sum); otherwise it zeroes the output rows and
 //    raises the sticky flag.  (Eager launches were seen to start their round-robin at XCD 0 and graph replays at XCD
 //    7: the XCD of a position differs between launches, but a launch's workgroups of one position share it.)
 //  * otherwise device-scope relaxed atomic stores (write-through: in memory when acknowledged), a device-scope atomic
-//    counter and device-scope atomic loads, all of which go through to the memory fabric: correct wherever the
+//    counter and loads, all of which go through to the memory fabric: correct wherever the
 //    workgroups run, but ~1.6 us per round trip.  (Device-scope release/acquire FENCES are not an option here: each
 //    one writes back / invalidates a whole L2, which made the launch 5x slower.)
 __device__ inline int xcc_id() { return (int)(__builtin_amdgcn_s_getreg((4 - 1) << 11 | 20) & 0xf); } // HW_REG_XCC_ID[3:0]
@@ -259,28 +259,20 @@ __device__ inline void store_part(float *p, float v)
     if constexpr (LOC) *(__attribute__((address_space(1))) float *)p = v;
     else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-template <bool LOC, int VEC>
-__device__ inline void load_part(const float *p, float (&out)[VEC])
+// A partial is read 16 bytes per lane, past this CU's vector L1 and past what this XCD's L2 may hold of another XCD's lines (sc1; nothing of
+// these loads is kept from one launch to the next).  Read through memory with device-scope atomic loads, of which 8 bytes is the widest, the merge
+// of a pair with 16 query heads and 37 pieces x 128 took one CU 8.6 us; now 5.8 (32 steps of 2 layers, 16/1 x 128, 9000 tokens 1103 -> 942 us, 2 x 30000
+// 2042 -> 1654; 32 chats x 16/4 x 64 1179 -> 1163; inside one XCD 2 pairs x 64 at 2048 tokens 423 -> 419).
+constexpr int kBufferSC1 = 16;
+__device__ inline f32x4 load_part(__amdgpu_buffer_rsrc_t rows, unsigned off)
 {
-    static_assert(LOC ? VEC == 4 : VEC == 2, "");
-    if constexpr (LOC) {
-        const f32x4 v = *(const __attribute__((address_space(1))) f32x4 *)p;
-        out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
-    } else {
-        const unsigned long long u = __hip_atomic_load((const unsigned long long *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        out[0] = __uint_as_float((unsigned)u); out[1] = __uint_as_float((unsigned)(u >> 32));
-    }
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, off, 0, kBufferSC1));
 }
-template <bool LOC>
-__device__ inline float2 load_ml(const float *p)
+__device__ inline float2 load_ml(__amdgpu_buffer_rsrc_t rows, unsigned off)
 {
-    if constexpr (LOC) {
-        typedef __attribute__((ext_vector_type(2))) float f32x2;
-        const f32x2 v = *(const __attribute__((address_space(1))) f32x2 *)p;
-        return make_float2(v.x, v.y);
-    }
-    const unsigned long long u = __hip_atomic_load((const unsigned long long *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return make_float2(__uint_as_float((unsigned)u), __uint_as_float((unsigned)(u >> 32)));
+    typedef __attribute__((ext_vector_type(2))) float f32x2;
+    const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rows, off, 0, kBufferSC1));
+    return make_float2(v.x, v.y);
 }
 
 // Arrival of a workgroup whose partial is stored: returns 0 if it is not the last of `expected` arrivals; else 1 (every
@@ -308,7 +300,6 @@ __device__ inline int arrive_last(unsigned long long *ticket, int expected)
     }
     __syncthreads();
     const int last = sm_last;
-    if (LOC && last) asm volatile("buffer_inv sc0" ::: "memory");   // this CU's vector L1: read the partials from the L2
     return last;
 }
 
@@ -317,7 +308,7 @@ __device__ inline int arrive_last(unsigned long long *ticket, int expected)
 // workgroup first evaluates the gate g = sum exp(a^P) / (sum exp(a^P) + sum exp(a^D)) of Eq. 4 for its
 // query heads from the proximal partials of MODE 3 and the lowest layer's distant sums, records
 // which heads have g >= tau, and leaves if all of its heads do.
-template <int D, bool LOC, int NW>
+template <int D, int NW>
 __device__ void merge_and_store(const decode_params &p, const decode_hot &hot, int b, int h, int nd, int np, bool special, bool valid,
                                 bool bad);
 template <int D, bool LOC, int NW, int MODE>
@@ -833,7 +824,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
                 valid = false; bad = true;
             }
         }
-        merge_and_store<D, LOC, NW>(p, hot, b, h, nd_eff, np_eff, FUSE == 2, valid, bad);
+        merge_and_store<D, NW>(p, hot, b, h, nd_eff, np_eff, FUSE == 2, valid, bad);
         trace_out();
     }
 }
@@ -876,11 +867,11 @@ __device__ inline float wave_sum(float v)
 // nd, np: distant and proximal pieces that stored a partial; special: a step's extra partial in slot hot.nc, whose
 // normaliser is negative if the step's validation failed; it is the state the head's first wave starts from.
 // Called by every thread of the workgroup.
-template <int D, bool LOC, int NW, int SPLIT>
+template <int D, int NW, int SPLIT>
 __device__ void merge_and_store_split(const decode_params &p, const decode_hot &hot, int b, int h, int nd, int np, bool special, bool valid,
                                       bool bad)
 {
-    constexpr int VEC = LOC ? 4 : 2, LPR = D / VEC, NGW = 64 / LPR, CAP = 32 / NGW, ROWS = CAP * NGW;   // ROWS = 32 per wave
+    constexpr int VEC = 4, LPR = D / VEC, NGW = 64 / LPR, CAP = 32 / NGW, ROWS = CAP * NGW;   // ROWS = 32 per wave
     constexpr unsigned ROWB = D * sizeof(float);
     __shared__ float sm_a[NW][D], sm_ml[NW][2];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, x = lane % LPR, g = lane / LPR;
@@ -893,20 +884,18 @@ __device__ void merge_and_store_split(const decode_params &p, const decode_hot &
         const int head = h * hot.rep + (active ? r : 0);
         // (wave-uniform bases and 32-bit lane offsets: the address arithmetic stands between the arrival and the first
         // load, so it is kept to two or three instructions per load)
-        const char *ml = (const char *)(hot.part_ml + ((size_t)b * hot.hq + head) * stride * 2);
-        const char *pa = (const char *)(hot.part_acc + ((size_t)b * hot.hq + head) * stride * D);
+        const auto ml = __builtin_amdgcn_make_buffer_rsrc(hot.part_ml + ((size_t)b * hot.hq + head) * stride * 2, 0, (int)stride * 8, kRawBuffer);
+        const auto pa = __builtin_amdgcn_make_buffer_rsrc(hot.part_acc + ((size_t)b * hot.hq + head) * stride * D, 0, (int)(stride * ROWB), kRawBuffer);
         float m_run = kNegBig, L = 0.f, a[VEC];
 #pragma unroll
         for (int e = 0; e < VEC; ++e) a[e] = 0.f;
         if (active) {
             float2 mark = make_float2(kNegBig, 0.f);
-            float as[VEC];
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) as[e] = 0.f;
+            f32x4 as = {0.f, 0.f, 0.f, 0.f};
             const bool mine = special && s == 0;
             if (mine) {
-                mark = load_ml<LOC>((const float *)(ml + (unsigned)hot.nc * 8u));
-                load_part<LOC, VEC>((const float *)(pa + ((unsigned)hot.nc * ROWB + VEC * 4u * x)), as);
+                mark = load_ml(ml, (unsigned)hot.nc * 8u);
+                as = load_part(pa, (unsigned)hot.nc * ROWB + VEC * 4u * x);
             }
             // this wave's i-th row of a block starting at v0 is partial v0 + i * split + s; lane group g takes its
             // rows g, g + NGW, ...
@@ -916,22 +905,20 @@ __device__ void merge_and_store_split(const decode_params &p, const decode_hot &
                 const int vl = first + lane * split;
                 const bool have = lane < ROWS && vl < nv;
                 float2 mk = make_float2(kNegBig, 0.f);
-                if (have) mk = load_ml<LOC>((const float *)(ml + (unsigned)vl * 8u));
+                if (have) mk = load_ml(ml, (unsigned)vl * 8u);
                 // rows past the end read the lane group's last valid row (or the wave's first) and get weight 0
                 const int gfirst = first + g * split;
                 int cnt = gfirst < nv ? (nv - gfirst + NGW * split - 1) / (NGW * split) : 0;
                 cnt = cnt < CAP ? cnt : CAP;
                 const unsigned off0 = (unsigned)gfirst * ROWB + VEC * 4u * x;
                 const unsigned off_last = cnt > 0 ? off0 + (unsigned)(cnt - 1) * kstride : (unsigned)first * ROWB + VEC * 4u * x;
-                float ak[CAP][VEC];
+                f32x4 ak[CAP];
 #pragma unroll
                 for (int k = 0; k < CAP; ++k) {
                     const unsigned off = off0 + (unsigned)k * kstride;
                     // (wave-uniform: whole instructions past the end are not issued)
-                    if (first + k * NGW * split < nv) load_part<LOC, VEC>((const float *)(pa + (off < off_last ? off : off_last)), ak[k]);
-                    else
-#pragma unroll
-                        for (int e = 0; e < VEC; ++e) ak[k][e] = 0.f;
+                    if (first + k * NGW * split < nv) ak[k] = load_part(pa, off < off_last ? off : off_last);
+                    else ak[k] = f32x4{0.f, 0.f, 0.f, 0.f};
                 }
                 if (v0 == 0 && mine) {     // (loaded above, so that its latency overlaps the block's)
                     if (mark.y < 0.f) { valid = false; bad = true; }
@@ -1001,12 +988,12 @@ __device__ void merge_and_store_split(const decode_params &p, const decode_hot &
     }
     if (bad && threadIdx.x == 0) atomicOr(p.flag, 2);
 }
-template <int D, bool LOC, int NW>
+template <int D, int NW>
 __device__ void merge_and_store(const decode_params &p, const decode_hot &hot, int b, int h, int nd, int np, bool special, bool valid,
                                 bool bad)
 {
-    if (hot.rep * 2 <= NW) merge_and_store_split<D, LOC, NW, 2>(p, hot, b, h, nd, np, special, valid, bad);
-    else merge_and_store_split<D, LOC, NW, 1>(p, hot, b, h, nd, np, special, valid, bad);
+    if (hot.rep * 2 <= NW) merge_and_store_split<D, NW, 2>(p, hot, b, h, nd, np, special, valid, bad);
+    else merge_and_store_split<D, NW, 1>(p, hot, b, h, nd, np, special, valid, bad);
 }
 
 __device__ inline float dot8_bf16(u32x4 a, u32x4 b)
@@ -1446,7 +1433,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_para
                     valid = false; bad = true;
                 }
             }
-            merge_and_store<D, false, NW>(p, hot, done_b, done_h, done_parts, 0, STEP, valid, bad);
+            merge_and_store<D, NW>(p, hot, done_b, done_h, done_parts, 0, STEP, valid, bad);
         }
     }
     if (p.trace && threadIdx.x == 0 && w < p.bal_nwg && w < p.trace_cap) { // measurement aid: walking workgroup, XCD and CU, clock at start and end
