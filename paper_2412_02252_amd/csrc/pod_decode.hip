@@ -855,6 +855,20 @@ __device__ inline float wave_sum(float v)
     return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
+// The value of the lane whose number differs in bit `off` (16 or 32): a swap of lane halves instead of a round trip through LDS
+// (about 60 ns).  Both registers of a swap get the same value; one of the two results holds the lane's own.  Call with all lanes active.
+__device__ inline float other_half(float v, int off)
+{
+    unsigned a = __float_as_uint(v), b = a;
+    asm volatile("" : "+v"(b)); // (given the same value twice the compiler takes the results for equal)
+    const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    unsigned lo, hi;
+    if (off == 32) { const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false); lo = r[0]; hi = r[1]; }
+    else { const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false); lo = r[0]; hi = r[1]; }
+    asm volatile("" : "+v"(lo), "+v"(hi));
+    return __uint_as_float(lane & off ? lo : hi);
+}
+
 // The merge of a (sequence, kv head) pair's partials by the last workgroup to arrive: the same merge as
 // decode_combine_kernel (the paper's gate, Eq. 4, applied to unnormalised sums).  Its time is the time of one CU's
 // loads, so as many waves as possible take part and every load of a wave is in flight before the first is used:
@@ -988,11 +1002,75 @@ __device__ void merge_and_store_split(const decode_params &p, const decode_hot &
     }
     if (bad && threadIdx.x == 0) atomicOr(p.flag, 2);
 }
+// The same for few rows, where the chain of one wave is all there is: a head has one wave, whose lane groups of LPR lanes (4 floats each)
+// take every NGW-th row; all loads go out together, none behind a branch (rows past the end fall out of the buffers' range, read as zeros and
+// get weight 0); and a lane reads the (maximum, normaliser) pairs of just its own rows (all lanes of the group the same ones) and forms their
+// weights itself, so that nothing is reduced over lanes and no weight comes from another lane until the groups meet at the end.
+// us from the counted arrival to the end, merge_and_store_split -> this: 2 pairs x 64 with 10 rows 1.40 -> 1.06; 8 x 128 with 6 rows 1.72 -> 1.36.  With more
+// rows the many small loads of one line lose: 8 x 128 with 18 rows 1.86 -> 3.3.
+constexpr int kFewRows = 16;
+template <int D, int NW>
+__device__ void merge_and_store_few(const decode_params &p, const decode_hot &hot, int b, int h, int nv, bool special, bool valid, bool bad)
+{
+    constexpr int LPR = D / 4, NGW = 64 / LPR, CAP = kFewRows / NGW;
+    constexpr unsigned ROWB = D * sizeof(float);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, x = lane % LPR, g = lane / LPR;
+    const int rows = nv + (special ? 1 : 0), stride = hot.nc + (special ? 1 : 0);
+    for (int r = wave; r < hot.rep; r += NW) {
+        const size_t head = (size_t)b * hot.hq + (size_t)h * hot.rep + r;
+        const auto ml = __builtin_amdgcn_make_buffer_rsrc(hot.part_ml + head * stride * 2, 0, stride * 8, kRawBuffer);
+        const auto pa = __builtin_amdgcn_make_buffer_rsrc(hot.part_acc + head * stride * D, 0, stride * (int)ROWB, kRawBuffer);
+        float2 mk[CAP];
+        f32x4 ak[CAP];
+#pragma unroll
+        for (int k = 0; k < CAP; ++k) {
+            const int v = g + k * NGW;
+            const unsigned slot = v < nv ? (unsigned)v : v < rows ? (unsigned)hot.nc : 0xffffu; // (past the end: out of range)
+            mk[k] = load_ml(ml, slot * 8u);
+            ak[k] = load_part(pa, slot * ROWB + 16u * x);
+            if (v >= rows) mk[k].x = kNegBig;
+        }
+        float m = mk[0].x, L = 0.f;
+        f32x4 a = {0.f, 0.f, 0.f, 0.f};
+        bool failed = false;
+#pragma unroll
+        for (int k = 1; k < CAP; ++k) m = fmaxf(m, mk[k].x);
+#pragma unroll
+        for (int k = 0; k < CAP; ++k) {
+            failed = failed || mk[k].y < 0.f;   // (the step's validation)
+            const float w = fast_exp2(mk[k].x - m);
+            L = fmaf(w, mk[k].y, L);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[e] = fmaf(w, ak[k][e], a[e]);
+        }
+#pragma unroll
+        for (int off = LPR; off < 64; off <<= 1) {
+            const float m2 = other_half(m, off), L2 = other_half(L, off);
+            const float M = fmaxf(m, m2), f1 = fast_exp2(m - M), f2 = fast_exp2(m2 - M);
+            L = f1 * L + f2 * L2;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[e] = f1 * a[e] + f2 * other_half(a[e], off);
+            m = M;
+        }
+        if (__any(failed)) { valid = false; bad = true; }
+        if (g == 0) {
+            uint2 res = make_uint2(0u, 0u);
+            if (valid) {
+                const float inv = 1.f / L;
+                res.x = pack_bf16(a[0] * inv, a[1] * inv);
+                res.y = pack_bf16(a[2] * inv, a[3] * inv);
+            }
+            ((uint2 *)(p.out + head * D))[x] = res;
+        }
+    }
+    if (bad && lane == 0) atomicOr(p.flag, 2);
+}
 template <int D, int NW>
 __device__ void merge_and_store(const decode_params &p, const decode_hot &hot, int b, int h, int nd, int np, bool special, bool valid,
                                 bool bad)
 {
-    if (hot.rep * 2 <= NW) merge_and_store_split<D, NW, 2>(p, hot, b, h, nd, np, special, valid, bad);
+    if (nd + np + (special ? 1 : 0) <= kFewRows) merge_and_store_few<D, NW>(p, hot, b, h, nd + np, special, valid, bad);
+    else if (hot.rep * 2 <= NW) merge_and_store_split<D, NW, 2>(p, hot, b, h, nd, np, special, valid, bad);
     else merge_and_store_split<D, NW, 1>(p, hot, b, h, nd, np, special, valid, bad);
 }
 

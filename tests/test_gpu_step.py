@@ -240,6 +240,27 @@ def test_merge_inside_the_launch_with_many_pieces_per_pair(d, Hq, Hkv, n, monkey
     c.gpu.pod_cache_check()
 
 
+@pytest.mark.parametrize("xcd_local", ["1", "0"])
+@pytest.mark.parametrize("d,Hq,Hkv", [(128, 8, 2), (64, 4, 1), (128, 16, 1)])
+@pytest.mark.parametrize("pieces", [13, 14, 15, 16])
+def test_merge_at_the_line_between_few_and_many_partials(pieces, d, Hq, Hkv, xcd_local, monkeypatch):
+    """Pieces of 256 tokens, one of them proximal: 13 .. 16 distant ones make 14 .. 17 partials, one more in a step, on both sides of
+    the 16 that a head's one wave takes in one go."""
+    monkeypatch.setenv("POD_DECODE_CHUNK", "256")
+    monkeypatch.setenv("POD_DECODE_XCD_LOCAL", xcd_local)
+    S, W = 16, 240
+    n = S + W + 256 * pieces - 3
+    c = Case(2, 2, Hq, Hkv, d, S, W, 1, n + 8, seed=530 + pieces)
+    for layer in range(2):
+        c.fill(layer, 0, n)
+    for layer in range(2):
+        assert_close(c.decode(layer, [n]), c.decode_ref(layer, [n]), f"decode layer {layer}")
+    for s in range(2):
+        for layer in range(2):
+            assert_close(c.step(layer, [n + s]), c.decode_ref(layer, [n + s + 1]), f"step {s} layer {layer}")
+    c.gpu.pod_cache_check()
+
+
 def test_pairs_that_do_not_divide_over_the_xcds_evenly():
     """13 sequences x 5 kv heads = 65 (sequence, kv head) pairs on 8 XCDs: the XCD-local hand-off is still used (the
     one-dimensional launch is padded to 72 pair positions, the surplus workgroups leave at once), ragged lengths,
