@@ -46,6 +46,7 @@ constexpr int kWaves = 4;          // waves per workgroup ...
 // ... but 8 where the last workgroup of a (sequence, kv head) pair merges the partials: that merge is one CU reading
 // every partial of the pair, which goes the faster the fewer and larger the pieces are and the more waves read
 // (measured, one workgroup reading 128 KB it finds in the L2: 4 waves 1.7 us, 8 waves 0.9 us).
+// (Small launches take four all the same: pod_launch_decode.)
 constexpr int fuse_waves(int fuse) { return fuse == 1 || fuse == 2 ? 8 : kWaves; }
 constexpr int kTile = 32;          // tokens per wave iteration
 constexpr float kNegBig = -1.0e30f; // stands in for -inf (keeps exp2 arguments finite)
@@ -303,6 +304,51 @@ __device__ inline int arrive_last(unsigned long long *ticket, int expected)
     return last;
 }
 
+// Reductions over the 64 lanes of a wave without LDS round trips (a cross-lane read through LDS takes about 60 ns,
+// and a reduction is a chain of six): four DPP steps inside the rows of 16 lanes, then the four rows through SGPRs.
+// Call with all lanes active.
+template <int CTRL>
+__device__ inline float dpp_move(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__device__ inline float lane_value(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
+__device__ inline float wave_max(float v)
+{
+    v = fmaxf(v, dpp_move<0xB1>(v));    // quad_perm [1, 0, 3, 2]
+    v = fmaxf(v, dpp_move<0x4E>(v));    // quad_perm [2, 3, 0, 1]
+    v = fmaxf(v, dpp_move<0x141>(v));   // row_half_mirror
+    v = fmaxf(v, dpp_move<0x140>(v));   // row_mirror
+    return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
+}
+__device__ inline float row_sum(float v) // over each row of 16 lanes
+{
+    v += dpp_move<0xB1>(v);
+    v += dpp_move<0x4E>(v);
+    v += dpp_move<0x141>(v);
+    v += dpp_move<0x140>(v);
+    return v;
+}
+__device__ inline float wave_sum(float v)
+{
+    v = row_sum(v);
+    return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+
+// The value of the lane whose number differs in bit `off` (16 or 32): a swap of lane halves instead of a round trip through LDS
+// (about 60 ns).  Both registers of a swap get the same value; one of the two results holds the lane's own.  Call with all lanes active.
+__device__ inline float other_half(float v, int off)
+{
+    unsigned a = __float_as_uint(v), b = a;
+    asm volatile("" : "+v"(b)); // (given the same value twice the compiler takes the results for equal)
+    const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    unsigned lo, hi;
+    if (off == 32) { const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false); lo = r[0]; hi = r[1]; }
+    else { const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false); lo = r[0]; hi = r[1]; }
+    asm volatile("" : "+v"(lo), "+v"(hi));
+    return __uint_as_float(lane & off ? lo : hi);
+}
+
 // MODE 3 and 4 are the two launches of a gated upper layer (appendix "Computation Optimization for Distant
 // Tokens"): MODE 3 walks the proximal chunks only; MODE 4 walks the distant chunks, and each
 // workgroup first evaluates the gate g = sum exp(a^P) / (sum exp(a^P) + sum exp(a^D)) of Eq. 4 for its
@@ -311,6 +357,12 @@ __device__ inline int arrive_last(unsigned long long *ticket, int expected)
 template <int D, int NW>
 __device__ void merge_and_store(const decode_params &p, const decode_hot &hot, int b, int h, int nd, int np, bool special, bool valid,
                                 bool bad);
+struct step_rows { u32x4 kn, vn, ko, vo; bool ok; }; // a lane's 16-byte pieces of the new and the displaced token's rows; whether the position is valid
+template <int D, bool LOC, int NW, int MODE>
+__device__ step_rows step_partial(const decode_params &p, const decode_hot &hot, int b, int h, int pos, int head_arg);
+template <int D>
+__device__ void step_update(const decode_params &p, const decode_hot &hot, int b, int h, int pos, int head_arg, const step_rows &rows);
+__device__ void step_count(const decode_params &p, const decode_hot &hot, int b, int pos, bool ok);
 template <int D, bool LOC, int NW, int MODE>
 __device__ void step_workgroup(const decode_params &p, const decode_hot &hot, int b, int h, int pos, int head_arg);
 
@@ -417,7 +469,29 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
     const bool own_host = HOST == 1 || (HOST == 2 && (hot.use_hlen & 2) != 0);
     const bool hosts_step = STEP && c == (own_host ? hot.nc : FUSE == 2 && nd_eff > 0 ? nd_eff - 1 : max_nd);
     const int expected = nd_eff + (own_host ? np_eff + 1 : FUSE == 2 && np_eff == 0 ? 1 : np_eff);
-    if (hosts_step) step_workgroup<D, LOC, NW, MODE>(p, hot, b, h, n, head_arg);
+    step_rows rows = {};
+    if (hosts_step) {
+        if constexpr (MERGE) {
+            // what the merge waits for first; a workgroup of its own changes the cache once it has arrived
+            rows = step_partial<D, LOC, NW, MODE>(p, hot, b, h, n, head_arg);
+            if (!own_host) {
+                __syncthreads(); // every wave holds the old rows it needs
+                step_update<D>(p, hot, b, h, n, head_arg, rows);
+            }
+        } else step_workgroup<D, LOC, NW, MODE>(p, hot, b, h, n, head_arg);
+    }
+    // (a step tags from the workgroup that hosts the step: the first distant piece may have no row to walk yet)
+    if (MODE == 1 && (STEP ? hosts_step : c == 0) && threadIdx.x == 0) { // tag this head's logits: which token, which block's keys
+        p.score_hdr[4 * ((size_t)b * hkv + h)] = STEP ? n + 1 : n;   // (the context the attention is over)
+        p.score_hdr[4 * ((size_t)b * hkv + h) + 1] = head_arg & 0x7fffffff;
+        p.score_hdr[4 * ((size_t)b * hkv + h) + 2] = __float_as_int(hot.scale_log2e);
+        // word 3: 1 once the heads' distant (maximum, sum) pairs are there too (decode_combine_kernel leaves them after a
+        // pod_decode_attention_reuse / _gated call; a step and the merge inside the launch do not), which is what a
+        // gated upper layer needs besides the logits
+        if (MERGE || STEP) p.score_hdr[4 * ((size_t)b * hkv + h) + 3] = 0;
+    }
+    const int NC = hot.nc + (STEP ? 1 : 0); // (a step keeps one more slot per head: step_workgroup's)
+    if (!(own_host && hosts_step)) { // (a workgroup that only takes the step has stored its partial: on to its arrival)
     const bool distant = c < max_nd;
     const int region_len = distant ? n_dist : n_prox;
     const int chunk = distant ? (hot.chunk & 0xffff) : chunk_p;
@@ -431,16 +505,6 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
     // are those of a real token, so the masked products stay finite)
     const int excl = (STEP && !distant && n >= prows) ? p.sink + (n - p.sink) % p.window : -1;
 
-    // (a step tags from the workgroup that hosts the step: the first distant piece may have no row to walk yet)
-    if (MODE == 1 && (STEP ? hosts_step : c == 0) && threadIdx.x == 0) { // tag this head's logits: which token, which block's keys
-        p.score_hdr[4 * ((size_t)b * hkv + h)] = STEP ? n + 1 : n;   // (the context the attention is over)
-        p.score_hdr[4 * ((size_t)b * hkv + h) + 1] = head_arg & 0x7fffffff;
-        p.score_hdr[4 * ((size_t)b * hkv + h) + 2] = __float_as_int(hot.scale_log2e);
-        // word 3: 1 once the heads' distant (maximum, sum) pairs are there too (decode_combine_kernel leaves them after a
-        // pod_decode_attention_reuse / _gated call; a step and the merge inside the launch do not), which is what a
-        // gated upper layer needs besides the logits
-        if (MERGE || STEP) p.score_hdr[4 * ((size_t)b * hkv + h) + 3] = 0;
-    }
     // (pointers rebuilt from the raw argument words are generic; say they are global memory)
     typedef const __attribute__((address_space(1))) u32x4 *gvec_ptr;
     const size_t pair = (size_t)b * hkv + h;
@@ -757,9 +821,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
         if (j == 0) { sm_m[wave][m16] = m_run; sm_l[wave][m16] = l_run; }
     }
     __syncthreads();
-    const int NC = hot.nc + (STEP ? 1 : 0); // (a step keeps one more slot per head: step_workgroup's)
-    const int values = own_host && hosts_step ? 0 : hot.rep * D; // (a workgroup that only took the step has stored its partial)
-    for (int t = threadIdx.x; t < values; t += blockDim.x) {
+    for (int t = threadIdx.x; t < hot.rep * D; t += blockDim.x) {
         const int head = t / D, dim = t % D;
         float M = sm_m[0][head];
 #pragma unroll
@@ -783,6 +845,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
             if (dim == 0) { ((gfloat_ptr)hot.part_ml)[slot * 2] = M; ((gfloat_ptr)hot.part_ml)[slot * 2 + 1] = Lsum; }
         }
     }
+    }
     if constexpr (!MERGE) {
         const size_t wg = ((size_t)b * hkv + h) * hot.nc + c;
         if (p.trace && threadIdx.x == 0 && wg < (size_t)p.trace_cap) {
@@ -796,6 +859,11 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
         if (p.trace) tr_t2 = wall_clock64();
         const int last = arrive_last<LOC>(p.tickets + (size_t)b * hkv + h, expected);
         const unsigned long long tr_t3 = p.trace ? wall_clock64() : 0;
+        if constexpr (STEP)
+            if (hosts_step) { // (every wave has passed the arrival's barrier: nobody needs the ring slot's old rows or the stored length any more)
+                if (own_host) step_update<D>(p, hot, b, h, n, head_arg, rows);
+                step_count(p, hot, b, n, rows.ok);
+            }
         auto trace_out = [&]() {
             const size_t wg = LOC ? (size_t)blockIdx.x : ((size_t)b * hkv + h) * (hot.nc + (own_host ? 1 : 0)) + c;
             if (p.trace && threadIdx.x == 0 && wg < (size_t)p.trace_cap) {
@@ -827,46 +895,6 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
         merge_and_store<D, NW>(p, hot, b, h, nd_eff, np_eff, FUSE == 2, valid, bad);
         trace_out();
     }
-}
-
-// Reductions over the 64 lanes of a wave without LDS round trips (a cross-lane read through LDS takes about 60 ns,
-// and a reduction is a chain of six): four DPP steps inside the rows of 16 lanes, then the four rows through SGPRs.
-// Call with all lanes active.
-template <int CTRL>
-__device__ inline float dpp_move(float v)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-__device__ inline float lane_value(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
-__device__ inline float wave_max(float v)
-{
-    v = fmaxf(v, dpp_move<0xB1>(v));    // quad_perm [1, 0, 3, 2]
-    v = fmaxf(v, dpp_move<0x4E>(v));    // quad_perm [2, 3, 0, 1]
-    v = fmaxf(v, dpp_move<0x141>(v));   // row_half_mirror
-    v = fmaxf(v, dpp_move<0x140>(v));   // row_mirror
-    return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
-}
-__device__ inline float wave_sum(float v)
-{
-    v += dpp_move<0xB1>(v);
-    v += dpp_move<0x4E>(v);
-    v += dpp_move<0x141>(v);
-    v += dpp_move<0x140>(v);
-    return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
-}
-
-// The value of the lane whose number differs in bit `off` (16 or 32): a swap of lane halves instead of a round trip through LDS
-// (about 60 ns).  Both registers of a swap get the same value; one of the two results holds the lane's own.  Call with all lanes active.
-__device__ inline float other_half(float v, int off)
-{
-    unsigned a = __float_as_uint(v), b = a;
-    asm volatile("" : "+v"(b)); // (given the same value twice the compiler takes the results for equal)
-    const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-    unsigned lo, hi;
-    if (off == 32) { const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false); lo = r[0]; hi = r[1]; }
-    else { const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false); lo = r[0]; hi = r[1]; }
-    asm volatile("" : "+v"(lo), "+v"(hi));
-    return __uint_as_float(lane & off ? lo : hi);
 }
 
 // The merge of a (sequence, kv head) pair's partials by the last workgroup to arrive: the same merge as
@@ -1002,30 +1030,34 @@ __device__ void merge_and_store_split(const decode_params &p, const decode_hot &
     }
     if (bad && threadIdx.x == 0) atomicOr(p.flag, 2);
 }
-// The same for few rows, where the chain of one wave is all there is: a head has one wave, whose lane groups of LPR lanes (4 floats each)
-// take every NGW-th row; all loads go out together, none behind a branch (rows past the end fall out of the buffers' range, read as zeros and
-// get weight 0); and a lane reads the (maximum, normaliser) pairs of just its own rows (all lanes of the group the same ones) and forms their
-// weights itself, so that nothing is reduced over lanes and no weight comes from another lane until the groups meet at the end.
-// us from the counted arrival to the end, merge_and_store_split -> this: 2 pairs x 64 with 10 rows 1.40 -> 1.06; 8 x 128 with 6 rows 1.72 -> 1.36.  With more
-// rows the many small loads of one line lose: 8 x 128 with 18 rows 1.86 -> 3.3.
-constexpr int kFewRows = 16;
-template <int D, int NW>
+// The same for few rows, where the chain of one wave is all there is: all loads go out together, none behind a branch (rows past the end fall
+// out of the buffers' range, read as zeros and get weight 0), and a lane reads the (maximum, normaliser) pairs of just its own rows (all
+// lanes of a group the same ones) and forms their weights itself, so that nothing is reduced over lanes and no weight comes from another lane.
+// BY_HEAD (up to 8 rows): a head has one lane group of LPR lanes (4 floats each), a wave several heads.  Else (up to CAP rows per group): a head
+// has one wave, whose groups take every NGW-th row and meet at the end.
+// us from the counted arrival to the end, merge_and_store_split -> the second form: 2 pairs x 64 with 10 rows 1.40 -> 1.06; 8 x 128 with 6 rows 1.72 -> 1.36; more
+// rows at D = 128 lose, by their many small loads of one line: 8 x 128 with 18 rows 1.86 -> 3.3.  The second form -> the first, per step: 8 pairs x 128 at 777 tokens
+// (5 rows) 8.5 -> 7.9 us, one pair with 16 query heads 11.0 -> 9.8.
+constexpr int kHeadRows = 8;
+template <int D, int NW, int CAP, bool BY_HEAD>
 __device__ void merge_and_store_few(const decode_params &p, const decode_hot &hot, int b, int h, int nv, bool special, bool valid, bool bad)
 {
-    constexpr int LPR = D / 4, NGW = 64 / LPR, CAP = kFewRows / NGW;
+    constexpr int LPR = D / 4, NGW = 64 / LPR, HEADS = BY_HEAD ? NGW : 1, GROUPS = BY_HEAD ? 1 : NGW; // heads per wave, groups per head
     constexpr unsigned ROWB = D * sizeof(float);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, x = lane % LPR, g = lane / LPR;
     const int rows = nv + (special ? 1 : 0), stride = hot.nc + (special ? 1 : 0);
-    for (int r = wave; r < hot.rep; r += NW) {
-        const size_t head = (size_t)b * hot.hq + (size_t)h * hot.rep + r;
-        const auto ml = __builtin_amdgcn_make_buffer_rsrc(hot.part_ml + head * stride * 2, 0, stride * 8, kRawBuffer);
-        const auto pa = __builtin_amdgcn_make_buffer_rsrc(hot.part_acc + head * stride * D, 0, stride * (int)ROWB, kRawBuffer);
+    const size_t head0 = (size_t)b * hot.hq + (size_t)h * hot.rep;
+    const auto ml = __builtin_amdgcn_make_buffer_rsrc(hot.part_ml + head0 * stride * 2, 0, hot.rep * stride * 8, kRawBuffer);
+    const auto pa = __builtin_amdgcn_make_buffer_rsrc(hot.part_acc + head0 * stride * D, 0, hot.rep * stride * (int)ROWB, kRawBuffer);
+    for (int r0 = wave * HEADS; r0 < hot.rep; r0 += NW * HEADS) {
+        const int r = r0 + (BY_HEAD ? g : 0);
+        const unsigned row0 = (unsigned)((r < hot.rep ? r : hot.rep - 1) * stride);
         float2 mk[CAP];
         f32x4 ak[CAP];
 #pragma unroll
         for (int k = 0; k < CAP; ++k) {
-            const int v = g + k * NGW;
-            const unsigned slot = v < nv ? (unsigned)v : v < rows ? (unsigned)hot.nc : 0xffffu; // (past the end: out of range)
+            const int v = (BY_HEAD ? 0 : g) + k * GROUPS;
+            const unsigned slot = v < nv ? row0 + v : v < rows ? row0 + hot.nc : 0x200000u; // (past the end: out of range)
             mk[k] = load_ml(ml, slot * 8u);
             ak[k] = load_part(pa, slot * ROWB + 16u * x);
             if (v >= rows) mk[k].x = kNegBig;
@@ -1043,24 +1075,25 @@ __device__ void merge_and_store_few(const decode_params &p, const decode_hot &ho
 #pragma unroll
             for (int e = 0; e < 4; ++e) a[e] = fmaf(w, ak[k][e], a[e]);
         }
+        if constexpr (!BY_HEAD)
 #pragma unroll
-        for (int off = LPR; off < 64; off <<= 1) {
-            const float m2 = other_half(m, off), L2 = other_half(L, off);
-            const float M = fmaxf(m, m2), f1 = fast_exp2(m - M), f2 = fast_exp2(m2 - M);
-            L = f1 * L + f2 * L2;
+            for (int off = LPR; off < 64; off <<= 1) {
+                const float m2 = other_half(m, off), L2 = other_half(L, off);
+                const float M = fmaxf(m, m2), f1 = fast_exp2(m - M), f2 = fast_exp2(m2 - M);
+                L = f1 * L + f2 * L2;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) a[e] = f1 * a[e] + f2 * other_half(a[e], off);
-            m = M;
-        }
+                for (int e = 0; e < 4; ++e) a[e] = f1 * a[e] + f2 * other_half(a[e], off);
+                m = M;
+            }
         if (__any(failed)) { valid = false; bad = true; }
-        if (g == 0) {
+        if (BY_HEAD ? r < hot.rep : g == 0) {
             uint2 res = make_uint2(0u, 0u);
             if (valid) {
                 const float inv = 1.f / L;
                 res.x = pack_bf16(a[0] * inv, a[1] * inv);
                 res.y = pack_bf16(a[2] * inv, a[3] * inv);
             }
-            ((uint2 *)(p.out + head * D))[x] = res;
+            ((uint2 *)(p.out + (head0 + r) * D))[x] = res;
         }
     }
     if (bad && lane == 0) atomicOr(p.flag, 2);
@@ -1069,7 +1102,10 @@ template <int D, int NW>
 __device__ void merge_and_store(const decode_params &p, const decode_hot &hot, int b, int h, int nd, int np, bool special, bool valid,
                                 bool bad)
 {
-    if (nd + np + (special ? 1 : 0) <= kFewRows) merge_and_store_few<D, NW>(p, hot, b, h, nd + np, special, valid, bad);
+    const int rows = nd + np + (special ? 1 : 0);
+    if (rows <= kHeadRows) merge_and_store_few<D, NW, kHeadRows, true>(p, hot, b, h, nd + np, special, valid, bad);
+    else if (rows <= 16) merge_and_store_few<D, NW, D / 16, false>(p, hot, b, h, nd + np, special, valid, bad);
+    else if (D == 64 && rows <= 32) merge_and_store_few<D, NW, 8, false>(p, hot, b, h, nd + np, special, valid, bad);
     else if (hot.rep * 2 <= NW) merge_and_store_split<D, NW, 2>(p, hot, b, h, nd, np, special, valid, bad);
     else merge_and_store_split<D, NW, 1>(p, hot, b, h, nd, np, special, valid, bad);
 }
@@ -1095,16 +1131,17 @@ __device__ inline float dot8_bf16(u32x4 a, u32x4 b)
 // stores, exactly as the append kernel does.  Nobody else in the launch reads or writes those rows' results: the other
 // workgroups walk the rows held before the call and leave the ring slot out.  (4) The last of a sequence's kv heads
 // to finish advances the stored length; (5) the partial (in the slot behind the pieces' slots) takes part in the merge
-// like any other.
+// like any other.  Where the launch merges inside, only (1) and (2) stand in front of the workgroup's arrival, and (4) behind it; one that
+// walks no piece also leaves (3) for then (32 steps of 2 layers, us: 16/1 x 128 at 9000 tokens 871 -> 855, 2 x 30000 1631 -> 1593, 32/8 x 128 at 777
+// 497 -> 490; kept for after the merge, (4) costs the launches' registers 1-2 %).
 // With score reuse (MODE 1: this layer is the lowest of the block; MODE 2: an upper layer) the displaced token's
 // distant logit is computed once, by the lowest layer, which stores it at that token's place in the score tiles (the
 // workgroups that walk the rows held before the call leave that place alone); the block's upper layers read it there.
 template <int D, bool LOC, int NW, int MODE>
-__device__ void step_workgroup(const decode_params &p, const decode_hot &hot, int b, int h, int pos, int head_arg)
+__device__ step_rows step_partial(const decode_params &p, const decode_hot &hot, int b, int h, int pos, int head_arg)
 {
     constexpr int CPR = D / 8;
     typedef const __attribute__((address_space(1))) u32x4 *gvec_ptr;
-    typedef __attribute__((address_space(1))) u32x4 *gvec_w;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int prows = hot.prows;
     const int v_pos = p.positions[b], v_dev = hot.lens_layer[b], v_low = hot.lens_lowest[b];
@@ -1115,9 +1152,8 @@ __device__ void step_workgroup(const decode_params &p, const decode_hot &hot, in
     const size_t pair = (size_t)b * hot.hkv + h;
     const bool low_head = head_arg < 0;
     const size_t t = demote ? (size_t)(pos - prows) : 0;   // distant row of position pos - W
-    const gvec_w proxK = (gvec_w)(hot.kprox + (pair * prows + slot) * CPR), proxV = (gvec_w)(hot.vprox + (pair * prows + slot) * CPR);
-    const gvec_w dV = (gvec_w)(hot.vdist + (pair * hot.cd + t) * CPR);
-    const gvec_w dK = (gvec_w)(hot.kdist + (((size_t)(head_arg & 0x7fffffff) + b) * hot.cd + t) * CPR);
+    const gvec_ptr proxK = (gvec_ptr)(hot.kprox + (pair * prows + slot) * CPR), proxV = (gvec_ptr)(hot.vprox + (pair * prows + slot) * CPR);
+    const gvec_ptr dK = (gvec_ptr)(hot.kdist + (((size_t)(head_arg & 0x7fffffff) + b) * hot.cd + t) * CPR);
     const int i = lane < CPR ? lane : 0;        // this lane's 16-byte piece of a row
     const u32x4 kn = ((gvec_ptr)p.k_new)[pair * CPR + i], vn = ((gvec_ptr)p.v_new)[pair * CPR + i];
     u32x4 ko = {0u, 0u, 0u, 0u}, vo = ko, kd = ko;
@@ -1132,8 +1168,8 @@ __device__ void step_workgroup(const decode_params &p, const decode_hot &hot, in
         const size_t head = (size_t)b * hot.hq + (size_t)h * hot.rep + r;
         const u32x4 qn = ((gvec_ptr)(hot.q + head * D))[i], qd = ((gvec_ptr)(qd_src + head * D))[i];
         float sn = lane < CPR ? dot8_bf16(qn, kn) : 0.f, sd = (MODE != 2 && lane < CPR && demote) ? dot8_bf16(qd, kd) : 0.f;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) { sn += __shfl_xor(sn, off); sd += __shfl_xor(sd, off); }
+        sn = row_sum(sn); // (a row of the cache is at most 16 lanes wide)
+        sd = row_sum(sd);
         sn *= hot.scale_log2e;
         sd = demote ? sd * hot.scale_log2e : kNegBig;
         if constexpr (MODE == 1 || MODE == 2) {
@@ -1161,26 +1197,46 @@ __device__ void step_workgroup(const decode_params &p, const decode_hot &hot, in
             store_part<LOC>(hot.part_ml + ps * 2 + 1, ok ? pn + pd : -1.f);
         }
     }
-    __syncthreads(); // every wave holds the old rows it needs
-    if (ok && wave == 0 && lane < CPR) {
-        if (demote) {
-            dV[lane] = vo;
-            if (low_head) dK[lane] = ko;
-        }
-        proxK[lane] = kn;
-        proxV[lane] = vn;
+    return {kn, vn, ko, vo, ok};
+}
+// (3) of the above, once every wave holds the old rows it needs
+template <int D>
+__device__ void step_update(const decode_params &p, const decode_hot &hot, int b, int h, int pos, int head_arg, const step_rows &rows)
+{
+    constexpr int CPR = D / 8;
+    typedef __attribute__((address_space(1))) u32x4 *gvec_w;
+    const int lane = threadIdx.x;
+    if (!rows.ok || lane >= CPR) return;
+    const int prows = hot.prows, slot = pos < p.sink ? pos : p.sink + (pos - p.sink) % p.window;
+    const size_t pair = (size_t)b * hot.hkv + h;
+    if (pos >= prows) {
+        const size_t t = (size_t)(pos - prows);
+        ((gvec_w)(hot.vdist + (pair * hot.cd + t) * CPR))[lane] = rows.vo;
+        if (head_arg < 0) ((gvec_w)(hot.kdist + (((size_t)(head_arg & 0x7fffffff) + b) * hot.cd + t) * CPR))[lane] = rows.ko;
     }
-    // every kv head's workgroup has compared the position with the stored length before the length moves
-    // (a sequence's kv heads run on different XCDs; nothing but the count travels through this counter, and nobody
-    // waits for it; by this barrier every wave has used the stored length it loaded)
+    ((gvec_w)(hot.kprox + (pair * prows + slot) * CPR))[lane] = rows.kn;
+    ((gvec_w)(hot.vprox + (pair * prows + slot) * CPR))[lane] = rows.vn;
+}
+// (4): every kv head's workgroup has compared the position with the stored length before the length moves
+// (a sequence's kv heads run on different XCDs; nothing but the count travels through this counter, and nobody
+// waits for it).  After a barrier by which every wave has used the stored length it loaded.
+__device__ void step_count(const decode_params &p, const decode_hot &hot, int b, int pos, bool ok)
+{
+    if (threadIdx.x != 0) return;
+    const int old = __hip_atomic_fetch_add(p.step_done + b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (old == hot.hkv - 1) {
+        __hip_atomic_store(p.step_done + b, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (ok) p.lens_w[b] = pos + 1;
+    }
+}
+template <int D, bool LOC, int NW, int MODE>
+__device__ void step_workgroup(const decode_params &p, const decode_hot &hot, int b, int h, int pos, int head_arg)
+{
+    const step_rows rows = step_partial<D, LOC, NW, MODE>(p, hot, b, h, pos, head_arg);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const int old = __hip_atomic_fetch_add(p.step_done + b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (old == hot.hkv - 1) {
-            __hip_atomic_store(p.step_done + b, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (ok) p.lens_w[b] = pos + 1;
-        }
-    }
+    step_update<D>(p, hot, b, h, pos, head_arg, rows);
+    __syncthreads();
+    step_count(p, hot, b, pos, rows.ok);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2016,8 +2072,23 @@ int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *
     // the reading launch (the others); a layer with heads of both kinds takes both.  (No gated form.)
     const bool reuse_step = step && scores;
     if (reuse_step && tau >= 0.f) return pod_fail(POD_ERR_INVALID_ARG, "a decode step has no gated form");
-    const pod_decode_plan_t pl = pod_plan_decode(cus, B, ly.Hkv, ly.P, max_len, c->tune_chunk, c->tune_chunk_prox, scores && !reuse_step,
+    pod_decode_plan_t pl = pod_plan_decode(cus, B, ly.Hkv, ly.P, max_len, c->tune_chunk, c->tune_chunk_prox, scores && !reuse_step,
                                                  scores && !lowest_all && tau >= 0.f, c->fused_merge != 0, reuse_step && !lowest_any);
+    // Small launches that merge inside one XCD's L2: workgroups of four waves instead of eight where all of them still get a CU.  A launch of one
+    // tile per wave is then spread over twice the CUs, and ends sooner by the half of what each of them has to load and to bring together.
+    // At head dimension 128 as long as a pair has no more than the 8 rows that a head's one lane group merges; at 64, where that costs
+    // less, also where eight waves leave more than these 8, and with up to two query heads per kv head.  Per step, us, eight -> four waves: 32/8 x 128
+    // at 300 tokens 7.8 -> 6.6, 777 7.9 -> 6.9; 32/4 8.4 -> 7.4, but at 1100 (10 rows) 8.4 -> 8.8; 16/1 9.8 -> 8.9, 10.1 -> 10.6; 16/4 x 64 777 6.9 -> 6.2, 1500 (13 rows instead
+    // of 7) 6.8 -> 7.2, 3600 8.0 -> 7.6; 4/2 x 64 2048 7.3 -> 6.5, 3600 7.3 -> 6.8.
+    bool four = false;
+    const long xcd_cus = c->nxcd >= 1 ? cus / c->nxcd : 0, xcd_pairs = c->nxcd >= 1 ? (npairs + c->nxcd - 1) / c->nxcd : 0;
+    if (pl.merge_inside && c->xcd_local && c->nxcd >= 1 && c->tune_chunk <= 0 && c->tune_chunk_prox <= 0) {
+        const pod_decode_plan_t small = pod_plan_decode(cus, B, ly.Hkv, ly.P, max_len, 0, 0, false, false, false, reuse_step && !lowest_any);
+        const int rows = small.nc + 1;
+        four = xcd_pairs * rows <= xcd_cus &&
+               (rows <= kHeadRows || (ly.D == 64 && rows <= 32 && (ly.rep <= 2 || pl.nc + 1 > kHeadRows)));
+        if (four) { pl = small; pl.merge_inside = true; }
+    }
     const bool merge_inside = pl.merge_inside;
     p.hot.chunk = (int)((unsigned)pl.chunk | ((unsigned)pl.chunk_p << 16));
     p.hot.max_nd = pl.max_nd;
@@ -2064,7 +2135,6 @@ int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *
     // they are so few and short that each XCD's pieces have a CU each: the launch is then its latency, and one L2 hands a
     // partial over sooner than memory does (per step: 2 pairs x 64 at 2048 tokens 7.05 -> 6.61 us, 3 pairs x 128 with 8 query
     // heads 10.4 -> 9.1, 1 pair x 128 with 16 13.8 -> 11.2; at the line, 31 pieces of 256 tokens x 128 on one XCD, 18.1 either way).
-    const long xcd_cus = c->nxcd >= 1 ? cus / c->nxcd : 0, xcd_pairs = c->nxcd >= 1 ? (npairs + c->nxcd - 1) / c->nxcd : 0;
     const bool loc = merge_inside && c->xcd_local && c->nxcd >= 1 &&
                      (npairs % c->nxcd == 0 || npairs >= 8 * c->nxcd || xcd_pairs * p.hot.nc <= xcd_cus);
     // The step's own workgroup: the new token's chain of short dependent accesses then runs beside the pieces instead of in front
@@ -2095,6 +2165,7 @@ int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *
     // (Plain steps with and without a workgroup of their own: one kernel that is told, since as a constant the walk through memory
     // came out 10 % longer.  Score reuse: two kernels, since as a flag the reader's registers cost every launch of it 2-4 %.)
 #define POD_LAUNCH_HOST(DD, MM, HOST)                                                        \
+    if (four) hipLaunchKernelGGL((decode_partial_kernel<DD, MM, 2, true, (MM == 0 ? 2 : 1), 4>), grid, dim3(256), 0, st, p); else \
     if (loc) hipLaunchKernelGGL((decode_partial_kernel<DD, MM, 2, true, HOST>), grid, dim3(fuse_waves(2) * 64), 0, st, p); \
     else hipLaunchKernelGGL((decode_partial_kernel<DD, MM, 2, false, HOST>), grid, dim3(fuse_waves(2) * 64), 0, st, p);
 #define POD_LAUNCH_STEP(DD, MM)                                                              \
@@ -2114,6 +2185,7 @@ int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *
         }                                                                                    \
     }                                                                                        \
     else if (fuse == 2) POD_LAUNCH_STEP(DD, 0)                                               \
+    else if (fuse == 1 && four) hipLaunchKernelGGL((decode_partial_kernel<DD, 0, 1, true, 0, 4>), grid, dim3(256), 0, st, p); \
     else if (fuse == 1 && loc) hipLaunchKernelGGL((decode_partial_kernel<DD, 0, 1, true>), grid, dim3(fuse_waves(1) * 64), 0, st, p); \
     else if (fuse == 3) hipLaunchKernelGGL((decode_partial_kernel<DD, 0, 3>), grid, dim3(kWaves * 64), 0, st, p);               \
     else if (fuse == 1) hipLaunchKernelGGL((decode_partial_kernel<DD, 0, 1>), grid, dim3(fuse_waves(1) * 64), 0, st, p);    \

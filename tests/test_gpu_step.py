@@ -261,6 +261,26 @@ def test_merge_at_the_line_between_few_and_many_partials(pieces, d, Hq, Hkv, xcd
     c.gpu.pod_cache_check()
 
 
+@pytest.mark.parametrize("d,Hq,Hkv", [(128, 8, 2), (128, 32, 8), (128, 16, 1), (64, 2, 1), (64, 16, 4), (64, 16, 2)])
+@pytest.mark.parametrize("n", [1, 100, 128 * 7 - 2, 128 * 8 - 2, 128 * 15 - 2, 128 * 31 - 2])
+def test_small_launches_of_four_waves(n, d, Hq, Hkv):
+    """Short contexts in pieces of 128 tokens, one tile per wave, up to the numbers of partials (8, 16 and 32, one of them the step's) at
+    which the merge takes another form or the launch eight waves: plain decode, steps and score-reuse steps on both sides of each."""
+    c = Case(2, 2, Hq, Hkv, d, 16, 112, 1, n + 16, seed=560 + Hq)
+    for layer in range(2):
+        c.fill(layer, 0, n)
+    scores = c.gpu.new_score_buffer()
+    for layer in range(2):
+        assert_close(c.decode(layer, [n]), c.decode_ref(layer, [n]), f"decode layer {layer}")
+    for s in range(6):
+        for layer in range(2):
+            out = c.step(layer, [n + s]) if s < 3 else c.step_reuse(layer, [n + s], scores)
+            assert_close(out, c.decode_ref(layer, [n + s + 1]), f"step {s} layer {layer}")
+    for layer in range(2):
+        c.assert_cache_equal(layer, 0)
+    c.gpu.pod_cache_check()
+
+
 def test_pairs_that_do_not_divide_over_the_xcds_evenly():
     """13 sequences x 5 kv heads = 65 (sequence, kv head) pairs on 8 XCDs: the XCD-local hand-off is still used (the
     one-dimensional launch is padded to 72 pair positions, the surplus workgroups leave at once), ragged lengths,
