@@ -1105,7 +1105,7 @@ __device__ void merge_and_store(const decode_params &p, const decode_hot &hot, i
     const int rows = nd + np + (special ? 1 : 0);
     if (rows <= kHeadRows) merge_and_store_few<D, NW, kHeadRows, true>(p, hot, b, h, nd + np, special, valid, bad);
     else if (rows <= 16) merge_and_store_few<D, NW, D / 16, false>(p, hot, b, h, nd + np, special, valid, bad);
-    else if (D == 64 && rows <= 32) merge_and_store_few<D, NW, 8, false>(p, hot, b, h, nd + np, special, valid, bad);
+    else if (D == 64 && NW == 4 && rows <= 32) merge_and_store_few<D, NW, 8, false>(p, hot, b, h, nd + np, special, valid, bad);
     else if (hot.rep * 2 <= NW) merge_and_store_split<D, NW, 2>(p, hot, b, h, nd, np, special, valid, bad);
     else merge_and_store_split<D, NW, 1>(p, hot, b, h, nd, np, special, valid, bad);
 }
@@ -1268,7 +1268,7 @@ template <int D, bool STEP, int MODE, bool MERGE = false>
 __global__ __launch_bounds__(kWaves * 64, 2) void decode_even_kernel(decode_params p)
 {
     static_assert(MODE == 0 || (MODE == 2 && STEP), "plain launches, and score-reuse decode steps of upper layers");
-    static_assert(!MERGE || (MODE == 0 && D == 64), "the merge inside is for plain launches at head dimension 64");
+    static_assert(!MERGE || MODE == 0, "the merge inside is for plain launches");
     constexpr int NW = kWaves;
     constexpr int CPR = D / 8, RPI = 64 / CPR, NLD = kTile / RPI, KST = D / 32, NPV = D / 16;
     typedef typename v_piece<D>::type vpiece;
@@ -2089,37 +2089,64 @@ int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *
                (rows <= kHeadRows || (ly.D == 64 && rows <= 32 && (ly.rep <= 2 || pl.nc + 1 > kHeadRows)));
         if (four) { pl = small; pl.merge_inside = true; }
     }
+    // The even split (decode_even_kernel) for plain launches whose lengths the host knows: one round of two workgroups per CU, every workgroup
+    // the same number of kUnit-token units.  It takes launches of several rounds, and of those that would merge fixed pieces inside ...
+    const int even_mode = reuse_step ? 2 : 0;
+    pod_even_plan_t ev;
+    bool padded = false;
+    const bool can_even = p.hot.use_hlen && c->even_split && (p.mode == 0 || (reuse_step && !lowest_any)) && !four &&
+                          pod_plan_even_launch(2 * cus, B, H, ly.P, even_unit_distant(even_mode), p.hlen, p.unit_cum, &ev, &padded);
+    const int even_rows = can_even ? ev.most + (step ? 1 : 0) : 0;
+    // (a batch of one very long and many short sequences cuts the long one into more parts than fixed pieces
+    // would: where the caller's scratch does not hold them the launch keeps to fixed pieces)
+    const bool even_fits = can_even && (size_t)B * ly.Hq * (size_t)even_rows * (ly.D + 2) * sizeof(float) <= ws_bytes;
+    if (pl.merge_inside && even_fits && p.mode == 0 && c->fused_merge && c->tune_chunk <= 0 && c->tune_chunk_prox <= 0) {
+        long sum = 0;
+        for (int b = 0; b < B; ++b) sum += p.hlen[b];
+        const long slots = (long)npairs * pl.nc;
+        const bool one_tile = pl.chunk <= kTile * pl.waves;
+        const bool host_fits = c->xcd_local && c->nxcd >= 1 && (npairs % c->nxcd == 0 || npairs >= 8 * c->nxcd || xcd_pairs * pl.nc <= xcd_cus)
+                                   ? xcd_pairs * (pl.nc + 1) <= xcd_cus : slots + npairs <= cus;
+        // ... those with more slots than CUs, whose second round costs as much as the first (per step, us, fixed -> even: 35 of 882 tokens x 16/4 x 64, 280 slots,
+        // 20.1 -> 14.3; 18 of 0.1-0.6K x 32/8 x 128 20.5 -> 13.9; at 272 slots of 68 pairs x 128 it is 16.6 -> 17.6) ...
+        const bool cheap = step || ly.rep <= 4; // (attention without a step, whose merge is then a launch: 13 of 0.2-2.2K x 32/4 13.1 -> 14.3, 5 of 0.7-6.5K 13.5 -> 14.6)
+        bool take = slots > cus && cheap;
+        // ... more than 16 partials per pair with more query heads than the merging workgroup has waves, where so few workgroups merge them through
+        // memory (16/1 x 128: 2 of 14-27K 20.3 -> 16.3, 4 of 4-40K 21.4 -> 19.0, but 5 of 7K 14.3 -> 14.9, 7 of 2-4K 12.7 -> 13.3, 10 of 1-11K 16.4 -> 18.8);
+        take = take || (ly.rep > 8 && pl.nc + (step ? 1 : 0) > 16 && 2 * npairs <= p.nxcd);
+        // ... lengths so different that an even share is shorter by more tokens than the even split's hand-over costs: 256 at head dimension 64, at 128 384 where
+        // it merges inside and 640 where not (saved tokens: 5 of 3.6-36K x 16/4 x 64 544: 30.3 -> 19.7; 7 of 0.5-5K x 32/8 x 128 467: 24.2 -> 21.0; 3 of 3-30K x 32/4 692: 28.8 -> 23.4, 17 of
+        // 0.3-3.4K 376: 21.6 -> 22.2, 6 of 0.6-6K 359: 13.1 -> 15.7);
+        const long saved = pl.chunk - sum * H / cus;
+        take = take || (!one_tile && cheap && saved > (ly.D == 64 ? 256 : ly.rep <= 4 ? 384 : 640));
+        // ... and at head dimension 64, where its tile loop is the faster one and its hand-over cheap, long pieces (4 of 19K x 16/4 19.2 -> 16.7, 3 of 49K 35.2 -> 28.8,
+        // but 2 of 59K, 64 partials per pair, 22.7 -> 24.6; without a step 10 of 13K 32.7 -> 25.6, but 9 of 4-7.6K, pieces of 1088, 13.6 -> 14.8, and 32 of 1-2K x 8/8 in one
+        // piece each 21.0 -> 23.8), and steps without room for a workgroup of their own where it leaves few partials per pair
+        // (11 of 0.6-1.2K 9.6 -> 8.6; but 2 of 18K, 47 partials, 11.9 -> 13.5).
+        take = take || (ly.D == 64 && ((pl.nc > 1 && pl.chunk > (step ? 1024 : 1536) && even_rows <= 48) || (step && !host_fits && even_rows <= 16)));
+        if (take) pl = pod_plan_decode(cus, B, ly.Hkv, ly.P, max_len, 0, 0, false, false, false);
+    }
     const bool merge_inside = pl.merge_inside;
     p.hot.chunk = (int)((unsigned)pl.chunk | ((unsigned)pl.chunk_p << 16));
     p.hot.max_nd = pl.max_nd;
     p.hot.nc = pl.nc;
-    // The even split (decode_even_kernel) for plain launches of several rounds whose lengths the host knows: one round
-    // of two workgroups per CU, every workgroup the same number of kUnit-token units.
     p.bal_q = 0; p.bal_nwg = 0; p.bal_total = 0;
     // (score reuse: the decode step of a layer none of whose kv heads starts a block.  A layer that writes the logits
     // gains nothing from it: 16 sequences 218 us either way, 4 x 128K tokens 399 against 387 us.)
-    const int even_mode = reuse_step ? 2 : 0;
     bool even_merge = false;
-    bool even = !merge_inside && p.hot.use_hlen && c->even_split && (p.mode == 0 || (reuse_step && !lowest_any));
+    const bool even = !merge_inside && even_fits;
     if (even) {
-        pod_even_plan_t ev;
-        bool padded = false;
-        even = pod_plan_even_launch(2 * cus, B, H, ly.P, even_unit_distant(even_mode), p.hlen, p.unit_cum, &ev, &padded);
-        // Where no workgroup crosses, each hands over once, at its end, and the last of a pair's merges: at head dimension 64 with few query
-        // heads per kv head, whose partials are small, that costs less than the second launch.  Requests, us, second launch -> inside: 32 chats
-        // x 16/4 x 64 1294 -> 1194, 4 of 3-30K x 8/8 x 64 898 -> 846, 20 of 0.5-5K 817 -> 781.  28 of 0.3-3.6K at 1, 2, 4, 8 and 16 query heads per kv
-        // head (4 x 64) 642 -> 613, 649 -> 623, 664 -> 624, 686 -> 676, 766 -> 795; 8 heads x 64 at 8 each, 4 of 3-30K (22 partials) 906 -> 911.  At head dimension
-        // 128 24 of 0.2-2.5K x 32/8 1039 -> 1036, 12 of 1.5-15K x 32/4 1585 -> 1619.
-        even_merge = even && padded && c->fused_merge && ly.D == 64 && ly.rep <= 4;
+        // Where no workgroup crosses, each hands over once, at its end, and the last of a pair's merges: up to 4 query heads per kv head, and 8
+        // with no more than 16 partials, that costs less than the second launch.  Requests, us, second launch -> inside: 32 chats
+        // x 16/4 x 64 1294 -> 1194, 4 of 3-30K x 8/8 x 64 898 -> 846, 28 of 0.3-3.6K at 1, 2, 4, 8 and 16 query heads per kv
+        // head (4 x 64) 642 -> 613, 649 -> 623, 664 -> 624, 686 -> 676, 766 -> 795; 8 heads x 64 at 8 each, 4 of 3-30K (22 partials) 906 -> 911.  Per step at head
+        // dimension 128: 4 of 0.5-5K x 32/8 17.0 -> 15.7, 8 of 5-10K 49.5 -> 47.9; x 32/4 18 of 0.1-0.9K 14.2 -> 12.5, but 1 of 8K (36 partials) 13.3 -> 18.7; x 16/1
+        // 19 of 6-12K 24.0 -> 26.3.
+        even_merge = padded && c->fused_merge && even_mode == 0 && (ly.rep <= 4 || (ly.rep <= 8 && even_rows <= 16));
         if (!step) // (an empty sequence has no workgroup that would write its rows)
             for (int b = 0; b < B; ++b) even_merge = even_merge && p.hlen[b] > 0;
-        // (a batch of one very long and many short sequences cuts the long one into more parts than fixed pieces
-        // would: where the caller's scratch does not hold them the launch keeps to fixed pieces)
-        if (even && (size_t)B * ly.Hq * ((size_t)ev.most + (step ? 1 : 0)) * (ly.D + 2) * sizeof(float) > ws_bytes) even = false;
-        if (even) {
-            p.bal_q = ev.q; p.bal_total = ev.total; p.bal_nwg = ev.nwg;
-            p.hot.nc = ev.most; p.hot.max_nd = ev.most;
-        }
+        p.bal_q = ev.q; p.bal_total = ev.total; p.bal_nwg = ev.nwg;
+        p.hot.nc = ev.most; p.hot.max_nd = ev.most;
     }
     const size_t NC = (size_t)p.hot.nc + (step ? 1 : 0); // partial slots per query head (a step keeps one more)
     const size_t acc_bytes = (size_t)B * ly.Hq * NC * ly.D * sizeof(float);
@@ -2202,8 +2229,8 @@ int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *
         const dim3 egrid((unsigned)p.bal_nwg + (step ? (unsigned)npairs : 0u));
 #define POD_LAUNCH_EVEN(DD)                                                                                                   \
         if (even_mode == 2) hipLaunchKernelGGL((decode_even_kernel<DD, true, 2>), egrid, dim3(kWaves * 64), 0, st, p);    \
-        else if (even_merge && step) hipLaunchKernelGGL((decode_even_kernel<64, true, 0, true>), egrid, dim3(kWaves * 64), 0, st, p);  \
-        else if (even_merge) hipLaunchKernelGGL((decode_even_kernel<64, false, 0, true>), egrid, dim3(kWaves * 64), 0, st, p); \
+        else if (even_merge && step) hipLaunchKernelGGL((decode_even_kernel<DD, true, 0, true>), egrid, dim3(kWaves * 64), 0, st, p);  \
+        else if (even_merge) hipLaunchKernelGGL((decode_even_kernel<DD, false, 0, true>), egrid, dim3(kWaves * 64), 0, st, p); \
         else if (step) hipLaunchKernelGGL((decode_even_kernel<DD, true, 0>), egrid, dim3(kWaves * 64), 0, st, p);              \
         else hipLaunchKernelGGL((decode_even_kernel<DD, false, 0>), egrid, dim3(kWaves * 64), 0, st, p);
         if (ly.D == 128) { POD_LAUNCH_EVEN(128) } else { POD_LAUNCH_EVEN(64) }

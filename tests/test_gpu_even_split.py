@@ -306,3 +306,34 @@ def test_walk_direction_does_not_change_the_result(rounds, monkeypatch):
         c.gpu.pod_cache_check()
     for a, b in zip(outs["1"], outs["0"]):
         assert (a - b).abs().max() <= 2.0 ** -7 * b.abs().max()
+
+
+@pytest.mark.parametrize("d,Hq,Hkv,B,lo,hi", [(128, 32, 8, 18, 59, 592),     # more slots than CUs: even, merged inside
+                                              (128, 32, 4, 18, 93, 938),     # the same with 8 query heads per kv head, few partials
+                                              (128, 32, 4, 3, 900, 9000),    # ... with many: the merge is a launch of its own
+                                              (128, 4, 4, 40, 300, 900),     # one query head per kv head
+                                              (128, 16, 1, 2, 9000, 12000),  # 16 query heads and more than 16 partials of few pairs
+                                              (64, 16, 4, 5, 700, 7000),     # lengths that fill half of the slots
+                                              (64, 8, 8, 11, 200, 900)])     # no room for the steps' own workgroups
+def test_launches_that_leave_the_fixed_pieces(d, Hq, Hkv, B, lo, hi):
+    """Ragged batches and shapes on the side of each rule where the even split takes over from fixed pieces merged inside one round:
+    plain decode (one empty sequence among them at the end) and steps against the oracle."""
+    S, W = 16, 240
+    lens = [lo + (i * 7919) % (hi - lo + 1) for i in range(B)]
+    lens[-1] = hi
+    c = Case(2, 2, Hq, Hkv, d, S, W, B, hi + 8, seed=590 + B)
+    for layer in range(2):
+        for b, n in enumerate(lens):
+            c.fill(layer, b, n)
+    for layer in range(2):
+        assert_close(c.decode(layer, lens), c.decode_ref(layer, lens), f"decode layer {layer}")
+    for s in range(2):
+        pos = [n + s for n in lens]
+        for layer in range(2):
+            assert_close(c.step(layer, pos), c.decode_ref(layer, [p + 1 for p in pos]), f"step {s} layer {layer}")
+    ctx = [n + 2 for n in lens[:-1]] + [0]
+    out = c.decode(1, ctx)
+    assert float(out[-1].float().abs().max()) == 0.0
+    for b in (0, B - 1):
+        c.assert_cache_equal(0, b)
+        c.assert_cache_equal(1, b)
