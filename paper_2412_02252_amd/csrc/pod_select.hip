@@ -67,14 +67,37 @@ __device__ inline void load_row_fragments(const pod_bf16 *row, int lane, sel_u32
     for (int kk = 0; kk < D / 16; ++kk) f[kk] = p[2 * kk];
 }
 
-__device__ inline const pod_bf16 *query_row(const select_params &p, int h, int r, int D)
-{
-    const int rr = r < p.R ? r : 0; // rows past the end read row 0 and are left out by the caller
-    return p.q_obs + ((size_t)(rr / p.rep) * p.Hq + (size_t)h * p.rep + rr % p.rep) * D;
-}
-
 // v_exp_f32: 2^x to 1 ulp; results below the smallest normal number come out as 0, which a softmax weight may
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// Over the 64 lanes of a wave by DPP steps inside the rows of 16 lanes, the rows through SGPRs or row broadcasts, for whole numbers (the
+// order of the sums is not __shfl_xor's).  A value through LDS (__shfl) takes a round trip each, and a reduction or a scan is a chain of
+// six: the top-k kernel, nine of them one after the other at 14272 tokens and 8 kv heads, 17.5 -> 16.2 us.  Call with all lanes active.
+template <int CTRL, int ROWS = 0xf>
+__device__ inline unsigned dpp(unsigned v) { return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, true); }
+template <class F>
+__device__ inline unsigned wave_reduce(unsigned v, F &&f)
+{
+    v = f(v, dpp<0xB1>(v));  // quad_perm [1, 0, 3, 2]
+    v = f(v, dpp<0x4E>(v));  // quad_perm [2, 3, 0, 1]
+    v = f(v, dpp<0x141>(v)); // row_half_mirror
+    v = f(v, dpp<0x140>(v)); // row_mirror
+    const auto lane = [&](int i) { return (unsigned)__builtin_amdgcn_readlane((int)v, i); };
+    return f(f(lane(0), lane(16)), f(lane(32), lane(48)));
+}
+__device__ inline unsigned min_of(unsigned a, unsigned b) { return a < b ? a : b; }
+__device__ inline unsigned max_of(unsigned a, unsigned b) { return a > b ? a : b; }
+__device__ inline unsigned sum_of(unsigned a, unsigned b) { return a + b; }
+__device__ inline unsigned wave_scan(unsigned v) // sum over this lane and those below it
+{
+    v += dpp<0x111>(v); // row_shr:1, 2, 4, 8
+    v += dpp<0x112>(v);
+    v += dpp<0x114>(v);
+    v += dpp<0x118>(v);
+    v += dpp<0x142, 0xa>(v); // row_bcast:15 into rows 1 and 3
+    v += dpp<0x143, 0xc>(v); // row_bcast:31 into rows 2 and 3
+    return v;
+}
 
 // where the key of position `key` of kv head h is: in the caller's array, or in the cache (sink slot, distant row,
 // or the ring slot of a recent position)
@@ -113,12 +136,18 @@ __device__ inline void stage_query_rows(const select_params &p, int h, int row0,
     constexpr int PER = kSelChunkRows * cpr / kSelThreads, RPS = kSelThreads / cpr; // pieces per thread; rows between two of them
     static_assert(kSelChunkRows * cpr % kSelThreads == 0 && kSelThreads % cpr == 0, "");
     const int c = threadIdx.x % cpr, first = threadIdx.x / cpr;
+    // (a row's position and query head are counted on from piece to piece, without a division by rep for each)
+    int pos = (row0 + first) / p.rep, qh = (row0 + first) % p.rep;
+    const int dpos = RPS / p.rep, dqh = RPS % p.rep;
     sel_u32x4 val[PER];
 #pragma unroll
     for (int x = 0; x < PER; ++x) {
-        const int row = row0 + first + x * RPS;
         val[x] = sel_u32x4{0, 0, 0, 0}; // rows past the end: zeros (their logits are never used)
-        if (row < p.R) val[x] = *(const sel_u32x4 *)(query_row(p, h, row, D) + c * 8);
+        if (row0 + first + x * RPS < p.R)
+            val[x] = *(const sel_u32x4 *)(p.q_obs + ((size_t)pos * p.Hq + (size_t)h * p.rep + qh) * D + c * 8);
+        pos += dpos;
+        qh += dqh;
+        if (qh >= p.rep) { qh -= p.rep; ++pos; }
     }
 #pragma unroll
     for (int x = 0; x < PER; ++x) *(sel_u32x4 *)(lds + (first + x * RPS) * kSelRowBytes<D> + c * 16) = val[x];
@@ -158,12 +187,16 @@ __global__ __launch_bounds__(kSelThreads) void select_stat_kernel(select_params 
     __syncthreads();
     float m[kSelChunkBlocks], l[kSelChunkBlocks];
     int qpos[kSelChunkBlocks]; // the row's own position: it sees keys 0 .. qpos
+    int pos = (row0 + (lane & 31)) / p.rep, qh = (row0 + (lane & 31)) % p.rep;
+    const int dpos = 32 / p.rep, dqh = 32 % p.rep;
 #pragma unroll
     for (int rb = 0; rb < kSelChunkBlocks; ++rb) {
-        const int r = row0 + rb * 32 + (lane & 31);
         m[rb] = -INFINITY;
         l[rb] = 0.f;
-        qpos[rb] = p.n - p.obs + (r < p.R ? r : 0) / p.rep;
+        qpos[rb] = p.n - p.obs + (row0 + rb * 32 + (lane & 31) < p.R ? pos : 0);
+        pos += dpos;
+        qh += dqh;
+        if (qh >= p.rep) { qh -= p.rep; ++pos; }
     }
     for (; key0 < key_hi; key0 += kSelKeysPerIter) {
 #pragma unroll
@@ -423,20 +456,12 @@ __global__ __launch_bounds__(kTopThreads) void select_top_kernel(const float *__
     };
     unsigned lo = ~0u, hi = 0u; // smallest and largest key
     each_key([&](int, unsigned key) { lo = key < lo ? key : lo; hi = key > hi ? key : hi; });
-    for (int o = 32; o >= 1; o >>= 1) {
-        const unsigned a = __shfl_xor(lo, o), b = __shfl_xor(hi, o);
-        lo = a < lo ? a : lo;
-        hi = b > hi ? b : hi;
-    }
+    lo = wave_reduce(lo, min_of);
+    hi = wave_reduce(hi, max_of);
     if (lane == 0) { wave_tot[0][wave] = lo; wave_tot[1][wave] = hi; }
     __syncthreads();
-    lo = wave_tot[0][lane % (kTopThreads / 64)];
-    hi = wave_tot[1][lane % (kTopThreads / 64)];
-    for (int o = kTopThreads / 128; o >= 1; o >>= 1) {
-        const unsigned a = __shfl_xor(lo, o), b = __shfl_xor(hi, o);
-        lo = a < lo ? a : lo;
-        hi = b > hi ? b : hi;
-    }
+    lo = wave_reduce(wave_tot[0][lane % (kTopThreads / 64)], min_of);
+    hi = wave_reduce(wave_tot[1][lane % (kTopThreads / 64)], max_of);
     unsigned need = (unsigned)keep; // the threshold is the need-th largest of the keys in [lo, hi]; the same in every thread, like lo and hi
     for (;;) {
         const unsigned range = hi - lo;
@@ -451,18 +476,12 @@ __global__ __launch_bounds__(kTopThreads) void select_top_kernel(const float *__
         unsigned c[4], own = 0;
 #pragma unroll
         for (int x = 0; x < 4; ++x) { c[x] = hist[4 * tid + x]; own += c[x]; }
-        unsigned from_here = own;
-        for (int o = 1; o < 64; o <<= 1) {
-            const unsigned up = __shfl_down(from_here, o);
-            if (lane + o < 64) from_here += up;
-        }
-        if (lane == 0) wave_tot[0][wave] = from_here;
+        const unsigned up_to = wave_scan(own), all = (unsigned)__builtin_amdgcn_readlane((int)up_to, 63);
+        unsigned from_here = all - up_to + own;
+        if (lane == 0) wave_tot[0][wave] = all;
         __syncthreads();
-        {   // what the waves above hold: their totals in one read, added up in a butterfly
-            unsigned up = lane > wave && lane < kTopThreads / 64 ? wave_tot[0][lane] : 0u;
-            for (int o = kTopThreads / 128; o >= 1; o >>= 1) up += __shfl_xor(up, o);
-            from_here += __shfl(up, 0);
-        }
+        // and what the waves above hold: their totals in one read
+        from_here += wave_reduce(lane > wave && lane < kTopThreads / 64 ? wave_tot[0][lane] : 0u, sum_of);
         unsigned above = from_here - own;
         if (above < need && need <= from_here) { // exactly one thread: the need-th largest lies in one of its counters
 #pragma unroll
@@ -485,20 +504,12 @@ __global__ __launch_bounds__(kTopThreads) void select_top_kernel(const float *__
     // tokens above / at the threshold in this thread's run, then in all runs before it
     unsigned n_gt = 0, n_eq = 0;
     each_key([&](int, unsigned key) { n_gt += key > thr; n_eq += key == thr; });
-    unsigned inc_gt = n_gt, inc_eq = n_eq;
-    for (int o = 1; o < 64; o <<= 1) {
-        const unsigned a = __shfl_up(inc_gt, o), b = __shfl_up(inc_eq, o);
-        if (lane >= o) { inc_gt += a; inc_eq += b; }
-    }
+    const unsigned inc_gt = wave_scan(n_gt), inc_eq = wave_scan(n_eq);
     if (lane == 63) { wave_tot[0][wave] = inc_gt; wave_tot[1][wave] = inc_eq; }
     __syncthreads();
     unsigned gt_before = inc_gt - n_gt, eq_before = inc_eq - n_eq;
-    {   // (the waves below, as above)
-        unsigned a = lane < wave ? wave_tot[0][lane] : 0u, b = lane < wave ? wave_tot[1][lane] : 0u;
-        for (int o = kTopThreads / 128; o >= 1; o >>= 1) { a += __shfl_xor(a, o); b += __shfl_xor(b, o); }
-        gt_before += __shfl(a, 0);
-        eq_before += __shfl(b, 0);
-    }
+    gt_before += wave_reduce(lane < wave ? wave_tot[0][lane] : 0u, sum_of); // (the waves below)
+    eq_before += wave_reduce(lane < wave ? wave_tot[1][lane] : 0u, sum_of);
     each_key([&](int t, unsigned key) {
         const bool gt = key > thr, eq = key == thr;
         if (gt || (eq && eq_before < need)) {

@@ -75,6 +75,18 @@ def test_votes_match_the_oracle(d, Hq, Hkv, S, W, n, obs):
     assert torch.equal(votes, again)
 
 
+@pytest.mark.parametrize("d,Hq,Hkv,obs", [ # group sizes that divide neither 16 nor 32, the rows between two pieces of a thread and between two row blocks
+    (128, 15, 1, 20),   # 300 rows: a second chunk
+    (128, 26, 2, 21),
+    (64, 11, 1, 9),
+    (64, 30, 2, 18),
+    (128, 21, 3, 40),
+    (128, 9, 3, 64),
+])
+def test_votes_of_query_rows_counted_on_from_row_to_row(d, Hq, Hkv, obs):
+    test_votes_match_the_oracle(d, Hq, Hkv, 3, 64, 400, obs)
+
+
 def test_votes_of_a_peaked_prompt_with_large_logits():
     # one key per head draws nearly all attention (logit ~ +60 above the rest): maxima move, weights span 26 decades
     d, Hq, Hkv, S, W, n, obs = 128, 4, 2, 2, 20, 500, 8
