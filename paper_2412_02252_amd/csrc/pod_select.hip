@@ -129,12 +129,12 @@ template <int D> constexpr int kSelRowBytes = D * 2 + 16;
 
 // A thread's pieces are all requested before the first is stored: one after the other they are a chain of as many round trips
 // (one wave-wide load per round trip of an L2).
-template <int D>
+template <int D, int THREADS>
 __device__ inline void stage_query_rows(const select_params &p, int h, int row0, char *lds)
 {
     constexpr int cpr = D / 8; // 16-byte pieces per row
-    constexpr int PER = kSelChunkRows * cpr / kSelThreads, RPS = kSelThreads / cpr; // pieces per thread; rows between two of them
-    static_assert(kSelChunkRows * cpr % kSelThreads == 0 && kSelThreads % cpr == 0, "");
+    constexpr int PER = kSelChunkRows * cpr / THREADS, RPS = THREADS / cpr; // pieces per thread; rows between two of them
+    static_assert(kSelChunkRows * cpr % THREADS == 0 && THREADS % cpr == 0, "");
     const int c = threadIdx.x % cpr, first = threadIdx.x / cpr;
     // (a row's position and query head are counted on from piece to piece, without a division by rep for each)
     int pos = (row0 + first) / p.rep, qh = (row0 + first) % p.rep;
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(kSelThreads) void select_stat_kernel(select_params 
     };
     int key0 = key_lo + wave * 32;
     if (key0 < key_hi) load_row_fragments<D>(key_row(key0), lane, kn); // (on their way while the query rows are staged)
-    stage_query_rows<D>(p, h, row0, ldsq);
+    stage_query_rows<D, kSelThreads>(p, h, row0, ldsq);
     __syncthreads();
     float m[kSelChunkBlocks], l[kSelChunkBlocks];
     int qpos[kSelChunkBlocks]; // the row's own position: it sees keys 0 .. qpos
@@ -289,14 +289,16 @@ __global__ __launch_bounds__(kSelThreads) void select_reduce_kernel(select_param
     if (lane == 0) p.stat[(size_t)h * (p.nrb * 32) + r] = r < p.R && L > 0.f ? M + log2f(L) : INFINITY; // (every row sees key 0: L > 0)
 }
 
-// Second pass.  Workgroup = (kSelVoteKeys distant keys, kv head); a wave takes key blocks of 32 and, per key block,
-// every chunk's row blocks: S = Q K^T, a lane owns key lane % 32 and adds up the weights of 16 query rows per MFMA
-// tile.  A distant key is older than every query of the observation window (obs <= W): no causal test.
-constexpr int kSelVoteBlocks = 2;                                  // key blocks per wave (4 leave half of the wave slots empty: 20.0 us, 2: 17.3, 1: 19.1)
-constexpr int kSelVoteKeys = kSelVoteBlocks * kSelKeysPerIter;     // keys per workgroup
+// Second pass.  Workgroup = (256 distant keys, kv head); a wave takes 32 of them and every row block of every chunk: S = Q K^T,
+// a lane owns key lane % 32 and adds up the weights of 16 query rows per MFMA tile.  A distant key is older than every query of the
+// observation window (obs <= W): no causal test.  Eight waves share one staging of the query rows, and two such workgroups fit a CU (120
+// registers, 70 KB): four waves per SIMD.  Four waves that take two key blocks each, one after the other (214 registers, two waves per SIMD),
+// took 15.8 instead of 13.8 us at 14272 distant tokens, 8 kv heads and 256 rows; one block each without the shared staging 19.1.
+constexpr int kVoteThreads = 512;
+constexpr int kSelVoteKeys = kVoteThreads / 2;     // keys per workgroup: 32 per wave
 
 template <int D>
-__global__ __launch_bounds__(kSelThreads) void select_vote_kernel(select_params p)
+__global__ __launch_bounds__(kVoteThreads, 4) void select_vote_kernel(select_params p)
 {
     const int h = blockIdx.y;
     if (!((p.head_mask >> h) & 1)) return;
@@ -305,72 +307,58 @@ __global__ __launch_bounds__(kSelThreads) void select_vote_kernel(select_params 
     const int wg_key0 = p.S + blockIdx.x * kSelVoteKeys;
     __shared__ __align__(16) char ldsq[kSelChunkRows * kSelRowBytes<D>];
     __shared__ __align__(16) float ldsb[kSelChunkRows];
-    float vote[kSelVoteBlocks];
-#pragma unroll
-    for (int kb = 0; kb < kSelVoteBlocks; ++kb) vote[kb] = 0.f;
-    sel_u32x4 kn[D / 16];
-    auto request_keys = [&](int kb) { // (clamped past the end: what is loaded there is not used)
-        const int key0 = wg_key0 + (kb * (kSelThreads / 64) + wave) * 32;
+    const int key0 = wg_key0 + wave * 32;
+    const bool have = key0 < dist_hi; // (the same in the whole wave)
+    float vote = 0.f;
+    sel_u32x4 kf[D / 16];
+    {   // (clamped past the end: what is loaded there is not used)
         const int key = key0 + (lane & 31) < dist_hi ? key0 + (lane & 31) : dist_hi - 1;
-        load_row_fragments<D>(key_address(p, h, key, D), lane, kn);
-    };
+        load_row_fragments<D>(key_address(p, h, key, D), lane, kf);
+    }
     for (int row0 = 0; row0 < p.R; row0 += kSelChunkRows) {
-        request_keys(0);
         if (row0) __syncthreads(); // everyone is done with the previous chunk
-        stage_query_rows<D>(p, h, row0, ldsq);
-        {
+        stage_query_rows<D, kVoteThreads>(p, h, row0, ldsq);
+        if (threadIdx.x < kSelChunkRows) {
             const int r = row0 + threadIdx.x; // one row of the chunk per thread
             ldsb[threadIdx.x] = r < p.nrb * 32 ? p.stat[(size_t)h * (p.nrb * 32) + r] : INFINITY;
         }
         __syncthreads();
+        if (!have) continue;
         const int nblk = (p.R - row0 + 31) / 32 < kSelChunkBlocks ? (p.R - row0 + 31) / 32 : kSelChunkBlocks;
+        auto logits = [&](int rb) {
+            sel_u32x4 qf[D / 16];
+            lds_row_fragments<D>(ldsq, rb, lane, qf);
+            sel_f32x16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-        for (int kb = 0; kb < kSelVoteBlocks; ++kb) {
-            const int key0 = wg_key0 + (kb * (kSelThreads / 64) + wave) * 32;
-            if (key0 >= dist_hi) continue; // (whole wave; no barrier inside)
-            sel_u32x4 kf[D / 16];
+            for (int kk = 0; kk < D / 16; ++kk)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(sel_bf16x8, qf[kk]),
+                                                               __builtin_bit_cast(sel_bf16x8, kf[kk]), acc, 0, 0, 0);
+            return acc;
+        };
+        // accumulator e of this lane: query row rb * 32 + 8 (e / 4) + 4 (lane / 32) + e % 4 of the chunk, key lane % 32
+        auto add_tile = [&](int rb, const sel_f32x16 &acc) {
 #pragma unroll
-            for (int kk = 0; kk < D / 16; ++kk) kf[kk] = kn[kk];
-            if (kb + 1 < kSelVoteBlocks) request_keys(kb + 1);
-            auto logits = [&](int rb) {
-                sel_u32x4 qf[D / 16];
-                lds_row_fragments<D>(ldsq, rb, lane, qf);
-                sel_f32x16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+            for (int e4 = 0; e4 < 4; ++e4) {
+                typedef __attribute__((ext_vector_type(4))) float f32x4;
+                const f32x4 bq = *(const f32x4 *)(ldsb + rb * 32 + 8 * e4 + 4 * (lane >> 5));
 #pragma unroll
-                for (int kk = 0; kk < D / 16; ++kk)
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(sel_bf16x8, qf[kk]),
-                                                                   __builtin_bit_cast(sel_bf16x8, kf[kk]), acc, 0, 0, 0);
-                return acc;
-            };
-            // accumulator e of this lane: query row rb * 32 + 8 (e / 4) + 4 (lane / 32) + e % 4 of the chunk, key lane % 32
-            auto add_tile = [&](int rb, const sel_f32x16 &acc) {
-#pragma unroll
-                for (int e4 = 0; e4 < 4; ++e4) {
-                    typedef __attribute__((ext_vector_type(4))) float f32x4;
-                    const f32x4 bq = *(const f32x4 *)(ldsb + rb * 32 + 8 * e4 + 4 * (lane >> 5));
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) vote[kb] += fast_exp2(acc[4 * e4 + j] * p.scale_log2 - bq[j]);
-                }
-            };
-            if (nblk == kSelChunkBlocks) { // (the next block's products beside this one's exponentials, as in the first pass)
-                sel_f32x16 next = logits(0);
-#pragma unroll
-                for (int rb = 0; rb < kSelChunkBlocks; ++rb) {
-                    const sel_f32x16 acc = next;
-                    if (rb + 1 < kSelChunkBlocks) next = logits(rb + 1);
-                    add_tile(rb, acc);
-                }
-            } else {
-                for (int rb = 0; rb < nblk; ++rb) add_tile(rb, logits(rb));
+                for (int j = 0; j < 4; ++j) vote += fast_exp2(acc[4 * e4 + j] * p.scale_log2 - bq[j]);
             }
+        };
+        if (nblk == kSelChunkBlocks) { // (the next block's products beside this one's exponentials, as in the first pass)
+            sel_f32x16 next = logits(0);
+#pragma unroll
+            for (int rb = 0; rb < kSelChunkBlocks; ++rb) {
+                const sel_f32x16 acc = next;
+                if (rb + 1 < kSelChunkBlocks) next = logits(rb + 1);
+                add_tile(rb, acc);
+            }
+        } else {
+            for (int rb = 0; rb < nblk; ++rb) add_tile(rb, logits(rb));
         }
     }
-#pragma unroll
-    for (int kb = 0; kb < kSelVoteBlocks; ++kb) {
-        const int key0 = wg_key0 + (kb * (kSelThreads / 64) + wave) * 32;
-        const float v = vote[kb] + __shfl_xor(vote[kb], 32); // the two lanes of a key hold different query rows
-        if (lane < 32 && key0 + lane < dist_hi) p.votes[(size_t)h * (dist_hi - p.S) + (key0 + lane - p.S)] = v;
-    }
+    const float v = vote + __shfl_xor(vote, 32); // the two lanes of a key hold different query rows
+    if (lane < 32 && key0 + lane < dist_hi) p.votes[(size_t)h * (dist_hi - p.S) + (key0 + lane - p.S)] = v;
 }
 
 // order-preserving map of a float's bits to an unsigned (larger float = larger unsigned)
@@ -731,11 +719,11 @@ int pod_launch_select_votes(const pod_cache *c, int layer, int b, uint64_t head_
     if (ly.D == 128) {
         hipLaunchKernelGGL(select_stat_kernel<128>, g1, dim3(kSelThreads), 0, st, p);
         hipLaunchKernelGGL(select_reduce_kernel, g2, dim3(kSelThreads), 0, st, p);
-        hipLaunchKernelGGL(select_vote_kernel<128>, g3, dim3(kSelThreads), 0, st, p);
+        hipLaunchKernelGGL(select_vote_kernel<128>, g3, dim3(kVoteThreads), 0, st, p);
     } else {
         hipLaunchKernelGGL(select_stat_kernel<64>, g1, dim3(kSelThreads), 0, st, p);
         hipLaunchKernelGGL(select_reduce_kernel, g2, dim3(kSelThreads), 0, st, p);
-        hipLaunchKernelGGL(select_vote_kernel<64>, g3, dim3(kSelThreads), 0, st, p);
+        hipLaunchKernelGGL(select_vote_kernel<64>, g3, dim3(kVoteThreads), 0, st, p);
     }
     POD_HIP_TRY(hipGetLastError());
     return POD_OK;

@@ -87,6 +87,12 @@ def test_votes_of_query_rows_counted_on_from_row_to_row(d, Hq, Hkv, obs):
     test_votes_match_the_oracle(d, Hq, Hkv, 3, 64, 400, obs)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("distant", [1, 32, 33, 255, 256, 257, 480, 513]) # 32 keys per wave, 256 per workgroup
+def test_votes_at_the_edges_of_waves_and_workgroups_of_keys(d, distant):
+    test_votes_match_the_oracle(d, 5, 1, 2, 64, 2 + 64 + distant, 55) # 275 rows: the waves without keys pass the second chunk's barriers too
+
+
 def test_votes_of_a_peaked_prompt_with_large_logits():
     # one key per head draws nearly all attention (logit ~ +60 above the rest): maxima move, weights span 26 decades
     d, Hq, Hkv, S, W, n, obs = 128, 4, 2, 2, 20, 500, 8
