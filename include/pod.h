@@ -529,15 +529,17 @@ int pod_profile_mfma_feed(int variant, int iters, void *dev_out, size_t out_byte
  * overrides (proximal_rows = sink + window).  plan[0] waves per workgroup, plan[1] tokens per distant piece, plan[2]
  * tokens per proximal piece, plan[3] distant pieces per (sequence, kv head) pair, plan[4] all pieces per pair,
  * plan[5] 1 if the last workgroup of a pair merges these pieces' partials inside the launch, 0 if a second kernel does
- * (or the launch takes the even split below instead).
+ * (or the launch takes the even split below instead).  Two more choices look at more than these arguments: plain launches with plan[5] 1 whose
+ * lengths the host knows take the even split where it ends sooner, and small ones run workgroups of four waves (plan[0] 4 in effect, the
+ * pieces of a plan with plan[5] 0) that still merge inside.
  * Pieces are whole tiles of 32 tokens and cover the regions; plan[4] never exceeds what pod_workspace_bytes provides for.
  * Returns POD_ERR_INVALID_ARG for non-positive arguments or a NULL plan.
  */
 int pod_decode_plan(int num_cus, int batch, int num_kv_heads, int proximal_rows, int max_context_len, int32_t plan[6]);
 
 /*
- * Host logic, no device needed: the even split of a launch where pod_decode_plan's plan[5] is 0 and the host
- * knows the lengths (batch <= 256, lengths not taken from the device): plain launches, and score-reuse decode steps
+ * Host logic, no device needed: the even split of a launch where pod_decode_plan's plan[5] is 0 (or a plain one that it ends
+ * sooner) and the host knows the lengths (batch <= 256, lengths not taken from the device): plain launches, and score-reuse decode steps
  * of layers none of whose kv heads starts a block (they read logits).  context_lens: HOST int32 [batch], tokens each sequence holds (<= 0:
  * none).  The rows of the batch stand in one line - sequence after sequence, inside a sequence kv head after kv head,
  * inside such a pair its distant rows (tokens beyond proximal_rows), then its proximal rows - counted in units:
@@ -555,9 +557,9 @@ int pod_decode_even_plan(int num_cus, int batch, int num_kv_heads, int proximal_
  * Host logic, no device needed: the split such a launch really takes.  The same, but with 128-token distant units every
  * pair's units are padded to a multiple of plan[0] where all workgroups still fit one round (2 num_cus): then plan[4] is 1, unit_cum
  * and plan[2] count the padding, no workgroup walks rows of two pairs, every pair that holds a token has
- * (unit_cum[b + 1] - unit_cum[b]) / plan[0] workgroups, each with rows of its own, and at head dimension 64 with at most
- * four query heads per kv head (and no empty sequence, or a decode step) the last of them merges the pair's partials inside
- * the launch.  plan[4] is 0 where pod_decode_even_plan's split is taken as it is.
+ * (unit_cum[b + 1] - unit_cum[b]) / plan[0] workgroups, each with rows of its own, and with at most four query heads per
+ * kv head, or eight and at most 16 partials per pair (and no empty sequence, or a decode step), the last of them merges the pair's partials
+ * inside the launch.  plan[4] is 0 where pod_decode_even_plan's split is taken as it is.
  */
 int pod_decode_even_launch(int num_cus, int batch, int num_kv_heads, int proximal_rows, int distant_unit_tokens,
                            const int32_t *context_lens, int32_t plan[5], int32_t *unit_cum);

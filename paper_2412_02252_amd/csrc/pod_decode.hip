@@ -1240,7 +1240,7 @@ __device__ void step_workgroup(const decode_params &p, const decode_hot &hot, in
 }
 
 // ---------------------------------------------------------------------------------------------
-// Launches of several rounds of workgroups (large batches, long contexts): the even split.  MODE 0: plain.  MODE 2: the
+// Launches of several rounds of workgroups (large batches, long contexts), and those of one that it ends sooner: the even split.  MODE 0: plain.  MODE 2: the
 // decode step of an upper layer with score reuse (distant rows: values and the lowest layer's logits, no keys).
 //
 // With one piece of a fixed number of tokens per workgroup such a launch ends with a round that is partly empty, and

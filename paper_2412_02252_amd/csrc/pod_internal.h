@@ -74,7 +74,7 @@ struct pod_cache {
     int tune_chunk, tune_chunk_prox;
     bool fused_merge;      // plain decode merges its partials inside the streaming kernel (POD_DECODE_FUSED=0: separate kernel)
     bool walk_turns;       // the layers of a block walk the block's distant keys in alternating directions (POD_DECODE_WALK_TURNS=0: all forward)
-    bool even_split;       // launches of several rounds give every workgroup the same number of rows (POD_DECODE_EVEN=0: fixed pieces)
+    bool even_split;       // launches of several rounds, and uneven ones of one, give every workgroup the same number of rows (POD_DECODE_EVEN=0: fixed pieces)
     bool xcd_local;        // hand partials over inside one XCD's L2 where the launch shape allows (POD_DECODE_XCD_LOCAL=0: never)
     int nxcd;              // XCDs a one-dimensional launch is spread over round-robin (0: no such pattern seen by the probe)
     bool chunk_in_place;   // chunk attention reads keys and values where the cache holds them (POD_CHUNK_IN_PLACE=0: from a contiguous copy)
@@ -200,7 +200,7 @@ struct pod_step_args { const void *k_new, *v_new; const int32_t *positions; };
 struct pod_decode_plan_t { int waves, chunk, chunk_p, max_nd, nc; bool merge_inside; };
 pod_decode_plan_t pod_plan_decode(int cus, int B, int Hkv, int P, int max_len, int env_chunk, int env_chunk_prox, bool scores,
                                   bool small_prox, bool fused_allowed, bool reader = false);
-// the even split of a plain launch of several rounds (host logic, pod_decode.hip): units per workgroup, workgroups,
+// the even split of a plain launch (host logic, pod_decode.hip): units per workgroup, workgroups,
 // units in all, partials of the (sequence, kv head) pair that is cut into most parts; unit_cum has B + 1 entries;
 // unit_d = tokens per unit of distant rows (128, or 256 for an upper layer that reads logits instead of keys)
 struct pod_even_plan_t { int32_t q, nwg, total, most; };
