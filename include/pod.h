@@ -530,8 +530,8 @@ int pod_profile_mfma_feed(int variant, int iters, void *dev_out, size_t out_byte
  * tokens per proximal piece, plan[3] distant pieces per (sequence, kv head) pair, plan[4] all pieces per pair,
  * plan[5] 1 if the last workgroup of a pair merges these pieces' partials inside the launch, 0 if a second kernel does
  * (or the launch takes the even split below instead).  Two more choices look at more than these arguments: plain launches with plan[5] 1 whose
- * lengths the host knows take the even split where it ends sooner, and small ones run workgroups of four waves (plan[0] 4 in effect, the
- * pieces of a plan with plan[5] 0) that still merge inside.
+ * lengths the host knows take the even split where it ends sooner, and small ones run workgroups of four waves that still merge inside;
+ * pod_decode_launch_plan tells what is launched.
  * Pieces are whole tiles of 32 tokens and cover the regions; plan[4] never exceeds what pod_workspace_bytes provides for.
  * Returns POD_ERR_INVALID_ARG for non-positive arguments or a NULL plan.
  */
@@ -563,6 +563,25 @@ int pod_decode_even_plan(int num_cus, int batch, int num_kv_heads, int proximal_
  */
 int pod_decode_even_launch(int num_cus, int batch, int num_kv_heads, int proximal_rows, int distant_unit_tokens,
                            const int32_t *context_lens, int32_t plan[5], int32_t *unit_cum);
+
+/*
+ * Host logic, no device needed: how a decode call is launched without tuning overrides: the choice the call itself makes, of fixed
+ * pieces (pod_decode_plan's, or those of a small launch's four-wave workgroups) or the even split (pod_decode_even_launch).  call:
+ * POD_CALL_ATTENTION pod_decode_attention, POD_CALL_STEP pod_decode_step, POD_CALL_REUSE_FIRST / POD_CALL_REUSE_UPPER pod_decode_step_reuse at a layer
+ * where all / none of the kv heads start a block.  num_xcds: pod_cache_launch_info's info[0].  max_context_len >= 1: the call's bound (its
+ * default is the longest context attended to, a step's new token included).  context_lens: HOST int32 [batch], tokens each sequence holds
+ * before the call, or NULL where the host's lengths are not used (pod_cache_set_length_source, batch > 256).  workspace_bytes: the call's scratch.
+ * plan[0] 1 even split, 0 fixed pieces; plan[1] 1 if the launch merges its partials itself, 0 if a second kernel does; plan[2] waves per
+ * workgroup; plan[3] 1 if partials are handed over inside one XCD's L2; plan[4] 1 if a step has a workgroup of its own per pair; plan[5] tokens
+ * per distant piece (even split: units per workgroup); plan[6] tokens per proximal piece (even split: 1 if padded to whole pairs); plan[7] partials per
+ * query head the scratch holds, a step's own among them.
+ */
+#define POD_CALL_ATTENTION 0
+#define POD_CALL_STEP 1
+#define POD_CALL_REUSE_FIRST 2
+#define POD_CALL_REUSE_UPPER 3
+int pod_decode_launch_plan(int num_cus, int num_xcds, int batch, int num_q_heads, int num_kv_heads, int head_dim, int proximal_rows,
+                           int max_context_len, const int32_t *context_lens, int call, size_t workspace_bytes, int32_t plan[8]);
 
 /*
  * Measurement aid: while dev_buf is set (NULL = off), every workgroup of a pod_decode_step / fused

@@ -24,7 +24,7 @@ EXPORTS = [
     "pod_group_layers", "pod_layer_similarity", "pod_similarity_plan", "pod_fill_plan",
     "pod_decode_attention_static", "pod_cache_region_counts", "pod_decode_step", "pod_cache_set_length_source", "pod_cache_launch_info",
     "pod_cache_sync_lengths", "pod_cache_append_many", "pod_prefill_chunk_workspace_bytes", "pod_prefill_chunk_in_place_bytes", "pod_prefill_attention_chunk", "pod_decode_even_plan", "pod_decode_even_launch",
-    "pod_decode_plan", "pod_decode_step_reuse",
+    "pod_decode_plan", "pod_decode_launch_plan", "pod_decode_step_reuse",
     "pod_select_workspace_bytes", "pod_select_votes", "pod_select_top", "pod_cache_compact",
 ]
 
@@ -74,6 +74,7 @@ def load():
         "pod_decode_plan": [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int32)],
         "pod_decode_even_plan": [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.POINTER(C.c_int32)],
         "pod_decode_even_launch": [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.POINTER(C.c_int32)],
+        "pod_decode_launch_plan": [C.c_int] * 8 + [C.POINTER(C.c_int32), C.c_int, C.c_size_t, C.POINTER(C.c_int32)],
         "pod_cache_append": [vp, C.c_int, vp, vp, i32p, C.c_int, vp],
         "pod_cache_fill": [vp, C.c_int, C.c_int, C.c_int, vp, vp, vp],
         "pod_decode_attention": [vp, C.c_int, vp, vp, i32p, C.c_int, C.c_int, C.c_float, vp, C.c_size_t, vp, vp],
@@ -258,6 +259,23 @@ def pod_decode_even_launch(num_cus: int, num_kv_heads: int, proximal_rows: int, 
     cum = (C.c_int32 * (B + 1))()
     _check(load().pod_decode_even_launch(num_cus, B, num_kv_heads, proximal_rows, distant_unit_tokens, lens, plan, cum))
     return dict(units_per_workgroup=plan[0], workgroups=plan[1], units=plan[2], partials_per_pair=plan[3], padded=bool(plan[4]), unit_cum=list(cum))
+
+
+CALL_ATTENTION, CALL_STEP, CALL_REUSE_FIRST, CALL_REUSE_UPPER = 0, 1, 2, 3
+
+
+def pod_decode_launch_plan(num_cus: int, num_xcds: int, num_q_heads: int, num_kv_heads: int, head_dim: int, proximal_rows: int,
+                           context_lens, call: int = CALL_STEP, max_context_len: int = 0, workspace_bytes: int = 1 << 40, lens_known: bool = True) -> dict:
+    """Host logic (no GPU): how a decode call on sequences that hold context_lens tokens is launched (lens_known=False: as where the host's
+    lengths are not used)."""
+    B = len(context_lens)
+    lens = (C.c_int32 * B)(*[int(n) for n in context_lens])
+    plan = (C.c_int32 * 8)()
+    bound = max_context_len or max(max(context_lens) + (call != CALL_ATTENTION), 1)
+    _check(load().pod_decode_launch_plan(num_cus, num_xcds, B, num_q_heads, num_kv_heads, head_dim, proximal_rows, bound,
+                                         lens if lens_known else None, call, workspace_bytes, plan))
+    r = dict(even=bool(plan[0]), merge_inside=bool(plan[1]), waves=plan[2], xcd_local=bool(plan[3]), own_workgroup=bool(plan[4]), partials=plan[7])
+    return dict(r, units_per_workgroup=plan[5], padded=bool(plan[6])) if r["even"] else dict(r, chunk=plan[5], chunk_prox=plan[6])
 
 
 def pod_profile_stream_read(buf: torch.Tensor, nbytes: int, cache=None):

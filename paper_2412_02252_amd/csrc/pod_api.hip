@@ -356,6 +356,34 @@ extern "C" int pod_decode_even_launch(int num_cus, int batch, int num_kv_heads, 
     return POD_OK;
 }
 
+extern "C" int pod_decode_launch_plan(int num_cus, int num_xcds, int batch, int num_q_heads, int num_kv_heads, int head_dim, int proximal_rows,
+                                      int max_context_len, const int32_t *context_lens, int call, size_t workspace_bytes, int32_t plan[8])
+{
+    if (!plan) return pod_fail(POD_ERR_INVALID_ARG, "plan is NULL");
+    if (num_cus < 1 || num_xcds < 0 || batch < 1 || num_q_heads < 1 || num_kv_heads < 1 || proximal_rows < 1 || max_context_len < 1)
+        return pod_fail(POD_ERR_INVALID_ARG, "num_cus, batch, head counts, proximal_rows and max_context_len must be positive, num_xcds not negative");
+    if (num_q_heads % num_kv_heads || num_q_heads / num_kv_heads > 16 || (head_dim != 64 && head_dim != 128))
+        return pod_fail(POD_ERR_INVALID_ARG, "num_q_heads must be 1 to 16 times num_kv_heads, head_dim 64 or 128");
+    if (call < POD_CALL_ATTENTION || call > POD_CALL_REUSE_UPPER) return pod_fail(POD_ERR_INVALID_ARG, "call %d outside [0, 3]", call);
+    if (context_lens && batch > 256) return pod_fail(POD_ERR_INVALID_ARG, "lengths of %d sequences: at most 256", batch);
+    if ((long long)batch * num_q_heads > 0x7fffffffLL || (long long)batch * num_kv_heads * max_context_len > (1LL << 50))
+        return pod_fail(POD_ERR_INVALID_ARG, "shape too large");
+    const bool reuse = call >= POD_CALL_REUSE_FIRST, first = call == POD_CALL_REUSE_FIRST;
+    const pod_decode_shape_t shape = {num_cus, num_xcds, batch, num_kv_heads, num_q_heads / num_kv_heads, head_dim, proximal_rows, max_context_len,
+                                      context_lens, workspace_bytes, call != POD_CALL_ATTENTION, reuse, false, first, first, true, true, true, 0, 0};
+    int32_t unit_cum[256 + 1];
+    const pod_decode_choice_t ch = pod_choose_decode(shape, unit_cum);
+    plan[0] = ch.even;
+    plan[1] = ch.even ? ch.even_merge : ch.pl.merge_inside;
+    plan[2] = ch.even ? 4 : ch.pl.waves;
+    plan[3] = ch.loc;
+    plan[4] = shape.step && (ch.even || ch.own_host);
+    plan[5] = ch.even ? ch.ev.q : ch.pl.chunk;
+    plan[6] = ch.even ? ch.padded : ch.pl.chunk_p;
+    plan[7] = (ch.even ? ch.ev.most : ch.pl.nc) + (shape.step ? 1 : 0);
+    return POD_OK;
+}
+
 extern "C" int pod_profile_set_trace(pod_cache *cache, void *dev_buf, size_t bytes)
 {
     if (!cache) return pod_fail(POD_ERR_INVALID_ARG, "cache is NULL");

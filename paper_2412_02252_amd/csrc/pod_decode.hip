@@ -2006,6 +2006,102 @@ bool pod_plan_even_launch(int slots, int B, int Hkv, int P, int unit_d, const in
     return true;
 }
 
+// How a decode call is launched (host logic; pod_launch_decode launches it, pod_decode_launch_plan reports it).  unit_cum: kMaxHostLens + 1 entries, the
+// prefix sums of the even split where the launch takes it.
+pod_decode_choice_t pod_choose_decode(const pod_decode_shape_t &s, int32_t *unit_cum)
+{
+    const bool reuse_step = s.step && s.scores, reader = reuse_step && !s.lowest_any;
+    const int npairs = s.B * s.Hkv;
+    const long xcd_cus = s.nxcd >= 1 ? s.cus / s.nxcd : 0, xcd_pairs = s.nxcd >= 1 ? (npairs + s.nxcd - 1) / s.nxcd : 0;
+    // XCD-local hand-off: where the pairs spread evenly over the XCDs (else some would sit idle while others stream), or where
+    // they are so few and short that each XCD's pieces have a CU each: the launch is then its latency, and one L2 hands a
+    // partial over sooner than memory does (per step: 2 pairs x 64 at 2048 tokens 7.05 -> 6.61 us, 3 pairs x 128 with 8 query
+    // heads 10.4 -> 9.1, 1 pair x 128 with 16 13.8 -> 11.2; at the line, 31 pieces of 256 tokens x 128 on one XCD, 18.1 either way).
+    const auto loc_of = [&](const pod_decode_plan_t &pl) {
+        return pl.merge_inside && s.xcd_local && s.nxcd >= 1 &&
+               (npairs % s.nxcd == 0 || npairs >= 8 * s.nxcd || xcd_pairs * pl.nc <= xcd_cus);
+    };
+    // The step's own workgroup: the new token's chain of short dependent accesses then runs beside the pieces instead of in front
+    // of one.  XCD-local launches have one where every workgroup of the XCD still gets a CU (2 pairs x 64 at 2048 tokens
+    // 8.92 -> 7.05 us, 8 pairs x 128 at 2048 9.8 -> 8.3), launches that hand over through memory where every workgroup of the
+    // chip does; full ones keep the host inside, where one more workgroup would wait for a CU.  32 steps of a layer through memory,
+    // us, without -> with: plain x 128, 2 pairs at 14000 tokens (114 workgroups) 410 -> 373, 7 pairs at 20000 (252) 579 -> 557,
+    // 1 pair with 16 heads at 60000 (236) 1577 -> 1580; score reuse x 64, 3 pairs at 14000 (168) 343 -> 334.  Score reuse x 128 stops at
+    // half of the CUs: 2 pairs at 14000 405 -> 392, but 2 pairs at 20000 (162) 455 -> 461 and 3 at 14000 (171) 372 -> 382.
+    const auto host_fits = [&](const pod_decode_plan_t &pl) {
+        return loc_of(pl) ? xcd_pairs * (pl.nc + 1) <= xcd_cus
+                          : (long)npairs * (pl.nc + 1) <= (reuse_step && s.D == 128 ? s.cus / 2 : s.cus);
+    };
+    pod_decode_plan_t pl = pod_plan_decode(s.cus, s.B, s.Hkv, s.P, s.max_len, s.tune_chunk, s.tune_chunk_prox, s.scores && !reuse_step,
+                                           s.gated && !s.lowest_all, s.fused_merge, reader);
+    // Small launches that merge inside one XCD's L2: workgroups of four waves instead of eight where all of them still get a CU.  A launch of one
+    // tile per wave is then spread over twice the CUs, and ends sooner by the half of what each of them has to load and to bring together.
+    // At head dimension 128 as long as a pair has no more than the 8 rows that a head's one lane group merges; at 64, where that costs
+    // less, also where eight waves leave more than these 8, and with up to two query heads per kv head.  Per step, us, eight -> four waves: 32/8 x 128
+    // at 300 tokens 7.8 -> 6.6, 777 7.9 -> 6.9; 32/4 8.4 -> 7.4, but at 1100 (10 rows) 8.4 -> 8.8; 16/1 9.8 -> 8.9, 10.1 -> 10.6; 16/4 x 64 777 6.9 -> 6.2, 1500 (13 rows instead
+    // of 7) 6.8 -> 7.2, 3600 8.0 -> 7.6; 4/2 x 64 2048 7.3 -> 6.5, 3600 7.3 -> 6.8.
+    bool four = false;
+    if (pl.merge_inside && s.xcd_local && s.nxcd >= 1 && s.tune_chunk <= 0 && s.tune_chunk_prox <= 0) {
+        const pod_decode_plan_t small = pod_plan_decode(s.cus, s.B, s.Hkv, s.P, s.max_len, 0, 0, false, false, false, reader);
+        const int rows = small.nc + 1;
+        four = xcd_pairs * rows <= xcd_cus &&
+               (rows <= kHeadRows || (s.D == 64 && rows <= 32 && (s.rep <= 2 || pl.nc + 1 > kHeadRows)));
+        if (four) { pl = small; pl.merge_inside = true; }
+    }
+    // The even split (decode_even_kernel) for plain launches whose lengths the host knows: one round of two workgroups per CU, every workgroup
+    // the same number of kUnit-token units.  It takes launches of several rounds, and of those that would merge fixed pieces inside ...
+    const int even_mode = reuse_step ? 2 : 0;
+    pod_even_plan_t ev = {0, 0, 0, 0};
+    bool padded = false;
+    const bool can_even = s.lens && s.even_split && (!s.scores || reader) && !four &&
+                          pod_plan_even_launch(2 * s.cus, s.B, s.Hkv, s.P, even_unit_distant(even_mode), s.lens, unit_cum, &ev, &padded);
+    const int even_rows = can_even ? ev.most + (s.step ? 1 : 0) : 0;
+    // (a batch of one very long and many short sequences cuts the long one into more parts than fixed pieces
+    // would: where the caller's scratch does not hold them the launch keeps to fixed pieces)
+    const bool even_fits = can_even && (size_t)npairs * s.rep * (size_t)even_rows * (s.D + 2) * sizeof(float) <= s.ws_bytes;
+    if (pl.merge_inside && even_fits && !s.scores && s.fused_merge && s.tune_chunk <= 0 && s.tune_chunk_prox <= 0) {
+        long sum = 0;
+        for (int b = 0; b < s.B; ++b) sum += s.lens[b];
+        const long slots = (long)npairs * pl.nc;
+        const bool one_tile = pl.chunk <= kTile * pl.waves;
+        // ... those with more slots than CUs, whose second round costs as much as the first (per step, us, fixed -> even: 35 of 882 tokens x 16/4 x 64, 280 slots,
+        // 20.1 -> 14.3; 18 of 0.1-0.6K x 32/8 x 128 20.5 -> 13.9; at 272 slots of 68 pairs x 128 it is 16.6 -> 17.6) ...
+        const bool cheap = s.step || s.rep <= 4; // (attention without a step, whose merge is then a launch: 13 of 0.2-2.2K x 32/4 13.1 -> 14.3, 5 of 0.7-6.5K 13.5 -> 14.6)
+        bool take = slots > s.cus && cheap;
+        // ... more than 16 partials per pair with more query heads than the merging workgroup has waves, where so few workgroups merge them through
+        // memory (16/1 x 128: 2 of 14-27K 20.3 -> 16.3, 4 of 4-40K 21.4 -> 19.0, but 5 of 7K 14.3 -> 14.9, 7 of 2-4K 12.7 -> 13.3, 10 of 1-11K 16.4 -> 18.8);
+        take = take || (s.rep > 8 && pl.nc + (s.step ? 1 : 0) > 16 && 2 * npairs <= (s.nxcd > 0 ? s.nxcd : 1));
+        // ... lengths so different that an even share is shorter by more tokens than the even split's hand-over costs: 256 at head dimension 64, at 128 384 where
+        // it merges inside and 640 where not (saved tokens: 5 of 3.6-36K x 16/4 x 64 544: 30.3 -> 19.7; 7 of 0.5-5K x 32/8 x 128 467: 24.2 -> 21.0; 3 of 3-30K x 32/4 692: 28.8 -> 23.4, 17 of
+        // 0.3-3.4K 376: 21.6 -> 22.2, 6 of 0.6-6K 359: 13.1 -> 15.7);
+        const long saved = pl.chunk - sum * s.Hkv / s.cus;
+        take = take || (!one_tile && cheap && saved > (s.D == 64 ? 256 : s.rep <= 4 ? 384 : 640));
+        // ... and at head dimension 64, where its tile loop is the faster one and its hand-over cheap, long pieces (4 of 19K x 16/4 19.2 -> 16.7, 3 of 49K 35.2 -> 28.8,
+        // but 2 of 59K, 64 partials per pair, 22.7 -> 24.6; without a step 10 of 13K 32.7 -> 25.6, but 9 of 4-7.6K, pieces of 1088, 13.6 -> 14.8, and 32 of 1-2K x 8/8 in one
+        // piece each 21.0 -> 23.8), and steps without room for a workgroup of their own where it leaves few partials per pair
+        // (11 of 0.6-1.2K 9.6 -> 8.6; but 2 of 18K, 47 partials, 11.9 -> 13.5).
+        take = take || (s.D == 64 && ((pl.nc > 1 && pl.chunk > (s.step ? 1024 : 1536) && even_rows <= 48) || (s.step && !host_fits(pl) && even_rows <= 16)));
+        if (take) pl = pod_plan_decode(s.cus, s.B, s.Hkv, s.P, s.max_len, 0, 0, false, false, false);
+    }
+    // (score reuse: the decode step of a layer none of whose kv heads starts a block.  A layer that writes the logits
+    // gains nothing from it: 16 sequences 218 us either way, 4 x 128K tokens 399 against 387 us.)
+    bool even_merge = false;
+    const bool even = !pl.merge_inside && even_fits;
+    if (even) {
+        // Where no workgroup crosses, each hands over once, at its end, and the last of a pair's merges: up to 4 query heads per kv head, and 8
+        // with no more than 16 partials, that costs less than the second launch.  Requests, us, second launch -> inside: 32 chats
+        // x 16/4 x 64 1294 -> 1194, 4 of 3-30K x 8/8 x 64 898 -> 846, 28 of 0.3-3.6K at 1, 2, 4, 8 and 16 query heads per kv
+        // head (4 x 64) 642 -> 613, 649 -> 623, 664 -> 624, 686 -> 676, 766 -> 795; 8 heads x 64 at 8 each, 4 of 3-30K (22 partials) 906 -> 911.  Per step at head
+        // dimension 128: 4 of 0.5-5K x 32/8 17.0 -> 15.7, 8 of 5-10K 49.5 -> 47.9; x 32/4 18 of 0.1-0.9K 14.2 -> 12.5, but 1 of 8K (36 partials) 13.3 -> 18.7; x 16/1
+        // 19 of 6-12K 24.0 -> 26.3.
+        even_merge = padded && s.fused_merge && even_mode == 0 && (s.rep <= 4 || (s.rep <= 8 && even_rows <= 16));
+        if (!s.step) // (an empty sequence has no workgroup that would write its rows)
+            for (int b = 0; b < s.B; ++b) even_merge = even_merge && s.lens[b] > 0;
+    }
+    const bool loc = loc_of(pl), own_host = s.step && pl.merge_inside && host_fits(pl);
+    return {pl, ev, four, even, padded, even_merge, loc, own_host};
+}
+
 int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *q_shared, const int32_t *ctx, int B,
                       int max_len, float scale, void *ws, size_t ws_bytes, void *scores, float tau, void *out,
                       hipStream_t st, const pod_step_args *step)
@@ -2072,82 +2168,17 @@ int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *
     // the reading launch (the others); a layer with heads of both kinds takes both.  (No gated form.)
     const bool reuse_step = step && scores;
     if (reuse_step && tau >= 0.f) return pod_fail(POD_ERR_INVALID_ARG, "a decode step has no gated form");
-    pod_decode_plan_t pl = pod_plan_decode(cus, B, ly.Hkv, ly.P, max_len, c->tune_chunk, c->tune_chunk_prox, scores && !reuse_step,
-                                                 scores && !lowest_all && tau >= 0.f, c->fused_merge != 0, reuse_step && !lowest_any);
-    // Small launches that merge inside one XCD's L2: workgroups of four waves instead of eight where all of them still get a CU.  A launch of one
-    // tile per wave is then spread over twice the CUs, and ends sooner by the half of what each of them has to load and to bring together.
-    // At head dimension 128 as long as a pair has no more than the 8 rows that a head's one lane group merges; at 64, where that costs
-    // less, also where eight waves leave more than these 8, and with up to two query heads per kv head.  Per step, us, eight -> four waves: 32/8 x 128
-    // at 300 tokens 7.8 -> 6.6, 777 7.9 -> 6.9; 32/4 8.4 -> 7.4, but at 1100 (10 rows) 8.4 -> 8.8; 16/1 9.8 -> 8.9, 10.1 -> 10.6; 16/4 x 64 777 6.9 -> 6.2, 1500 (13 rows instead
-    // of 7) 6.8 -> 7.2, 3600 8.0 -> 7.6; 4/2 x 64 2048 7.3 -> 6.5, 3600 7.3 -> 6.8.
-    bool four = false;
-    const long xcd_cus = c->nxcd >= 1 ? cus / c->nxcd : 0, xcd_pairs = c->nxcd >= 1 ? (npairs + c->nxcd - 1) / c->nxcd : 0;
-    if (pl.merge_inside && c->xcd_local && c->nxcd >= 1 && c->tune_chunk <= 0 && c->tune_chunk_prox <= 0) {
-        const pod_decode_plan_t small = pod_plan_decode(cus, B, ly.Hkv, ly.P, max_len, 0, 0, false, false, false, reuse_step && !lowest_any);
-        const int rows = small.nc + 1;
-        four = xcd_pairs * rows <= xcd_cus &&
-               (rows <= kHeadRows || (ly.D == 64 && rows <= 32 && (ly.rep <= 2 || pl.nc + 1 > kHeadRows)));
-        if (four) { pl = small; pl.merge_inside = true; }
-    }
-    // The even split (decode_even_kernel) for plain launches whose lengths the host knows: one round of two workgroups per CU, every workgroup
-    // the same number of kUnit-token units.  It takes launches of several rounds, and of those that would merge fixed pieces inside ...
+    const pod_decode_shape_t shape = {cus, c->nxcd, B, ly.Hkv, ly.rep, ly.D, ly.P, max_len, p.hot.use_hlen ? p.hlen : nullptr, ws_bytes,
+                                      step != nullptr, scores != nullptr, p.mode == 3, lowest_all, lowest_any,
+                                      c->xcd_local, c->fused_merge, c->even_split, c->tune_chunk, c->tune_chunk_prox};
+    const pod_decode_choice_t ch = pod_choose_decode(shape, p.unit_cum);
+    const pod_decode_plan_t &pl = ch.pl;
+    const bool merge_inside = pl.merge_inside, four = ch.four, even = ch.even, even_merge = ch.even_merge, loc = ch.loc, own_host = ch.own_host;
     const int even_mode = reuse_step ? 2 : 0;
-    pod_even_plan_t ev;
-    bool padded = false;
-    const bool can_even = p.hot.use_hlen && c->even_split && (p.mode == 0 || (reuse_step && !lowest_any)) && !four &&
-                          pod_plan_even_launch(2 * cus, B, H, ly.P, even_unit_distant(even_mode), p.hlen, p.unit_cum, &ev, &padded);
-    const int even_rows = can_even ? ev.most + (step ? 1 : 0) : 0;
-    // (a batch of one very long and many short sequences cuts the long one into more parts than fixed pieces
-    // would: where the caller's scratch does not hold them the launch keeps to fixed pieces)
-    const bool even_fits = can_even && (size_t)B * ly.Hq * (size_t)even_rows * (ly.D + 2) * sizeof(float) <= ws_bytes;
-    if (pl.merge_inside && even_fits && p.mode == 0 && c->fused_merge && c->tune_chunk <= 0 && c->tune_chunk_prox <= 0) {
-        long sum = 0;
-        for (int b = 0; b < B; ++b) sum += p.hlen[b];
-        const long slots = (long)npairs * pl.nc;
-        const bool one_tile = pl.chunk <= kTile * pl.waves;
-        const bool host_fits = c->xcd_local && c->nxcd >= 1 && (npairs % c->nxcd == 0 || npairs >= 8 * c->nxcd || xcd_pairs * pl.nc <= xcd_cus)
-                                   ? xcd_pairs * (pl.nc + 1) <= xcd_cus : slots + npairs <= cus;
-        // ... those with more slots than CUs, whose second round costs as much as the first (per step, us, fixed -> even: 35 of 882 tokens x 16/4 x 64, 280 slots,
-        // 20.1 -> 14.3; 18 of 0.1-0.6K x 32/8 x 128 20.5 -> 13.9; at 272 slots of 68 pairs x 128 it is 16.6 -> 17.6) ...
-        const bool cheap = step || ly.rep <= 4; // (attention without a step, whose merge is then a launch: 13 of 0.2-2.2K x 32/4 13.1 -> 14.3, 5 of 0.7-6.5K 13.5 -> 14.6)
-        bool take = slots > cus && cheap;
-        // ... more than 16 partials per pair with more query heads than the merging workgroup has waves, where so few workgroups merge them through
-        // memory (16/1 x 128: 2 of 14-27K 20.3 -> 16.3, 4 of 4-40K 21.4 -> 19.0, but 5 of 7K 14.3 -> 14.9, 7 of 2-4K 12.7 -> 13.3, 10 of 1-11K 16.4 -> 18.8);
-        take = take || (ly.rep > 8 && pl.nc + (step ? 1 : 0) > 16 && 2 * npairs <= p.nxcd);
-        // ... lengths so different that an even share is shorter by more tokens than the even split's hand-over costs: 256 at head dimension 64, at 128 384 where
-        // it merges inside and 640 where not (saved tokens: 5 of 3.6-36K x 16/4 x 64 544: 30.3 -> 19.7; 7 of 0.5-5K x 32/8 x 128 467: 24.2 -> 21.0; 3 of 3-30K x 32/4 692: 28.8 -> 23.4, 17 of
-        // 0.3-3.4K 376: 21.6 -> 22.2, 6 of 0.6-6K 359: 13.1 -> 15.7);
-        const long saved = pl.chunk - sum * H / cus;
-        take = take || (!one_tile && cheap && saved > (ly.D == 64 ? 256 : ly.rep <= 4 ? 384 : 640));
-        // ... and at head dimension 64, where its tile loop is the faster one and its hand-over cheap, long pieces (4 of 19K x 16/4 19.2 -> 16.7, 3 of 49K 35.2 -> 28.8,
-        // but 2 of 59K, 64 partials per pair, 22.7 -> 24.6; without a step 10 of 13K 32.7 -> 25.6, but 9 of 4-7.6K, pieces of 1088, 13.6 -> 14.8, and 32 of 1-2K x 8/8 in one
-        // piece each 21.0 -> 23.8), and steps without room for a workgroup of their own where it leaves few partials per pair
-        // (11 of 0.6-1.2K 9.6 -> 8.6; but 2 of 18K, 47 partials, 11.9 -> 13.5).
-        take = take || (ly.D == 64 && ((pl.nc > 1 && pl.chunk > (step ? 1024 : 1536) && even_rows <= 48) || (step && !host_fits && even_rows <= 16)));
-        if (take) pl = pod_plan_decode(cus, B, ly.Hkv, ly.P, max_len, 0, 0, false, false, false);
-    }
-    const bool merge_inside = pl.merge_inside;
     p.hot.chunk = (int)((unsigned)pl.chunk | ((unsigned)pl.chunk_p << 16));
-    p.hot.max_nd = pl.max_nd;
-    p.hot.nc = pl.nc;
-    p.bal_q = 0; p.bal_nwg = 0; p.bal_total = 0;
-    // (score reuse: the decode step of a layer none of whose kv heads starts a block.  A layer that writes the logits
-    // gains nothing from it: 16 sequences 218 us either way, 4 x 128K tokens 399 against 387 us.)
-    bool even_merge = false;
-    const bool even = !merge_inside && even_fits;
-    if (even) {
-        // Where no workgroup crosses, each hands over once, at its end, and the last of a pair's merges: up to 4 query heads per kv head, and 8
-        // with no more than 16 partials, that costs less than the second launch.  Requests, us, second launch -> inside: 32 chats
-        // x 16/4 x 64 1294 -> 1194, 4 of 3-30K x 8/8 x 64 898 -> 846, 28 of 0.3-3.6K at 1, 2, 4, 8 and 16 query heads per kv
-        // head (4 x 64) 642 -> 613, 649 -> 623, 664 -> 624, 686 -> 676, 766 -> 795; 8 heads x 64 at 8 each, 4 of 3-30K (22 partials) 906 -> 911.  Per step at head
-        // dimension 128: 4 of 0.5-5K x 32/8 17.0 -> 15.7, 8 of 5-10K 49.5 -> 47.9; x 32/4 18 of 0.1-0.9K 14.2 -> 12.5, but 1 of 8K (36 partials) 13.3 -> 18.7; x 16/1
-        // 19 of 6-12K 24.0 -> 26.3.
-        even_merge = padded && c->fused_merge && even_mode == 0 && (ly.rep <= 4 || (ly.rep <= 8 && even_rows <= 16));
-        if (!step) // (an empty sequence has no workgroup that would write its rows)
-            for (int b = 0; b < B; ++b) even_merge = even_merge && p.hlen[b] > 0;
-        p.bal_q = ev.q; p.bal_total = ev.total; p.bal_nwg = ev.nwg;
-        p.hot.nc = ev.most; p.hot.max_nd = ev.most;
-    }
+    p.hot.max_nd = even ? ch.ev.most : pl.max_nd;
+    p.hot.nc = even ? ch.ev.most : pl.nc;
+    p.bal_q = even ? ch.ev.q : 0; p.bal_total = even ? ch.ev.total : 0; p.bal_nwg = even ? ch.ev.nwg : 0;
     const size_t NC = (size_t)p.hot.nc + (step ? 1 : 0); // partial slots per query head (a step keeps one more)
     const size_t acc_bytes = (size_t)B * ly.Hq * NC * ly.D * sizeof(float);
     const size_t ml_bytes = (size_t)B * ly.Hq * NC * 2 * sizeof(float);
@@ -2158,21 +2189,6 @@ int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *
     p.hot.part_ml = (float *)((char *)ws + acc_bytes);
 
     const int fuse = step ? (merge_inside ? 2 : 3) : (merge_inside ? 1 : 0);
-    // XCD-local hand-off: where the pairs spread evenly over the XCDs (else some would sit idle while others stream), or where
-    // they are so few and short that each XCD's pieces have a CU each: the launch is then its latency, and one L2 hands a
-    // partial over sooner than memory does (per step: 2 pairs x 64 at 2048 tokens 7.05 -> 6.61 us, 3 pairs x 128 with 8 query
-    // heads 10.4 -> 9.1, 1 pair x 128 with 16 13.8 -> 11.2; at the line, 31 pieces of 256 tokens x 128 on one XCD, 18.1 either way).
-    const bool loc = merge_inside && c->xcd_local && c->nxcd >= 1 &&
-                     (npairs % c->nxcd == 0 || npairs >= 8 * c->nxcd || xcd_pairs * p.hot.nc <= xcd_cus);
-    // The step's own workgroup: the new token's chain of short dependent accesses then runs beside the pieces instead of in front
-    // of one.  XCD-local launches have one where every workgroup of the XCD still gets a CU (2 pairs x 64 at 2048 tokens
-    // 8.92 -> 7.05 us, 8 pairs x 128 at 2048 9.8 -> 8.3), launches that hand over through memory where every workgroup of the
-    // chip does; full ones keep the host inside, where one more workgroup would wait for a CU.  32 steps of a layer through memory,
-    // us, without -> with: plain x 128, 2 pairs at 14000 tokens (114 workgroups) 410 -> 373, 7 pairs at 20000 (252) 579 -> 557,
-    // 1 pair with 16 heads at 60000 (236) 1577 -> 1580; score reuse x 64, 3 pairs at 14000 (168) 343 -> 334.  Score reuse x 128 stops at
-    // half of the CUs: 2 pairs at 14000 405 -> 392, but 2 pairs at 20000 (162) 455 -> 461 and 3 at 14000 (171) 372 -> 382.
-    const int host_room = reuse_step && ly.D == 128 ? cus / 2 : cus;
-    const bool own_host = fuse == 2 && (loc ? xcd_pairs * (p.hot.nc + 1) <= xcd_cus : (long)npairs * (p.hot.nc + 1) <= host_room);
     if (own_host && !reuse_step) p.hot.use_hlen |= 2;
     const size_t WGS = (size_t)p.hot.nc + (own_host ? 1 : 0);   // workgroups per (sequence, kv head) pair
     p.slots = (int32_t)WGS;

@@ -207,6 +207,19 @@ struct pod_even_plan_t { int32_t q, nwg, total, most; };
 bool pod_plan_even(int slots, int B, int Hkv, int P, int unit_d, const int32_t *lens, int32_t *unit_cum, pod_even_plan_t *pl);
 // ... as the launch takes it: with every pair's units padded to whole workgroups where that fits (*padded)
 bool pod_plan_even_launch(int slots, int B, int Hkv, int P, int unit_d, const int32_t *lens, int32_t *unit_cum, pod_even_plan_t *pl, bool *padded);
+// what the launch of a decode call depends on, and how it is launched (host logic, pod_decode.hip): fixed pieces (four: workgroups of four waves that
+// merge inside) or the even split, merged inside or by a second kernel, handed over inside one XCD's L2 (loc) or through memory, a step in a
+// workgroup of its own or not.  lens: tokens each sequence holds (for a step before it), NULL where the host does not know; gated, scores, lowest_*: as
+// pod_launch_decode's arguments and layer have it; the rest as in pod_cache.
+struct pod_decode_shape_t {
+    int cus, nxcd, B, Hkv, rep, D, P, max_len;
+    const int32_t *lens;
+    size_t ws_bytes;
+    bool step, scores, gated, lowest_all, lowest_any, xcd_local, fused_merge, even_split;
+    int tune_chunk, tune_chunk_prox;
+};
+struct pod_decode_choice_t { pod_decode_plan_t pl; pod_even_plan_t ev; bool four, even, padded, even_merge, loc, own_host; };
+pod_decode_choice_t pod_choose_decode(const pod_decode_shape_t &s, int32_t *unit_cum);
 int pod_launch_decode(const pod_cache *c, int layer, const void *q, const void *q_shared,
                       const int32_t *ctx, int B, int max_len, float scale, void *ws, size_t ws_bytes,
                       void *scores, float tau, void *out, hipStream_t st, const pod_step_args *step = nullptr);

@@ -1,0 +1,75 @@
+"""How a decode call is launched (host logic, no GPU): pod_decode_launch_plan, the choice that pod_launch_decode makes."""
+import numpy as np
+import pytest
+
+import paper_2412_02252_amd as pod
+
+CUS, XCDS = 256, 8
+
+
+def launch(Hq, Hkv, d, P, lens, call=pod.CALL_STEP, **kw):
+    return pod.pod_decode_launch_plan(CUS, XCDS, Hq, Hkv, d, P, lens, call, **kw)
+
+
+def form(pl):
+    return ("even" if pl["even"] else "fixed", "inside" if pl["merge_inside"] else "second launch", pl["waves"])
+
+
+@pytest.mark.parametrize("seed", range(40))
+def test_the_choice_agrees_with_the_plans_it_is_made_of(seed):
+    """Fixed pieces of eight waves are pod_decode_plan's, the even split is pod_decode_even_launch's; who merges, who hands over inside one XCD and
+    which scratch suffices follow from that."""
+    rng = np.random.default_rng(8100 + seed)
+    for _ in range(60):
+        Hkv, rep, d = int(rng.choice([1, 2, 3, 4, 8, 16])), int(rng.choice([1, 2, 4, 5, 8, 16])), int(rng.choice([64, 128]))
+        P, B = int(rng.choice([40, 272, 2112])), int(rng.choice([1, 1, 2, 3, 8, 17, 40, 200]))
+        hi = int(2 ** rng.uniform(0, 17))
+        lens = [int(x) for x in rng.integers(max(0, int(hi * rng.choice([0, 0.1, 0.9]))), hi + 1, size=B)]
+        call, known = int(rng.integers(0, 4)), bool(rng.integers(0, 8))
+        pl = launch(Hkv * rep, Hkv, d, P, lens, call, lens_known=known)
+        what = (Hkv, rep, d, P, lens, call, known, pl)
+        step, bound = call != pod.CALL_ATTENTION, max(max(lens) + (call != pod.CALL_ATTENTION), 1)
+        plain = call in (pod.CALL_ATTENTION, pod.CALL_STEP)
+        fixed = pod.pod_decode_plan(CUS, B, Hkv, P, bound)
+        if pl["even"]:
+            ev = pod.pod_decode_even_launch(CUS, Hkv, P, lens, 128 if plain else 256)
+            assert known and call != pod.CALL_REUSE_FIRST and pl["waves"] == 4 and not pl["xcd_local"], what
+            assert pl["units_per_workgroup"] == ev["units_per_workgroup"] and pl["partials"] == ev["partials_per_pair"] + step, what
+            assert pl["padded"] == ev["padded"] and pl["own_workgroup"] == step, what
+            assert not pl["merge_inside"] or (pl["padded"] and plain and (step or min(lens) > 0)), what
+            # in less scratch than its partials take the launch keeps to fixed pieces
+            need = B * Hkv * rep * pl["partials"] * (d + 2) * 4
+            assert launch(Hkv * rep, Hkv, d, P, lens, call, workspace_bytes=need)["even"]
+            assert not launch(Hkv * rep, Hkv, d, P, lens, call, workspace_bytes=need - 1)["even"]
+        else:
+            pieces = pl["partials"] - step
+            assert pl["merge_inside"] or not (pl["xcd_local"] or pl["own_workgroup"] or pl["waves"] == 8), what
+            assert step or not pl["own_workgroup"], what
+            if pl["waves"] == 8 and plain:
+                assert fixed["merge_inside"] and (pl["chunk"], pl["chunk_prox"], pieces) == (fixed["chunk"], fixed["chunk_prox"], fixed["pieces"]), what
+            if pl["waves"] == 4 and pl["merge_inside"]: # a small launch: a CU for each of an XCD's workgroups
+                assert pl["xcd_local"] and -(-B * Hkv // XCDS) * pl["partials"] <= CUS // XCDS, what
+            if pl["own_workgroup"]:
+                assert B * Hkv * pl["partials"] <= (-(-B * Hkv // XCDS) * XCDS * (CUS // XCDS) if pl["xcd_local"] else CUS), what
+
+
+def test_forms_of_usual_calls():
+    chats = [300 + 122 * i for i in range(28)]
+    assert form(launch(4, 2, 64, 272, [2048])) == ("fixed", "inside", 4)
+    assert form(launch(32, 8, 128, 2112, [32768])) == ("fixed", "inside", 8)
+    assert form(launch(16, 4, 64, 528, chats)) == ("even", "inside", 4)
+    assert form(launch(32, 8, 128, 2112, [4000 + 1800 * i for i in range(16)])) == ("even", "second launch", 4)
+    assert form(launch(32, 8, 128, 2112, [32768], pod.CALL_REUSE_FIRST)) == ("fixed", "inside", 8)
+    assert form(launch(32, 8, 128, 4224, [131072] * 4, pod.CALL_REUSE_FIRST)) == ("fixed", "second launch", 4)
+    assert form(launch(32, 8, 128, 4224, [131072] * 4, pod.CALL_REUSE_UPPER)) == ("even", "second launch", 4)
+    assert form(launch(16, 4, 64, 528, chats, lens_known=False)) == ("fixed", "second launch", 4)
+
+
+def test_bad_arguments_are_rejected():
+    good = dict(num_cus=CUS, num_xcds=XCDS, num_q_heads=8, num_kv_heads=2, head_dim=64, proximal_rows=72, context_lens=[100])
+    pod.pod_decode_launch_plan(**good)
+    for bad in (dict(num_cus=0), dict(num_xcds=-1), dict(num_q_heads=7), dict(num_q_heads=34), dict(num_kv_heads=0), dict(head_dim=96),
+                dict(proximal_rows=0), dict(call=4), dict(call=-1), dict(max_context_len=-1), dict(context_lens=[100] * 257)):
+        with pytest.raises(pod.PodError) as e:
+            pod.pod_decode_launch_plan(**{**good, **bad})
+        assert e.value.code == pod.binding.ERR_INVALID_ARG
