@@ -2036,16 +2036,17 @@ pod_decode_choice_t pod_choose_decode(const pod_decode_shape_t &s, int32_t *unit
                                            s.gated && !s.lowest_all, s.fused_merge, reader);
     // Small launches that merge inside one XCD's L2: workgroups of four waves instead of eight where all of them still get a CU.  A launch of one
     // tile per wave is then spread over twice the CUs, and ends sooner by the half of what each of them has to load and to bring together.
-    // At head dimension 128 as long as a pair has no more than the 8 rows that a head's one lane group merges; at 64, where that costs
-    // less, also where eight waves leave more than these 8, and with up to two query heads per kv head.  Per step, us, eight -> four waves: 32/8 x 128
+    // As long as a pair has no more than the 8 rows that a head's one lane group merges; at head dimension 64, where more rows cost less, up to 32 with one or two
+    // query heads per kv head, and with three or four where eight waves leave more than these 8 too.  Per step, us, eight -> four waves: 32/8 x 128
     // at 300 tokens 7.8 -> 6.6, 777 7.9 -> 6.9; 32/4 8.4 -> 7.4, but at 1100 (10 rows) 8.4 -> 8.8; 16/1 9.8 -> 8.9, 10.1 -> 10.6; 16/4 x 64 777 6.9 -> 6.2, 1500 (13 rows instead
-    // of 7) 6.8 -> 7.2, 3600 8.0 -> 7.6; 4/2 x 64 2048 7.3 -> 6.5, 3600 7.3 -> 6.8.
+    // of 7) 6.8 -> 7.2, 3600 8.0 -> 7.6; 4/2 x 64 2048 7.3 -> 6.5, 3600 7.3 -> 6.8.  With more query heads the four waves merge one after the other: x 64, 32/4 at 3055 (24 rows, attention)
+    // 8.0 -> 8.8, 40/5 at 2493 7.7 -> 8.5, 16/1 at 3130 9.1 -> 10.2 (over 80 drawn shapes of 6, 8 and 16 with 9 to 32 rows 0.83-0.99 of the rate of eight waves).
     bool four = false;
     if (pl.merge_inside && s.xcd_local && s.nxcd >= 1 && s.tune_chunk <= 0 && s.tune_chunk_prox <= 0) {
         const pod_decode_plan_t small = pod_plan_decode(s.cus, s.B, s.Hkv, s.P, s.max_len, 0, 0, false, false, false, reader);
-        const int rows = small.nc + 1;
+        const int own = s.step ? 1 : 0, rows = small.nc + own;
         four = xcd_pairs * rows <= xcd_cus &&
-               (rows <= kHeadRows || (s.D == 64 && rows <= 32 && (s.rep <= 2 || pl.nc + 1 > kHeadRows)));
+               (rows <= kHeadRows || (s.D == 64 && rows <= 32 && (s.rep <= 2 || (s.rep <= 4 && pl.nc + own > kHeadRows))));
         if (four) { pl = small; pl.merge_inside = true; }
     }
     // The even split (decode_even_kernel) for plain launches whose lengths the host knows: one round of two workgroups per CU, every workgroup

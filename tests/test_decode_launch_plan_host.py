@@ -65,6 +65,23 @@ def test_forms_of_usual_calls():
     assert form(launch(16, 4, 64, 528, chats, lens_known=False)) == ("fixed", "second launch", 4)
 
 
+@pytest.mark.parametrize("d,Hq,Hkv,call,n,waves", [
+    (128, 32, 8, pod.CALL_ATTENTION, 1000, 4),  # 8 pieces: attention keeps no row for a step ...
+    (128, 32, 8, pod.CALL_STEP, 1000, 8),       # ... and a step has 9
+    (128, 32, 8, pod.CALL_ATTENTION, 1025, 8),  # 9 pieces
+    (64, 40, 5, pod.CALL_ATTENTION, 1000, 4),   # 8 rows: any number of query heads
+    (64, 40, 5, pod.CALL_ATTENTION, 2493, 8),   # 20 rows, 8 query heads per kv head: eight waves merge them sooner
+    (64, 16, 1, pod.CALL_STEP, 2007, 8),
+    (64, 6, 1, pod.CALL_REUSE_FIRST, 2007, 8),
+    (64, 16, 4, pod.CALL_STEP, 2493, 4),        # four: sooner than eight waves' 11 rows
+    (64, 16, 4, pod.CALL_STEP, 1500, 8),        # eight waves leave 7
+    (64, 4, 2, pod.CALL_STEP, 1500, 4),
+])
+def test_which_small_launches_run_workgroups_of_four_waves(d, Hq, Hkv, call, n, waves):
+    pl = launch(Hq, Hkv, d, 256, [n], call)
+    assert form(pl) == ("fixed", "inside", waves), pl
+
+
 def test_bad_arguments_are_rejected():
     good = dict(num_cus=CUS, num_xcds=XCDS, num_q_heads=8, num_kv_heads=2, head_dim=64, proximal_rows=72, context_lens=[100])
     pod.pod_decode_launch_plan(**good)
