@@ -557,8 +557,8 @@ int pod_decode_even_plan(int num_cus, int batch, int num_kv_heads, int proximal_
  * Host logic, no device needed: the split such a launch really takes.  The same, but with 128-token distant units every
  * pair's units are padded to a multiple of plan[0] where all workgroups still fit one round (2 num_cus): then plan[4] is 1, unit_cum
  * and plan[2] count the padding, no workgroup walks rows of two pairs, every pair that holds a token has
- * (unit_cum[b + 1] - unit_cum[b]) / plan[0] workgroups, each with rows of its own, and with at most four query heads per
- * kv head, or eight and at most 16 partials per pair (and no empty sequence, or a decode step), the last of them merges the pair's partials
+ * (unit_cum[b + 1] - unit_cum[b]) / plan[0] workgroups, each with rows of its own, and where a pair's partials times its query heads
+ * are few (pod_decode_launch_plan tells; and no sequence is empty, or it is a decode step) the last of them merges the pair's partials
  * inside the launch.  plan[4] is 0 where pod_decode_even_plan's split is taken as it is.
  */
 int pod_decode_even_launch(int num_cus, int batch, int num_kv_heads, int proximal_rows, int distant_unit_tokens,

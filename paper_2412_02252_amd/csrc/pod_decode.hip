@@ -2060,6 +2060,16 @@ pod_decode_choice_t pod_choose_decode(const pod_decode_shape_t &s, int32_t *unit
     // (a batch of one very long and many short sequences cuts the long one into more parts than fixed pieces
     // would: where the caller's scratch does not hold them the launch keeps to fixed pieces)
     const bool even_fits = can_even && (size_t)npairs * s.rep * (size_t)even_rows * (s.D + 2) * sizeof(float) <= s.ws_bytes;
+    // Where no workgroup crosses, each hands over once, at its end, and the last of a pair's merges all its query heads' partials: one CU, so the line is how many
+    // these are.  Up to 128 (with up to four query heads per kv head 192, and 272 at head dimension 64), no more than 96 of a head, that costs less than the second launch.
+    // Requests, us, second launch -> inside: 32 chats x 16/4 x 64 1294 -> 1194, 4 of 3-30K x 8/8 x 64 898 -> 846.  Per step at head dimension 128: 4 of 0.5-5K x 32/8
+    // 17.0 -> 15.7, 8 of 5-10K 49.5 -> 47.9; one of 259K (260 partials) 165.5 -> 167.7, of 193K x 16/4 (504) 66.2 -> 68.5.  Mean gain of one launch in 2307 drawn ones, us, by
+    // the partials of a pair, up to 64 / 128 / 192 / 256 / 384: one to four query heads x 64 +1.6 +1.4 +0.8 0.0 -0.8 (four alone, 193 to 272: +0.9), x 128 +1.5 +1.1 +0.5 -0.2 -1.8;
+    // five to eight x 64 +1.9 +0.7 +0.2 0.0 0.0, x 128 +1.8 +0.3 +0.3 -0.3 -1.4; sixteen x 64 +2.6 +1.8 -0.4 -0.5 -1.6, x 128 +2.8 +1.1 -1.6 -1.7 -1.8.
+    const int merge_room = s.rep > 4 ? 128 : s.D == 64 ? 272 : 192;
+    bool even_merge = can_even && padded && s.fused_merge && even_mode == 0 && s.rep * even_rows <= merge_room && even_rows <= 96;
+    if (!s.step) // (an empty sequence has no workgroup that would write its rows)
+        for (int b = 0; b < s.B && even_merge; ++b) even_merge = s.lens[b] > 0;
     if (pl.merge_inside && even_fits && !s.scores && s.fused_merge && s.tune_chunk <= 0 && s.tune_chunk_prox <= 0) {
         long sum = 0;
         for (int b = 0; b < s.B; ++b) sum += s.lens[b];
@@ -2086,19 +2096,8 @@ pod_decode_choice_t pod_choose_decode(const pod_decode_shape_t &s, int32_t *unit
     }
     // (score reuse: the decode step of a layer none of whose kv heads starts a block.  A layer that writes the logits
     // gains nothing from it: 16 sequences 218 us either way, 4 x 128K tokens 399 against 387 us.)
-    bool even_merge = false;
     const bool even = !pl.merge_inside && even_fits;
-    if (even) {
-        // Where no workgroup crosses, each hands over once, at its end, and the last of a pair's merges: up to 4 query heads per kv head, and 8
-        // with no more than 16 partials, that costs less than the second launch.  Requests, us, second launch -> inside: 32 chats
-        // x 16/4 x 64 1294 -> 1194, 4 of 3-30K x 8/8 x 64 898 -> 846, 28 of 0.3-3.6K at 1, 2, 4, 8 and 16 query heads per kv
-        // head (4 x 64) 642 -> 613, 649 -> 623, 664 -> 624, 686 -> 676, 766 -> 795; 8 heads x 64 at 8 each, 4 of 3-30K (22 partials) 906 -> 911.  Per step at head
-        // dimension 128: 4 of 0.5-5K x 32/8 17.0 -> 15.7, 8 of 5-10K 49.5 -> 47.9; x 32/4 18 of 0.1-0.9K 14.2 -> 12.5, but 1 of 8K (36 partials) 13.3 -> 18.7; x 16/1
-        // 19 of 6-12K 24.0 -> 26.3.
-        even_merge = padded && s.fused_merge && even_mode == 0 && (s.rep <= 4 || (s.rep <= 8 && even_rows <= 16));
-        if (!s.step) // (an empty sequence has no workgroup that would write its rows)
-            for (int b = 0; b < s.B; ++b) even_merge = even_merge && s.lens[b] > 0;
-    }
+    even_merge = even && even_merge;
     const bool loc = loc_of(pl), own_host = s.step && pl.merge_inside && host_fits(pl);
     return {pl, ev, four, even, padded, even_merge, loc, own_host};
 }

@@ -82,6 +82,27 @@ def test_which_small_launches_run_workgroups_of_four_waves(d, Hq, Hkv, call, n, 
     assert form(pl) == ("fixed", "inside", waves), pl
 
 
+@pytest.mark.parametrize("d,Hq,Hkv,lens,partials,inside", [ # partials per query head, without a step's
+    (128, 32, 8, [131072], 61, False),         # 4 x 61: one workgroup would merge 244
+    (128, 32, 8, [65536] * 2, 31, True),       # 4 x 31
+    (128, 16, 8, [131072], 61, True),          # 2 x 61
+    (128, 4, 1, [1000000], 489, False),
+    (128, 1, 1, [1000000], 489, False),        # one query head, but a chain of 489
+    (64, 32, 8, [131072], 61, True),           # head dimension 64: 4 x 62
+    (64, 32, 8, [88826], 64, True),            # 4 x 65, a whole chip's share for eight kv heads and a step's own
+    (64, 16, 4, [300000], 124, False),
+    (128, 32, 4, [600 + 20 * i for i in range(36)], 4, True),      # 8 x 4
+    (128, 32, 4, [40000] * 4, 32, False),      # 8 x 32
+    (128, 64, 4, [900 + 10 * i for i in range(40)], 3, True),      # 16 x 3
+    (128, 16, 1, [30000, 16000], 236, False),
+])
+def test_the_even_split_merges_inside_where_one_workgroup_has_few_partials(d, Hq, Hkv, lens, partials, inside):
+    for call in (pod.CALL_ATTENTION, pod.CALL_STEP):
+        pl = launch(Hq, Hkv, d, 272, lens, call)
+        assert pl["even"] and pl["padded"] and pl["partials"] == partials + (call == pod.CALL_STEP), pl
+        assert pl["merge_inside"] == inside, pl
+
+
 def test_bad_arguments_are_rejected():
     good = dict(num_cus=CUS, num_xcds=XCDS, num_q_heads=8, num_kv_heads=2, head_dim=64, proximal_rows=72, context_lens=[100])
     pod.pod_decode_launch_plan(**good)

@@ -161,12 +161,24 @@ def test_parts_of_whole_pairs_and_parts_that_cross(d, Hq, Hkv, B, lo, step, monk
     c.gpu.pod_cache_check()
 
 
-@pytest.mark.parametrize("Hq,Hkv,B,lo,step", [(8, 8, 24, 300, 37), (16, 4, 44, 130, 91), (6, 2, 80, 3, 77)])
-def test_parts_of_whole_pairs_merged_inside(Hq, Hkv, B, lo, step):
-    """Head dimension 64 and few query heads per kv head: the last part of a pair merges.  Steps, then the same attention again;
+def launched(c, lens, call=pod.CALL_STEP):
+    """How a call on sequences that hold `lens` tokens is launched on this device."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    return pod.pod_decode_launch_plan(cus, c.gpu.pod_cache_launch_info()["xcds"], c.Hq, c.Hkv, c.d, c.S + c.W, lens, call)
+
+
+@pytest.mark.parametrize("d,Hq,Hkv,B,lo,step", [(64, 8, 8, 24, 300, 37), (64, 16, 4, 44, 130, 91), (64, 6, 2, 80, 3, 77),
+                                                (128, 8, 8, 24, 300, 37), (128, 16, 4, 44, 130, 91), (128, 6, 2, 80, 3, 77),
+                                                (64, 32, 4, 44, 130, 91), (128, 30, 5, 30, 130, 91), (128, 32, 4, 44, 130, 91),
+                                                (64, 64, 4, 44, 130, 91), (128, 64, 4, 44, 130, 91)])
+def test_parts_of_whole_pairs_merged_inside(d, Hq, Hkv, B, lo, step):
+    """Few query heads' partials per pair: the last part of a pair merges.  Steps, then the same attention again;
     wrong lengths and positions, whose rows come out zero; a graph replayed three times."""
     lens = [lo + (step * i * i) % 900 for i in range(B)]
-    c = Case(2, 2, Hq, Hkv, 64, 8, 64, B, 1210, seed=9360 + B)
+    c = Case(2, 2, Hq, Hkv, d, 8, 64, B, 1210, seed=9360 + B)
+    for call in (pod.CALL_STEP, pod.CALL_ATTENTION):
+        pl = launched(c, lens, call)
+        assert pl["even"] and pl["merge_inside"], pl
     fill_all(c, lens)
     for s in range(2):
         pos = [n + s for n in lens]
@@ -203,7 +215,7 @@ def test_parts_of_whole_pairs_merged_inside(Hq, Hkv, B, lo, step):
     assert float(got[1].float().abs().max()) == 0.0
     keep = [i for i in range(B) if i != 1]
     assert_close(got[keep], refs[0][keep], "the other sequences")
-    k, v = torch.randn((2, B, Hkv, 64), device=c.dev).to(torch.bfloat16)
+    k, v = torch.randn((2, B, Hkv, d), device=c.dev).to(torch.bfloat16)
     bad = ctx_dev.clone()
     bad[2] += 1                                                              # sequence 2 holds one token less
     got = c.gpu.pod_decode_step(0, k, v, qs[0], None, bad, c.scale)
