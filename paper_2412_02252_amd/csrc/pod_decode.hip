@@ -2075,23 +2075,33 @@ pod_decode_choice_t pod_choose_decode(const pod_decode_shape_t &s, int32_t *unit
         for (int b = 0; b < s.B; ++b) sum += s.lens[b];
         const long slots = (long)npairs * pl.nc;
         const bool one_tile = pl.chunk <= kTile * pl.waves;
-        // ... those with more slots than CUs, whose second round costs as much as the first (per step, us, fixed -> even: 35 of 882 tokens x 16/4 x 64, 280 slots,
-        // 20.1 -> 14.3; 18 of 0.1-0.6K x 32/8 x 128 20.5 -> 13.9; at 272 slots of 68 pairs x 128 it is 16.6 -> 17.6) ...
-        const bool cheap = s.step || s.rep <= 4; // (attention without a step, whose merge is then a launch: 13 of 0.2-2.2K x 32/4 13.1 -> 14.3, 5 of 0.7-6.5K 13.5 -> 14.6)
-        bool take = slots > s.cus && cheap;
-        // ... more than 16 partials per pair with more query heads than the merging workgroup has waves, where so few workgroups merge them through
-        // memory (16/1 x 128: 2 of 14-27K 20.3 -> 16.3, 4 of 4-40K 21.4 -> 19.0, but 5 of 7K 14.3 -> 14.9, 7 of 2-4K 12.7 -> 13.3, 10 of 1-11K 16.4 -> 18.8);
-        take = take || (s.rep > 8 && pl.nc + (s.step ? 1 : 0) > 16 && 2 * npairs <= (s.nxcd > 0 ? s.nxcd : 1));
-        // ... lengths so different that an even share is shorter by more tokens than the even split's hand-over costs: 256 at head dimension 64, at 128 384 where
-        // it merges inside and 640 where not (saved tokens: 5 of 3.6-36K x 16/4 x 64 544: 30.3 -> 19.7; 7 of 0.5-5K x 32/8 x 128 467: 24.2 -> 21.0; 3 of 3-30K x 32/4 692: 28.8 -> 23.4, 17 of
-        // 0.3-3.4K 376: 21.6 -> 22.2, 6 of 0.6-6K 359: 13.1 -> 15.7);
-        const long saved = pl.chunk - sum * s.Hkv / s.cus;
-        take = take || (!one_tile && cheap && saved > (s.D == 64 ? 256 : s.rep <= 4 ? 384 : 640));
-        // ... and at head dimension 64, where its tile loop is the faster one and its hand-over cheap, long pieces (4 of 19K x 16/4 19.2 -> 16.7, 3 of 49K 35.2 -> 28.8,
-        // but 2 of 59K, 64 partials per pair, 22.7 -> 24.6; without a step 10 of 13K 32.7 -> 25.6, but 9 of 4-7.6K, pieces of 1088, 13.6 -> 14.8, and 32 of 1-2K x 8/8 in one
-        // piece each 21.0 -> 23.8), and steps without room for a workgroup of their own where it leaves few partials per pair
-        // (11 of 0.6-1.2K 9.6 -> 8.6; but 2 of 18K, 47 partials, 11.9 -> 13.5).
-        take = take || (s.D == 64 && ((pl.nc > 1 && pl.chunk > (s.step ? 1024 : 1536) && even_rows <= 48) || (s.step && !host_fits(pl) && even_rows <= 16)));
+        const long mean = sum * s.Hkv / s.cus, saved = pl.chunk - mean, longest = pl.chunk > pl.chunk_p ? pl.chunk : pl.chunk_p; // mean: tokens per CU
+        // ... those with more slots than CUs, whose second round costs as much as the first: per step, us, fixed -> even: 35 of 882 tokens x 16/4 x 64, 280 slots,
+        // 20.1 -> 14.3; 18 of 0.1-0.6K x 32/8 x 128 20.5 -> 13.9; 68 of 71 x 64/4 x 128 21.2 -> 19.0.  Where a second launch has to merge, attention with more than four
+        // query heads is left out (3 of 11-24K x 64/8 x 128 35.0 -> 37.0), and pairs of one piece with more than eight x 128 if they are short (79 of 0.2-0.4K x 64/4, 385 tokens per CU, 29.2 -> 32.2, 74 of 302
+        // 28.2 -> 30.7; but 66 of 0.6-0.7K, 692, 37.5 -> 36.4, 71 of 2K 79.2 -> 71.4, and x 64 34 of 0.4-0.8K x 128/8 24.0 -> 21.7) ...
+        const bool few_heads = s.step || s.rep <= 4;
+        const bool short_pairs = s.D == 128 && s.rep > 8 && pl.nc == 1 && mean < 576;
+        bool take = slots > s.cus && (even_merge || (few_heads && !short_pairs));
+        // ... many partials per pair with more query heads than the merging workgroup has waves, where so few workgroups merge them through
+        // memory (16/1 x 128: 2 of 14-27K 20.3 -> 16.3, 4 of 4-40K 21.4 -> 19.0, but 5 of 7K 14.3 -> 14.9, 7 of 2-4K 12.7 -> 13.3, 10 of 1-11K 16.4 -> 18.8); x 64 more than 32
+        // (2 of 13-14K 12.8 -> 12.1, attention of 2 of 7.3-8.8K, 36 pieces, 12.4 -> 11.2, but 4 of 4856, 20, 9.6 -> 11.6, one of 6066, 25, 9.8 -> 11.3);
+        take = take || (s.rep > 8 && pl.nc + (s.step ? 1 : 0) > (s.D == 64 ? 32 : 16) && npairs <= 4);
+        // ... lengths so different that an even share is shorter by more tokens than the even split's hand-over costs.  Merged inside: at head dimension 128 384
+        // with up to four query heads and 640 with more; at 64 256, 320 without a step, 384 with more than four.  By a second launch 640; at head dimension 64, there and with more than 48 partials,
+        // 700 of the longest piece, the proximal one among them, and 800 with sixteen.  (Saved tokens: 5 of 3.6-36K x 16/4 x 64 544: 30.3 -> 19.7; 7 of 0.5-5K x 32/8 x 128 467: 24.2 -> 21.0; 17 of
+        // 0.3-3.4K x 32/4 376: 21.6 -> 22.2, 6 of 0.6-6K 359: 13.1 -> 15.7; second launch: 8 of 5.5-6.1K x 32/8 x 128 501: 33.4 -> 35.3, 2 of 3.7-21.8K x 16/4 x 64 306: 12.4 -> 12.8, 4 of 11-22K
+        // x 80/5 x 64 732: 21.0 -> 24.1, 19 of 0.5-2.9K x 64/4 813: 16.1 -> 14.9; attention of 16 of 1159 x 8/8 x 64 317: 12.3 -> 13.5);
+        if (s.D == 64 && (!even_merge || even_rows > 48)) take = take || (!one_tile && few_heads && (s.rep > 8 ? saved > 800 : longest - mean > 700));
+        else take = take || (!one_tile && few_heads && saved > (s.D == 128 ? (even_merge && s.rep <= 4 ? 384 : 640) : s.rep > 4 ? 384 : s.step ? 256 : 320));
+        // ... and at head dimension 64, where its tile loop is the faster one and its hand-over cheap, what it merges inside: long pieces with up to four query heads (4 of 19K x 16/4 19.2 ->
+        // 16.7; 3 of 35-38K, 43 partials, 22.0 -> 23.3; without a step 8 of 32K x 4/2, 32 partials, 23.2 -> 24.5, 9 of 4-7.6K, pieces of 1088, 13.6 -> 14.8, and 32 of 1-2K x 8/8 in one
+        // piece each 21.0 -> 23.8; 7 of 34K x 16/2 21.6 -> 25.9), and steps without room for a workgroup of their own where it leaves few partials per pair
+        // (11 of 0.6-1.2K 9.6 -> 8.6; but 2 of 18K, 47 partials, 11.9 -> 13.5; with more than four query heads where it saves more than 64 tokens: 8 of 0.5-0.9K x 64/8 10.1 -> 9.5, 28 of 0.1-1.1K x
+        // 16/2 10.1 -> 9.8, but 21 of 2394 10.9 -> 11.6, 17 of 2.5-2.8K x 32/4 15.0 -> 15.5, 13 of 1.2-1.3K x 64/4, 7 partials, 10.9 -> 11.0, 3 of 1087 x 256/16, 11, 10.3 -> 13.2).
+        take = take || (s.D == 64 && even_merge &&
+                        ((s.rep <= 4 && pl.nc > 1 && pl.chunk > (s.step ? 1024 : 1536) && even_rows <= (s.step ? 32 : 16)) ||
+                         (s.step && !host_fits(pl) && even_rows <= 16 && (s.rep <= 4 || (s.rep * even_rows <= 96 && saved > 64)))));
         if (take) pl = pod_plan_decode(s.cus, s.B, s.Hkv, s.P, s.max_len, 0, 0, false, false, false);
     }
     // (score reuse: the decode step of a layer none of whose kv heads starts a block.  A layer that writes the logits

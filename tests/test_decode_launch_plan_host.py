@@ -103,6 +103,38 @@ def test_the_even_split_merges_inside_where_one_workgroup_has_few_partials(d, Hq
         assert pl["merge_inside"] == inside, pl
 
 
+@pytest.mark.parametrize("d,Hq,Hkv,P,lens,call,want", [
+    # more pieces than CUs
+    (128, 32, 8, 272, [59 + 31 * i for i in range(18)], pod.CALL_STEP, "even inside"),
+    (128, 64, 4, 528, [71] * 68, pod.CALL_STEP, "even inside"),
+    (128, 64, 4, 528, [210 + i * 204 // 78 for i in range(79)], pod.CALL_STEP, "fixed"),     # a second launch for short pairs costs more
+    (128, 64, 4, 4224, [1976] * 71, pod.CALL_STEP, "even second launch"),
+    (64, 128, 8, 4224, [400 + i * 11 for i in range(34)], pod.CALL_STEP, "even second launch"),
+    (128, 64, 8, 2112, [10940, 17000, 23853], pod.CALL_ATTENTION, "fixed"),
+    # many partials of few pairs with sixteen query heads
+    (128, 16, 1, 272, [14000, 27000], pod.CALL_STEP, "even second launch"),
+    (64, 16, 1, 272, [4856] * 4, pod.CALL_STEP, "fixed"),
+    (64, 16, 1, 4224, [12856, 13977], pod.CALL_STEP, "even second launch"),
+    # lengths that differ, merged inside and by a second launch
+    (128, 32, 8, 272, [500, 800, 1200, 2000, 3000, 4000, 5000], pod.CALL_STEP, "even inside"),
+    (128, 32, 8, 272, [5502 + 80 * i for i in range(7)] + [6085], pod.CALL_STEP, "fixed"),
+    (64, 16, 4, 528, [700, 1500, 2500, 4000, 12000], pod.CALL_STEP, "even inside"),
+    (64, 16, 4, 2112, [3691, 21823], pod.CALL_STEP, "fixed"),
+    (64, 8, 8, 272, [1159] * 16, pod.CALL_ATTENTION, "fixed"),
+    # long pieces, and steps without room for their own workgroups, at head dimension 64
+    (64, 16, 4, 528, [19000] * 4, pod.CALL_STEP, "even inside"),
+    (64, 16, 2, 1004, [33661] * 7, pod.CALL_ATTENTION, "fixed"),
+    (64, 16, 4, 528, [600 + 60 * i for i in range(11)], pod.CALL_STEP, "even inside"),
+    (64, 64, 8, 272, [457 + 60 * i for i in range(8)], pod.CALL_STEP, "even inside"),
+    (64, 256, 16, 528, [1087] * 3, pod.CALL_STEP, "fixed"),
+])
+def test_launches_of_one_round_that_leave_the_fixed_pieces(d, Hq, Hkv, P, lens, call, want):
+    """Each rule on the side where the even split ends sooner and on the one where fixed pieces do."""
+    assert pod.pod_decode_plan(CUS, len(lens), Hkv, P, max(lens) + (call == pod.CALL_STEP))["merge_inside"]
+    pl = launch(Hq, Hkv, d, P, lens, call)
+    assert " ".join(form(pl)[:2]) == ("fixed inside" if want == "fixed" else want), pl
+
+
 def test_bad_arguments_are_rejected():
     good = dict(num_cus=CUS, num_xcds=XCDS, num_q_heads=8, num_kv_heads=2, head_dim=64, proximal_rows=72, context_lens=[100])
     pod.pod_decode_launch_plan(**good)
