@@ -2042,7 +2042,9 @@ pod_decode_choice_t pod_choose_decode(const pod_decode_shape_t &s, int32_t *unit
     // of 7) 6.8 -> 7.2, 3600 8.0 -> 7.6; 4/2 x 64 2048 7.3 -> 6.5, 3600 7.3 -> 6.8.  With more query heads the four waves merge one after the other: x 64, 32/4 at 3055 (24 rows, attention)
     // 8.0 -> 8.8, 40/5 at 2493 7.7 -> 8.5, 16/1 at 3130 9.1 -> 10.2 (over 80 drawn shapes of 6, 8 and 16 with 9 to 32 rows 0.83-0.99 of the rate of eight waves).
     bool four = false;
-    if (pl.merge_inside && s.xcd_local && s.nxcd >= 1 && s.tune_chunk <= 0 && s.tune_chunk_prox <= 0) {
+    // (four waves' pieces are of one tile per wave where they get a CU each: how many they are is known before the plan is made)
+    const int max_prox = s.max_len < s.P ? s.max_len : s.P, tiles = chunk_slots(s.max_len - max_prox, kTile * kWaves) + chunk_slots(max_prox, kTile * kWaves);
+    if (pl.merge_inside && s.xcd_local && s.nxcd >= 1 && s.tune_chunk <= 0 && s.tune_chunk_prox <= 0 && xcd_pairs * (tiles + (s.step ? 1 : 0)) <= xcd_cus) {
         const pod_decode_plan_t small = pod_plan_decode(s.cus, s.B, s.Hkv, s.P, s.max_len, 0, 0, false, false, false, reader);
         const int own = s.step ? 1 : 0, rows = small.nc + own;
         four = xcd_pairs * rows <= xcd_cus &&
@@ -2054,7 +2056,19 @@ pod_decode_choice_t pod_choose_decode(const pod_decode_shape_t &s, int32_t *unit
     const int even_mode = reuse_step ? 2 : 0;
     pod_even_plan_t ev = {0, 0, 0, 0};
     bool padded = false;
-    const bool can_even = s.lens && s.even_split && (!s.scores || reader) && !four &&
+    // (What the rules below ask for and the split does not decide comes first: the plan of a split takes the host 0.7 to 1.4 us at 16 to 40 sequences,
+    // and most launches that merge inside hold on to fixed pieces.)
+    const bool few_heads = s.step || s.rep <= 4, one_tile = pl.chunk <= kTile * pl.waves;
+    const long slots = (long)npairs * pl.nc, longest = pl.chunk > pl.chunk_p ? pl.chunk : pl.chunk_p;
+    long sum = 0;
+    bool look = !pl.merge_inside;
+    if (!look && s.lens && !s.scores && s.fused_merge && s.tune_chunk <= 0 && s.tune_chunk_prox <= 0) {
+        for (int b = 0; b < s.B; ++b) sum += s.lens[b];
+        look = slots > s.cus || (s.rep > 8 && npairs <= 4) || (!one_tile && few_heads && longest - sum * s.Hkv / s.cus > 256) ||
+               (s.D == 64 && ((s.rep <= 4 && pl.nc > 1 && pl.chunk > (s.step ? 1024 : 1536)) || (s.step && !host_fits(pl))));
+    }
+    const long mean = sum * s.Hkv / s.cus, saved = pl.chunk - mean; // mean: tokens per CU
+    const bool can_even = look && s.lens && s.even_split && (!s.scores || reader) && !four &&
                           pod_plan_even_launch(2 * s.cus, s.B, s.Hkv, s.P, even_unit_distant(even_mode), s.lens, unit_cum, &ev, &padded);
     const int even_rows = can_even ? ev.most + (s.step ? 1 : 0) : 0;
     // (a batch of one very long and many short sequences cuts the long one into more parts than fixed pieces
@@ -2070,17 +2084,11 @@ pod_decode_choice_t pod_choose_decode(const pod_decode_shape_t &s, int32_t *unit
     bool even_merge = can_even && padded && s.fused_merge && even_mode == 0 && s.rep * even_rows <= merge_room && even_rows <= 96;
     if (!s.step) // (an empty sequence has no workgroup that would write its rows)
         for (int b = 0; b < s.B && even_merge; ++b) even_merge = s.lens[b] > 0;
-    if (pl.merge_inside && even_fits && !s.scores && s.fused_merge && s.tune_chunk <= 0 && s.tune_chunk_prox <= 0) {
-        long sum = 0;
-        for (int b = 0; b < s.B; ++b) sum += s.lens[b];
-        const long slots = (long)npairs * pl.nc;
-        const bool one_tile = pl.chunk <= kTile * pl.waves;
-        const long mean = sum * s.Hkv / s.cus, saved = pl.chunk - mean, longest = pl.chunk > pl.chunk_p ? pl.chunk : pl.chunk_p; // mean: tokens per CU
+    if (pl.merge_inside && even_fits && !s.scores) {
         // ... those with more slots than CUs, whose second round costs as much as the first: per step, us, fixed -> even: 35 of 882 tokens x 16/4 x 64, 280 slots,
         // 20.1 -> 14.3; 18 of 0.1-0.6K x 32/8 x 128 20.5 -> 13.9; 68 of 71 x 64/4 x 128 21.2 -> 19.0.  Where a second launch has to merge, attention with more than four
         // query heads is left out (3 of 11-24K x 64/8 x 128 35.0 -> 37.0), and pairs of one piece with more than eight x 128 if they are short (79 of 0.2-0.4K x 64/4, 385 tokens per CU, 29.2 -> 32.2, 74 of 302
         // 28.2 -> 30.7; but 66 of 0.6-0.7K, 692, 37.5 -> 36.4, 71 of 2K 79.2 -> 71.4, and x 64 34 of 0.4-0.8K x 128/8 24.0 -> 21.7) ...
-        const bool few_heads = s.step || s.rep <= 4;
         const bool short_pairs = s.D == 128 && s.rep > 8 && pl.nc == 1 && mean < 576;
         bool take = slots > s.cus && (even_merge || (few_heads && !short_pairs));
         // ... many partials per pair with more query heads than the merging workgroup has waves, where so few workgroups merge them through

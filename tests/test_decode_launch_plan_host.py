@@ -143,3 +143,25 @@ def test_bad_arguments_are_rejected():
         with pytest.raises(pod.PodError) as e:
             pod.pod_decode_launch_plan(**{**good, **bad})
         assert e.value.code == pod.binding.ERR_INVALID_ARG
+
+
+def test_a_launch_that_keeps_fixed_pieces_is_chosen_without_planning_the_even_split():
+    """250 pairs of one short piece each: the split of such a batch costs the host more than everything else of the choice."""
+    import ctypes as C
+    import time
+    L, B = pod.load(), 250
+    lens, plan, cum = (C.c_int32 * B)(*[100] * B), (C.c_int32 * 8)(), (C.c_int32 * (B + 1))()
+
+    def fastest(call):
+        best = float("inf")
+        for _ in range(100):
+            t0 = time.perf_counter()
+            for _ in range(20):
+                assert call() == 0
+            best = min(best, time.perf_counter() - t0)
+        return best / 20
+
+    choice = lambda known: fastest(lambda: L.pod_decode_launch_plan(CUS, XCDS, B, 8, 1, 128, 272, 101, lens if known else None, pod.CALL_STEP, 1 << 30, plan))
+    split = fastest(lambda: L.pod_decode_even_launch(CUS, B, 1, 272, 128, lens, plan, cum)) - fastest(lambda: L.pod_decode_even_launch(CUS, 1, 1, 272, 128, lens, plan, cum))
+    assert not launch(8, 1, 128, 272, [100] * B)["even"]
+    assert choice(True) - choice(False) < 0.5 * split, (choice(True), choice(False), split)
