@@ -587,8 +587,8 @@ int pod_decode_launch_plan(int num_cus, int num_xcds, int batch, int num_q_heads
  * Measurement aid: while dev_buf is set (NULL = off), every workgroup of a pod_decode_step / fused
  * pod_decode_attention launch that stores a partial result leaves 8 uint64 words in it, at index (workgroup number
  * in the launch) * 8: (sequence * num_kv_heads + kv head) << 32 | piece (bit 31 set: this workgroup merged), the id of
- * the XCD it ran on, and the device's 100 MHz clock at its start, at the end of its tile loop, when its partial was
- * stored, when its arrival was counted, and at its end.  Launches whose partials a second kernel merges record too:
+ * the XCD it ran on, and the device's 100 MHz clock at its start, at the end of its tile loop (its start
+ * again where it only takes a step), when its partial was stored, when its arrival was counted, and at its end.  Launches whose partials a second kernel merges record too:
  * words 0, 2, 3 and 6 as above (start, end of the tile loop, end), word 1 = XCD id | hardware id register << 8 (which
  * CU); an even-split launch (pod_decode_even_launch) records per walking workgroup its number, that word 1, and the
  * clock at its start (words 2 and 3) and end (word 6).  bytes / 64 workgroups are recorded; later launches overwrite

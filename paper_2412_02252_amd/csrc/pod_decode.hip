@@ -870,7 +870,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void decode_partial_kernel(decode_
                 unsigned long long *t = p.trace + 8 * wg;
                 t[0] = ((unsigned long long)(b * hkv + h) << 32) | (unsigned)c | (last ? 0x80000000u : 0u);
                 t[1] = (unsigned long long)xcc_id();
-                t[2] = tr_t0; t[3] = tr_t1; t[4] = tr_t2; t[5] = tr_t3; t[6] = wall_clock64();
+                t[2] = tr_t0; t[3] = tr_t1 ? tr_t1 : tr_t0; t[4] = tr_t2; t[5] = tr_t3; t[6] = wall_clock64(); // (one that only takes the step walks no tile)
             }
         };
         if (!last) { trace_out(); return; }

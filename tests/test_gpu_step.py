@@ -389,6 +389,26 @@ def test_the_step_has_a_workgroup_of_its_own_only_where_that_pays(reuse, d, room
         assert plan["pieces"] == pieces and own == (pieces != 85 and (room, pieces) != (2, 42))
 
 
+@pytest.mark.parametrize("d,Hq,Hkv,n,reuse,waves,local", [(128, 32, 8, 500, False, 4, True), (64, 2, 1, 3000, True, 4, True), (128, 32, 8, 3000, False, 8, True),
+                                                          (128, 3, 3, 10000, False, 8, False)])
+def test_every_workgroup_of_a_step_records_its_clocks_in_order(d, Hq, Hkv, n, reuse, waves, local):
+    """Start, end of the tile loop, stored, counted, end: also of the workgroups that only take the step and walk no tile."""
+    c = Case(1, 1, Hq, Hkv, d, 8, 120, 1, n + 8, seed=533)
+    c.fill(0, 0, n)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    pl = pod.pod_decode_launch_plan(cus, c.gpu.pod_cache_launch_info()["xcds"], Hq, Hkv, d, 128, [n], pod.CALL_REUSE_FIRST if reuse else pod.CALL_STEP)
+    assert (pl["waves"], pl["xcd_local"], pl["merge_inside"], pl["own_workgroup"]) == (waves, local, True, True), pl
+    trace = torch.zeros(8 * 1024, dtype=torch.int64, device=c.dev)
+    c.gpu.pod_profile_set_trace(trace)
+    out = c.step_reuse(0, [n], c.gpu.new_score_buffer()) if reuse else c.step(0, [n])
+    c.gpu.pod_profile_set_trace(None)
+    assert_close(out, c.decode_ref(0, [n + 1]))
+    words = trace.view(-1, 8).cpu()
+    words = words[words[:, 6] != 0]
+    assert len(words) == Hkv * pl["partials"]
+    assert (words[:, 2] > 0).all() and (words[:, 3:7] >= words[:, 2:6]).all(), words[(words[:, 3:7] < words[:, 2:6]).any(1)]
+
+
 def test_steps_from_empty_caches_with_more_pairs_than_free_cus():
     """160 pairs of one or two pieces: no CU is left for a workgroup that only takes the step, also while the cache is empty
     and that workgroup's piece with it."""
