@@ -134,10 +134,16 @@ def _ptr(t, dtype=None):
     return t.data_ptr()
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
     # (the handle itself: torch.cuda.current_stream() builds a Stream object for it, 3.0 us against 0.2, of the 8 us that a call of
-    # this binding took the host; a prompt of 110 tokens and its first decode step, five calls, 43.1 -> 31.2 us)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    # this binding took the host; a prompt of 110 tokens and its first decode step, five calls, 43.1 -> 31.2 us.  A torch without
+    # that entry, which is not a public one, takes the Stream object)
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def make_config(num_layers, group_size, num_q_heads, num_kv_heads, head_dim, sink, window, max_batch,

@@ -102,3 +102,25 @@ def test_fills_go_past_the_caches_by_what_is_held_not_by_what_fits():
     for held, slot, n in (([0, 0], 2, 10), ([0, 0], -1, 10), ([0, 0], 0, 0), ([0, 0], 0, 1001), ([0, -1], 0, 10)):
         with pytest.raises(pod.PodError):
             pod.pod_fill_plan(cfg, held, slot, n)
+
+
+def test_the_current_stream_is_found_without_torchs_private_entry(monkeypatch):
+    class Stream:
+        cuda_stream = 0x1230
+    monkeypatch.delattr(pod.binding.torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(pod.binding, "_raw_stream", getattr(pod.binding.torch._C, "_cuda_getCurrentRawStream", None), raising=False)
+    monkeypatch.setattr(pod.binding.torch.cuda, "current_stream", Stream)
+    monkeypatch.setattr(pod.binding.torch.cuda, "current_device", lambda: 0)
+    assert pod.binding._stream() == 0x1230
+
+
+@pytest.mark.gpu
+def test_the_current_stream_is_the_same_with_and_without_it(monkeypatch):
+    torch = pod.binding.torch
+    side = torch.cuda.Stream()
+    for stream in (torch.cuda.current_stream(), side):
+        with torch.cuda.stream(stream):
+            fast = pod.binding._stream()
+            with monkeypatch.context() as m:
+                m.setattr(pod.binding, "_raw_stream", None)
+                assert pod.binding._stream() == fast == stream.cuda_stream
