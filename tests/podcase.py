@@ -123,6 +123,11 @@ class Case:
             self.cpu.append(layer, gen.bf16_bits(kc), gen.bf16_bits(vc), positions)
         return out
 
+    def launched(self, lens, call):
+        """How a call (pod.CALL_*) on sequences that hold `lens` tokens is launched on this device: pod_decode_launch_plan."""
+        cus = torch.cuda.get_device_properties(0).multi_processor_count
+        return pod.pod_decode_launch_plan(cus, self.gpu.pod_cache_launch_info()["xcds"], self.Hq, self.Hkv, self.d, self.S + self.W, lens, call)
+
     def decode_queries(self, layer, ctx, device):
         """Query of the token at position ctx[b]-1 of each sequence: [B][Hq][d]."""
         return torch.cat([self.queries(layer, b, 1, device, pos0=max(n, 1) - 1) for b, n in enumerate(ctx)]).contiguous()

@@ -161,12 +161,6 @@ def test_parts_of_whole_pairs_and_parts_that_cross(d, Hq, Hkv, B, lo, step, monk
     c.gpu.pod_cache_check()
 
 
-def launched(c, lens, call=pod.CALL_STEP):
-    """How a call on sequences that hold `lens` tokens is launched on this device."""
-    cus = torch.cuda.get_device_properties(0).multi_processor_count
-    return pod.pod_decode_launch_plan(cus, c.gpu.pod_cache_launch_info()["xcds"], c.Hq, c.Hkv, c.d, c.S + c.W, lens, call)
-
-
 @pytest.mark.parametrize("d,Hq,Hkv,B,lo,step", [(64, 8, 8, 24, 300, 37), (64, 16, 4, 44, 130, 91), (64, 6, 2, 80, 3, 77),
                                                 (128, 8, 8, 24, 300, 37), (128, 16, 4, 44, 130, 91), (128, 6, 2, 80, 3, 77),
                                                 (64, 32, 4, 44, 130, 91), (128, 30, 5, 30, 130, 91), (128, 32, 4, 44, 130, 91),
@@ -177,7 +171,7 @@ def test_parts_of_whole_pairs_merged_inside(d, Hq, Hkv, B, lo, step):
     lens = [lo + (step * i * i) % 900 for i in range(B)]
     c = Case(2, 2, Hq, Hkv, d, 8, 64, B, 1210, seed=9360 + B)
     for call in (pod.CALL_STEP, pod.CALL_ATTENTION):
-        pl = launched(c, lens, call)
+        pl = c.launched(lens, call)
         assert pl["even"] and pl["merge_inside"], pl
     fill_all(c, lens)
     for s in range(2):
@@ -228,13 +222,16 @@ def test_parts_of_whole_pairs_merged_inside(d, Hq, Hkv, B, lo, step):
 @pytest.mark.parametrize("Hq,Hkv,d,B", [(16, 4, 64, 44), (8, 8, 64, 24), (8, 4, 128, 44)])
 def test_empty_sequences_in_the_padded_split(Hq, Hkv, d, B):
     """First, in the middle and last in the batch: no part walks them.  Attention leaves the merge to the second launch, which writes their
-    zero rows; a step gives each its first token, which the merging kernel's own workgroup for the pair (d = 64) takes alone; then both
+    zero rows; a step gives each its first token, which the merging kernel's own workgroup for the pair takes alone; then both
     again with nothing empty."""
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     lens = [0 if b in (0, 7, 8, B - 1) else 130 + (91 * b * b) % 900 for b in range(B)]
     empty, held = [b for b in range(B) if not lens[b]], [b for b in range(B) if lens[b]]
     assert cus != 256 or (pod.pod_decode_even_launch(cus, Hkv, 72, lens)["padded"] and not pod.pod_decode_plan(cus, B, Hkv, 72, max(lens))["merge_inside"])
     c = Case(2, 2, Hq, Hkv, d, 8, 64, B, 1210, seed=9370 + B)
+    for call, inside in ((pod.CALL_ATTENTION, False), (pod.CALL_STEP, True)):
+        pl = c.launched(lens, call)
+        assert pl["even"] and pl["merge_inside"] == inside, pl
     one = Case(2, 2, Hq, Hkv, d, 8, 64, B, 1210, seed=9370 + B)              # (the oracle wants a token in each: its reference for the others)
     fill_all(c, lens)
     fill_all(one, [max(n, 1) for n in lens])
@@ -255,13 +252,15 @@ def test_empty_sequences_in_the_padded_split(Hq, Hkv, d, B):
     c.gpu.pod_cache_check()
 
 
-@pytest.mark.parametrize("d", [64, 128])
-def test_the_trace_holds_the_walking_workgroups_of_the_launched_split(d):
-    """Steps merged inside (d = 64) and by the second launch: one record per workgroup of pod_decode_even_launch's split, none for the
+@pytest.mark.parametrize("d,Hq,inside", [(64, 16, True), (128, 16, True), (64, 56, False), (128, 56, False)])
+def test_the_trace_holds_the_walking_workgroups_of_the_launched_split(d, Hq, inside):
+    """Steps merged inside and by the second launch: one record per workgroup of pod_decode_even_launch's split, none for the
     workgroups that only take the new token."""
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    lens = [130 + (91 * i * i) % 900 for i in range(44)]
-    c = Case(2, 2, 16, 4, d, 8, 64, len(lens), 1210, seed=9380 + d)
+    lens = [130 + (91 * i * i) % 900 for i in range(44)] if inside else [2500 + (91 * i * i) % 9000 for i in range(12)]
+    c = Case(2, 2, Hq, 4, d, 8, 64, len(lens), max(lens) + 8, seed=9380 + d)
+    pl = c.launched(lens, pod.CALL_STEP)
+    assert pl["even"] and pl["merge_inside"] == inside, pl
     fill_all(c, lens)
     split = pod.pod_decode_even_launch(cus, 4, 72, lens)
     assert cus != 256 or split["padded"]
@@ -320,20 +319,32 @@ def test_walk_direction_does_not_change_the_result(rounds, monkeypatch):
         assert (a - b).abs().max() <= 2.0 ** -7 * b.abs().max()
 
 
-@pytest.mark.parametrize("d,Hq,Hkv,B,lo,hi", [(128, 32, 8, 18, 59, 592),     # more slots than CUs: even, merged inside
-                                              (128, 32, 4, 18, 93, 938),     # the same with 8 query heads per kv head, few partials
-                                              (128, 32, 4, 3, 900, 9000),    # ... with many: the merge is a launch of its own
-                                              (128, 4, 4, 40, 300, 900),     # one query head per kv head
-                                              (128, 16, 1, 2, 9000, 12000),  # 16 query heads and more than 16 partials of few pairs
-                                              (64, 16, 4, 5, 700, 7000),     # lengths that fill half of the slots
-                                              (64, 8, 8, 11, 200, 900)])     # no room for the steps' own workgroups
-def test_launches_that_leave_the_fixed_pieces(d, Hq, Hkv, B, lo, hi):
-    """Ragged batches and shapes on the side of each rule where the even split takes over from fixed pieces merged inside one round:
+EVEN, EVEN2, FIXED = (True, True), (True, False), (False, True) # (the even split, merged inside)
+
+
+@pytest.mark.parametrize("d,Hq,Hkv,B,lo,hi,attention,step", [
+    (128, 32, 8, 18, 59, 592, EVEN, EVEN),       # more slots than CUs, merged inside
+    (128, 32, 4, 70, 40, 200, EVEN, EVEN),       # ... with 8 query heads per kv head
+    (128, 64, 4, 68, 60, 80, EVEN, EVEN),        # ... with 16
+    (128, 4, 4, 66, 60, 220, EVEN, EVEN),        # ... with one
+    (128, 32, 4, 18, 93, 938, FIXED, FIXED),     # fewer slots than CUs
+    (128, 32, 4, 3, 3000, 30000, FIXED, EVEN2),  # lengths that fill half of the slots; many partials of 8 query heads
+    (128, 32, 4, 3, 900, 9000, FIXED, FIXED),
+    (128, 32, 8, 7, 500, 5000, EVEN, EVEN),
+    (128, 16, 1, 2, 9000, 12000, EVEN2, EVEN2),  # 16 query heads and more than 16 partials of few pairs
+    (64, 16, 4, 5, 700, 7000, EVEN, EVEN),
+    (64, 8, 8, 11, 200, 900, EVEN, EVEN),        # no room for the steps' own workgroups
+    (64, 64, 8, 8, 200, 900, FIXED, EVEN)])
+def test_launches_that_leave_the_fixed_pieces(d, Hq, Hkv, B, lo, hi, attention, step):
+    """Ragged batches and shapes on both sides of each rule where the even split takes over from fixed pieces merged inside one round:
     plain decode (one empty sequence among them at the end) and steps against the oracle."""
     S, W = 16, 240
     lens = [lo + (i * 7919) % (hi - lo + 1) for i in range(B)]
     lens[-1] = hi
     c = Case(2, 2, Hq, Hkv, d, S, W, B, hi + 8, seed=590 + B)
+    for call, want in ((pod.CALL_ATTENTION, attention), (pod.CALL_STEP, step)):
+        pl = c.launched(lens, call)
+        assert (pl["even"], pl["merge_inside"]) == want, pl
     for layer in range(2):
         for b, n in enumerate(lens):
             c.fill(layer, b, n)

@@ -267,6 +267,12 @@ def test_small_launches_of_four_waves(n, d, Hq, Hkv):
     """Short contexts in pieces of 128 tokens, one tile per wave, up to the numbers of partials (8, 16 and 32, one of them the step's) at
     which the merge takes another form or the launch eight waves: plain decode, steps and score-reuse steps on both sides of each."""
     c = Case(2, 2, Hq, Hkv, d, 16, 112, 1, n + 16, seed=560 + Hq)
+    for held, call in [(n, pod.CALL_ATTENTION)] + [(n + s, pod.CALL_STEP) for s in range(3)] + [(n + s, pod.CALL_REUSE_UPPER) for s in range(3, 6)]:
+        own = int(call != pod.CALL_ATTENTION)
+        rows, eight = (-(-max(held + own - 128, 0) // piece) + 1 + own for piece in (128, 256))  # partials of four and of eight waves
+        four = rows <= 8 or (d == 64 and rows <= 32 and (Hq // Hkv <= 2 or (Hq // Hkv == 4 and eight > 8)))
+        pl = c.launched([held], call)
+        assert pl["waves"] == (4 if four or pl["even"] else 8) and pl["even"] == (n == 128 * 31 - 2 and d == 128 and Hq // Hkv == 16 and call == pod.CALL_STEP), pl
     for layer in range(2):
         c.fill(layer, 0, n)
     scores = c.gpu.new_score_buffer()
