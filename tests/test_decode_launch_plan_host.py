@@ -49,6 +49,7 @@ def test_the_choice_agrees_with_the_plans_it_is_made_of(seed):
                 assert fixed["merge_inside"] and (pl["chunk"], pl["chunk_prox"], pieces) == (fixed["chunk"], fixed["chunk_prox"], fixed["pieces"]), what
             if pl["waves"] == 4 and pl["merge_inside"]: # a small launch: a CU for each of an XCD's workgroups
                 assert pl["xcd_local"] and -(-B * Hkv // XCDS) * pl["partials"] <= CUS // XCDS, what
+                assert pl["own_workgroup"] == step, what # (score reuse's kernel of four waves has one as a constant)
             if pl["own_workgroup"]:
                 assert B * Hkv * pl["partials"] <= (-(-B * Hkv // XCDS) * XCDS * (CUS // XCDS) if pl["xcd_local"] else CUS), what
 
