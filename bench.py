@@ -175,9 +175,14 @@ def run_large(workload, K, Wm, variant):
             ceil = {"what": "plain read-only kernel (non-temporal loads) over the same number of bytes of the cache buffer, a different part each launch, same event timing",
                     "us": stats(cus), "GBs": round(part / (cmed * 1e-6) / 1e9, 1), "frac_of_peak": round(part / (cmed * 1e-6) / 1e9 / HBM_PEAK_GBS, 4),
                     "kernel_vs_ceiling": round(cmed / kus * per_launch / part, 4)}
+        step = variant == "step"
+        pl = pod.pod_decode_launch_plan(torch.cuda.get_device_properties(0).multi_processor_count, cache.pod_cache_launch_info()["xcds"], Hq, Hkv, d, S + W,
+                                        [n + total - 1 + (not step) for n in lens], pod.CALL_STEP if step else pod.CALL_ATTENTION)
+        kernel = (f"decode_even_kernel<{d}, {str(step).lower()}, 0, {str(pl['merge_inside']).lower()}> ({'step' if step else 'attention'}; one round of workgroups, the batch's rows "
+                  f"split evenly over them; {'the last of a pair' if pl['merge_inside'] else 'decode_combine_kernel'} merges)"
+                  if pl["even"] else f"decode_partial_kernel<{d}, 0, ...> (fixed pieces)")
         res.update({"GBs": round(nbytes / dt / 1e9, 1), "frac_of_hbm_peak": round(nbytes / dt / 1e9 / HBM_PEAK_GBS, 4),
-                    "kernel": {"name": ("decode_even_kernel<128, true, 0> (step; one round of workgroups, the batch's rows split evenly over them; decode_combine_kernel merges)"
-                                        if variant == "step" else "decode_even_kernel<128, false, 0>"),
+                    "kernel": {"name": kernel,
                                "bytes_per_launch": int(per_launch), "median_us": round(kus, 3),
                                "GBs": round(per_launch / (kus * 1e-6) / 1e9, 1),
                                "frac_of_hbm_peak": round(per_launch / (kus * 1e-6) / 1e9 / HBM_PEAK_GBS, 4), "launches": len(each)}})
